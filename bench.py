@@ -59,6 +59,8 @@ METRICS = {
 }
 # stages that time exactly one kernel (launched once, or several times alike)
 KERNEL_OF_STAGE = {
+    "vargen_part": "k_gen_part",
+    "part_split": "k_part_split",
     "vargen_hash": "k_vargen_hash",
     "hash_passes": "k_scatter_counted",
     "hash_counted_pass": "k_scatter_counted",
@@ -66,7 +68,7 @@ KERNEL_OF_STAGE = {
     "sort_passes": "k_onesweep",
     "emit": "k_emit_runs",
 }
-HBM_STAGES = ("hash_passes", "hash_counted_pass", "sort_passes")
+HBM_STAGES = ("vargen_part", "part_split", "hash_passes", "hash_counted_pass", "sort_passes")
 
 
 def log(msg):
@@ -632,8 +634,8 @@ def main():
                 "algorithmic_bytes_per_launch": per_launch_bytes}
 
     single = [x for x in stage_ms if x in KERNEL_OF_STAGE and stage_launch[x] > 0]
-    # the dominant HBM-bound kernel (variant generation is ALU-bound, the
-    # grouping LDS/latency-bound; their stage times are in stages_ms)
+    # the dominant kernel that streams the elements through HBM (the grouping
+    # is LDS/latency-bound; every stage time is in stages_ms)
     hbm = [x for x in single if x in HBM_STAGES] or single
     dom = max(hbm, key=lambda x: stage_ms[x] / max(1, stage_launch[x]))
     roofline = roof(dom)

@@ -1,0 +1,44 @@
+// Candidate pairs into bins by a hash of the pair (the input of pairs.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "sd_device.h"
+#include "sd_internal.h"
+
+namespace sdk {
+
+// (both halves mixed twice: the ids of a cluster are often consecutive, and one
+// multiplication would leave their pairs on a lattice)
+__device__ __forceinline__ uint64_t pair_hash(uint64_t v) {
+  v = (v ^ (v >> 32)) * 0x9E3779B97F4A7C15ull;
+  v = (v ^ (v >> 29)) * 0xBF58476D1CE4E5B9ull;
+  return v ^ (v >> 32);
+}
+
+// `bits` hash bits below the lb bits that name the bin
+__device__ __forceinline__ uint32_t pair_hash_below(uint64_t v, int lb, int bits) {
+  return (uint32_t)(pair_hash(v) >> (64 - lb - bits)) & ((1u << bits) - 1);
+}
+
+// Adds a candidate to its bin (or, with lb = 0, to its XCD's list, one
+// reservation for the active lanes); one that finds its region full is only
+// counted.
+// Each bin has a region per XCD (nxl = 3), so that an XCD's L2 completes the
+// lines of its own regions.
+__device__ __forceinline__ void pair_put(const sd::PairBins& o, uint64_t v) {
+  const uint32_t x = o.nxl ? blockIdx.x & 7u : 0u;
+  if (o.lb == 0) {
+    const uint64_t act = __ballot(true);
+    uint32_t at = 0;
+    if (mask_rank(act) == 0) at = atomicAdd(&o.cursor[x], (uint32_t)__popcll(act));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + mask_rank(act);
+    if (at < o.region) o.base[(uint64_t)x * o.region + at] = v;
+    return;
+  }
+  const uint32_t b = (uint32_t)(pair_hash(v) >> (64 - o.lb));
+  const uint32_t slot = atomicAdd(&o.cursor[x * o.nbins + b], 1u);
+  if (slot < o.region) o.base[(uint64_t)((b << o.nxl) + x) * o.region + slot] = v;
+}
+
+}  // namespace sdk

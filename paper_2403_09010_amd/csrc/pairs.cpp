@@ -1,0 +1,196 @@
+// Host side of the binned candidate pairs (pairs.hip): sizes, buffers and the
+// one read-back of a search, and what happens when a guess was too small.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <string>
+
+#include "sd_host.h"
+
+namespace sd {
+
+namespace {
+
+// Bins for an expected number of candidates. A bin's hash set lies in LDS:
+// 2,048 slots for a mean of up to 768 candidates; from 8M candidates on, and
+// with three deletions (a pair can repeat 2,325 times), 8,192 slots for a mean
+// of up to 4,096. Regions hold the mean, a quarter more and room for its
+// deviation: bins are as even as the pair hash, but a pair comes with all its
+// repeats (about 9 on average; up to 100 for equal sequences, so the variance
+// is taken as 32 times the mean). spread > 0, after a bin overflowed all the
+// same: half as many candidates per bin each time, and whole hash sets.
+//
+// Few candidates go straight to their bins. From 8M on, the scattered 8-byte
+// writes would leave the L2 as partial lines (85M candidates into 2^15 bins
+// from the grouping kernel: 2.2 ms); they are appended to one list per XCD and
+// split in two levels instead, a coalesced read and write each (0.65 ms). A
+// list may get more than its share, since all pairs of a group of equal
+// variants come from one XCD: with spread it is twice as long each time.
+struct Shape {
+  PairBins b{};           // the final bins
+  PairBins l0{}, l1{};    // split: the lists the producer appends to, the first level
+  bool wide = false;      // 8,192 slots
+  bool split = false;
+  bool fits = true;       // positions fit 32 bits
+  uint64_t slots = 0;
+};
+
+// Bins of one level (2^lb bins, 2^nxl regions each).
+PairBins level(Scratch& sc, uint64_t guess, int lb, int nxl, double var, uint32_t most,
+               hipStream_t s) {
+  PairBins b{};
+  b.lb = lb;
+  b.nbins = 1u << lb;
+  b.nxl = nxl;
+  const uint64_t nc = (uint64_t)b.nbins << nxl;
+  const double mean = (double)guess / (double)nc;
+  b.region =
+      (uint32_t)std::min<double>(most, mean * 1.25 + 6.0 * std::sqrt(var * mean) + 32);
+  b.cursor = sc.get<uint32_t>(nc);
+  launch_fill_u32(b.cursor, 0, nc, s);
+  return b;
+}
+
+Shape shape(Scratch& sc, uint64_t guess, int k, int spread, hipStream_t s) {
+  Shape sh;
+  sh.split = guess >= (8ull << 20);
+  sh.wide = sh.split || k >= 3;
+  const uint64_t mean_max = (sh.wide ? 4096u : 768u) >> spread;
+  int lb = 6;
+  while ((guess >> lb) > mean_max) ++lb;
+  const int nxl = sh.split ? 3 : 0;
+  const uint32_t most = pair_bin_max(sh.wide) >> nxl;
+  sh.b = level(sc, guess, lb, nxl, spread ? 1e6 : 32, most, s);
+  sh.slots = ((uint64_t)sh.b.nbins << nxl) * sh.b.region;
+  sh.fits = sh.slots < 0xFFFFFFFFull && guess < 3000000000ull && lb <= 18;
+  if (!sh.fits) return sh;
+  sh.b.base = sc.get<uint64_t>(sh.slots);
+  if (sh.split) {
+    const uint32_t all = (uint32_t)guess;
+    sh.l0 = level(sc, std::min<uint64_t>(guess << spread, 8 * guess), 0, 3, 4096, all, s);
+    sh.l0.base = sc.get<uint64_t>((uint64_t)sh.l0.region << 3);
+    sh.l1 = level(sc, guess, (lb + 1) / 2, 3, spread ? 16384 : 1024, all, s);
+    sh.l1.base = sc.get<uint64_t>(((uint64_t)sh.l1.nbins << 3) * sh.l1.region);
+  }
+  return sh;
+}
+
+}  // namespace
+
+bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q,
+                  const std::function<void(const PairBins&)>& produce,
+                  const std::function<PairNext(const uint32_t*, uint64_t*)>& check,
+                  const std::function<TileOut(uint64_t*, uint64_t)>& sort_pairs,
+                  const char* stage, TileOut* out) {
+  sd_ctx* c = cl0.c;
+  hipStream_t s = cl0.s;
+  // candidates expected: a share of the variants by radius, or what the last
+  // search of this kind on the context made, scaled down to this one's
+  // variants (never up: one input of many copies must not size the next)
+  constexpr double first[4] = {1.0 / 64, 1.0 / 48, 1.0 / 22, 1.0 / 9};
+  const std::string hint_raw(hint), hint_keys = hint_raw + "/variants";
+  double expect = (double)nkeys * first[q.k & 3];
+  if (c->out_hint.count(hint_raw)) {
+    const double last = (double)c->out_hint[hint_raw], keys = (double)c->out_hint[hint_keys];
+    expect = std::max(expect, 1.1 * last * std::min(1.0, (double)nkeys / std::max(keys, 1.0)));
+  }
+  uint64_t guess = (uint64_t)expect + 1024;
+  uint64_t cap = guess;
+  int spread = 0;
+  for (int attempt = 0; attempt < 8; ++attempt) {
+    Scratch sc(c);
+    Call cl{c, s, sc, cl0.tm, cl0.counters};
+    Shape sh = shape(sc, guess, q.k, spread, s);
+    if (!sh.fits) return false;
+    PairBufs b{};
+    b.icnt = sc.get<uint32_t>(q.na);
+    b.kv = sc.get<uint64_t>(sh.slots);
+    b.rank = sc.get<uint32_t>(sh.slots);
+    b.kd = sc.get<uint8_t>(sh.slots);
+    b.kept = sc.get<uint32_t>(sh.b.nbins);
+    b.off = sc.get<uint64_t>(q.na + 1);
+    b.ti = sc.get<uint32_t>(sh.slots);
+    b.tj = sc.get<uint32_t>(sh.slots);
+    b.td = sc.get<uint8_t>(sh.slots);
+    b.long_cap = (uint32_t)std::min<uint64_t>(sh.slots / 64 + 1, q.na);
+    b.longs = sc.get<uint32_t>(b.long_cap);
+    b.state = sc.get<PairState>(1);
+    b.err = cl.lb_err();
+    launch_fill_u32(b.icnt, 0, q.na, s);
+    launch_fill_u32(reinterpret_cast<uint32_t*>(b.state), 0, sizeof(PairState) / 4, s);
+    produce(sh.split ? sh.l0 : sh.b);
+    cl.tm.mark(stage, (double)nkeys * 8 + (double)guess * 8, 1);
+    if (sh.split) {
+      launch_pair_split(sh.l0, sh.l1, b.state, s);
+      launch_pair_split(sh.l1, sh.b, b.state, s);
+      cl.tm.mark("pair_split", (double)guess * 32, 2);
+    }
+    launch_pair_verify(sh.b, sh.wide, q, b, s);
+    cl.tm.mark("pair_verify", (double)guess * (8 + 32), 1);
+    const uint64_t tiles = (q.na + scan_tile() - 1) / scan_tile();
+    const uint32_t epoch = next_epoch(c, tiles, s);
+    launch_scan_excl(b.icnt, b.off, q.na, c->status, cl.tile_counter(), epoch, cl.lb_err(), s);
+    launch_pair_place(sh.b, b, s);
+    Scratch res(c);  // the result arrays, handed over at the end
+    uint32_t* oi = res.get<uint32_t>(cap);
+    uint32_t* oj = res.get<uint32_t>(cap);
+    uint8_t* od = res.get<uint8_t>(cap);
+    launch_pair_order(b, q.na, oi, oj, od, cap, cl.counters + CNT_LBERR, s);
+    cl.tm.mark("pair_order", (double)q.na * 20, 4);
+    PairState st;
+    std::memcpy(&st, readback(c, b.state, sizeof(st), s), sizeof(st));
+    uint64_t raw = 0, more = 0;
+    for (uint64_t x : st.raw) raw += x;
+    const uint64_t kept = st.count;
+    if (st.counters[0] & SD_ERRBIT_LOOKBACK)
+      throw Error{SD_E_HIP, "internal error: a look-back wait timed out"};
+    const bool overflow = st.flags & PF_OVERFLOW;
+    if (overflow)  // (a split reads slots that lost candidates never filled)
+      launch_fill_u32(cl.lb_err(), 0, 1, s);
+    else if (st.counters[0] & SD_ERRBIT_INDEX)
+      throw Error{SD_E_HIP, "internal error: a candidate id out of range"};
+    const PairNext next = check(st.counters, &more);
+    if (next == PairNext::give_up) return false;
+    if (raw + more >= 0xFFFFFFFFull)
+      throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 candidate pairs"};
+    if (overflow || next == PairNext::again) {
+      // more room: what was counted and what comes; where the room was there
+      // but pairs have very many repeats, fewer of them per bin
+      const uint64_t want = raw + more + raw / 16 + 1024;
+      if (want <= guess) ++spread;
+      guess = std::max(guess, want);
+      cap = guess;
+      continue;
+    }
+    c->out_hint[hint_raw] = raw;
+    c->out_hint[hint_keys] = nkeys;
+    out->ncand = raw;
+    if (st.flags & PF_LONG) {
+      // a first id with thousands of pairs: the kept pairs take the radix sort
+      uint64_t* cand = sc.get<uint64_t>(kept);
+      launch_join_pairs(b.ti, b.tj, kept, cand, s);
+      *out = sort_pairs(cand, kept);
+      out->ncand = raw;
+      return true;
+    }
+    if (kept > cap) {  // the guess held the candidates but not the pairs
+      for (void* p : res.blocks) dfree(c, p);
+      res.blocks.clear();
+      oi = res.get<uint32_t>(kept);
+      oj = res.get<uint32_t>(kept);
+      od = res.get<uint8_t>(kept);
+      launch_pair_order(b, q.na, oi, oj, od, kept, cl.counters + CNT_LBERR, s);
+    }
+    res.blocks.clear();
+    out->i = oi;
+    out->j = oj;
+    out->d = od;
+    out->n = kept;
+    return true;
+  }
+  return false;
+}
+
+}  // namespace sd

@@ -1,0 +1,691 @@
+// Partitioned grouping path for gfx950: the automatic path of self searches.
+//
+//   k_gen_part      generates every distinct <= k-deletion variant as a 64-bit
+//                   element [hash | id] into an LDS tile, orders the tile by
+//                   the top `lb` hash bits and writes each bin's run to the
+//                   bin's region: one write of the elements, no sort pass
+//   k_filter_group  one workgroup per bin: an LDS bitmap finds the elements
+//                   whose hash may be shared, which are grouped by their full
+//                   stored hash in LDS and emit their id pairs
+//
+// Equal variants have equal hashes and so share a bin; a collision of hashes
+// only adds a candidate that the verification rejects.
+#include <algorithm>
+
+#include "hashtab.h"
+#include "pair_put.h"
+#include "partition_tail.h"
+#include "sd_device.h"
+#include "sd_internal.h"
+
+namespace sdk {
+
+static __constant__ HashTab kHashTab = make_hash_tab();
+
+// ------------------------------------------------------------------ generator
+
+// Inclusive prefix XOR over each 32-lane half of the wave.
+__device__ __forceinline__ uint32_t half_xor_scan(uint32_t v) {
+  v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);  // row_shr:1
+  v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);  // row_shr:2
+  v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);  // row_shr:4
+  v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);  // row_shr:8
+  v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, true);  // row_bcast:15
+  return v;
+}
+
+__device__ __forceinline__ uint32_t read_lane(uint32_t v, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+
+// Lane i's value of lane i + 1 (the last lane gets 0).
+__device__ __forceinline__ uint32_t next_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, true);  // wave_shl:1
+}
+
+// 64-bit words as two 32-bit halves (rotations by less than 32 are one
+// v_alignbit per half).
+struct W2 {
+  uint32_t lo, hi;
+};
+__device__ __forceinline__ W2 operator^(W2 a, W2 b) { return W2{a.lo ^ b.lo, a.hi ^ b.hi}; }
+__device__ __forceinline__ W2 w2(uint64_t v) { return W2{(uint32_t)v, (uint32_t)(v >> 32)}; }
+__device__ __forceinline__ W2 rotr_w2(W2 v, uint32_t n) {
+  return W2{__builtin_amdgcn_alignbit(v.hi, v.lo, n), __builtin_amdgcn_alignbit(v.lo, v.hi, n)};
+}
+__device__ __forceinline__ W2 rotl_w2(W2 v, uint32_t n) {  // 0 < n < 32
+  return W2{__builtin_amdgcn_alignbit(v.lo, v.hi, 32 - n),
+            __builtin_amdgcn_alignbit(v.hi, v.lo, 32 - n)};
+}
+
+// Residue t (t <= 23) of a packed key.
+__device__ __forceinline__ uint32_t residue_at(u128 key, uint32_t t) {
+  const uint64_t lo = (uint64_t)key, top = (uint64_t)(key >> 56);
+  const uint32_t s = 115 - 5 * t;
+  return (uint32_t)((s >= 56 ? top : lo) >> (s >= 56 ? s - 56 : s)) & 31u;
+}
+
+// Deletion pairs in colexicographic order (pair u = p2 (p2 - 1) / 2 + p1, the
+// same for every length: a string of length L has the first C(L, 2)): the LDS
+// byte offsets of the pair's two words in its sequence's rows, and the bits of
+// n1 and n2 that a canonical pair has (p2 in n1; p1 in n1, or in n2 if p2 =
+// p1 + 1). Unused entries need bit 31, which no mask has.
+constexpr int GP_ROW = KEY_MAX_LEN;
+constexpr int GP_CHUNKS = (KEY_MAX_LEN * (KEY_MAX_LEN - 1) / 2 + 63) / 64;
+
+struct PairLanes {
+  uint4 e[GP_CHUNKS * 64];
+};
+
+constexpr PairLanes make_pair_lanes() {
+  PairLanes t{};
+  for (int u = 0; u < GP_CHUNKS * 64; ++u) t.e[u] = uint4{0, GP_ROW * 8, 1u << 31, 0};
+  int u = 0;
+  for (int p2 = 1; p2 < KEY_MAX_LEN; ++p2)
+    for (int p1 = 0; p1 < p2; ++p1, ++u) {
+      const bool adj = p2 == p1 + 1;
+      t.e[u].x = (unsigned)p1 * 8;
+      t.e[u].y = (unsigned)(GP_ROW + p2) * 8;
+      t.e[u].z = (1u << p2) | (adj ? 0u : 1u << p1);
+      t.e[u].w = adj ? 1u << p1 : 0u;
+    }
+  return t;
+}
+
+static __constant__ PairLanes kPairLanes = make_pair_lanes();
+
+// With P[p] the prefix XORs of the position terms rotr(B[s_t], t) (the hash
+// of hashtab.h) and Q[p] = P[p] ^ rotl(P[p + 1], 1), the variant without
+// p1 < p2 < p3 hashes to
+//   C[L - 3] ^ rotl(P[L], 3) ^ Q[p1] ^ rotl(Q[p2], 1) ^ rotl(Q[p3], 2)
+// and with fewer deletions to the same form with fewer terms: one table word
+// per deletion.
+//
+// A wave takes two sequences, one per 32-lane half: lane t holds residue t,
+// the prefix XORs come from a scan over the lanes, the canonical-test masks
+// (sd_device.h: n1, n2, n3) from ballots, and the variants with at most one
+// deletion leave straight from the lanes' own values. The deletion pairs in
+// colexicographic order (larger position major) are the same for every
+// length, so lane l's pairs l, l + 64, ... are fixed for the whole kernel:
+// their LDS offsets and the mask bits they need stay in registers. Triples
+// run over the largest position p3 (uniform): their first two positions are
+// the pairs below p3, whose hash words are already in registers and whose
+// canonical lanes are a prefix of the pairs' ballots, except the range with
+// p2 = p3 - 1, which has its own.
+//
+// Bound: vector instructions and LDS operations, then the element writes.
+template <int NT, int TILE, bool K3>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_gen_part(const u128* __restrict__ seq,
+                                                 const uint32_t* __restrict__ vcnt, uint32_t nseq,
+                                                 int k, uint32_t idbits, uint32_t spb,
+                                                 sd::PartOut o) {
+  constexpr int NW = NT / 64, QS = GP_ROW;
+  extern __shared__ __align__(16) unsigned char lds[];
+  const uint32_t nb = 1u << o.lb;
+  uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
+  uint64_t* s_q = s_e + TILE;   // [NW][2][2][QS]: per sequence Q, then rotl(Q, 1) ^ base
+  uint64_t* s_b = s_q + NW * 4 * QS;                 // [32]
+  uint64_t* s_c = s_b + 32;                          // [32]
+  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_c + 32);
+  uint32_t* s_pref = s_cnt + nb;                      // [NT + 1]
+  uint32_t* s_tmp = s_pref + NT + 1;                 // [NW]
+  const uint32_t s0 = blockIdx.x * spb;
+  const uint32_t ns = min(spb, nseq - s0);
+  const uint32_t lane = threadIdx.x & 63u, half = lane >> 5, t = lane & 31u;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lomask = idbits >= 32 ? 0u : ~((1u << idbits) - 1u);
+  const int binshift = 32 - o.lb;  // bin = high word of the element >> binshift
+  {
+    const uint32_t c = threadIdx.x < ns ? vcnt[s0 + threadIdx.x] : 0u;
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<NT>(c, s_tmp, &total);
+    if (threadIdx.x <= ns) s_pref[threadIdx.x] = ex;
+    if (threadIdx.x == NT - 1 && ns == NT) s_pref[NT] = total;
+  }
+  if (threadIdx.x < 32) s_b[threadIdx.x] = kHashTab.b[threadIdx.x];
+  if (threadIdx.x < 32) s_c[threadIdx.x] = kHashTab.c[threadIdx.x];
+  __syncthreads();
+  // the block's sequences in chunks that fit the tile (one chunk unless the
+  // sequences have far more variants than the mean)
+  uint32_t xa = 0;
+  while (xa < ns) {
+    uint32_t lo = xa + 1, hi = ns;  // the last xb with s_pref[xb] - s_pref[xa] <= TILE
+    const uint32_t p0 = s_pref[xa];
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi + 1) >> 1;
+      if (s_pref[mid] - p0 <= (uint32_t)TILE)
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    const uint32_t xb = lo;
+    // (the pack kernel counted exactly the canonical sets, so the positions
+    // handed out below end where the next sequence's begin)
+    auto put = [&](W2 h, uint32_t id, uint32_t pos) {
+      s_e[pos] = ((uint64_t)h.hi << 32) | ((h.lo & lomask) | id);
+      atomicAdd(&s_cnt[h.hi >> binshift], 1u);
+    };
+    // this lane's deletion pairs (read for every chunk: their registers are
+    // free while the tile is written; the empty asm keeps the compiler from
+    // moving the loads out of the loop)
+    uint32_t pl_lane = lane;
+    asm volatile("" : "+v"(pl_lane));
+    uint32_t pa[GP_CHUNKS], pb[GP_CHUNKS], need1[GP_CHUNKS], need2[GP_CHUNKS];
+#pragma unroll
+    for (int c = 0; c < GP_CHUNKS; ++c) {
+      const uint4 v = kPairLanes.e[c * 64 + pl_lane];
+      pa[c] = v.x;
+      pb[c] = v.y;
+      need1[c] = v.z;
+      need2[c] = v.w;
+    }
+    uint32_t x = xa + 2 * w;
+    // each half's sequence, loaded one step ahead
+    u128 key = x < xb ? seq[s0 + min(x + half, xb - 1)] : (u128)0;
+    for (uint32_t i = threadIdx.x; i < nb; i += NT) s_cnt[i] = 0;
+    __syncthreads();
+    for (; x < xb; x += 2 * NW) {
+      const bool two = x + 1 < xb;
+      const u128 cur = key;
+      key = seq[s0 + min(x + 2 * NW + half, xb - 1)];
+      const uint32_t at0 = s_pref[min(x + half, xb)] - p0;
+      // lane t of each half: residue t and its position term
+      const uint32_t L = key_len(cur);
+      const uint32_t r = t < L ? residue_at(cur, t < 24u ? t : 0u) : 31u;
+      W2 term = rotr_w2(w2(s_b[r]), t);
+      if (t >= L) term = W2{0, 0};
+      const W2 incl{half_xor_scan(term.lo), half_xor_scan(term.hi)};
+      const W2 q = incl ^ term ^ rotl_w2(incl, 1);
+      const W2 plA{read_lane(incl.lo, 31), read_lane(incl.hi, 31)};
+      const W2 plB{read_lane(incl.lo, 63), read_lane(incl.hi, 63)};
+      const W2 pl{half ? plB.lo : plA.lo, half ? plB.hi : plA.hi};
+      // n1 bit p: p = L - 1 or s[p] != s[p + 1] (residues past the end read
+      // as 31, which no residue equals)
+      const uint32_t r1 = next_lane(r);
+      const bool c1 = t < L && (r != r1 || t + 1 == L);
+      const uint64_t n1 = __ballot(c1);
+      if (k >= 2 && t < (uint32_t)QS) {
+        const W2 base2 = w2(s_c[L >= 2 ? L - 2 : 0]) ^ rotl_w2(pl, 2);
+        uint64_t* row = s_q + (w * 2 + half) * 2 * QS;
+        const W2 q2 = rotl_w2(q, 1) ^ base2;
+        row[t] = ((uint64_t)q.hi << 32) | q.lo;
+        row[QS + t] = ((uint64_t)q2.hi << 32) | q2.lo;
+      }
+      uint32_t atA, atB;
+      {
+        // none (lane L, where q = P[L] ^ rotl(P[L], 1)) and one deletion
+        const bool keep = ((k >= 1 && c1) || t == L) && (!half || two);
+        const W2 h = w2(s_c[t < L ? L - 1 : L & 31u]) ^ rotl_w2(pl, 1) ^ q;
+        const uint64_t bal = __ballot(keep);
+        const uint32_t na = (uint32_t)__popc((uint32_t)bal);
+        const uint32_t rank = mask_rank(bal) - (half ? na : 0u);
+        if (keep) put(h, s0 + x + half, at0 + rank);
+        atA = read_lane(at0, 0) + na;
+        atB = read_lane(at0, 32) + (uint32_t)__popc((uint32_t)(bal >> 32));
+      }
+      if (k < 2) continue;
+      const uint32_t r2 = next_lane(r1);
+      const uint64_t n2 = __ballot(t < L && (r != r2 || t + 2 >= L));
+      uint64_t n3 = 0;
+      if (K3) n3 = __ballot(t < L && (r != next_lane(r2) || t + 3 >= L));
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (uint32_t sI = 0; sI < (two ? 2u : 1u); ++sI) {
+        const uint32_t SL = read_lane(L, sI ? 32 : 0);
+        const uint32_t m1 = (uint32_t)(n1 >> (sI * 32)), m2 = (uint32_t)(n2 >> (sI * 32));
+        const unsigned char* Q = reinterpret_cast<const unsigned char*>(s_q + (w * 2 + sI) * 2 * QS);
+        const uint32_t id = s0 + x + sI;
+        uint32_t at = sI ? atB : atA;
+        const uint32_t np = SL * (SL - 1) / 2;
+        W2 pw[GP_CHUNKS];
+        uint64_t kp[GP_CHUNKS], kq[GP_CHUNKS];
+        const uint32_t m3 = (uint32_t)(n3 >> (sI * 32));
+        // (the words of two chunks are read at once: most lengths have two)
+        auto pair_word = [&](int c) {
+          return w2(*reinterpret_cast<const uint64_t*>(Q + pa[c])) ^
+                 w2(*reinterpret_cast<const uint64_t*>(Q + pb[c]));
+        };
+        pw[0] = pair_word(0);
+        pw[1] = pair_word(1);
+#pragma unroll
+        for (int c = 0; c < GP_CHUNKS; ++c) {
+          if ((uint32_t)c * 64 >= np) break;  // uniform
+          if (c >= 2) pw[c] = pair_word(c);
+          const W2 h = pw[c];
+          const bool keep = ((need1[c] & ~m1) | (need2[c] & ~m2)) == 0;
+          const uint64_t bal = __ballot(keep);
+          if (keep) put(h, id, at + mask_rank(bal));
+          at += (uint32_t)__popcll(bal);
+          if (K3) {
+            kp[c] = bal;
+            // with p3 = p2 + 1: p2 needs n2, p1 needs n1, or n3 if p1, p2, p3 adjoin
+            const uint32_t b2 = 1u << ((pb[c] >> 3) - QS), b1 = need1[c] & ~b2;
+            kq[c] = __ballot(((b2 & ~m2) | (b1 & ~m1) | (need2[c] & ~m3)) == 0 &&
+                             (need1[c] >> 31) == 0);
+          }
+        }
+        if (K3 && SL >= 3) {
+          const W2 pls = sI ? plB : plA;
+          // pw holds base2 ^ Q[p1] ^ rotl(Q[p2], 1)
+          const W2 sw = w2(s_c[SL - 2]) ^ rotl_w2(pls, 2) ^ w2(s_c[SL - 3]) ^ rotl_w2(pls, 3);
+          for (uint32_t p3 = 2; p3 < SL; ++p3) {
+            if (!((m1 >> p3) & 1u)) continue;
+            const W2 tw = sw ^ rotl_w2(w2(*reinterpret_cast<const uint64_t*>(Q + p3 * 8)), 2);
+            const uint32_t u0 = (p3 - 1) * (p3 - 2) / 2, u1 = p3 * (p3 - 1) / 2;
+#pragma unroll
+            for (int c = 0; c < GP_CHUNKS; ++c) {
+              const uint32_t c0 = (uint32_t)c * 64;
+              if (c0 >= u1) break;  // uniform
+              const uint64_t below0 = u0 >= c0 + 64 ? ~0ull : u0 > c0 ? (1ull << (u0 - c0)) - 1 : 0;
+              const uint64_t below1 = u1 >= c0 + 64 ? ~0ull : (1ull << (u1 - c0)) - 1;
+              const uint64_t bal = (kp[c] & below0) | (kq[c] & below1 & ~below0);
+              if ((bal >> lane) & 1u) put(pw[c] ^ tw, id, at + mask_rank(bal));
+              at += (uint32_t)__popcll(bal);
+            }
+          }
+        }
+      }
+      // the next sequences' rows overwrite these
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    const int shift = 64 - o.lb;
+    partition_tail<NT, TILE, NT >= 1024 ? sd::PART_MAX_LB : 11, false>(
+        s_e, s_pref[xb] - p0, s_cnt, s_tmp, o.lb,
+        [&](uint64_t v) { return (uint32_t)(v >> shift); }, 0, o.elem, o.cursor, o.region, o.nbins,
+        o.nxl, o.slots, o.fill, o.cap, o.over_count);
+    __syncthreads();
+    xa = xb;
+  }
+}
+
+// ------------------------------------------------------------------ second level
+
+// Splits the regions of a first partition by `lb` more hash bits, for inputs
+// whose bins would be too large for k_filter_group. Consecutive workgroups take
+// consecutive tiles of one sub-region of the first level, so the open lines of
+// few bins are in each L2 at a time.
+template <int NT, int TILE>
+__global__ __launch_bounds__(NT) void k_part_split(sd::PartOut in, sd::PartOut o,
+                                                   uint32_t tiles) {
+  constexpr int PER = TILE / NT;
+  extern __shared__ __align__(16) unsigned char lds[];
+  const uint32_t lb = (uint32_t)(o.lb - in.lb), nb = 1u << lb;
+  uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
+  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_e + TILE);
+  uint32_t* s_tmp = s_cnt + nb;
+  const uint32_t sub = blockIdx.x / tiles;
+  const uint32_t bin = sub >> in.nxl, x = in.nxl ? sub & 7u : 0u;
+  const uint32_t cu = x * in.nbins + bin;
+  uint32_t c = in.cursor[cu];
+  if (c > in.region) c = in.fill[cu];
+  const uint32_t t0 = (blockIdx.x - sub * tiles) * TILE;
+  if (t0 >= c) return;
+  const uint32_t m = min((uint32_t)TILE, c - t0);
+  const uint64_t* __restrict__ src = in.elem + (uint64_t)((bin << in.nxl) + x) * in.region + t0;
+  const int shift = 64 - o.lb;
+  for (uint32_t i = threadIdx.x; i < nb; i += NT) s_cnt[i] = 0;
+  __syncthreads();
+  uint64_t e[PER];
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const uint32_t i = threadIdx.x + r * NT;
+    e[r] = i < m ? src[i] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const uint32_t i = threadIdx.x + r * NT;
+    if (i < m) {
+      s_e[i] = e[r];
+      atomicAdd(&s_cnt[(uint32_t)(e[r] >> shift) & (nb - 1)], 1u);
+    }
+  }
+  __syncthreads();
+  partition_tail<NT, TILE, 8, false>(
+      s_e, m, s_cnt, s_tmp, (int)lb, [&](uint64_t v) { return (uint32_t)(v >> shift) & (nb - 1); },
+      bin << lb, o.elem, o.cursor, o.region, o.nbins, o.nxl, o.slots, o.fill, o.cap, o.over_count);
+}
+
+// ------------------------------------------------------------------ filter and group
+
+// Elements a round groups in LDS at once, and the buckets it sorts them into.
+template <int SB>
+struct FilterShape {
+  // the bitmap of 2^SB bits holds, once it is no longer read, the candidates
+  // (7/8 of it) and their bucket table (1/8)
+  static constexpr int BYTES = (1 << SB) / 8;
+  static constexpr int CAP = BYTES / 8 * 7 / 8;
+  static constexpr int FULL = CAP - CAP / 8;  // candidates of a round: the rest holds pairs
+  static constexpr int NBK = BYTES / 8 / 4;
+  static constexpr int TB = SB - 3;  // bits of the second bitmap (log2)
+};
+constexpr int FG_LOADS = 8;      // elements in flight per thread
+constexpr int FG_MAX_ROUNDS = 64;
+
+// One workgroup per bin. First pass over the bin's elements: each sets the bit
+// of its low hash bits in a bitmap of 2^SB bits; one that finds its bit set
+// makes two marks in a second, independently indexed bitmap of an eighth of
+// the size. Second pass: the elements whose marks are set (every element of a
+// group of equal hashes, and 6% of the others at 0.1 elements per bit) are
+// collected in LDS, put in order of a few more hash bits, and compared inside
+// each of these small buckets; equal hashes give an id pair. If more
+// candidates are found than LDS holds they are grouped in several rounds by
+// further hash bits, each a pass over the elements. A bin that overflowed its
+// regions, or whose round still does not fit (thousands of elements of one
+// hash), is listed in big[] for the sort-and-runs path.
+//
+// Bound: the two reads of the elements (the second mostly from the Infinity
+// Cache) and LDS atomics. 100M random elements in 2048 bins: 0.28 ms.
+template <int NT, int SB>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_filter_group(sd::PartOut in, uint32_t idbits, sd::PairBins out,
+                                                     uint64_t* __restrict__ big,
+                                                     unsigned long long* __restrict__ nbig) {
+  using F = FilterShape<SB>;
+  constexpr int PER = (F::FULL + NT - 1) / NT;
+  static_assert(F::NBK <= 4 * NT, "bucket scan");
+  extern __shared__ __align__(16) unsigned char lds[];
+  uint32_t* s_seen = reinterpret_cast<uint32_t*>(lds);
+  uint32_t* s_tw = reinterpret_cast<uint32_t*>(lds + F::BYTES);
+  uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
+  uint32_t* s_bk = reinterpret_cast<uint32_t*>(lds + F::CAP * 8);
+  __shared__ uint32_t s_n, s_np;
+  __shared__ uint32_t s_tmp[NT / 64];
+  const uint32_t bin = blockIdx.x, nx = 1u << in.nxl;
+  const uint32_t lane = threadIdx.x & 63u;
+  if (bin == 0 && threadIdx.x == 0 && *in.over_count) {
+    // the overflow area (elements of overflowed bins only)
+    const unsigned long long y = atomicAdd(nbig, 1ull);
+    big[2 * y] = in.slots;
+    big[2 * y + 1] = min(in.slots + *in.over_count, in.cap);
+  }
+  uint32_t total = 0;
+  bool over = false;
+  for (uint32_t x = 0; x < nx; ++x) {
+    const uint32_t c = in.cursor[x * in.nbins + bin];
+    over |= c > in.region;
+    total += c;
+  }
+  if (total < 2) return;
+  const uint64_t base = (uint64_t)(bin << in.nxl) * in.region;
+  if (over) {
+    // its elements lie in the regions and in the overflow area
+    if (threadIdx.x < nx) {
+      const uint32_t cu = threadIdx.x * in.nbins + bin;
+      uint32_t c = in.cursor[cu];
+      if (c > in.region) c = in.fill[cu];
+      const unsigned long long y = atomicAdd(nbig, 1ull);
+      big[2 * y] = base + (uint64_t)threadIdx.x * in.region;
+      big[2 * y + 1] = base + (uint64_t)threadIdx.x * in.region + c;
+    }
+    return;
+  }
+  for (uint32_t i = threadIdx.x; i < (uint32_t)(F::BYTES + (1 << F::TB) / 8) / 4; i += NT)
+    s_seen[i] = 0;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  // every element of the bin: waves share out the regions, and each takes
+  // FG_LOADS rows of 64 elements at a time
+  constexpr uint32_t NW = NT / 64, ROW = 64 * FG_LOADS;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t parts = NW > nx ? NW / nx : 1u;
+  auto stream = [&](auto&& f) {
+    for (uint32_t x = w & (nx - 1); x < nx; x += NW) {
+      const uint32_t c = in.cursor[x * in.nbins + bin];
+      const uint64_t* __restrict__ p = in.elem + base + (uint64_t)x * in.region;
+      for (uint32_t t0 = (w >> in.nxl) * ROW; t0 < c; t0 += parts * ROW) {
+        uint64_t e[FG_LOADS];
+#pragma unroll
+        for (int u = 0; u < FG_LOADS; ++u) {
+          const uint32_t i = t0 + u * 64 + lane;
+          e[u] = i < c ? p[i] : 0;
+        }
+        f(e, c - t0);
+      }
+    }
+  };
+  // two marks per element in the second bitmap
+  auto mark = [&](uint64_t e) { return (uint32_t)(e >> idbits) * 0x9E3779B1u; };
+  constexpr uint32_t TM = (1u << F::TB) - 1;
+  stream([&](const uint64_t(&e)[FG_LOADS], uint32_t left) {
+    uint32_t old[FG_LOADS];
+#pragma unroll
+    for (int u = 0; u < FG_LOADS; ++u) {
+      const uint32_t i = (uint32_t)(e[u] >> idbits) & ((1u << SB) - 1);
+      old[u] = 0;
+      if (u * 64 + lane < left) old[u] = atomicOr(&s_seen[i >> 5], 1u << (i & 31u)) >> (i & 31u);
+    }
+#pragma unroll
+    for (int u = 0; u < FG_LOADS; ++u)
+      if (old[u] & 1u) {
+        const uint32_t j = mark(e[u]), j1 = j >> (32 - F::TB), j2 = (j >> 3) & TM;
+        atomicOr(&s_tw[j1 >> 5], 1u << (j1 & 31u));
+        atomicOr(&s_tw[j2 >> 5], 1u << (j2 & 31u));
+      }
+  });
+  __syncthreads();
+  const uint64_t idmask = (1ull << idbits) - 1;
+  const int bkshift = 64 - in.lb - __builtin_ctz(F::NBK);  // bucket: the bits below the bin's
+  uint32_t rounds = 1;
+  for (uint32_t round = 0; round < rounds; ++round) {
+    stream([&](const uint64_t(&e)[FG_LOADS], uint32_t left) {
+      uint64_t bal[FG_LOADS];
+      uint32_t tot = 0;
+#pragma unroll
+      for (int u = 0; u < FG_LOADS; ++u) {
+        const uint32_t j = mark(e[u]), j1 = j >> (32 - F::TB), j2 = (j >> 3) & TM;
+        bool keep = u * 64 + lane < left && ((s_tw[j1 >> 5] >> (j1 & 31u)) & 1u);
+        if (keep) keep = (s_tw[j2 >> 5] >> (j2 & 31u)) & 1u;
+        if (rounds > 1) keep = keep && ((uint32_t)(e[u] >> (bkshift - 6)) & (rounds - 1)) == round;
+        bal[u] = __ballot(keep);
+        tot += (uint32_t)__popcll(bal[u]);
+      }
+      if (tot) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s_n, tot);
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (at + tot <= (uint32_t)F::FULL) {
+#pragma unroll
+          for (int u = 0; u < FG_LOADS; ++u) {
+            if ((bal[u] >> lane) & 1u) s_e[at + mask_rank(bal[u])] = e[u];
+            at += (uint32_t)__popcll(bal[u]);
+          }
+        }
+      }
+    });
+    __syncthreads();
+    const uint32_t m = s_n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      s_n = 0;
+      s_np = 0;
+    }
+    if (m > (uint32_t)F::FULL) {
+      if (rounds == 1) {
+        // again in rounds of about half a capacity
+        while (rounds < (uint32_t)FG_MAX_ROUNDS && rounds * (uint32_t)F::FULL < 2 * m) rounds <<= 1;
+        round = ~0u;
+        __syncthreads();
+        continue;
+      }
+      if (threadIdx.x < nx) {
+        const uint32_t c = in.cursor[threadIdx.x * in.nbins + bin];
+        const unsigned long long y = atomicAdd(nbig, 1ull);
+        big[2 * y] = base + (uint64_t)threadIdx.x * in.region;
+        big[2 * y + 1] = base + (uint64_t)threadIdx.x * in.region + c;
+      }
+      return;
+    }
+    // order the candidates by bucket
+    uint64_t e[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const uint32_t i = threadIdx.x + r * NT;
+      e[r] = i < m ? s_e[i] : 0;
+    }
+    for (uint32_t i = threadIdx.x; i < (uint32_t)F::NBK; i += NT) s_bk[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+      if (threadIdx.x + r * NT < m)
+        atomicAdd(&s_bk[(uint32_t)(e[r] >> bkshift) & (F::NBK - 1)], 1u);
+    __syncthreads();
+    {
+      constexpr int BPT = (F::NBK + NT - 1) / NT;
+      uint32_t c[BPT], sum = 0;
+#pragma unroll
+      for (int q = 0; q < BPT; ++q) {
+        const uint32_t b = threadIdx.x * BPT + q;
+        c[q] = b < (uint32_t)F::NBK ? s_bk[b] : 0;
+        sum += c[q];
+      }
+      uint32_t tot;
+      uint32_t ex = block_excl_scan<NT>(sum, s_tmp, &tot);
+#pragma unroll
+      for (int q = 0; q < BPT; ++q) {
+        const uint32_t b = threadIdx.x * BPT + q;
+        if (b < (uint32_t)F::NBK) s_bk[b] = ex;
+        ex += c[q];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+      if (threadIdx.x + r * NT < m)
+        s_e[atomicAdd(&s_bk[(uint32_t)(e[r] >> bkshift) & (F::NBK - 1)], 1u)] = e[r];
+    __syncthreads();
+    // (every bucket's entry is its end now)
+    // each element pairs with the later ones of its bucket that share its hash
+    auto each_pair = [&](auto&& f) {
+#pragma unroll
+      for (int r = 0; r < PER; ++r) {
+        const uint32_t i = threadIdx.x + r * NT;
+        if (i >= m) break;
+        const uint64_t a = s_e[i];
+        const uint32_t end = s_bk[(uint32_t)(a >> bkshift) & (F::NBK - 1)];
+        for (uint32_t y = i + 1; y < end; ++y) {
+          const uint64_t b = s_e[y];
+          if (((b ^ a) >> idbits) == 0) {
+            const uint64_t ia = a & idmask, ib = b & idmask;
+            f(ia < ib ? ia << 32 | ib : ib << 32 | ia);
+          }
+        }
+      }
+    };
+    if (out.lb == 0) {
+      // a list per XCD: the pairs are counted, reserved together and written
+      // (a few bins hold groups of thousands: nothing here is per pair but
+      // its write)
+      uint32_t cnt = 0, tot;
+      each_pair([&](uint64_t) { ++cnt; });
+      uint32_t at = block_excl_scan<NT>(cnt, s_tmp, &tot);
+      const uint32_t x = blockIdx.x & ((1u << out.nxl) - 1);
+      if (threadIdx.x == 0 && tot) s_np = atomicAdd(&out.cursor[x], tot);
+      __syncthreads();
+      if (cnt) {
+        at += s_np;
+        uint64_t* dst = out.base + (uint64_t)x * out.region;
+        each_pair([&](uint64_t v) {
+          if (at < out.region) dst[at] = v;
+          ++at;
+        });
+      }
+    } else {
+      // to their bins: pairs collect behind the candidates and leave together,
+      // so that their reservations are in flight side by side
+      uint64_t* s_pair = s_e + m;
+      const uint32_t room = F::CAP - m;
+      each_pair([&](uint64_t v) {
+        const uint32_t at = atomicAdd(&s_np, 1u);
+        if (at < room)
+          s_pair[at] = v;
+        else
+          pair_put(out, v);
+      });
+      __syncthreads();
+      const uint32_t np = min(s_np, room);
+      for (uint32_t i = threadIdx.x; i < np; i += NT) pair_put(out, s_pair[i]);
+    }
+    __syncthreads();  // the next round rewrites the LDS
+  }
+}
+
+}  // namespace sdk
+
+namespace sd {
+
+// Dynamic LDS beyond the default limit, once per kernel and device.
+template <class F>
+static void allow_lds(F* f, size_t bytes) {
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(f),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+    (void)hipGetLastError();  // the launch reports any real problem
+}
+
+template <int NT, int TILE>
+static size_t gen_lds(int lb) {
+  return (size_t)TILE * 8 + (NT / 64) * 4 * KEY_MAX_LEN * 8 + 64 * 8 + ((size_t)4 << lb) +
+         (NT + 1) * 4 + (NT / 64) * 4;
+}
+
+template <int NT, int TILE>
+static void gen_t(const u128* seq, const uint32_t* vcnt, uint32_t n, int k, uint32_t idbits,
+                  uint32_t spb, const PartOut& o, hipStream_t s) {
+  const unsigned g = (n + spb - 1) / spb;
+  if (k == 3) {
+    const size_t lds = gen_lds<NT, TILE>(o.lb);
+    allow_lds(&sdk::k_gen_part<NT, TILE, true>, lds);
+    hipLaunchKernelGGL((sdk::k_gen_part<NT, TILE, true>), dim3(g), dim3(NT), lds, s, seq, vcnt,
+                       n, k, idbits, spb, o);
+  } else {
+    const size_t lds = gen_lds<NT, TILE>(o.lb);
+    allow_lds(&sdk::k_gen_part<NT, TILE, false>, lds);
+    hipLaunchKernelGGL((sdk::k_gen_part<NT, TILE, false>), dim3(g), dim3(NT), lds, s, seq, vcnt,
+                       n, k, idbits, spb, o);
+  }
+}
+
+void launch_gen_part(const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nkeys,
+                     int k, uint32_t idbits, const PartOut& o, hipStream_t s) {
+  if (!n) return;
+  // sequences per workgroup: their variants fill 15/16 of the tile on average
+  auto spb = [&](uint32_t tile, uint32_t most) {
+    const uint64_t per = (uint64_t)tile * 15 / 16 * n / std::max<uint64_t>(nkeys, 1);
+    return (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(1, per));
+  };
+  if (nkeys < PART_BIG_KEYS)
+    gen_t<256, 4096>(seq, vcnt, (uint32_t)n, k, idbits, spb(4096, 256), o, s);
+  else if (o.lb <= 11)  // two workgroups on a CU
+    gen_t<512, 7680>(seq, vcnt, (uint32_t)n, k, idbits, spb(7680, 512), o, s);
+  else
+    gen_t<1024, 14336>(seq, vcnt, (uint32_t)n, k, idbits, spb(14336, 1024), o, s);
+}
+
+void launch_part_split(const PartOut& in, const PartOut& o, hipStream_t s) {
+  constexpr int NT = 512, TILE = 8192;
+  const size_t lds = (size_t)TILE * 8 + ((size_t)4 << (o.lb - in.lb)) + NT / 64 * 4;
+  allow_lds(&sdk::k_part_split<NT, TILE>, lds);
+  const uint32_t tiles = (in.region + TILE - 1) / TILE;
+  hipLaunchKernelGGL((sdk::k_part_split<NT, TILE>), dim3(tiles * (in.nbins << in.nxl)), dim3(NT),
+                     lds, s, in, o, tiles);
+}
+
+template <int NT, int SB>
+static void filter_t(const PartOut& in, uint32_t idbits, const PairBins& out, uint64_t* big,
+                     unsigned long long* nbig, hipStream_t s) {
+  const size_t lds = (size_t)sdk::FilterShape<SB>::BYTES + (1 << sdk::FilterShape<SB>::TB) / 8;
+  allow_lds(&sdk::k_filter_group<NT, SB>, lds);
+  hipLaunchKernelGGL((sdk::k_filter_group<NT, SB>), dim3(in.nbins), dim3(NT), lds, s, in, idbits,
+                     out, big, nbig);
+}
+
+void launch_filter_group(const PartOut& in, uint64_t nkeys, uint32_t idbits, const PairBins& out,
+                         uint64_t* big, unsigned long long* nbig, hipStream_t s) {
+  // bins of up to 10K elements fill a small bitmap to a twelfth
+  if (nkeys >> in.lb <= 10240)
+    filter_t<256, 17>(in, idbits, out, big, nbig, s);
+  else
+    filter_t<1024, 19>(in, idbits, out, big, nbig, s);
+}
+
+}  // namespace sd

@@ -135,6 +135,8 @@ Cands oversized_group(Call& cl, const uint64_t* E, const uint64_t* big, uint64_t
 
 Cands group_segments(Call& cl, const uint64_t* E, uint32_t nk, int cap, int bits,
                      uint32_t idbits);
+void add_oversized(Call& cl, Cands& cand, const uint64_t* E, const uint64_t* big, uint64_t nb,
+                   uint32_t idbits);
 
 // Hashed grouping: elements [hash | id], LSD passes over the top `bits` hash
 // bits, grouping of each segment by its full hash in LDS.
@@ -251,24 +253,60 @@ Cands group_segments(Call& cl, const uint64_t* E, uint32_t nk, int cap, int bits
   uint64_t nb[2];
   std::memcpy(nb, readback(c, nbig, 16, s), 16);
   if (nb[0] > nbig_cap) throw Error{SD_E_HIP, "internal error: listed ranges exceed their bound"};
-  const uint64_t nb2 = nb[1];
-  c->stats.n_big_segments = (int64_t)nb2;
-  if (nb2) {
-    Cands extra = oversized_group(cl, E, big2, nb2, idbits);
-    if (extra.n) {
-      uint64_t* merged = dalloc_t<uint64_t>(c, cand.n + extra.n);
-      if (cand.n)
-        hip_check(hipMemcpyAsync(merged, cand.p, cand.n * 8, hipMemcpyDeviceToDevice, s), "merge");
-      hip_check(hipMemcpyAsync(merged + cand.n, extra.p, extra.n * 8, hipMemcpyDeviceToDevice, s),
-                "merge");
-      dfree(c, cand.p);
-      cand.p = merged;
-      cand.n += extra.n;
-    }
-    dfree(c, extra.p);
-    cl.tm.mark("oversized", 0, 0);
-  }
+  add_oversized(cl, cand, E, big2, nb[1], idbits);
   return cand;
+}
+
+// The candidates of nb listed ranges of E appended to cand.
+void add_oversized(Call& cl, Cands& cand, const uint64_t* E, const uint64_t* big, uint64_t nb,
+                   uint32_t idbits) {
+  sd_ctx* c = cl.c;
+  hipStream_t s = cl.s;
+  c->stats.n_big_segments = (int64_t)nb;
+  if (!nb) return;
+  Cands extra = oversized_group(cl, E, big, nb, idbits);
+  if (extra.n) {
+    uint64_t* merged = dalloc_t<uint64_t>(c, cand.n + extra.n);
+    if (cand.n)
+      hip_check(hipMemcpyAsync(merged, cand.p, cand.n * 8, hipMemcpyDeviceToDevice, s), "merge");
+    hip_check(hipMemcpyAsync(merged + cand.n, extra.p, extra.n * 8, hipMemcpyDeviceToDevice, s),
+              "merge");
+    dfree(c, cand.p);
+    cand.p = merged;
+    cand.n += extra.n;
+  }
+  dfree(c, extra.p);
+  cl.tm.mark("oversized", 0, 0);
+}
+
+// Whether an input of nk variants takes the partitioned grouping: the
+// automatic path with none of the knobs of the sorted path set, and
+// element positions that fit 32 bits with the regions' slack.
+bool partition_applies(const sd_ctx* c, uint64_t nk) {
+  return c->path == 0 && !c->group_cap && !c->group_bits && !c->group_batches && !c->group_shape &&
+         !c->pair_sort && !c->sort_items && nk > 0 && nk < 3000000000ull;
+}
+
+// Bins and regions of one partition level. Regions hold an eighth more than
+// their mean share (small inputs: twice it) and six standard deviations of
+// it: bins are even, since the hash is, unless single variants are shared by
+// thousands of sequences (such bins overflow and are grouped by a sort).
+PartOut part_out(Call& cl, uint64_t nk, int lb, int nxl, uint64_t over_cap, uint32_t* over_count) {
+  PartOut o{};
+  o.lb = lb;
+  o.nxl = nxl;
+  o.nbins = 1u << lb;
+  const double mean = (double)nk / (double)((uint64_t)o.nbins << nxl);
+  o.region = ((uint32_t)(mean * (nxl ? 1.125 : 2.0) + 6.0 * std::sqrt(mean)) + 64 + 15) / 16 * 16;
+  o.slots = (o.region * o.nbins) << nxl;
+  o.cap = o.slots + (uint32_t)over_cap;
+  o.elem = cl.sc.get<uint64_t>(o.cap);
+  const uint64_t nc = (uint64_t)o.nbins << nxl;
+  o.cursor = cl.sc.get<uint32_t>(nc);
+  o.fill = cl.sc.get<uint32_t>(nc);
+  o.over_count = over_count;
+  launch_fill_u32(o.cursor, 0, nc, cl.s);
+  return o;
 }
 
 }  // namespace
@@ -445,6 +483,123 @@ Verified sort_and_verify(Call& cl, uint64_t* cand, uint64_t nc, uint64_t n, int 
     throw;
   }
   return v;
+}
+
+// Partitioned grouping: the generator writes the variants straight into bins
+// of their top hash bits, and one workgroup per bin filters and groups them.
+// The id pairs go through the pair bins (pairs.cpp). Returns false if the input
+// has so many copies of single variants that even the overflow area was too
+// small (the sorted path then takes it).
+//
+// The bins. Small inputs take 2^8 bins of 512 elements or more, so that every
+// CU has one, and more bins only to keep them under 10K elements (what the
+// small bitmap filters well). Large inputs take bins of 27K to 53K elements:
+// with fewer a tile's runs get short (100M elements of 1M sequences: 0.52 ms
+// into 2^11 bins, 0.60 into 2^12), with more the filter lets too many through.
+// Beyond 2^12 bins of that size the partition takes a second level, into bins
+// a quarter as large since more bins cost little there (and their second read
+// comes from the L2): scattering 100M elements into 2^13 bins at once takes
+// 0.92 ms, two levels of 2^8 and 2^5 0.43 + 0.33; 1G elements group in 6.9 ms
+// in bins of 31K elements and in 2.8 in bins of 15K.
+bool partitioned_search(Call& cl0, const u128* seq, const u128* planes, const uint32_t* vcnt,
+                        uint64_t n, int k, uint64_t nk, Verified* v) {
+  sd_ctx* c = cl0.c;
+  hipStream_t s = cl0.s;
+  Scratch sc(c);
+  Call cl{c, s, sc, cl0.tm, cl0.counters};
+  const uint32_t idbits = n <= (1ull << 24) ? 24u : 32u;
+  int lb = 1;
+  if (nk < PART_BIG_KEYS) {
+    while (lb < 11 && ((nk >> lb) > 10240 || (lb < 8 && (nk >> lb) > 512))) ++lb;
+  } else {
+    lb = 11;
+    while ((nk >> lb) > 53248) ++lb;
+    if (lb > PART_MAX_LB) lb += 2;
+  }
+  const int nxl = nk >= (2u << 20) ? 3 : 0;
+  const int lb1 = lb > PART_MAX_LB ? 8 : lb;
+  const uint64_t over_cap = nk / 16 + 65536;
+  uint32_t* over = cl.counters + CNT_OVER;
+  launch_fill_u32(over, 0, 2, s);
+  PartOut p = part_out(cl, nk, lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
+  launch_gen_part(seq, vcnt, n, nk, k, idbits, p, s);
+  cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
+  if (lb1 < lb) {
+    const PartOut p2 = part_out(cl, nk, lb, nxl, over_cap, over);
+    launch_part_split(p, p2, s);
+    cl.tm.mark("part_split", (double)nk * 16, 1);
+    p = p2;
+  }
+  const uint64_t nbig_cap = ((uint64_t)p.nbins << nxl) + 1;
+  uint64_t* big = cl.sc.get<uint64_t>(2 * nbig_cap);
+  unsigned long long* nbig = reinterpret_cast<unsigned long long*>(cl.counters + CNT_NBIG);
+  const PairSeqs q{c->metric == SD_METRIC_HAMMING ? seq : planes, seq, nullptr, nullptr, n, n, k,
+                   c->metric == SD_METRIC_HAMMING ? 1 : 0, 1, nullptr, 0, 0};
+  Cands extra;  // candidates of the listed ranges
+  uint64_t listed = 0;
+  TileOut out;
+  const bool done = binned_pairs(
+      cl, "pairs/self", nk, q,
+      [&](const PairBins& bins) {
+        launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
+        launch_filter_group(p, nk, idbits, bins, big, nbig, s);
+        launch_pair_scatter(extra.p, extra.n, bins, s);
+      },
+      [&](const uint32_t* h, uint64_t* more) {
+        if (h[CNT_OVER1 - CNT_LBERR] || h[CNT_OVER - CNT_LBERR] > over_cap)
+          return PairNext::give_up;
+        uint64_t nb;
+        std::memcpy(&nb, h + (CNT_NBIG - CNT_LBERR), 8);
+        if (!nb || listed) return PairNext::done;
+        listed = nb;
+        extra = oversized_group(cl, p.elem, big, nb, idbits);
+        sc.blocks.push_back(extra.p);
+        *more = extra.n;
+        return PairNext::again;
+      },
+      [&](uint64_t* cand, uint64_t m) {
+        const Verified w = sort_and_verify(cl, cand, m, n, k, seq, planes);
+        TileOut t;
+        t.i = w.i;
+        t.j = w.j;
+        t.d = w.d;
+        t.n = w.n;
+        return t;
+      },
+      "group_local", &out);
+  if (!done) return false;
+  c->stats.n_big_segments = (int64_t)listed;
+  c->stats.n_cand_raw = (int64_t)out.ncand;
+  v->i = out.i;
+  v->j = out.j;
+  v->d = out.d;
+  v->n = out.n;
+  return true;
+}
+
+// Runs a path that needs more scratch than the sorted one; where the memory
+// does not suffice (a budget, a fixed area), everything it took is given back
+// and the sorted path runs instead.
+template <class F>
+bool if_memory_suffices(sd_ctx* c, F&& f) {
+  const size_t mark = c->arena_used;
+  bool done = false;
+  try {
+    done = f();
+  } catch (const Error& e) {
+    if (e.code != SD_E_NOMEM) throw;
+    done = false;
+  }
+  if (!done && c->arena) {
+    // (the look-back area may have moved into what is given back)
+    unsigned char* st = reinterpret_cast<unsigned char*>(c->status);
+    if (st >= c->arena + mark && st < c->arena + c->arena_size) {
+      c->status = nullptr;
+      c->status_words = 0;
+    }
+    c->arena_used = mark;
+  }
+  return done;
 }
 
 // Device bytes per element of a column group at its peak (the sharded
@@ -714,34 +869,45 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
   u128* planes = sc.get<u128>(n);
   uint32_t* vcnt = sc.get<uint32_t>(n);
   uint64_t* voff = sc.get<uint64_t>(n + 1);
-  // the hashed path generates each distinct variant string of a sequence once
-  launch_pack(in.codes, in.offs, n, k, c->path != 1, seq, planes, vcnt, counters + CNT_ERR, s);
+  // the hashed paths generate each distinct variant string of a sequence once
+  launch_pack(in.codes, in.offs, n, k, c->path != 1, seq, planes, vcnt, counters + CNT_ERR, s,
+              reinterpret_cast<unsigned long long*>(counters + CNT_SUMS));
+  tm.mark("pack", (double)n * (16 + 16 + 16 + 8 + 4), 1);
+  uint64_t nkeys = 0;
   {
+    // one read-back: validation flags and the key total
+    const uint32_t* h = static_cast<const uint32_t*>(readback(c, counters, CNT_TOTAL * 4, s));
+    raise_validation(h[CNT_ERR]);
+    uint64_t part[PACK_SUMS];
+    std::memcpy(part, h + CNT_SUMS, sizeof(part));
+    for (uint64_t x : part) nkeys += x;
+  }
+  c->stats.n_keys = (int64_t)nkeys;
+  // the sorted, streamed and full-key paths write variants at scanned offsets
+  auto scan_offsets = [&] {
     const uint64_t tiles = (n + scan_tile() - 1) / scan_tile();
     const uint32_t epoch = next_epoch(c, tiles, s);
     launch_scan_excl(vcnt, voff, n, c->status, cl.tile_counter(), epoch, cl.lb_err(), s);
-  }
-  tm.mark("pack_scan", (double)n * (16 + 16 + 16 + 8 + 4 + 4 + 8), 2);
-  uint64_t nkeys;
-  {
-    // one read-back: validation flags and the key total
-    hip_check(hipMemcpyAsync(counters + CNT_NKEYS, voff + n, 8, hipMemcpyDeviceToDevice, s), "copy");
-    const uint32_t* h = static_cast<const uint32_t*>(readback(c, counters, (CNT_NKEYS + 2) * 4, s));
-    raise_validation(h[CNT_ERR]);
-    std::memcpy(&nkeys, h + CNT_NKEYS, 8);
-  }
-  c->stats.n_keys = (int64_t)nkeys;
+    tm.mark("scan", (double)n * 12, 1);
+  };
 
   Verified v;
   const uint64_t group_elems = stream_group_elems(c, n, nkeys);
   if (group_elems) {
+    scan_offsets();
     v = streamed_search(cl, seq, planes, voff, n, k, nkeys, group_elems);
   } else {
     // 3-5: grouping and in-group emission
     const uint32_t nk = (uint32_t)nkeys;
     Cands cand;
     int passes = 0;
-    if (c->path == 1) {
+    const bool done = partition_applies(c, nkeys) && if_memory_suffices(c, [&] {
+                        return partitioned_search(cl, seq, planes, vcnt, n, k, nkeys, &v);
+                      });
+    if (done) {
+      // 3-7 in one
+    } else if (c->path == 1) {
+      scan_offsets();
       uint64_t* klo = sc.get<uint64_t>(nk);
       uint64_t* khi = sc.get<uint64_t>(nk);
       uint32_t* kid = sc.get<uint32_t>(nk);
@@ -749,13 +915,16 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
       tm.mark("vargen", (double)nk * 20 + (double)n * 24, 1);
       cand = fullkey_group(cl, klo, khi, kid, nk, passes);
     } else {
+      scan_offsets();
       cand = hashed_group(cl, seq, voff, n, k, nk, passes);
     }
-    sc.blocks.push_back(cand.p);
-    c->stats.n_sort_passes = passes;
-    c->stats.n_cand_raw = (int64_t)cand.n;
-    // 6-7: pair sort, verification
-    v = sort_and_verify(cl, cand.p, cand.n, n, k, seq, planes);
+    if (!done) {
+      sc.blocks.push_back(cand.p);
+      c->stats.n_sort_passes = passes;
+      c->stats.n_cand_raw = (int64_t)cand.n;
+      // 6-7: pair sort, verification
+      v = sort_and_verify(cl, cand.p, cand.n, n, k, seq, planes);
+    }
   }
   try {
     tm.finish();

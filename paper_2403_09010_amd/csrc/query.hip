@@ -17,6 +17,7 @@
 //                     distance is <= k and the score is <= max_score
 //   k_set_ranges      per-set slices of a (q, r)-sorted result
 //   k_slice_rebase    copy one set's slice with query ids made set-local
+#include "distance.h"
 #include "sd_device.h"
 #include "sd_internal.h"
 
@@ -171,40 +172,6 @@ __global__ __launch_bounds__(QNT) void k_join_seg(
 }
 
 // ------------------------------------------------------------------ weighted verify
-
-// Minimum-cost global alignment of a and b with substitution costs sub[20][20]
-// and a fixed indel cost, by the full dynamic programme (rows kept in
-// registers: both strings have at most 24 residues).
-__device__ __forceinline__ uint32_t weighted_keys(u128 a, u128 b, const uint8_t* sub,
-                                                  uint32_t indel) {
-  const uint32_t la = key_len(a), lb = key_len(b);
-  uint32_t row[KEY_MAX_LEN + 1];
-#pragma unroll
-  for (int y = 0; y <= KEY_MAX_LEN; ++y) row[y] = (uint32_t)y * indel;
-  for (uint32_t x = 1; x <= la; ++x) {
-    const uint32_t ca = key_residue(a, (int)x - 1);
-    uint32_t diag = row[0];
-    row[0] = x * indel;
-#pragma unroll
-    for (int y = 1; y <= KEY_MAX_LEN; ++y) {
-      if ((uint32_t)y <= lb) {
-        const uint32_t cb = key_residue(b, y - 1);
-        const uint32_t up = row[y];
-        uint32_t best = diag + sub[ca * 20 + cb];
-        const uint32_t del = up + indel, ins = row[y - 1] + indel;
-        best = del < best ? del : best;
-        best = ins < best ? ins : best;
-        diag = up;
-        row[y] = best;
-      }
-    }
-  }
-  uint32_t res = 0;
-#pragma unroll
-  for (int y = 0; y <= KEY_MAX_LEN; ++y)
-    if ((uint32_t)y == lb) res = row[y];
-  return res;
-}
 
 __device__ __forceinline__ uint32_t lev_small(u128 a, u128 b) {
   // unit-cost distance by the same programme (used only for the k filter)

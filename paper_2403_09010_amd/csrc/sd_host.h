@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <functional>
 #include <vector>
 
 #include "sd_internal.h"
@@ -60,7 +61,11 @@ enum : int {
   CNT_NBIG2 = 104,    // u64 count of ranges the second grouping pass lists
   CNT_CAND2 = 106,    // u64 candidate counter of the full-key emission
   CNT_STEPS = 108,    // u64 search comparisons of learned-index lookups
-  CNT_TOTAL = 128
+  CNT_OVER = 110,     // elements in the overflow area of a partition
+  CNT_OVER1 = 111,    // the same of its first level (the words from CNT_LBERR
+                      // on are the ones a PairState copies)
+  CNT_SUMS = 128,     // u64 partial sums of the variant counts
+  CNT_TOTAL = CNT_SUMS + 2 * PACK_SUMS
 };
 
 // The state of one library call on one stream. Several Call objects of one
@@ -318,6 +323,26 @@ void host_result(sd_ctx* c, uint64_t n, sd_pairs* out);
 void fill_host_slices(sd_ctx* c, const uint32_t* di, const uint32_t* dj, const uint8_t* dd,
                       uint64_t n, const std::vector<HostSlice>& slices, sd_pairs* outs,
                       hipStream_t s);
+
+// Candidates of a search through the bins of pairs.hip (pairs.cpp).
+// `produce` enqueues the kernels that put every candidate; it may run again,
+// with more room, after `check` looked at the call's counters (PAIR_COUNTERS
+// words from CNT_LBERR on). guess: the candidates expected.
+enum class PairNext {
+  done,     // every candidate was put
+  again,    // produce has more candidates to put now (`guess` more)
+  give_up   // the search takes another path
+};
+struct TileOut;
+// Returns false if check gave up, or if no shape of the bins held the
+// candidates. out: pairs sorted by (i, j), in pool blocks. sort_pairs orders a
+// dense array of distinct verified pairs instead, where one first id has
+// thousands of them.
+bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, const PairSeqs& q,
+                  const std::function<void(const PairBins&)>& produce,
+                  const std::function<PairNext(const uint32_t*, uint64_t*)>& check,
+                  const std::function<TileOut(uint64_t*, uint64_t)>& sort_pairs,
+                  const char* stage, TileOut* out);
 
 struct Cands {
   uint64_t* p = nullptr;  // pool block owned by the caller

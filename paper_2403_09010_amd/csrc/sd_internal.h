@@ -124,8 +124,11 @@ void launch_scan_excl(const uint32_t* in, uint64_t* out, uint64_t n, uint64_t* s
 // planes (optional): per sequence its residues' five bit planes (plane b in
 // bits [24 b, 24 b + 24)) and its length in bits 127..120, the pattern form
 // of the verification's distance
+// sums (optional): PACK_SUMS zeroed counters that receive the total of vcnt
+constexpr uint32_t PACK_SUMS = 64;
 void launch_pack(const uint8_t* codes, const int64_t* offs, uint64_t n, int k, bool distinct,
-                 u128* seq, u128* planes, uint32_t* vcnt, uint32_t* err, hipStream_t s);
+                 u128* seq, u128* planes, uint32_t* vcnt, uint32_t* err, hipStream_t s,
+                 unsigned long long* sums = nullptr);
 void launch_vargen(const u128* seq, const uint64_t* voff, uint64_t nseq, int k,
                    uint64_t* key_lo, uint64_t* key_hi, uint32_t* id, hipStream_t s);
 void launch_emit_runs(const uint64_t* key_lo, const uint64_t* key_hi, const uint32_t* id,
@@ -224,6 +227,99 @@ void launch_group_listed(int cap, const uint64_t* E, const uint64_t* big,
                          const unsigned long long* nlisted, uint64_t max_listed, uint32_t idbits,
                          uint32_t splitbit, const ShardArgs& out, uint64_t* big2,
                          unsigned long long* nbig2, hipStream_t s);
+// Partitioned grouping (partition.hip): elements in 2^lb bins by their top
+// hash bits. Bin b's elements lie in 2^nxl regions of `region` slots from
+// elem[(b << nxl) * region]; region x of it holds cursor[x * nbins + b] of
+// them. A run that did not fit its region went to elem[slots, slots +
+// *over_count) instead (nothing is written from cap on): the cursor then
+// exceeds the region, which holds fill[x * nbins + b] elements.
+struct PartOut {
+  uint64_t* elem;
+  uint32_t* cursor;      // nbins << nxl, zeroed before the kernel
+  uint32_t* fill;        // nbins << nxl, set only where the cursor exceeds the region
+  uint32_t* over_count;  // zeroed too
+  uint32_t region, slots, cap, nbins;
+  int lb, nxl;
+};
+// Inputs of at least this many variants are generated and grouped by the
+// large workgroups (1,024 threads, one or two on a CU).
+constexpr uint64_t PART_BIG_KEYS = 16ull << 20;
+// most bins (log2) one kernel partitions into
+constexpr int PART_MAX_LB = 12;
+// every distinct <= k-deletion variant of n packed sequences (vcnt: their
+// counts, nkeys in all), partitioned
+void launch_gen_part(const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nkeys, int k,
+                     uint32_t idbits, const PartOut& o, hipStream_t s);
+// the regions of `in` split into the bins of o (o.lb > in.lb); the overflow
+// area of `in` is not read
+void launch_part_split(const PartOut& in, const PartOut& o, hipStream_t s);
+// Candidate pairs (i << 32 | j) in 2^lb bins by a hash of the pair
+// (pair_put.h): bin b's lie in 2^nxl regions of `region` slots from
+// base[(b << nxl) * region]; region x of it received cursor[x * nbins + b] of
+// them (those past the region are lost and counted). lb = 0: plain lists, one
+// per region.
+struct PairBins {
+  uint64_t* base;
+  uint32_t* cursor;  // nbins << nxl, zeroed before the producer
+  uint32_t region, nbins;
+  int lb, nxl;
+};
+// Verification of binned candidates (pairs.hip). mode 0: Levenshtein distance
+// of a = bit planes of the first sequences and b = packed keys of the second;
+// 1: Hamming distance, a = packed keys; 2: the sum over both chains (a, b, a2,
+// b2); 3: Levenshtein within k, then the weighted score (a2 = packed keys of
+// the first). First ids are below na, second ids below nb. self_pairs: pairs
+// with i >= j are dropped.
+struct PairSeqs {
+  const u128 *a, *b, *a2, *b2;
+  uint64_t na, nb;
+  int k, mode, self_pairs;
+  const uint8_t* subst;
+  uint32_t indel, max_score;
+};
+constexpr uint32_t PF_OVERFLOW = 1;  // a region was full: candidates were lost
+constexpr uint32_t PF_LONG = 2;      // one first id has too many pairs to order in LDS
+constexpr uint32_t PAIR_COUNTERS = 16;
+struct PairState {  // zeroed before the producer; read back when the search is done
+  uint32_t flags, nlong;
+  unsigned long long count;           // pairs kept
+  unsigned long long raw[PACK_SUMS];  // candidates put, in parts
+  uint32_t counters[PAIR_COUNTERS];   // a copy of the call's counters
+};
+struct PairBufs {
+  uint64_t* kv;     // slots of the bins: kept pairs, ...
+  uint32_t* rank;   // ... their rank among their first id's pairs
+  uint8_t* kd;      // ... and distance
+  uint32_t* kept;   // nbins: how many
+  uint32_t* icnt;   // na, zeroed: pairs kept per first id
+  uint64_t* off;    // na + 1: exclusive scan of icnt
+  uint32_t* ti;     // slots: kept pairs by first id
+  uint32_t* tj;
+  uint8_t* td;
+  uint32_t* longs;  // first ids with many pairs
+  uint32_t long_cap;
+  PairState* state;
+  uint32_t* err;
+};
+// most candidates a bin may hold
+uint32_t pair_bin_max(bool large);
+// kv, rank, kd, kept, icnt, longs from the binned candidates
+void launch_pair_verify(const PairBins& in, bool large, const PairSeqs& q, const PairBufs& b,
+                        hipStream_t s);
+// the candidates of one level of bins to the next (o.lb > in.lb); what in's
+// regions lost is counted in state
+void launch_pair_split(const PairBins& in, const PairBins& o, PairState* state, hipStream_t s);
+// ti, tj, td from those and off
+void launch_pair_place(const PairBins& in, const PairBufs& b, hipStream_t s);
+// the placed pairs in order to o*[0, cap), their number and PAIR_COUNTERS words
+// of counters to b.state
+void launch_pair_order(const PairBufs& b, uint64_t n, uint32_t* oi, uint32_t* oj, uint8_t* od,
+                       uint64_t cap, const uint32_t* counters, hipStream_t s);
+void launch_pair_scatter(const uint64_t* cand, uint64_t n, const PairBins& o, hipStream_t s);
+// id pairs of equal hashes in every bin; big receives element ranges that
+// take the sort-and-runs path instead (at most (nbins << nxl) + 1)
+void launch_filter_group(const PartOut& in, uint64_t nkeys, uint32_t idbits, const PairBins& out,
+                         uint64_t* big, unsigned long long* nbig, hipStream_t s);
 void launch_gather_big(const uint64_t* E, const uint64_t* big, const uint64_t* out_off,
                        uint32_t nseg, uint64_t* out, hipStream_t s);
 void launch_emit_hash_runs(const uint64_t* E, uint64_t n, uint32_t idbits, uint64_t* cand,

@@ -1,0 +1,98 @@
+"""The automatic grouping of self searches (variants partitioned into hash bins,
+each filtered and grouped by one workgroup) against the sorted grouping path,
+at the sizes where its plan changes and on inputs that overflow its bins."""
+import numpy as np
+import pytest
+
+import cdr3gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def paths():
+    from paper_2403_09010_amd import Context
+    from paper_2403_09010_amd.symdel import OPT_PATH
+    a, b = Context(0), Context(0)
+    b.set_option(OPT_PATH, 2)
+    yield a, b
+    a.close()
+    b.close()
+
+
+def csr(strings):
+    offs = np.zeros(len(strings) + 1, dtype=np.int64)
+    offs[1:] = np.cumsum([len(s) for s in strings])
+    return np.frombuffer(b"".join(strings), dtype=np.uint8).copy(), offs
+
+
+def strings_of(seed, n):
+    c, o = cdr3gen.generate(seed, n)
+    return [c[o[t]:o[t + 1]].tobytes() for t in range(n)]
+
+
+def same(paths, c, o, k, hamming=False):
+    print(f"[partition] {len(o) - 1} sequences k={k} hamming={hamming}", flush=True)
+    a = paths[0].self_search(c, o, k, hamming=hamming)
+    b = paths[1].self_search(c, o, k, hamming=hamming)
+    assert len(a) == len(b)
+    assert np.array_equal(a.i, b.i) and np.array_equal(a.j, b.j) and np.array_equal(a.d, b.d)
+    sa, sb = paths[0].stats(), paths[1].stats()
+    assert sa["n_keys"] == sb["n_keys"] and sa["n_sort_passes"] == 0
+    return sa
+
+
+# one bin; bins at their smallest; around 2^21 variants (one region per bin,
+# then eight); around 2^24 (small and large workgroups); 2^12 bins; two levels
+@pytest.mark.parametrize("n,k", [(1, 2), (37, 0), (300, 2), (20_800, 2), (20_950, 2), (166_000, 2),
+                                 (168_500, 2), (1_250_000, 2), (470_000, 3), (2_100_000, 1)])
+def test_plan_sizes(paths, n, k):
+    same(paths, *cdr3gen.generate(100 + n % 97, n), k)
+
+
+def test_hamming(paths):
+    same(paths, *cdr3gen.generate(5, 60_000), 2, hamming=True)
+
+
+@pytest.mark.parametrize("length", [1, 2, 3, 23, 24])
+def test_lengths(paths, length):
+    rng = np.random.default_rng(length)
+    pick = rng.integers(0, 3 if length > 3 else 20, (400, length)).astype(np.uint8)
+    for k in (0, 1, 2, 3):
+        same(paths, *csr([bytes(x) for x in pick]), k)
+
+
+def test_sequences_sorted_by_length(paths):
+    # consecutive long sequences: workgroups hold more variants than the mean
+    s = sorted(strings_of(9, 30_000), key=len)
+    same(paths, *csr(s), 2)
+    same(paths, *csr(s), 3)
+
+
+def test_every_element_shared(paths):
+    # each sequence twice: every element passes the filter, so bins are
+    # grouped in several rounds
+    s = strings_of(7, 60_000)
+    assert same(paths, *csr(s + s), 2)["n_big_segments"] == 0
+
+
+def test_overflowing_bins(paths):
+    # 2,000 copies of one sequence among 200,000: its variants' bins overflow
+    # their regions and are grouped by a sort
+    s = strings_of(8, 200_000)
+    assert same(paths, *csr(s + [s[17]] * 2_000), 1)["n_big_segments"] > 0
+
+
+def test_overflow_area_too_small(paths):
+    # copies only: the overflow area overflows and the sorted path takes over
+    s = strings_of(11, 3)
+    from paper_2403_09010_amd.symdel import OPT_PATH  # noqa: F401
+    print("[partition] copies of three sequences", flush=True)
+    c, o = csr([s[t % 3] for t in range(9_000)])
+    a, b = paths[0].self_search(c, o, 1), paths[1].self_search(c, o, 1)
+    assert np.array_equal(a.i, b.i) and np.array_equal(a.j, b.j) and np.array_equal(a.d, b.d)
+
+
+def test_wide_ids(paths):
+    # more than 2^24 sequences: 32 id bits and 32 hash bits
+    same(paths, *cdr3gen.generate(13, (1 << 24) + 3), 0)
