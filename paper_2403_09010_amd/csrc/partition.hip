@@ -65,6 +65,21 @@ __device__ __forceinline__ uint32_t residue_at(u128 key, uint32_t t) {
   return (uint32_t)((s >= 56 ? top : lo) >> (s >= 56 ? s - 56 : s)) & 31u;
 }
 
+// The end of the chunk of sequences from xa on whose variants fit the tile.
+template <int TILE>
+__device__ __forceinline__ uint32_t chunk_end(const uint32_t* s_pref, uint32_t xa, uint32_t ns) {
+  uint32_t lo = xa + 1, hi = ns;
+  const uint32_t p0 = s_pref[xa];
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi + 1) >> 1;
+    if (s_pref[mid] - p0 <= (uint32_t)TILE)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
 // Deletion pairs in colexicographic order (pair u = p2 (p2 - 1) / 2 + p1, the
 // same for every length: a string of length L has the first C(L, 2)): the LDS
 // byte offsets of the pair's two words in its sequence's rows, and the bits of
@@ -114,6 +129,10 @@ static __constant__ PairLanes kPairLanes = make_pair_lanes();
 // p2 = p3 - 1, which has its own.
 //
 // Bound: vector instructions and LDS operations, then the element writes.
+// 100M variants of 1M sequences (k = 2): 0.47-0.52 ms, of which the generation
+// alone is 0.26; two workgroups of 512 threads on a CU, so that one generates
+// while the other writes (one of 1,024: 0.55). Generating them in sequence
+// order took 0.40 and the first radix pass another 0.39.
 template <int NT, int TILE, bool K3>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_gen_part(const u128* __restrict__ seq,
                                                  const uint32_t* __restrict__ vcnt, uint32_t nseq,
@@ -149,16 +168,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   // sequences have far more variants than the mean)
   uint32_t xa = 0;
   while (xa < ns) {
-    uint32_t lo = xa + 1, hi = ns;  // the last xb with s_pref[xb] - s_pref[xa] <= TILE
-    const uint32_t p0 = s_pref[xa];
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi + 1) >> 1;
-      if (s_pref[mid] - p0 <= (uint32_t)TILE)
-        lo = mid;
-      else
-        hi = mid - 1;
-    }
-    const uint32_t xb = lo;
+    const uint32_t p0 = s_pref[xa], xb = chunk_end<TILE>(s_pref, xa, ns);
     // (the pack kernel counted exactly the canonical sets, so the positions
     // handed out below end where the next sequence's begin)
     auto put = [&](W2 h, uint32_t id, uint32_t pos) {
@@ -288,6 +298,187 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
       // the next sequences' rows overwrite these
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    const int shift = 64 - o.lb;
+    partition_tail<NT, TILE, NT >= 1024 ? sd::PART_MAX_LB : 11, false>(
+        s_e, s_pref[xb] - p0, s_cnt, s_tmp, o.lb,
+        [&](uint64_t v) { return (uint32_t)(v >> shift); }, 0, o.elem, o.cursor, o.region, o.nbins,
+        o.nxl, o.slots, o.fill, o.cap, o.over_count);
+    __syncthreads();
+    xa = xb;
+  }
+}
+
+// ------------------------------------------------------------------ paired chains
+
+// Paired-chain records: a record (a, b) is the joined string a T b, whose
+// variants delete up to two residues and never T (residue code 20). T equals no
+// residue, so the canonical rule of single chains holds for the joined string
+// with T's own bits cleared from the masks.
+constexpr uint32_t PAIR_T = 20;
+
+__device__ __forceinline__ uint64_t low_bits(uint32_t n) { return n >= 64 ? ~0ull : (1ull << n) - 1; }
+
+// Distinct variants of each record with at most k <= 2 deletions (the sum over
+// the canonical sets), their total as in k_pack.
+__global__ __launch_bounds__(256) void k_paired_distinct(const u128* __restrict__ pa,
+                                                         const u128* __restrict__ pb, uint64_t n,
+                                                         int k, uint32_t* __restrict__ vcnt,
+                                                         unsigned long long* __restrict__ sums) {
+  __shared__ uint32_t s_tmp[4];
+  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  uint32_t c = 0;
+  if (i < n) {
+    const u128 a = pa[i], b = pb[i];
+    const uint32_t la = (uint32_t)(a >> 120), L = la + 1 + (uint32_t)(b >> 120);
+    uint64_t d1 = 0, d2 = 0;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+      const uint64_t x = (uint64_t)(a >> (24 * q)) & 0xFFFFFFu, y = (uint64_t)(b >> (24 * q)) & 0xFFFFFFu;
+      const uint64_t pl = x | (uint64_t)((PAIR_T >> q) & 1u) << la | y << (la + 1);
+      d1 |= pl ^ (pl >> 1);
+      d2 |= pl ^ (pl >> 2);
+    }
+    const uint64_t keep = ~(1ull << la);  // L >= 3
+    const uint64_t n1 = ((d1 & low_bits(L - 1)) | 1ull << (L - 1)) & keep;
+    const uint64_t n2 = ((d2 & low_bits(L - 2)) | 1ull << (L - 2)) & keep;
+    c = 1;
+    if (k >= 1) c += (uint32_t)__popcll(n1);
+    if (k >= 2)
+      for (uint64_t m = n1 & ~1ull; m; m &= m - 1) {
+        const uint32_t p2 = (uint32_t)__builtin_ctzll(m);
+        c += (uint32_t)__popcll(n1 & low_bits(p2 - 1)) + (uint32_t)((n2 >> (p2 - 1)) & 1u);
+      }
+    vcnt[i] = c;
+  }
+  uint32_t total;
+  block_excl_scan<256>(c, s_tmp, &total);
+  if (threadIdx.x == 0 && total)
+    atomicAdd(&sums[blockIdx.x % sd::PACK_SUMS], (unsigned long long)total);
+}
+
+// k_gen_part for paired-chain records: one record per wave, lane t holding
+// position t of the joined string. The larger deleted position p2 is uniform
+// and lane p1 has the other's hash word, so a pair costs one XOR with a word
+// of p2 and the canonical lanes are mask bits; two values of p2 <= 32 share a
+// step, one per half of the wave. Bound: vector instructions and LDS
+// operations. 1M records, k = 2: 2.1 ms for 382M distinct variants; unranking
+// each deletion set and hashing its whole joined string took 12.1 (470M).
+template <int NT, int TILE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_gen_part_paired(
+    const u128* __restrict__ sa, const u128* __restrict__ sb, const uint32_t* __restrict__ vcnt,
+    uint32_t nrec, int k, uint32_t idbits, uint32_t spb, sd::PartOut o) {
+  constexpr int NW = NT / 64;
+  extern __shared__ __align__(16) unsigned char lds[];
+  const uint32_t nb = 1u << o.lb;
+  uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
+  uint64_t* s_b = s_e + TILE;                        // [32]
+  uint64_t* s_c = s_b + 32;                          // [64]
+  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_c + 64);
+  uint32_t* s_pref = s_cnt + nb;                     // [NT + 1]
+  uint32_t* s_tmp = s_pref + NT + 1;                 // [NW]
+  const uint32_t s0 = blockIdx.x * spb;
+  const uint32_t ns = min(spb, nrec - s0);
+  const uint32_t t = threadIdx.x & 63u, half = t >> 5;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lomask = idbits >= 32 ? 0u : ~((1u << idbits) - 1u);
+  const int binshift = 32 - o.lb;
+  {
+    const uint32_t c = threadIdx.x < ns ? vcnt[s0 + threadIdx.x] : 0u;
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<NT>(c, s_tmp, &total);
+    if (threadIdx.x <= ns) s_pref[threadIdx.x] = ex;
+    if (threadIdx.x == NT - 1 && ns == NT) s_pref[NT] = total;
+  }
+  if (threadIdx.x < 32) s_b[threadIdx.x] = kHashTab.b[threadIdx.x];
+  if (threadIdx.x < 64) s_c[threadIdx.x] = kHashTab.c[threadIdx.x];
+  __syncthreads();
+  uint32_t xa = 0;
+  while (xa < ns) {
+    const uint32_t p0 = s_pref[xa], xb = chunk_end<TILE>(s_pref, xa, ns);
+    auto put = [&](W2 h, uint32_t id, uint32_t pos) {
+      s_e[pos] = ((uint64_t)h.hi << 32) | ((h.lo & lomask) | id);
+      atomicAdd(&s_cnt[h.hi >> binshift], 1u);
+    };
+    uint32_t x = xa + w;
+    u128 ka = 0, kb = 0;  // the wave's record, loaded one step ahead
+    if (x < xb) {
+      ka = sa[s0 + x];
+      kb = sb[s0 + x];
+    }
+    for (uint32_t i = threadIdx.x; i < nb; i += NT) s_cnt[i] = 0;
+    __syncthreads();
+    for (; x < xb; x += NW) {
+      const u128 a = ka, b = kb;
+      const uint32_t nx = min(x + NW, xb - 1);
+      ka = sa[s0 + nx];
+      kb = sb[s0 + nx];
+      const uint32_t id = s0 + x;
+      uint32_t at = __builtin_amdgcn_readfirstlane(s_pref[x] - p0);
+      const uint32_t la = key_len(a), L = la + 1 + key_len(b);
+      const uint32_t tb = t - la - 1;  // position in b
+      const uint32_t r = t < la    ? residue_at(a, min(t, 23u))
+                         : t == la ? PAIR_T
+                         : t < L   ? residue_at(b, min(tb, 23u))
+                                   : 31u;
+      W2 word = w2(s_b[r]);
+      if (half) word = W2{word.hi, word.lo};  // rotate by 32
+      W2 term = rotr_w2(word, t & 31u);
+      if (t >= L) term = W2{0, 0};
+      W2 incl{half_xor_scan(term.lo), half_xor_scan(term.hi)};
+      const W2 low{read_lane(incl.lo, 31), read_lane(incl.hi, 31)};
+      if (half) incl = incl ^ low;
+      const W2 q = incl ^ term ^ rotl_w2(incl, 1);
+      const W2 pl{read_lane(incl.lo, 63), read_lane(incl.hi, 63)};
+      // (residues past the end read as 31, which no position equals)
+      const uint32_t r1 = next_lane(r);
+      const bool c1 = t < L && t != la && (r != r1 || t + 1 == L);
+      const uint64_t n1 = __ballot(c1);
+      {
+        // none (lane L, where q = P[L] ^ rotl(P[L], 1)) and one deletion
+        const bool keep = (k >= 1 && c1) || t == L;
+        const W2 h = w2(s_c[t < L ? L - 1 : L]) ^ rotl_w2(pl, 1) ^ q;
+        const uint64_t bal = __ballot(keep);
+        if (keep) put(h, id, at + mask_rank(bal));
+        at += (uint32_t)__popcll(bal);
+      }
+      if (k < 2) continue;
+      const uint32_t r2 = next_lane(r1);
+      const uint64_t n2 = __ballot(t < L && t != la && (r != r2 || t + 2 >= L));
+      const W2 base = w2(s_c[L - 2]) ^ rotl_w2(pl, 2);
+      const W2 mine = base ^ q;  // lane p1's words
+      W2 both{(uint32_t)__shfl((int)mine.lo, (int)(t & 31u), 64),
+              (uint32_t)__shfl((int)mine.hi, (int)(t & 31u), 64)};
+      // lanes p1 < p2 of the canonical pairs with p2 >= 1
+      auto lanes_of = [&](uint32_t p2) {
+        return (n1 & low_bits(p2 - 1)) | (n2 & (1ull << (p2 - 1)));
+      };
+      auto word_of = [&](uint32_t p2) {
+        return rotl_w2(W2{read_lane(q.lo, (int)p2), read_lane(q.hi, (int)p2)}, 1);
+      };
+      uint64_t m = n1 & low_bits(33) & ~1ull;
+      while (m) {
+        const uint32_t a2 = (uint32_t)__builtin_ctzll(m);
+        m &= m - 1;
+        uint64_t bal = lanes_of(a2);
+        W2 wa = word_of(a2), wb = wa;
+        if (m) {
+          const uint32_t b2 = (uint32_t)__builtin_ctzll(m);
+          m &= m - 1;
+          bal |= lanes_of(b2) << 32;
+          wb = word_of(b2);
+        }
+        const W2 wd{half ? wb.lo : wa.lo, half ? wb.hi : wa.hi};
+        if ((bal >> t) & 1u) put(both ^ wd, id, at + mask_rank(bal));
+        at += (uint32_t)__popcll(bal);
+      }
+      for (m = n1 & ~low_bits(33); m; m &= m - 1) {
+        const uint32_t p2 = (uint32_t)__builtin_ctzll(m);
+        const uint64_t bal = lanes_of(p2);
+        if ((bal >> t) & 1u) put(mine ^ word_of(p2), id, at + mask_rank(bal));
+        at += (uint32_t)__popcll(bal);
+      }
     }
     __syncthreads();
     const int shift = 64 - o.lb;
@@ -645,20 +836,54 @@ static void gen_t(const u128* seq, const uint32_t* vcnt, uint32_t n, int k, uint
   }
 }
 
+// Sequences per workgroup (at most `most`): their variants fill 15/16 of the
+// tile on average.
+static uint32_t seqs_per_tile(uint64_t n, uint64_t nkeys, uint32_t tile, uint32_t most) {
+  const uint64_t per = (uint64_t)tile * 15 / 16 * n / std::max<uint64_t>(nkeys, 1);
+  return (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(1, per));
+}
+
 void launch_gen_part(const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nkeys,
                      int k, uint32_t idbits, const PartOut& o, hipStream_t s) {
   if (!n) return;
-  // sequences per workgroup: their variants fill 15/16 of the tile on average
-  auto spb = [&](uint32_t tile, uint32_t most) {
-    const uint64_t per = (uint64_t)tile * 15 / 16 * n / std::max<uint64_t>(nkeys, 1);
-    return (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(1, per));
-  };
   if (nkeys < PART_BIG_KEYS)
-    gen_t<256, 4096>(seq, vcnt, (uint32_t)n, k, idbits, spb(4096, 256), o, s);
+    gen_t<256, 4096>(seq, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 4096, 256), o, s);
   else if (o.lb <= 11)  // two workgroups on a CU
-    gen_t<512, 7680>(seq, vcnt, (uint32_t)n, k, idbits, spb(7680, 512), o, s);
+    gen_t<512, 7680>(seq, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 7680, 512), o, s);
   else
-    gen_t<1024, 14336>(seq, vcnt, (uint32_t)n, k, idbits, spb(14336, 1024), o, s);
+    gen_t<1024, 14336>(seq, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 14336, 1024), o, s);
+}
+
+void launch_paired_distinct(const u128* pa, const u128* pb, uint64_t n, int k, uint32_t* vcnt,
+                            unsigned long long* sums, hipStream_t s) {
+  if (!n) return;
+  hipLaunchKernelGGL(sdk::k_paired_distinct, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pa,
+                     pb, n, k, vcnt, sums);
+}
+
+template <int NT, int TILE>
+static void gen_paired_t(const u128* sa, const u128* sb, const uint32_t* vcnt, uint32_t n, int k,
+                         uint32_t idbits, uint32_t spb, const PartOut& o, hipStream_t s) {
+  const size_t lds = (size_t)TILE * 8 + 96 * 8 + ((size_t)4 << o.lb) + (NT + 1) * 4 + NT / 64 * 4;
+  allow_lds(&sdk::k_gen_part_paired<NT, TILE>, lds);
+  hipLaunchKernelGGL((sdk::k_gen_part_paired<NT, TILE>), dim3((n + spb - 1) / spb), dim3(NT), lds,
+                     s, sa, sb, vcnt, n, k, idbits, spb, o);
+}
+
+void launch_gen_part_paired(const u128* sa, const u128* sb, const uint32_t* vcnt, uint64_t n,
+                            uint64_t nkeys, int k, uint32_t idbits, const PartOut& o,
+                            hipStream_t s) {
+  if (!n) return;
+  if (k > 2) throw Error{SD_E_INVAL, "internal error: at most two deletions"};
+  if (nkeys < PART_BIG_KEYS)
+    gen_paired_t<256, 4096>(sa, sb, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 4096, 256),
+                            o, s);
+  else if (o.lb <= 11)
+    gen_paired_t<512, 7680>(sa, sb, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 7680, 512),
+                            o, s);
+  else
+    gen_paired_t<1024, 14336>(sa, sb, vcnt, (uint32_t)n, k, idbits,
+                              seqs_per_tile(n, nkeys, 14336, 1024), o, s);
 }
 
 void launch_part_split(const PartOut& in, const PartOut& o, hipStream_t s) {

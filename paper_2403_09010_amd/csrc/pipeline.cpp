@@ -485,8 +485,9 @@ Verified sort_and_verify(Call& cl, uint64_t* cand, uint64_t nc, uint64_t n, int 
   return v;
 }
 
-// Partitioned grouping: the generator writes the variants straight into bins
-// of their top hash bits, and one workgroup per bin filters and groups them.
+// Partitioned grouping: `generate` (given the regions and the id bits) writes
+// the nk variants of n sequences straight into bins of their top hash bits, and
+// one workgroup per bin filters and groups them.
 // The id pairs go through the pair bins (pairs.cpp). Returns false if the input
 // has so many copies of single variants that even the overflow area was too
 // small (the sorted path then takes it).
@@ -501,8 +502,10 @@ Verified sort_and_verify(Call& cl, uint64_t* cand, uint64_t nc, uint64_t n, int 
 // comes from the L2): scattering 100M elements into 2^13 bins at once takes
 // 0.92 ms, two levels of 2^8 and 2^5 0.43 + 0.33; 1G elements group in 6.9 ms
 // in bins of 31K elements and in 2.8 in bins of 15K.
-bool partitioned_search(Call& cl0, const u128* seq, const u128* planes, const uint32_t* vcnt,
-                        uint64_t n, int k, uint64_t nk, Verified* v) {
+bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, const PairSeqs& q, const char* hint,
+                        const std::function<void(const PartOut&, uint32_t)>& generate,
+                        const std::function<Verified(Call&, uint64_t*, uint64_t)>& sort_pairs,
+                        Verified* v) {
   sd_ctx* c = cl0.c;
   hipStream_t s = cl0.s;
   Scratch sc(c);
@@ -522,7 +525,7 @@ bool partitioned_search(Call& cl0, const u128* seq, const u128* planes, const ui
   uint32_t* over = cl.counters + CNT_OVER;
   launch_fill_u32(over, 0, 2, s);
   PartOut p = part_out(cl, nk, lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
-  launch_gen_part(seq, vcnt, n, nk, k, idbits, p, s);
+  generate(p, idbits);
   cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
   if (lb1 < lb) {
     const PartOut p2 = part_out(cl, nk, lb, nxl, over_cap, over);
@@ -533,13 +536,11 @@ bool partitioned_search(Call& cl0, const u128* seq, const u128* planes, const ui
   const uint64_t nbig_cap = ((uint64_t)p.nbins << nxl) + 1;
   uint64_t* big = cl.sc.get<uint64_t>(2 * nbig_cap);
   unsigned long long* nbig = reinterpret_cast<unsigned long long*>(cl.counters + CNT_NBIG);
-  const PairSeqs q{c->metric == SD_METRIC_HAMMING ? seq : planes, seq, nullptr, nullptr, n, n, k,
-                   c->metric == SD_METRIC_HAMMING ? 1 : 0, 1, nullptr, 0, 0};
   Cands extra;  // candidates of the listed ranges
   uint64_t listed = 0;
   TileOut out;
   const bool done = binned_pairs(
-      cl, "pairs/self", nk, q,
+      cl, hint, nk, q,
       [&](const PairBins& bins) {
         launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
         launch_filter_group(p, nk, idbits, bins, big, nbig, s);
@@ -558,7 +559,7 @@ bool partitioned_search(Call& cl0, const u128* seq, const u128* planes, const ui
         return PairNext::again;
       },
       [&](uint64_t* cand, uint64_t m) {
-        const Verified w = sort_and_verify(cl, cand, m, n, k, seq, planes);
+        const Verified w = sort_pairs(cl, cand, m);
         TileOut t;
         t.i = w.i;
         t.j = w.j;
@@ -805,38 +806,71 @@ void paired_self_search(sd_ctx* c, const sd_seqs* a, const sd_seqs* b, int k, sd
   uint64_t* voff = sc.get<uint64_t>(n + 1);
   launch_pack(ia.codes, ia.offs, n, 0, false, sa, pa, nullptr, counters + CNT_ERR, s);
   launch_pack(ib.codes, ib.offs, n, 0, false, sb, pb, nullptr, counters + CNT_ERR, s);
-  launch_paired_count(sa, sb, n, k, vcnt, s);
-  {
+  auto read_counters = [&](uint64_t* nkeys) {
+    const uint32_t* h = static_cast<const uint32_t*>(readback(c, counters, CNT_TOTAL * 4, s));
+    raise_validation(h[CNT_ERR]);
+    uint64_t part[PACK_SUMS];
+    std::memcpy(part, h + CNT_SUMS, sizeof(part));
+    *nkeys = 0;
+    for (uint64_t x : part) *nkeys += x;
+  };
+  Verified v;
+  bool done = false;
+  uint64_t nkeys = 0;
+  // up to two deletions: each distinct variant once, as in the self search
+  if (k <= 2) {
+    launch_paired_distinct(pa, pb, n, k, vcnt,
+                           reinterpret_cast<unsigned long long*>(counters + CNT_SUMS), s);
+    tm.mark("pack", (double)n * 2 * (16 + 16 + 16 + 8) + (double)n * 4, 3);
+    read_counters(&nkeys);
+    c->stats.n_keys = (int64_t)nkeys;
+    const PairSeqs q{pa, sa, pb, sb, n, n, k, 2, 1, nullptr, 0, 0};
+    // verification reads the second chains' planes and keys: a2 = planes
+    done = partition_applies(c, nkeys) && if_memory_suffices(c, [&] {
+             return partitioned_search(
+                 cl, n, nkeys, q, "pairs/paired",
+                 [&](const PartOut& p, uint32_t idbits) {
+                   launch_gen_part_paired(sa, sb, vcnt, n, nkeys, k, idbits, p, s);
+                 },
+                 [&](Call& c2, uint64_t* cand_, uint64_t m) {
+                   return sort_and_verify(c2, cand_, m, n, k, sa, pa, sb, pb);
+                 },
+                 &v);
+           });
+  }
+  if (!done) {
+    launch_paired_count(sa, sb, n, k, vcnt, s);
     const uint64_t tiles = (n + scan_tile() - 1) / scan_tile();
     const uint32_t epoch = next_epoch(c, tiles, s);
     launch_scan_excl(vcnt, voff, n, c->status, cl.tile_counter(), epoch, cl.lb_err(), s);
+    tm.mark("pack_scan", (double)n * 2 * (16 + 16 + 16 + 8) + (double)n * 12, 4);
+    {
+      hip_check(hipMemcpyAsync(counters + CNT_NKEYS, voff + n, 8, hipMemcpyDeviceToDevice, s),
+                "copy");
+      const uint32_t* h =
+          static_cast<const uint32_t*>(readback(c, counters, (CNT_NKEYS + 2) * 4, s));
+      raise_validation(h[CNT_ERR]);
+      std::memcpy(&nkeys, h + CNT_NKEYS, 8);
+    }
+    if (nkeys >= 0xFFFFFFFFull) throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 deletion variants"};
+    c->stats.n_keys = (int64_t)nkeys;
+    const uint32_t nk = (uint32_t)nkeys;
+    const uint32_t idbits = n <= (1ull << 24) ? 24u : 32u;
+    uint64_t* e1 = sc.get<uint64_t>(nk);
+    uint64_t* e2 = sc.get<uint64_t>(nk);
+    launch_vargen_paired(sa, sb, voff, n, k, idbits, e1, s);
+    tm.mark("vargen_paired", (double)nk * 8 + (double)n * 40, 1);
+    int cap, bits;
+    hashed_plan(c, nk, &cap, &bits);
+    const std::vector<Digit> digits = bits ? top_digits(64 - bits) : std::vector<Digit>();
+    const bool flip = digits.empty() ? false : counted_sort(cl, e1, e2, nk, digits);
+    tm.mark("hash_passes", (double)nk * 24 * digits.size(), 4 * (int)digits.size());
+    c->stats.n_sort_passes = (int)digits.size();
+    Cands cand = group_segments(cl, flip ? e2 : e1, nk, cap, bits, idbits);
+    sc.blocks.push_back(cand.p);
+    c->stats.n_cand_raw = (int64_t)cand.n;
+    v = sort_and_verify(cl, cand.p, cand.n, n, k, sa, pa, sb, pb);
   }
-  tm.mark("pack_scan", (double)n * 2 * (16 + 16 + 16 + 8) + (double)n * 12, 4);
-  uint64_t nkeys;
-  {
-    hip_check(hipMemcpyAsync(counters + CNT_NKEYS, voff + n, 8, hipMemcpyDeviceToDevice, s), "copy");
-    const uint32_t* h = static_cast<const uint32_t*>(readback(c, counters, (CNT_NKEYS + 2) * 4, s));
-    raise_validation(h[CNT_ERR]);
-    std::memcpy(&nkeys, h + CNT_NKEYS, 8);
-  }
-  if (nkeys >= 0xFFFFFFFFull) throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 deletion variants"};
-  c->stats.n_keys = (int64_t)nkeys;
-  const uint32_t nk = (uint32_t)nkeys;
-  const uint32_t idbits = n <= (1ull << 24) ? 24u : 32u;
-  uint64_t* e1 = sc.get<uint64_t>(nk);
-  uint64_t* e2 = sc.get<uint64_t>(nk);
-  launch_vargen_paired(sa, sb, voff, n, k, idbits, e1, s);
-  tm.mark("vargen_paired", (double)nk * 8 + (double)n * 40, 1);
-  int cap, bits;
-  hashed_plan(c, nk, &cap, &bits);
-  const std::vector<Digit> digits = bits ? top_digits(64 - bits) : std::vector<Digit>();
-  const bool flip = digits.empty() ? false : counted_sort(cl, e1, e2, nk, digits);
-  tm.mark("hash_passes", (double)nk * 24 * digits.size(), 4 * (int)digits.size());
-  c->stats.n_sort_passes = (int)digits.size();
-  Cands cand = group_segments(cl, flip ? e2 : e1, nk, cap, bits, idbits);
-  sc.blocks.push_back(cand.p);
-  c->stats.n_cand_raw = (int64_t)cand.n;
-  const Verified v = sort_and_verify(cl, cand.p, cand.n, n, k, sa, pa, sb, pb);
   try {
     tm.finish();
   } catch (...) {
@@ -901,9 +935,21 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
     const uint32_t nk = (uint32_t)nkeys;
     Cands cand;
     int passes = 0;
-    const bool done = partition_applies(c, nkeys) && if_memory_suffices(c, [&] {
-                        return partitioned_search(cl, seq, planes, vcnt, n, k, nkeys, &v);
-                      });
+    const bool hamming = c->metric == SD_METRIC_HAMMING;
+    const PairSeqs q{hamming ? seq : planes, seq, nullptr, nullptr, n, n, k, hamming ? 1 : 0, 1,
+                     nullptr, 0, 0};
+    const bool done =
+        partition_applies(c, nkeys) && if_memory_suffices(c, [&] {
+          return partitioned_search(
+              cl, n, nkeys, q, "pairs/self",
+              [&](const PartOut& p, uint32_t idbits) {
+                launch_gen_part(seq, vcnt, n, nkeys, k, idbits, p, s);
+              },
+              [&](Call& c2, uint64_t* cand_, uint64_t m) {
+                return sort_and_verify(c2, cand_, m, n, k, seq, planes);
+              },
+              &v);
+        });
     if (done) {
       // 3-7 in one
     } else if (c->path == 1) {

@@ -250,6 +250,14 @@ constexpr int PART_MAX_LB = 12;
 // counts, nkeys in all), partitioned
 void launch_gen_part(const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nkeys, int k,
                      uint32_t idbits, const PartOut& o, hipStream_t s);
+// the same for paired-chain records, k <= 2 (packed keys of both chains), and
+// their distinct variant counts (bit planes of both), with totals as in
+// launch_pack
+void launch_paired_distinct(const u128* pa, const u128* pb, uint64_t n, int k, uint32_t* vcnt,
+                            unsigned long long* sums, hipStream_t s);
+void launch_gen_part_paired(const u128* sa, const u128* sb, const uint32_t* vcnt, uint64_t n,
+                            uint64_t nkeys, int k, uint32_t idbits, const PartOut& o,
+                            hipStream_t s);
 // the regions of `in` split into the bins of o (o.lb > in.lb); the overflow
 // area of `in` is not read
 void launch_part_split(const PartOut& in, const PartOut& o, hipStream_t s);

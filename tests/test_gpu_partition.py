@@ -96,3 +96,29 @@ def test_overflow_area_too_small(paths):
 def test_wide_ids(paths):
     # more than 2^24 sequences: 32 id bits and 32 hash bits
     same(paths, *cdr3gen.generate(13, (1 << 24) + 3), 0)
+
+
+def same_paired(paths, a, b, k):
+    print(f"[partition] {len(a[1]) - 1} paired records k={k}", flush=True)
+    x = paths[0].paired_self_search(a, b, k)
+    y = paths[1].paired_self_search(a, b, k)
+    assert len(x) == len(y)
+    assert np.array_equal(x.i, y.i) and np.array_equal(x.j, y.j) and np.array_equal(x.d, y.d)
+    # the sorted path writes repeated variants of a record too
+    assert paths[0].stats()["n_keys"] <= paths[1].stats()["n_keys"]
+
+
+# joined strings around the 32 and 64 positions where the generator's halves,
+# rotations and masks change form, down to one residue per chain
+@pytest.mark.parametrize("la,lb", [(1, 1), (1, 24), (24, 1), (24, 24), (15, 15), (15, 16), (16, 16),
+                                   (23, 9)])
+def test_paired_lengths(paths, la, lb):
+    rng = np.random.default_rng(la * 25 + lb)
+    a, b = (csr([bytes(x) for x in rng.integers(0, 3, (300, n)).astype(np.uint8)]) for n in (la, lb))
+    for k in (0, 1, 2, 3):
+        same_paired(paths, a, b, k)
+
+
+@pytest.mark.parametrize("n", [1, 2_000, 40_000, 250_000])
+def test_paired_sizes(paths, n):
+    same_paired(paths, *cdr3gen.paired(n % 89, n), 2)
