@@ -137,19 +137,19 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     uint32_t* oi = res.get<uint32_t>(cap);
     uint32_t* oj = res.get<uint32_t>(cap);
     uint8_t* od = res.get<uint8_t>(cap);
-    launch_pair_order(b, q.na, oi, oj, od, cap, cl.counters + CNT_LBERR, s);
+    launch_pair_order(b, q.na, oi, oj, od, cap, cl.counters, s);
     cl.tm.mark("pair_order", (double)q.na * 20, 4);
     PairState st;
     std::memcpy(&st, readback(c, b.state, sizeof(st), s), sizeof(st));
     uint64_t raw = 0, more = 0;
     for (uint64_t x : st.raw) raw += x;
     const uint64_t kept = st.count;
-    if (st.counters[0] & SD_ERRBIT_LOOKBACK)
+    if (st.counters[CNT_LBERR] & SD_ERRBIT_LOOKBACK)
       throw Error{SD_E_HIP, "internal error: a look-back wait timed out"};
     const bool overflow = st.flags & PF_OVERFLOW;
     if (overflow)  // (a split reads slots that lost candidates never filled)
       launch_fill_u32(cl.lb_err(), 0, 1, s);
-    else if (st.counters[0] & SD_ERRBIT_INDEX)
+    else if (st.counters[CNT_LBERR] & SD_ERRBIT_INDEX)
       throw Error{SD_E_HIP, "internal error: a candidate id out of range"};
     const PairNext next = check(st.counters, &more);
     if (next == PairNext::give_up) return false;
@@ -159,7 +159,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
       // more room: what was counted and what comes; where the room was there
       // but pairs have very many repeats, fewer of them per bin
       const uint64_t want = raw + more + raw / 16 + 1024;
-      if (want <= guess) ++spread;
+      if (overflow && want <= guess) ++spread;
       guess = std::max(guess, want);
       cap = guess;
       continue;
@@ -181,7 +181,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
       oi = res.get<uint32_t>(kept);
       oj = res.get<uint32_t>(kept);
       od = res.get<uint8_t>(kept);
-      launch_pair_order(b, q.na, oi, oj, od, kept, cl.counters + CNT_LBERR, s);
+      launch_pair_order(b, q.na, oi, oj, od, kept, cl.counters, s);
     }
     res.blocks.clear();
     out->i = oi;

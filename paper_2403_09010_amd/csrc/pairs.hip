@@ -230,8 +230,8 @@ __global__ __launch_bounds__(64) void k_pair_place(sd::PairBins in, sd::PairBufs
 
 // Position p's pair goes to the start of its first id's range plus the number
 // of smaller second ids there: most ranges hold one to three pairs, neighbours
-// in the same cache lines. The last kernel of a search also copies `words`
-// counters of the call beside its own, so that one read-back gets both.
+// in the same cache lines. The last kernel of a search also copies the call's
+// counters beside its own, so that one read-back gets both.
 __global__ __launch_bounds__(256) void k_pair_order(sd::PairBufs b, uint64_t n,
                                                     uint32_t* __restrict__ oi,
                                                     uint32_t* __restrict__ oj,

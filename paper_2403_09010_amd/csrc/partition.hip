@@ -109,6 +109,23 @@ constexpr PairLanes make_pair_lanes() {
 
 static __constant__ PairLanes kPairLanes = make_pair_lanes();
 
+// A lane's deletion pairs, one per 64 of them.
+struct LanePairs {
+  uint32_t pa[GP_CHUNKS], pb[GP_CHUNKS], need1[GP_CHUNKS], need2[GP_CHUNKS];
+  __device__ __forceinline__ void load(uint32_t lane) {
+#pragma unroll
+    for (int c = 0; c < GP_CHUNKS; ++c) {
+      const uint4 v = kPairLanes.e[c * 64 + lane];
+      pa[c] = v.x;
+      pb[c] = v.y;
+      need1[c] = v.z;
+      need2[c] = v.w;
+    }
+  }
+};
+
+// Every distinct variant with at most k deletions of a wave's two sequences.
+//
 // With P[p] the prefix XORs of the position terms rotr(B[s_t], t) (the hash
 // of hashtab.h) and Q[p] = P[p] ^ rotl(P[p + 1], 1), the variant without
 // p1 < p2 < p3 hashes to
@@ -116,17 +133,129 @@ static __constant__ PairLanes kPairLanes = make_pair_lanes();
 // and with fewer deletions to the same form with fewer terms: one table word
 // per deletion.
 //
-// A wave takes two sequences, one per 32-lane half: lane t holds residue t,
-// the prefix XORs come from a scan over the lanes, the canonical-test masks
-// (sd_device.h: n1, n2, n3) from ballots, and the variants with at most one
-// deletion leave straight from the lanes' own values. The deletion pairs in
-// colexicographic order (larger position major) are the same for every
-// length, so lane l's pairs l, l + 64, ... are fixed for the whole kernel:
-// their LDS offsets and the mask bits they need stay in registers. Triples
-// run over the largest position p3 (uniform): their first two positions are
-// the pairs below p3, whose hash words are already in registers and whose
-// canonical lanes are a prefix of the pairs' ballots, except the range with
-// p2 = p3 - 1, which has its own.
+// Each 32-lane half has one sequence (`key`; the upper half's counts only with
+// `two`): lane t holds residue t, the prefix XORs come from a scan over the
+// lanes, the canonical-test masks (sd_device.h: n1, n2, n3) from ballots, and
+// the variants with at most one deletion leave straight from the lanes' own
+// values. The deletion pairs in colexicographic order (larger position major)
+// are the same for every length, so lane l's pairs l, l + 64, ... are fixed for
+// the whole kernel: their LDS offsets and the mask bits they need stay in
+// registers. Triples run over the largest position p3 (uniform): their first
+// two positions are the pairs below p3, whose hash words are already in
+// registers and whose canonical lanes are a prefix of the pairs' ballots,
+// except the range with p2 = p3 - 1, which has its own.
+//
+// put(hash, id, position): the lower half's sequence has id id0 and positions
+// from its lanes' at0 on, the upper half's id0 + 1 and its own at0. rows: the
+// wave's 4 GP_ROW words of LDS.
+template <bool K3, class Put>
+__device__ __forceinline__ void gen_step(u128 key, uint32_t id0, bool two, uint32_t at0, int k,
+                                         uint64_t* rows, const uint64_t* s_b, const uint64_t* s_c,
+                                         const LanePairs& lp, Put&& put) {
+  constexpr int QS = GP_ROW;
+  const uint32_t lane = threadIdx.x & 63u, half = lane >> 5, t = lane & 31u;
+  const uint32_t L = key_len(key);
+  const uint32_t r = t < L ? residue_at(key, t < 24u ? t : 0u) : 31u;
+  W2 term = rotr_w2(w2(s_b[r]), t);
+  if (t >= L) term = W2{0, 0};
+  const W2 incl{half_xor_scan(term.lo), half_xor_scan(term.hi)};
+  const W2 q = incl ^ term ^ rotl_w2(incl, 1);
+  const W2 plA{read_lane(incl.lo, 31), read_lane(incl.hi, 31)};
+  const W2 plB{read_lane(incl.lo, 63), read_lane(incl.hi, 63)};
+  const W2 pl{half ? plB.lo : plA.lo, half ? plB.hi : plA.hi};
+  // n1 bit p: p = L - 1 or s[p] != s[p + 1] (residues past the end read
+  // as 31, which no residue equals)
+  const uint32_t r1 = next_lane(r);
+  const bool c1 = t < L && (r != r1 || t + 1 == L);
+  const uint64_t n1 = __ballot(c1);
+  if (k >= 2 && t < (uint32_t)QS) {
+    const W2 base2 = w2(s_c[L >= 2 ? L - 2 : 0]) ^ rotl_w2(pl, 2);
+    uint64_t* row = rows + half * 2 * QS;
+    const W2 q2 = rotl_w2(q, 1) ^ base2;
+    row[t] = ((uint64_t)q.hi << 32) | q.lo;
+    row[QS + t] = ((uint64_t)q2.hi << 32) | q2.lo;
+  }
+  uint32_t atA, atB;
+  {
+    // none (lane L, where q = P[L] ^ rotl(P[L], 1)) and one deletion
+    const bool keep = ((k >= 1 && c1) || t == L) && (!half || two);
+    const W2 h = w2(s_c[t < L ? L - 1 : L & 31u]) ^ rotl_w2(pl, 1) ^ q;
+    const uint64_t bal = __ballot(keep);
+    const uint32_t na = (uint32_t)__popc((uint32_t)bal);
+    const uint32_t rank = mask_rank(bal) - (half ? na : 0u);
+    if (keep) put(h, id0 + half, at0 + rank);
+    atA = read_lane(at0, 0) + na;
+    atB = read_lane(at0, 32) + (uint32_t)__popc((uint32_t)(bal >> 32));
+  }
+  if (k < 2) return;
+  const uint32_t r2 = next_lane(r1);
+  const uint64_t n2 = __ballot(t < L && (r != r2 || t + 2 >= L));
+  uint64_t n3 = 0;
+  if (K3) n3 = __ballot(t < L && (r != next_lane(r2) || t + 3 >= L));
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (uint32_t sI = 0; sI < (two ? 2u : 1u); ++sI) {
+    const uint32_t SL = read_lane(L, sI ? 32 : 0);
+    const uint32_t m1 = (uint32_t)(n1 >> (sI * 32)), m2 = (uint32_t)(n2 >> (sI * 32));
+    const unsigned char* Q = reinterpret_cast<const unsigned char*>(rows + sI * 2 * QS);
+    const uint32_t id = id0 + sI;
+    uint32_t at = sI ? atB : atA;
+    const uint32_t np = SL * (SL - 1) / 2;
+    W2 pw[GP_CHUNKS];
+    uint64_t kp[GP_CHUNKS], kq[GP_CHUNKS];
+    const uint32_t m3 = (uint32_t)(n3 >> (sI * 32));
+    // (the words of two chunks are read at once: most lengths have two)
+    auto pair_word = [&](int c) {
+      return w2(*reinterpret_cast<const uint64_t*>(Q + lp.pa[c])) ^
+             w2(*reinterpret_cast<const uint64_t*>(Q + lp.pb[c]));
+    };
+    pw[0] = pair_word(0);
+    pw[1] = pair_word(1);
+#pragma unroll
+    for (int c = 0; c < GP_CHUNKS; ++c) {
+      if ((uint32_t)c * 64 >= np) break;  // uniform
+      if (c >= 2) pw[c] = pair_word(c);
+      const W2 h = pw[c];
+      const bool keep = ((lp.need1[c] & ~m1) | (lp.need2[c] & ~m2)) == 0;
+      const uint64_t bal = __ballot(keep);
+      if (keep) put(h, id, at + mask_rank(bal));
+      at += (uint32_t)__popcll(bal);
+      if (K3) {
+        kp[c] = bal;
+        // with p3 = p2 + 1: p2 needs n2, p1 needs n1, or n3 if p1, p2, p3 adjoin
+        const uint32_t b2 = 1u << ((lp.pb[c] >> 3) - QS), b1 = lp.need1[c] & ~b2;
+        kq[c] = __ballot(((b2 & ~m2) | (b1 & ~m1) | (lp.need2[c] & ~m3)) == 0 &&
+                         (lp.need1[c] >> 31) == 0);
+      }
+    }
+    if (K3 && SL >= 3) {
+      const W2 pls = sI ? plB : plA;
+      // pw holds base2 ^ Q[p1] ^ rotl(Q[p2], 1)
+      const W2 sw = w2(s_c[SL - 2]) ^ rotl_w2(pls, 2) ^ w2(s_c[SL - 3]) ^ rotl_w2(pls, 3);
+      for (uint32_t p3 = 2; p3 < SL; ++p3) {
+        if (!((m1 >> p3) & 1u)) continue;
+        const W2 tw = sw ^ rotl_w2(w2(*reinterpret_cast<const uint64_t*>(Q + p3 * 8)), 2);
+        const uint32_t u0 = (p3 - 1) * (p3 - 2) / 2, u1 = p3 * (p3 - 1) / 2;
+#pragma unroll
+        for (int c = 0; c < GP_CHUNKS; ++c) {
+          const uint32_t c0 = (uint32_t)c * 64;
+          if (c0 >= u1) break;  // uniform
+          const uint64_t below0 = u0 >= c0 + 64 ? ~0ull : u0 > c0 ? (1ull << (u0 - c0)) - 1 : 0;
+          const uint64_t below1 = u1 >= c0 + 64 ? ~0ull : (1ull << (u1 - c0)) - 1;
+          const uint64_t bal = (kp[c] & below0) | (kq[c] & below1 & ~below0);
+          if ((bal >> lane) & 1u) put(pw[c] ^ tw, id, at + mask_rank(bal));
+          at += (uint32_t)__popcll(bal);
+        }
+      }
+    }
+  }
+  // the next sequences' rows overwrite these
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// gen_step over a block's sequences, into an LDS tile that partition_tail
+// orders and writes.
 //
 // Bound: vector instructions and LDS operations, then the element writes.
 // 100M variants of 1M sequences (k = 2): 0.47-0.52 ms, of which the generation
@@ -138,19 +267,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
                                                  const uint32_t* __restrict__ vcnt, uint32_t nseq,
                                                  int k, uint32_t idbits, uint32_t spb,
                                                  sd::PartOut o) {
-  constexpr int NW = NT / 64, QS = GP_ROW;
+  constexpr int NW = NT / 64;
   extern __shared__ __align__(16) unsigned char lds[];
   const uint32_t nb = 1u << o.lb;
   uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
-  uint64_t* s_q = s_e + TILE;   // [NW][2][2][QS]: per sequence Q, then rotl(Q, 1) ^ base
-  uint64_t* s_b = s_q + NW * 4 * QS;                 // [32]
+  uint64_t* s_q = s_e + TILE;   // [NW][2][2][GP_ROW]: per sequence Q, then rotl(Q, 1) ^ base
+  uint64_t* s_b = s_q + NW * 4 * GP_ROW;               // [32]
   uint64_t* s_c = s_b + 32;                          // [32]
   uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_c + 32);
   uint32_t* s_pref = s_cnt + nb;                      // [NT + 1]
   uint32_t* s_tmp = s_pref + NT + 1;                 // [NW]
   const uint32_t s0 = blockIdx.x * spb;
   const uint32_t ns = min(spb, nseq - s0);
-  const uint32_t lane = threadIdx.x & 63u, half = lane >> 5, t = lane & 31u;
+  const uint32_t lane = threadIdx.x & 63u, half = lane >> 5;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t lomask = idbits >= 32 ? 0u : ~((1u << idbits) - 1u);
   const int binshift = 32 - o.lb;  // bin = high word of the element >> binshift
@@ -180,15 +309,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // moving the loads out of the loop)
     uint32_t pl_lane = lane;
     asm volatile("" : "+v"(pl_lane));
-    uint32_t pa[GP_CHUNKS], pb[GP_CHUNKS], need1[GP_CHUNKS], need2[GP_CHUNKS];
-#pragma unroll
-    for (int c = 0; c < GP_CHUNKS; ++c) {
-      const uint4 v = kPairLanes.e[c * 64 + pl_lane];
-      pa[c] = v.x;
-      pb[c] = v.y;
-      need1[c] = v.z;
-      need2[c] = v.w;
-    }
+    LanePairs lp;
+    lp.load(pl_lane);
     uint32_t x = xa + 2 * w;
     // each half's sequence, loaded one step ahead
     u128 key = x < xb ? seq[s0 + min(x + half, xb - 1)] : (u128)0;
@@ -199,105 +321,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
       const u128 cur = key;
       key = seq[s0 + min(x + 2 * NW + half, xb - 1)];
       const uint32_t at0 = s_pref[min(x + half, xb)] - p0;
-      // lane t of each half: residue t and its position term
-      const uint32_t L = key_len(cur);
-      const uint32_t r = t < L ? residue_at(cur, t < 24u ? t : 0u) : 31u;
-      W2 term = rotr_w2(w2(s_b[r]), t);
-      if (t >= L) term = W2{0, 0};
-      const W2 incl{half_xor_scan(term.lo), half_xor_scan(term.hi)};
-      const W2 q = incl ^ term ^ rotl_w2(incl, 1);
-      const W2 plA{read_lane(incl.lo, 31), read_lane(incl.hi, 31)};
-      const W2 plB{read_lane(incl.lo, 63), read_lane(incl.hi, 63)};
-      const W2 pl{half ? plB.lo : plA.lo, half ? plB.hi : plA.hi};
-      // n1 bit p: p = L - 1 or s[p] != s[p + 1] (residues past the end read
-      // as 31, which no residue equals)
-      const uint32_t r1 = next_lane(r);
-      const bool c1 = t < L && (r != r1 || t + 1 == L);
-      const uint64_t n1 = __ballot(c1);
-      if (k >= 2 && t < (uint32_t)QS) {
-        const W2 base2 = w2(s_c[L >= 2 ? L - 2 : 0]) ^ rotl_w2(pl, 2);
-        uint64_t* row = s_q + (w * 2 + half) * 2 * QS;
-        const W2 q2 = rotl_w2(q, 1) ^ base2;
-        row[t] = ((uint64_t)q.hi << 32) | q.lo;
-        row[QS + t] = ((uint64_t)q2.hi << 32) | q2.lo;
-      }
-      uint32_t atA, atB;
-      {
-        // none (lane L, where q = P[L] ^ rotl(P[L], 1)) and one deletion
-        const bool keep = ((k >= 1 && c1) || t == L) && (!half || two);
-        const W2 h = w2(s_c[t < L ? L - 1 : L & 31u]) ^ rotl_w2(pl, 1) ^ q;
-        const uint64_t bal = __ballot(keep);
-        const uint32_t na = (uint32_t)__popc((uint32_t)bal);
-        const uint32_t rank = mask_rank(bal) - (half ? na : 0u);
-        if (keep) put(h, s0 + x + half, at0 + rank);
-        atA = read_lane(at0, 0) + na;
-        atB = read_lane(at0, 32) + (uint32_t)__popc((uint32_t)(bal >> 32));
-      }
-      if (k < 2) continue;
-      const uint32_t r2 = next_lane(r1);
-      const uint64_t n2 = __ballot(t < L && (r != r2 || t + 2 >= L));
-      uint64_t n3 = 0;
-      if (K3) n3 = __ballot(t < L && (r != next_lane(r2) || t + 3 >= L));
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      for (uint32_t sI = 0; sI < (two ? 2u : 1u); ++sI) {
-        const uint32_t SL = read_lane(L, sI ? 32 : 0);
-        const uint32_t m1 = (uint32_t)(n1 >> (sI * 32)), m2 = (uint32_t)(n2 >> (sI * 32));
-        const unsigned char* Q = reinterpret_cast<const unsigned char*>(s_q + (w * 2 + sI) * 2 * QS);
-        const uint32_t id = s0 + x + sI;
-        uint32_t at = sI ? atB : atA;
-        const uint32_t np = SL * (SL - 1) / 2;
-        W2 pw[GP_CHUNKS];
-        uint64_t kp[GP_CHUNKS], kq[GP_CHUNKS];
-        const uint32_t m3 = (uint32_t)(n3 >> (sI * 32));
-        // (the words of two chunks are read at once: most lengths have two)
-        auto pair_word = [&](int c) {
-          return w2(*reinterpret_cast<const uint64_t*>(Q + pa[c])) ^
-                 w2(*reinterpret_cast<const uint64_t*>(Q + pb[c]));
-        };
-        pw[0] = pair_word(0);
-        pw[1] = pair_word(1);
-#pragma unroll
-        for (int c = 0; c < GP_CHUNKS; ++c) {
-          if ((uint32_t)c * 64 >= np) break;  // uniform
-          if (c >= 2) pw[c] = pair_word(c);
-          const W2 h = pw[c];
-          const bool keep = ((need1[c] & ~m1) | (need2[c] & ~m2)) == 0;
-          const uint64_t bal = __ballot(keep);
-          if (keep) put(h, id, at + mask_rank(bal));
-          at += (uint32_t)__popcll(bal);
-          if (K3) {
-            kp[c] = bal;
-            // with p3 = p2 + 1: p2 needs n2, p1 needs n1, or n3 if p1, p2, p3 adjoin
-            const uint32_t b2 = 1u << ((pb[c] >> 3) - QS), b1 = need1[c] & ~b2;
-            kq[c] = __ballot(((b2 & ~m2) | (b1 & ~m1) | (need2[c] & ~m3)) == 0 &&
-                             (need1[c] >> 31) == 0);
-          }
-        }
-        if (K3 && SL >= 3) {
-          const W2 pls = sI ? plB : plA;
-          // pw holds base2 ^ Q[p1] ^ rotl(Q[p2], 1)
-          const W2 sw = w2(s_c[SL - 2]) ^ rotl_w2(pls, 2) ^ w2(s_c[SL - 3]) ^ rotl_w2(pls, 3);
-          for (uint32_t p3 = 2; p3 < SL; ++p3) {
-            if (!((m1 >> p3) & 1u)) continue;
-            const W2 tw = sw ^ rotl_w2(w2(*reinterpret_cast<const uint64_t*>(Q + p3 * 8)), 2);
-            const uint32_t u0 = (p3 - 1) * (p3 - 2) / 2, u1 = p3 * (p3 - 1) / 2;
-#pragma unroll
-            for (int c = 0; c < GP_CHUNKS; ++c) {
-              const uint32_t c0 = (uint32_t)c * 64;
-              if (c0 >= u1) break;  // uniform
-              const uint64_t below0 = u0 >= c0 + 64 ? ~0ull : u0 > c0 ? (1ull << (u0 - c0)) - 1 : 0;
-              const uint64_t below1 = u1 >= c0 + 64 ? ~0ull : (1ull << (u1 - c0)) - 1;
-              const uint64_t bal = (kp[c] & below0) | (kq[c] & below1 & ~below0);
-              if ((bal >> lane) & 1u) put(pw[c] ^ tw, id, at + mask_rank(bal));
-              at += (uint32_t)__popcll(bal);
-            }
-          }
-        }
-      }
-      // the next sequences' rows overwrite these
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      gen_step<K3>(cur, s0 + x, two, at0, k, s_q + w * 4 * GP_ROW, s_b, s_c, lp, put);
     }
     __syncthreads();
     const int shift = 64 - o.lb;
@@ -801,6 +825,356 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   }
 }
 
+// ------------------------------------------------------------------ queries against an index
+
+// First position in E[lo, hi) whose hash is at least h (E ascending), from a
+// guess: the bracket of 16 on either side first (hashes are uniform, so that a
+// segment of 1,200 elements misses by about 13), then wider ones, then a binary
+// search inside.
+__device__ __forceinline__ uint32_t lower_bound_near(const uint64_t* __restrict__ E, uint32_t lo,
+                                                     uint32_t hi, uint32_t guess, uint64_t h,
+                                                     uint32_t idbits) {
+  uint32_t w = 16;
+  while (true) {
+    const uint32_t a = guess - lo > w ? guess - w : lo, b = hi - guess > w ? guess + w : hi;
+    const bool below = a == lo || (E[a - 1] >> idbits) < h;
+    const bool above = b == hi || (E[b] >> idbits) >= h;
+    if (below && above) {
+      lo = a;
+      hi = b;
+      break;
+    }
+    // (the half that missed is narrowed to, and the guess moves to its end)
+    if (!below) hi = a;
+    else lo = b;
+    guess = below ? lo : hi;
+    w = w < (1u << 28) ? w * 8 : ~0u;
+  }
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if ((E[mid] >> idbits) < h)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+// Few queries: each variant is looked up in the index as it is generated, from
+// its place by interpolation in its directory segment; no query element is
+// written, sorted or read.
+//
+// Bound: the latency of three to four dependent loads per variant. A variant
+// shared by many references would hold its wave up: beyond the first PB_SHORT
+// of a run, the rest is left to the whole workgroup.
+constexpr uint32_t PB_SHORT = 4, PB_QUEUE = 1024;
+template <bool K3>
+__global__ __launch_bounds__(256) void k_gen_probe(const u128* __restrict__ seq, uint32_t nseq,
+                                                   int k, const uint64_t* __restrict__ E,
+                                                   uint32_t nkeys,
+                                                   const uint32_t* __restrict__ seg_start,
+                                                   const uint32_t* __restrict__ seg_end, int bits,
+                                                   uint32_t idbits, sd::PairBins out) {
+  __shared__ uint64_t s_q[4 * 4 * GP_ROW];
+  __shared__ uint64_t s_b[32], s_c[32];
+  __shared__ uint32_t s_run[PB_QUEUE], s_id[PB_QUEUE];  // runs left over: position, query
+  __shared__ uint32_t s_runs;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (threadIdx.x == 0) s_runs = 0;
+  if (threadIdx.x < 32) {
+    s_b[threadIdx.x] = kHashTab.b[threadIdx.x];
+    s_c[threadIdx.x] = kHashTab.c[threadIdx.x];
+  }
+  LanePairs lp;
+  lp.load(lane);
+  __syncthreads();
+  const uint64_t idmask = (1ull << idbits) - 1;
+  auto put = [&](W2 v, uint32_t id, uint32_t) {
+    const uint64_t full = (uint64_t)v.hi << 32 | v.lo, h = full >> idbits;
+    const uint32_t seg = bits ? v.hi >> (32 - bits) : 0u;
+    const uint32_t s = seg_start[seg], e = seg_end[seg];
+    if (s >= e) return;
+    const uint32_t frac = (uint32_t)((full << bits) >> 32);
+    uint32_t p = lower_bound_near(E, s, e, s + (uint32_t)(((uint64_t)(e - s) * frac) >> 32), h,
+                                  idbits);
+    for (uint32_t c = 0; p < e; ++p, ++c) {
+      const uint64_t r = E[p];
+      if ((r >> idbits) != h) break;
+      if (c == PB_SHORT) {
+        const uint32_t x = atomicAdd(&s_runs, 1u);
+        if (x < PB_QUEUE) {
+          s_run[x] = p;
+          s_id[x] = id;
+          break;
+        }
+      }
+      pair_put(out, (uint64_t)id << 32 | (r & idmask));
+    }
+  };
+  {
+    const uint32_t x = (blockIdx.x * 4 + w) * 2;
+    if (x < nseq) {
+      const u128 key = seq[min(x + (lane >> 5), nseq - 1)];
+      gen_step<K3>(key, x, x + 1 < nseq, 0, k, s_q + w * 4 * GP_ROW, s_b, s_c, lp, put);
+    }
+  }
+  __syncthreads();
+  const uint32_t runs = min(s_runs, PB_QUEUE);
+  for (uint32_t q = w; q < runs; q += 4) {  // a wave per run, 64 references at a time
+    const uint32_t p0 = s_run[q];
+    const uint64_t id = (uint64_t)s_id[q] << 32, h = E[p0] >> idbits;
+    for (uint32_t p = p0 + lane;; p += 64) {
+      const uint64_t r = p < nkeys && p >= p0 ? E[p] : ~h << idbits;
+      const bool same = (r >> idbits) == h;
+      if (same) pair_put(out, id | (r & idmask));
+      if (__ballot(same) != ~0ull) break;
+    }
+  }
+}
+
+// Many queries: one workgroup per hash segment reads the segment's query
+// elements (a bin of the generator, of which it takes 1 / 2^sub by further hash
+// bits) and its index elements once, and pairs equal hashes.
+//   1. the query elements set bits of a bitmap (SB: its bits, log2);
+//   2. the index elements whose bit is set (those with a query of the same hash
+//      and some of the others) collect in LDS and mark a smaller bitmap;
+//   3. the query elements with their marks collect in the first bitmap's place;
+//   4. the index survivors are put in order of a few more hash bits, and each
+//      query survivor is compared with its bucket.
+// If LDS does not hold the survivors, steps 2 to 4 run in rounds by further
+// hash bits; index survivors beyond any round (thousands of references sharing
+// a variant) are compared with every query survivor of the round piece by
+// piece.
+//
+// Bound: the one read of the index elements, at 8 bytes each. 200K queries
+// (20M variants) against 202M index elements: 0.48 ms (3.4 TB/s); looking each
+// element up by binary search in its sorted segment took 0.82, after two radix
+// passes over the queries.
+constexpr int JB_SB = 18;                      // query bitmap, bits (32 KiB)
+constexpr int JB_TB = 15;                      // mark bitmap, bits
+constexpr uint32_t JB_CAP = 4608;              // index survivors in LDS
+constexpr uint32_t JB_QCAP = (1u << JB_SB) / 64;  // query survivors
+constexpr int JB_NBK = 1024;
+constexpr size_t JB_LDS = (1 << JB_SB) / 8 + (1 << JB_TB) / 8 + JB_CAP * 8 + JB_NBK * 4;
+
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_join_bins(
+    sd::PartOut in, const uint64_t* __restrict__ E, const uint32_t* __restrict__ seg_start,
+    const uint32_t* __restrict__ seg_end, int bits, int sub, uint32_t idbits, sd::PairBins out) {
+  constexpr uint32_t NW = NT / 64, ROW = 64 * FG_LOADS;
+  constexpr uint32_t PER = (JB_CAP + NT - 1) / NT;
+  extern __shared__ __align__(16) unsigned char lds[];
+  uint32_t* s_bq = reinterpret_cast<uint32_t*>(lds);
+  uint64_t* s_qe = reinterpret_cast<uint64_t*>(lds);  // step 3 on
+  uint32_t* s_br = s_bq + (1 << JB_SB) / 32;
+  uint64_t* s_e = reinterpret_cast<uint64_t*>(s_br + (1 << JB_TB) / 32);
+  uint32_t* s_bk = reinterpret_cast<uint32_t*>(s_e + JB_CAP);
+  __shared__ uint32_t s_n, s_nq;
+  __shared__ uint32_t s_tmp[NW];
+  // the workgroups of a query bin follow each other on one XCD, whose L2 then
+  // has the bin's elements
+  const uint32_t nx = 1u << in.nxl, turn = blockIdx.x >> 3;
+  const uint32_t seg = in.nbins >= 8
+                           ? (((turn >> sub) * 8 + (blockIdx.x & 7u)) << sub) + (turn & ((1u << sub) - 1))
+                           : blockIdx.x;
+  const uint32_t bin = seg >> sub;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int segbits = in.lb + sub;
+  const uint32_t r0 = seg_start[seg << (bits - segbits)];
+  const uint32_t r1 = seg_end[((seg + 1) << (bits - segbits)) - 1];
+  if (r0 >= r1) return;
+  const uint64_t base = (uint64_t)(bin << in.nxl) * in.region;
+  const uint32_t parts = NW > nx ? NW / nx : 1u;
+  // the segment's query elements: f(element, whether it is one)
+  auto queries = [&](auto&& f) {
+    for (uint32_t x = w & (nx - 1); x < nx; x += NW) {
+      const uint32_t c = min(in.cursor[x * in.nbins + bin], in.region);
+      const uint64_t* __restrict__ p = in.elem + base + (uint64_t)x * in.region;
+      for (uint32_t t0 = (w >> in.nxl) * ROW; t0 < c; t0 += parts * ROW) {
+        uint64_t e[FG_LOADS];
+#pragma unroll
+        for (int u = 0; u < FG_LOADS; ++u) {
+          const uint32_t i = t0 + u * 64 + lane;
+          e[u] = i < c ? p[i] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < FG_LOADS; ++u)
+          if (t0 + u * 64 < c)
+            f(e[u], t0 + u * 64 + lane < c && (uint32_t)(e[u] >> (64 - segbits)) == seg);
+      }
+    }
+  };
+  auto mark = [&](uint64_t e) { return (uint32_t)(e >> idbits) * 0x9E3779B1u; };
+  constexpr uint32_t TM = (1u << JB_TB) - 1;
+  const uint64_t idmask = (1ull << idbits) - 1;
+  const int bkshift = 64 - segbits - __builtin_ctz(JB_NBK);
+  uint32_t rounds = 1;
+  for (uint32_t round = 0; round < rounds; ++round) {
+    auto mine = [&](uint64_t e) {
+      return rounds == 1 || ((uint32_t)(e >> (bkshift - 6)) & (rounds - 1)) == round;
+    };
+    for (uint32_t i = threadIdx.x; i < ((1 << JB_SB) + (1 << JB_TB)) / 32; i += NT) s_bq[i] = 0;
+    if (threadIdx.x == 0) {
+      s_n = 0;
+      s_nq = 0;
+    }
+    __syncthreads();
+    queries([&](uint64_t e, bool valid) {
+      const uint32_t i = (uint32_t)(e >> idbits) & ((1u << JB_SB) - 1);
+      if (valid && mine(e)) atomicOr(&s_bq[i >> 5], 1u << (i & 31u));
+    });
+    __syncthreads();
+    for (uint32_t t0 = r0 + w * ROW; t0 < r1; t0 += NW * ROW) {
+      uint64_t e[FG_LOADS], bal[FG_LOADS];
+#pragma unroll
+      for (int u = 0; u < FG_LOADS; ++u) {
+        const uint32_t i = t0 + u * 64 + lane;
+        e[u] = i < r1 ? E[i] : 0;
+      }
+      uint32_t tot = 0;
+#pragma unroll
+      for (int u = 0; u < FG_LOADS; ++u) {
+        const uint32_t i = (uint32_t)(e[u] >> idbits) & ((1u << JB_SB) - 1);
+        const bool keep = t0 + u * 64 + lane < r1 && ((s_bq[i >> 5] >> (i & 31u)) & 1u) && mine(e[u]);
+        bal[u] = __ballot(keep);
+        tot += (uint32_t)__popcll(bal[u]);
+        if (keep) {
+          const uint32_t j = mark(e[u]), j1 = j >> (32 - JB_TB), j2 = (j >> 2) & TM;
+          atomicOr(&s_br[j1 >> 5], 1u << (j1 & 31u));
+          atomicOr(&s_br[j2 >> 5], 1u << (j2 & 31u));
+        }
+      }
+      if (tot) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s_n, tot);
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (at + tot <= JB_CAP) {
+#pragma unroll
+          for (int u = 0; u < FG_LOADS; ++u) {
+            if ((bal[u] >> lane) & 1u) s_e[at + mask_rank(bal[u])] = e[u];
+            at += (uint32_t)__popcll(bal[u]);
+          }
+        }
+      }
+    }
+    __syncthreads();
+    const uint32_t m = s_n;
+    if (m == 0) {
+      __syncthreads();
+      continue;
+    }
+    if (m > JB_CAP && rounds < (uint32_t)FG_MAX_ROUNDS) {
+      // again in rounds of about half the capacity (in twice as many, if a
+      // round was still too large: what it found before is found again and
+      // dropped with the repeats)
+      const uint32_t least = rounds * 2;
+      while (rounds < (uint32_t)FG_MAX_ROUNDS && (rounds < least || rounds * JB_CAP < 2 * m))
+        rounds <<= 1;
+      round = ~0u;
+      __syncthreads();
+      continue;
+    }
+    // query survivors
+    queries([&](uint64_t e, bool valid) {
+      const uint32_t j = mark(e), j1 = j >> (32 - JB_TB), j2 = (j >> 2) & TM;
+      bool keep = valid && mine(e) && ((s_br[j1 >> 5] >> (j1 & 31u)) & 1u);
+      if (keep) keep = (s_br[j2 >> 5] >> (j2 & 31u)) & 1u;
+      const uint64_t bal = __ballot(keep);
+      if (bal) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s_nq, (uint32_t)__popcll(bal));
+        at = __builtin_amdgcn_readfirstlane(at) + mask_rank(bal);
+        if (keep && at < JB_QCAP) s_qe[at] = e;
+      }
+    });
+    __syncthreads();
+    const uint32_t nq = s_nq;
+    if (m > JB_CAP || nq > JB_QCAP) {
+      // one variant shared by thousands: every query element of the round
+      // against the sorted index segment
+      queries([&](uint64_t e, bool valid) {
+        if (!valid || !mine(e)) return;
+        uint32_t lo = r0, hi = r1;
+        const uint64_t h = e >> idbits;
+        while (lo < hi) {
+          const uint32_t mid = lo + ((hi - lo) >> 1);
+          if ((E[mid] >> idbits) < h)
+            lo = mid + 1;
+          else
+            hi = mid;
+        }
+        for (; lo < r1; ++lo) {
+          const uint64_t r = E[lo];
+          if ((r >> idbits) != h) break;
+          pair_put(out, (e & idmask) << 32 | (r & idmask));
+        }
+      });
+      __syncthreads();
+      continue;
+    }
+    // the index survivors by bucket
+    uint64_t e[PER];
+#pragma unroll
+    for (uint32_t r = 0; r < PER; ++r) {
+      const uint32_t i = threadIdx.x + r * NT;
+      e[r] = i < m ? s_e[i] : 0;
+    }
+    for (uint32_t i = threadIdx.x; i < (uint32_t)JB_NBK; i += NT) s_bk[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < PER; ++r)
+      if (threadIdx.x + r * NT < m)
+        atomicAdd(&s_bk[(uint32_t)(e[r] >> bkshift) & (JB_NBK - 1)], 1u);
+    __syncthreads();
+    {
+      static_assert(JB_NBK <= NT, "one bucket per thread");
+      const uint32_t c = threadIdx.x < (uint32_t)JB_NBK ? s_bk[threadIdx.x] : 0u;
+      uint32_t tot;
+      const uint32_t ex = block_excl_scan<NT>(c, s_tmp, &tot);
+      if (threadIdx.x < (uint32_t)JB_NBK) s_bk[threadIdx.x] = ex;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < PER; ++r)
+      if (threadIdx.x + r * NT < m)
+        s_e[atomicAdd(&s_bk[(uint32_t)(e[r] >> bkshift) & (JB_NBK - 1)], 1u)] = e[r];
+    __syncthreads();
+    // (every bucket's entry is its end now)
+    auto each_pair = [&](auto&& f) {
+      for (uint32_t i = threadIdx.x; i < nq; i += NT) {
+        const uint64_t a = s_qe[i];
+        const uint32_t bk = (uint32_t)(a >> bkshift) & (JB_NBK - 1);
+        const uint32_t end = s_bk[bk];
+        for (uint32_t y = bk ? s_bk[bk - 1] : 0u; y < end; ++y) {
+          const uint64_t b = s_e[y];
+          if (((b ^ a) >> idbits) == 0) f((a & idmask) << 32 | (b & idmask));
+        }
+      }
+    };
+    if (out.lb == 0) {  // a list per XCD, one reservation (see k_filter_group)
+      uint32_t cnt = 0, tot;
+      each_pair([&](uint64_t) { ++cnt; });
+      uint32_t at = block_excl_scan<NT>(cnt, s_tmp, &tot);
+      const uint32_t x = blockIdx.x & ((1u << out.nxl) - 1);
+      if (threadIdx.x == 0 && tot) s_n = atomicAdd(&out.cursor[x], tot);
+      __syncthreads();
+      if (cnt) {
+        at += s_n;
+        uint64_t* dst = out.base + (uint64_t)x * out.region;
+        each_pair([&](uint64_t v) {
+          if (at < out.region) dst[at] = v;
+          ++at;
+        });
+      }
+    } else {
+      each_pair([&](uint64_t v) { pair_put(out, v); });
+    }
+    __syncthreads();  // the next round rewrites the LDS
+  }
+}
+
 }  // namespace sdk
 
 namespace sd {
@@ -911,6 +1285,28 @@ void launch_filter_group(const PartOut& in, uint64_t nkeys, uint32_t idbits, con
     filter_t<256, 17>(in, idbits, out, big, nbig, s);
   else
     filter_t<1024, 19>(in, idbits, out, big, nbig, s);
+}
+
+void launch_gen_probe(const u128* seq, uint64_t n, int k, const uint64_t* E, uint32_t nkeys,
+                      const uint32_t* seg_start, const uint32_t* seg_end, int bits, uint32_t idbits,
+                      const PairBins& out, hipStream_t s) {
+  if (!n) return;
+  const unsigned g = (unsigned)((n + 7) / 8);
+  if (k == 3)
+    hipLaunchKernelGGL((sdk::k_gen_probe<true>), dim3(g), dim3(256), 0, s, seq, (uint32_t)n, k, E, nkeys,
+                       seg_start, seg_end, bits, idbits, out);
+  else
+    hipLaunchKernelGGL((sdk::k_gen_probe<false>), dim3(g), dim3(256), 0, s, seq, (uint32_t)n, k, E, nkeys,
+                       seg_start, seg_end, bits, idbits, out);
+}
+
+void launch_join_bins(const PartOut& in, const uint64_t* E, const uint32_t* seg_start,
+                      const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
+                      const PairBins& out, hipStream_t s) {
+  if (in.lb + sub > bits) throw Error{SD_E_HIP, "internal error: join segments finer than the index"};
+  allow_lds(&sdk::k_join_bins<1024>, sdk::JB_LDS);
+  hipLaunchKernelGGL((sdk::k_join_bins<1024>), dim3(in.nbins << sub), dim3(1024), sdk::JB_LDS, s, in,
+                     E, seg_start, seg_end, bits, sub, idbits, out);
 }
 
 }  // namespace sd

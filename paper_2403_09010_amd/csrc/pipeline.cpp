@@ -287,6 +287,8 @@ bool partition_applies(const sd_ctx* c, uint64_t nk) {
          !c->pair_sort && !c->sort_items && nk > 0 && nk < 3000000000ull;
 }
 
+}  // namespace
+
 // Bins and regions of one partition level. Regions hold an eighth more than
 // their mean share (small inputs: twice it) and six standard deviations of
 // it: bins are even, since the hash is, unless single variants are shared by
@@ -308,6 +310,8 @@ PartOut part_out(Call& cl, uint64_t nk, int lb, int nxl, uint64_t over_cap, uint
   launch_fill_u32(o.cursor, 0, nc, cl.s);
   return o;
 }
+
+namespace {
 
 }  // namespace
 
@@ -547,10 +551,10 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, const PairSeqs& q, c
         launch_pair_scatter(extra.p, extra.n, bins, s);
       },
       [&](const uint32_t* h, uint64_t* more) {
-        if (h[CNT_OVER1 - CNT_LBERR] || h[CNT_OVER - CNT_LBERR] > over_cap)
+        if (h[CNT_OVER1] || h[CNT_OVER] > over_cap)
           return PairNext::give_up;
         uint64_t nb;
-        std::memcpy(&nb, h + (CNT_NBIG - CNT_LBERR), 8);
+        std::memcpy(&nb, h + CNT_NBIG, 8);
         if (!nb || listed) return PairNext::done;
         listed = nb;
         extra = oversized_group(cl, p.elem, big, nb, idbits);
@@ -576,31 +580,6 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, const PairSeqs& q, c
   v->d = out.d;
   v->n = out.n;
   return true;
-}
-
-// Runs a path that needs more scratch than the sorted one; where the memory
-// does not suffice (a budget, a fixed area), everything it took is given back
-// and the sorted path runs instead.
-template <class F>
-bool if_memory_suffices(sd_ctx* c, F&& f) {
-  const size_t mark = c->arena_used;
-  bool done = false;
-  try {
-    done = f();
-  } catch (const Error& e) {
-    if (e.code != SD_E_NOMEM) throw;
-    done = false;
-  }
-  if (!done && c->arena) {
-    // (the look-back area may have moved into what is given back)
-    unsigned char* st = reinterpret_cast<unsigned char*>(c->status);
-    if (st >= c->arena + mark && st < c->arena + c->arena_size) {
-      c->status = nullptr;
-      c->status_words = 0;
-    }
-    c->arena_used = mark;
-  }
-  return done;
 }
 
 // Device bytes per element of a column group at its peak (the sharded
@@ -809,10 +788,7 @@ void paired_self_search(sd_ctx* c, const sd_seqs* a, const sd_seqs* b, int k, sd
   auto read_counters = [&](uint64_t* nkeys) {
     const uint32_t* h = static_cast<const uint32_t*>(readback(c, counters, CNT_TOTAL * 4, s));
     raise_validation(h[CNT_ERR]);
-    uint64_t part[PACK_SUMS];
-    std::memcpy(part, h + CNT_SUMS, sizeof(part));
-    *nkeys = 0;
-    for (uint64_t x : part) *nkeys += x;
+    *nkeys = pack_total(h);
   };
   Verified v;
   bool done = false;
@@ -912,9 +888,7 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
     // one read-back: validation flags and the key total
     const uint32_t* h = static_cast<const uint32_t*>(readback(c, counters, CNT_TOTAL * 4, s));
     raise_validation(h[CNT_ERR]);
-    uint64_t part[PACK_SUMS];
-    std::memcpy(part, h + CNT_SUMS, sizeof(part));
-    for (uint64_t x : part) nkeys += x;
+    nkeys = pack_total(h);
   }
   c->stats.n_keys = (int64_t)nkeys;
   // the sorted, streamed and full-key paths write variants at scanned offsets

@@ -82,6 +82,99 @@ int join_bits(const sd_ctx* c, const sd_index* idx, uint64_t nk) {
   return std::min(b, idx->bits);
 }
 
+// Up to one query variant per 64 index elements the variants are looked up one
+// by one, beyond that they are joined by reading the whole index: a lookup
+// costs three to four scattered cache lines, an index element 8 bytes. k = 2,
+// whole calls in ms, looked up / joined: 2M references, 10K queries 0.31 /
+// 0.49, 30K 0.56 / 0.55, 200K 2.53 / 0.74; 5M references, 60K 1.01 / 1.18, 100K
+// 1.49 / 1.29; 200K references, 3K 0.16 / 0.18, 10K 0.25 / 0.20.
+constexpr uint64_t PROBE_RATIO = 64;
+
+// A tile of queries against a hashed index through the pair bins: few queries
+// look their variants up as they are generated, many are partitioned into bins
+// and joined with the index's segments. Returns false where the general path
+// has to run (positions beyond 32 bits, no shape of the pair bins that fits).
+bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
+                       const WeightedSpec* w, TileOut* out) {
+  sd_ctx* c = cl0.c;
+  hipStream_t s = cl0.s;
+  Scratch sc(c);
+  Call cl{c, s, sc, cl0.tm, cl0.counters};
+  u128* seq = sc.get<u128>(q.n);
+  u128* planes = sc.get<u128>(q.n);
+  uint32_t* vcnt = sc.get<uint32_t>(q.n);
+  launch_pack(q.codes, q.offs, q.n, k, true, seq, planes, vcnt, cl.counters + CNT_ERR, s,
+              reinterpret_cast<unsigned long long*>(cl.counters + CNT_SUMS));
+  cl.tm.mark("q_pack_scan", (double)q.n * 48, 1);
+  // small sets are not waited for here: their variants are looked up whatever
+  // their number, and the flags are read with the result
+  static const uint32_t typical[4] = {1, 16, 110, 500};  // variants of 15 residues
+  uint64_t nk = q.n * typical[k];
+  const bool known = nk > (1u << 20) || nk * PROBE_RATIO > idx->n_keys;
+  if (known) {
+    const uint32_t* h = static_cast<const uint32_t*>(readback(c, cl.counters, CNT_TOTAL * 4, s));
+    raise_validation(h[CNT_ERR]);
+    nk = pack_total(h);
+    if (nk >= 0xFFFFFFFFull) throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 deletion variants"};
+  }
+  bool join = known && nk * PROBE_RATIO > idx->n_keys && idx->bits >= 1 && nk < 3000000000ull;
+  // bins of the query elements (2,048 at most: longer runs of the generator's
+  // tiles), and as few workgroups per bin as their LDS takes: each reads the
+  // bin's query elements, and of its index elements about 3% have a query of
+  // the same hash and as many others pass as the bitmap is filled
+  PartOut p{};
+  int sub = 0;
+  if (join) {
+    int lb = 1;
+    while (lb < std::min(11, idx->bits) && (nk >> lb) > 2048) ++lb;
+    auto too_many = [&] {
+      const double mq = (double)(nk >> lb) / (1 << sub);
+      const double mr = (double)(idx->n_keys >> lb) / (1 << sub);
+      return mq > JOIN_QUERY_MAX || mr * (mq / JOIN_BITMAP + 0.03) > JOIN_SURVIVORS;
+    };
+    while (lb + sub < idx->bits && too_many()) ++sub;
+    p = part_out(cl, nk, lb, nk >= (2u << 20) ? 3 : 0, 4096, cl.counters + CNT_OVER);
+    launch_gen_part(seq, vcnt, q.n, nk, k, idx->idbits, p, s);
+    cl.tm.mark("q_vargen_part", (double)nk * 8 + (double)q.n * 20, 1);
+  }
+  const bool hamming = c->metric == SD_METRIC_HAMMING;
+  const PairSeqs ps{w ? planes : hamming ? seq : planes,
+                    idx->ref_seq,
+                    w ? seq : nullptr,
+                    nullptr,
+                    q.n,
+                    idx->n_ref,
+                    k,
+                    w ? 3 : hamming ? 1 : 0,
+                    0,
+                    w ? w->subst : nullptr,
+                    w ? w->indel : 0,
+                    w ? w->max_score : 0};
+  const bool done = binned_pairs(
+      cl, join ? "pairs/join" : "pairs/probe", nk, ps,
+      [&](const PairBins& bins) {
+        if (join)
+          launch_join_bins(p, idx->E, idx->seg_start, idx->seg_end, idx->bits, sub, idx->idbits,
+                           bins, s);
+        else
+          launch_gen_probe(seq, q.n, k, idx->E, (uint32_t)idx->n_keys, idx->seg_start, idx->seg_end, idx->bits,
+                           idx->idbits, bins, s);
+      },
+      [&](const uint32_t* h, uint64_t*) {
+        if (!known) raise_validation(h[CNT_ERR]);
+        nk = pack_total(h);
+        if (!join || !h[CNT_OVER]) return PairNext::done;
+        join = false;  // copies of single variants overflow their bins: look them up
+        return PairNext::again;
+      },
+      [&](uint64_t* cand, uint64_t m) {
+        return verify_candidates(cl, seq, planes, q.n, idx->ref_seq, idx->n_ref, cand, m, k, w);
+      },
+      "join", out);
+  out->nkeys = nk;
+  return done;
+}
+
 // One tile of queries: returns pool blocks (i = tile-local query id, j = ref
 // id, d) sorted by (i, j) and their count.
 TileOut query_tile(Call& cl, const sd_index* idx, const DevSeqs& q, int k, const WeightedSpec* w) {
@@ -91,6 +184,12 @@ TileOut query_tile(Call& cl, const sd_index* idx, const DevSeqs& q, int k, const
   if (q.n == 0) return out;
   if (idx->learned) return learned_tile(cl, idx, q, k, w);
   if (q.n >= (1ull << idx->idbits)) throw Error{SD_E_TOO_MANY, "query tile exceeds the index id width"};
+  // (the knobs of the general path choose it)
+  if (!c->join_elems && !c->pair_sort && !c->sort_items && if_memory_suffices(c, [&] {
+        return query_tile_binned(cl, idx, q, k, w, &out);
+      }))
+    return out;
+  out = TileOut();
   const Packed p = pack_and_count(cl, q, k, true);
   out.nkeys = p.nkeys;
   const uint32_t nk = (uint32_t)p.nkeys;

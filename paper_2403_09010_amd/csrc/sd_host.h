@@ -62,11 +62,19 @@ enum : int {
   CNT_CAND2 = 106,    // u64 candidate counter of the full-key emission
   CNT_STEPS = 108,    // u64 search comparisons of learned-index lookups
   CNT_OVER = 110,     // elements in the overflow area of a partition
-  CNT_OVER1 = 111,    // the same of its first level (the words from CNT_LBERR
-                      // on are the ones a PairState copies)
+  CNT_OVER1 = 111,    // the same of its first level
   CNT_SUMS = 128,     // u64 partial sums of the variant counts
   CNT_TOTAL = CNT_SUMS + 2 * PACK_SUMS
 };
+static_assert(CNT_TOTAL <= (int)PAIR_COUNTERS, "a PairState copies all of them");
+
+// The total of the variant counts from the partial sums among the counters.
+inline uint64_t pack_total(const uint32_t* counters) {
+  uint64_t part[PACK_SUMS], total = 0;
+  std::memcpy(part, counters + CNT_SUMS, sizeof(part));
+  for (uint64_t x : part) total += x;
+  return total;
+}
 
 // The state of one library call on one stream. Several Call objects of one
 // call (a streamed search's column groups) share the counter area, so the
@@ -326,8 +334,8 @@ void fill_host_slices(sd_ctx* c, const uint32_t* di, const uint32_t* dj, const u
 
 // Candidates of a search through the bins of pairs.hip (pairs.cpp).
 // `produce` enqueues the kernels that put every candidate; it may run again,
-// with more room, after `check` looked at the call's counters (PAIR_COUNTERS
-// words from CNT_LBERR on). guess: the candidates expected.
+// with more room, after `check` looked at the call's counters. nkeys: about how
+// many variants produce the candidates.
 enum class PairNext {
   done,     // every candidate was put
   again,    // produce has more candidates to put now (`guess` more)
@@ -343,6 +351,34 @@ bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, const PairSeqs& q,
                   const std::function<PairNext(const uint32_t*, uint64_t*)>& check,
                   const std::function<TileOut(uint64_t*, uint64_t)>& sort_pairs,
                   const char* stage, TileOut* out);
+
+// Regions of one partition level, cursors zeroed (pipeline.cpp).
+PartOut part_out(Call& cl, uint64_t nk, int lb, int nxl, uint64_t over_cap, uint32_t* over_count);
+
+// Runs a path that needs more scratch than the sorted one; where the memory
+// does not suffice (a budget, a fixed area), everything it took is given back
+// and the sorted path runs instead.
+template <class F>
+bool if_memory_suffices(sd_ctx* c, F&& f) {
+  const size_t mark = c->arena_used;
+  bool done = false;
+  try {
+    done = f();
+  } catch (const Error& e) {
+    if (e.code != SD_E_NOMEM) throw;
+    done = false;
+  }
+  if (!done && c->arena) {
+    // (the look-back area may have moved into what is given back)
+    unsigned char* st = reinterpret_cast<unsigned char*>(c->status);
+    if (st >= c->arena + mark && st < c->arena + c->arena_size) {
+      c->status = nullptr;
+      c->status_words = 0;
+    }
+    c->arena_used = mark;
+  }
+  return done;
+}
 
 struct Cands {
   uint64_t* p = nullptr;  // pool block owned by the caller

@@ -287,7 +287,7 @@ struct PairSeqs {
 };
 constexpr uint32_t PF_OVERFLOW = 1;  // a region was full: candidates were lost
 constexpr uint32_t PF_LONG = 2;      // one first id has too many pairs to order in LDS
-constexpr uint32_t PAIR_COUNTERS = 16;
+constexpr uint32_t PAIR_COUNTERS = 256;
 struct PairState {  // zeroed before the producer; read back when the search is done
   uint32_t flags, nlong;
   unsigned long long count;           // pairs kept
@@ -324,6 +324,19 @@ void launch_pair_place(const PairBins& in, const PairBufs& b, hipStream_t s);
 void launch_pair_order(const PairBufs& b, uint64_t n, uint32_t* oi, uint32_t* oj, uint8_t* od,
                        uint64_t cap, const uint32_t* counters, hipStream_t s);
 void launch_pair_scatter(const uint64_t* cand, uint64_t n, const PairBins& o, hipStream_t s);
+// Query variants against a hashed index (E sorted by hash, a directory of
+// 2^bits segments), as (query << 32 | reference) candidates: looked up as they
+// are generated, or joined bin by bin from a partition of them (in.lb + sub <=
+// bits: 2^sub workgroups share a bin; elements in the overflow area are not
+// read).
+void launch_gen_probe(const u128* seq, uint64_t n, int k, const uint64_t* E, uint32_t nkeys,
+                      const uint32_t* seg_start, const uint32_t* seg_end, int bits, uint32_t idbits,
+                      const PairBins& out, hipStream_t s);
+// most query elements and (expected) index survivors a join workgroup takes well
+constexpr double JOIN_QUERY_MAX = 20000, JOIN_SURVIVORS = 2600, JOIN_BITMAP = 1 << 18;
+void launch_join_bins(const PartOut& in, const uint64_t* E, const uint32_t* seg_start,
+                      const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
+                      const PairBins& out, hipStream_t s);
 // id pairs of equal hashes in every bin; big receives element ranges that
 // take the sort-and-runs path instead (at most (nbins << nxl) + 1)
 void launch_filter_group(const PartOut& in, uint64_t nkeys, uint32_t idbits, const PairBins& out,

@@ -122,3 +122,53 @@ def test_paired_lengths(paths, la, lb):
 @pytest.mark.parametrize("n", [1, 2_000, 40_000, 250_000])
 def test_paired_sizes(paths, n):
     same_paired(paths, *cdr3gen.paired(n % 89, n), 2)
+
+
+@pytest.fixture(scope="module")
+def query_paths():
+    from paper_2403_09010_amd import Context
+    from paper_2403_09010_amd.symdel import OPT_JOIN_ELEMS
+    a, b = Context(0), Context(0)
+    b.set_option(OPT_JOIN_ELEMS, 1)  # the general path
+    yield a, b
+    a.close()
+    b.close()
+
+
+def same_query(paths, idx, q, k, subst=None):
+    print(f"[partition] {len(q[1]) - 1} queries k={k} weighted={subst is not None}", flush=True)
+    if subst is not None:
+        x, y = (c.query_weighted(idx, *q, subst, 8, 8) for c in paths)
+    else:
+        x, y = (c.query(idx, *q, k) for c in paths)
+    assert len(x) == len(y)
+    assert np.array_equal(x.i, y.i) and np.array_equal(x.j, y.j) and np.array_equal(x.d, y.d)
+    assert paths[0].stats()["n_keys"] == paths[1].stats()["n_keys"]
+
+
+# looked up one by one, joined with few and with many elements per workgroup,
+# and single queries; every radius up to the index's
+@pytest.mark.parametrize("nref,k,sizes", [(3_000, 3, (1, 9, 1_500)), (40, 2, (1, 700)),
+                                          (60_000, 2, (1, 900, 30_000)), (300_000, 2, (60_000,))])
+def test_query_sizes(query_paths, nref, k, sizes):
+    ref = cdr3gen.generate(nref % 83, nref)
+    idx = query_paths[0].build_index(*ref, k)
+    for n in sizes:
+        q = cdr3gen.generate_query(n % 71, n, *ref, ref_mut_frac=0.3)
+        for kk in range(k + 1):
+            same_query(query_paths, idx, q, kk)
+        if k == 2:
+            same_query(query_paths, idx, q, k, cdr3gen.cost_matrix())
+    idx.free()
+
+
+def test_query_copies(query_paths):
+    # variants shared by thousands of references, of queries, and of both
+    s = strings_of(17, 1_000)
+    many = csr([s[5]] * 9_000 + s)
+    few = csr([s[5]] * 3 + s[:50])
+    for ref, queries in ((many, (few, csr(s * 20))), (csr(strings_of(18, 50_000)), (many,))):
+        idx = query_paths[0].build_index(*ref, 1)
+        for q in queries:
+            same_query(query_paths, idx, q, 1)
+        idx.free()
