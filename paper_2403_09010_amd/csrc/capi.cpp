@@ -101,6 +101,7 @@ void* dalloc(sd_ctx* c, size_t bytes) {
   if (e != hipSuccess) {
     (void)hipGetLastError();
     release_cache(c);
+    if (c->index_pool) c->index_pool->release();
     e = hipMalloc(&p, sz);
   }
   if (e != hipSuccess || !p) {
@@ -126,6 +127,47 @@ void dfree(sd_ctx* c, void* p) {
   c->live.erase(it);
 }
 
+void* IndexPool::take(size_t bytes, size_t* size) {
+  std::lock_guard<std::mutex> g(m);
+  auto it = blocks.lower_bound(bytes);
+  if (it == blocks.end() || it->first > bytes + bytes / 8) return nullptr;
+  void* p = it->second;
+  *size = it->first;
+  held -= it->first;
+  blocks.erase(it);
+  return p;
+}
+
+bool IndexPool::put(void* const* p, const size_t* size, int n) {
+  std::lock_guard<std::mutex> g(m);
+  size_t sum = 0;
+  for (int x = 0; x < n; ++x) sum += size[x];
+  if (sum > limit) return false;
+  if (held + sum > limit) {  // the newest blocks stay
+    for (auto& b : blocks) (void)hipFree(b.second);
+    blocks.clear();
+    held = 0;
+  }
+  for (int x = 0; x < n; ++x) {
+    try {
+      blocks.insert({size[x], p[x]});
+      held += size[x];
+    } catch (...) {
+      (void)hipFree(p[x]);
+    }
+  }
+  return true;
+}
+
+void IndexPool::release() {
+  std::lock_guard<std::mutex> g(m);
+  if (blocks.empty()) return;
+  (void)hipSetDevice(device);
+  for (auto& b : blocks) (void)hipFree(b.second);
+  blocks.clear();
+  held = 0;
+}
+
 void* index_alloc(sd_ctx* c, sd_index* idx, size_t bytes) {
   if (!bytes) bytes = 16;
   void* p = nullptr;
@@ -136,19 +178,60 @@ void* index_alloc(sd_ctx* c, sd_index* idx, size_t bytes) {
     if (!p) throw Error{SD_E_NOMEM, "the allocator hook returned NULL for an index array"};
     return p;
   }
-  if (hipMalloc(&p, bytes) != hipSuccess || !p) {
+  size_t sz = bytes;
+  if (!c->budget) {
+    if (!c->index_pool) {
+      c->index_pool = std::make_shared<IndexPool>();
+      c->index_pool->device = c->device;
+      size_t total = 0;
+      if (hipDeviceTotalMem(&total, c->device) != hipSuccess) (void)hipGetLastError();
+      c->index_pool->limit = total / 32;
+    }
+    idx->pool = c->index_pool;
+    // a little more than asked for, so that the next index of about as many
+    // sequences takes the same blocks
+    sz = size_class(bytes);
+    if (sz > (64u << 20)) {
+      const size_t g = (size_t)1 << (63 - __builtin_clzll(sz) - 5);
+      sz = (sz + g - 1) / g * g;
+    }
+    p = idx->pool->take(sz, &sz);
+  }
+  if (!p && hipMalloc(&p, sz) != hipSuccess) {
+    (void)hipGetLastError();
+    if (c->index_pool) c->index_pool->release();
+    sz = bytes;
+    if (hipMalloc(&p, sz) != hipSuccess) p = nullptr;
+  }
+  if (!p) {
     (void)hipGetLastError();
     throw Error{SD_E_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes for an index failed"};
+  }
+  try {
+    idx->sizes[p] = sz;
+  } catch (...) {
+    (void)hipFree(p);
+    throw;
   }
   return p;
 }
 
-void index_release(sd_index* idx, void* p) {
-  if (!p) return;
-  if (idx->ufree)
-    idx->ufree(p, idx->uarg);
-  else
-    (void)hipFree(p);
+// Gives back n blocks of an index (null ones among them). Work that still reads
+// them on any stream has ended when this returns.
+void index_release(sd_index* idx, void* const* p, int n) {
+  void* own[16];
+  size_t size[16];
+  int m = 0;
+  for (int x = 0; x < n && x < 16; ++x)
+    if (p[x]) own[m++] = p[x];
+  if (!m) return;
+  if (idx->ufree) {
+    for (int x = 0; x < m; ++x) idx->ufree(own[x], idx->uarg);
+    return;
+  }
+  for (int x = 0; x < m; ++x) size[x] = idx->sizes[own[x]];
+  if (idx->pool && hipDeviceSynchronize() == hipSuccess && idx->pool->put(own, size, m)) return;
+  for (int x = 0; x < m; ++x) (void)hipFree(own[x]);
 }
 
 uint32_t next_epoch(sd_ctx* c, uint64_t words, hipStream_t s) {
@@ -477,6 +560,7 @@ int sd_set_allocator(sd_ctx* c, sd_alloc_fn alloc, sd_free_fn free_fn, void* use
     if (!c->live.empty())
       throw Error{SD_E_STATE, "results of this context are still live (release them with sd_pairs_free first)"};
     sd::release_cache(c);
+    if (c->index_pool) c->index_pool->release();
     c->ualloc = alloc;
     c->ufree = free_fn;
     c->uarg = user;

@@ -389,9 +389,9 @@ TileOut verify_candidates(Call& cl, const u128* qseq, const u128* qplanes, uint6
 void index_free(sd_index* idx) {
   if (!idx) return;
   (void)hipSetDevice(idx->device);
-  for (void* p : {(void*)idx->ref_seq, (void*)idx->E, (void*)idx->seg_start, (void*)idx->seg_end,
-                  (void*)idx->keys, (void*)idx->kid, (void*)idx->params, idx->coord, idx->leaves})
-    index_release(idx, p);
+  void* const blocks[] = {idx->ref_seq, idx->E,   idx->seg_start, idx->seg_end, idx->keys,
+                          idx->kid,     idx->params, idx->coord,     idx->leaves};
+  index_release(idx, blocks, 9);
   delete idx;
 }
 

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -412,6 +413,26 @@ struct Error {
 
 // ------------------------------------------------------------------ context
 
+namespace sd {
+// Device blocks of freed indexes, kept for the next index of the context that
+// built them: memory given back to the driver is cleared before it can be
+// handed out again, at about 35 GB/s, so a program that rebuilds an index over
+// and over waits for that once the card's clean memory is used up (2M
+// sequences, 1.6 GB: 45 ms a build, whatever the build takes). It keeps at most
+// `limit` bytes (a 32nd of the device's memory); an index that outlives its
+// context holds its pool's last reference.
+struct IndexPool {
+  std::mutex m;
+  int device = 0;
+  size_t limit = 0, held = 0;
+  std::multimap<size_t, void*> blocks;
+  void* take(size_t bytes, size_t* size);      // null if no block fits well
+  bool put(void* const* p, const size_t* size, int n);  // all of them, or false
+  void release();
+  ~IndexPool() { release(); }
+};
+}  // namespace sd
+
 struct sd_ctx {
   int device = 0;
   uint64_t budget = 0;  // 0 = unbounded
@@ -468,6 +489,7 @@ struct sd_ctx {
   std::map<std::string, uint64_t> out_hint;  // last output size of each sharded stage
   std::map<std::string, uint64_t> noalloc_hint;  // the same, for no-allocation calls
   std::vector<hipEvent_t> events;
+  std::shared_ptr<sd::IndexPool> index_pool;  // made by the first index
   // graph-captured batches (SD_OPT_BATCH_GRAPH): the cached plan of the last
   // batch shape, and the candidates per query variant seen so far (sizes the
   // candidate capacity of the next plan)
@@ -486,6 +508,8 @@ struct sd_index {
   // the allocator hook of the building context (null: hipMalloc / hipFree)
   sd_free_fn ufree = nullptr;
   void* uarg = nullptr;
+  std::shared_ptr<sd::IndexPool> pool;  // where its blocks go (none: hook or budget)
+  std::unordered_map<void*, size_t> sizes;  // of its blocks (none from a hook)
   int k = 0;
   int learned = 0;  // 0 hashed, 1 learned
   uint32_t idbits = 24;
@@ -513,9 +537,9 @@ namespace sd {
 void* dalloc(sd_ctx* c, size_t bytes);
 void dfree(sd_ctx* c, void* p);
 // a device array owned by an index (from the context's allocator hook if it
-// has one, else hipMalloc); released by index_free
+// has one, else from its index pool or hipMalloc); released by index_free
 void* index_alloc(sd_ctx* c, sd_index* idx, size_t bytes);
-void index_release(sd_index* idx, void* p);
+void index_release(sd_index* idx, void* const* p, int n);
 template <typename T>
 T* dalloc_t(sd_ctx* c, uint64_t count) {
   return static_cast<T*>(dalloc(c, (size_t)(count ? count : 1) * sizeof(T)));
