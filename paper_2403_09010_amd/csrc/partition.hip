@@ -254,6 +254,9 @@ __device__ __forceinline__ void gen_step(u128 key, uint32_t id0, bool two, uint3
   __builtin_amdgcn_wave_barrier();
 }
 
+// most bins (log2) that a workgroup's threads reserve runs of
+constexpr int tile_max_lb(int threads) { return threads >= 1024 ? sd::PART_MAX_LB : 11; }
+
 // gen_step over a block's sequences, into an LDS tile that partition_tail
 // orders and writes.
 //
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
     __syncthreads();
     const int shift = 64 - o.lb;
-    partition_tail<NT, TILE, NT >= 1024 ? sd::PART_MAX_LB : 11, false>(
+    partition_tail<NT, TILE, tile_max_lb(NT), false>(
         s_e, s_pref[xb] - p0, s_cnt, s_tmp, o.lb,
         [&](uint64_t v) { return (uint32_t)(v >> shift); }, 0, o.elem, o.cursor, o.region, o.nbins,
         o.nxl, o.slots, o.fill, o.cap, o.over_count);
@@ -506,7 +509,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
     __syncthreads();
     const int shift = 64 - o.lb;
-    partition_tail<NT, TILE, NT >= 1024 ? sd::PART_MAX_LB : 11, false>(
+    partition_tail<NT, TILE, tile_max_lb(NT), false>(
         s_e, s_pref[xb] - p0, s_cnt, s_tmp, o.lb,
         [&](uint64_t v) { return (uint32_t)(v >> shift); }, 0, o.elem, o.cursor, o.region, o.nbins,
         o.nxl, o.slots, o.fill, o.cap, o.over_count);
@@ -557,7 +560,7 @@ __global__ __launch_bounds__(NT) void k_part_split(sd::PartOut in, sd::PartOut o
     }
   }
   __syncthreads();
-  partition_tail<NT, TILE, 8, false>(
+  partition_tail<NT, TILE, sd::PART_MAX_SPLIT, false>(
       s_e, m, s_cnt, s_tmp, (int)lb, [&](uint64_t v) { return (uint32_t)(v >> shift) & (nb - 1); },
       bin << lb, o.elem, o.cursor, o.region, o.nbins, o.nxl, o.slots, o.fill, o.cap, o.over_count);
 }
@@ -823,6 +826,138 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     }
     __syncthreads();  // the next round rewrites the LDS
   }
+}
+
+// ------------------------------------------------------------------ sorted bins
+
+// An index keeps its elements in order of the whole word. Bins of the top hash
+// bits are in order already; each fits LDS, where a counting pass by the next
+// BITS hash bits leaves buckets of one or two elements on average, and an
+// element's place in its bucket is the number of smaller ones there.
+
+// elements of each bin
+__global__ __launch_bounds__(256) void k_bin_totals(sd::PartOut in, uint32_t* __restrict__ cnt) {
+  const uint32_t b = blockIdx.x * 256 + threadIdx.x;
+  if (b >= in.nbins) return;
+  uint32_t c = 0;
+  for (uint32_t x = 0; x < (1u << in.nxl); ++x) c += in.cursor[x * in.nbins + b];
+  cnt[b] = c;
+}
+
+// One workgroup per bin: its elements in order to out[off[bin], ...). A bin that
+// does not fit (single variants shared by thousands of sequences) is left out:
+// the element ranges of its regions go to big as [2x, 2x + 1), counted in *nbig.
+// *repeats counts the elements that equal the one before them in the output.
+//
+// Bound: LDS accesses, and its element reads and writes, which take two thirds
+// of its time at the rate of a copy (202M elements: 0.79 ms, 4.1 TB/s). Elements
+// stay in registers until their bucket's start is known, one LDS write instead
+// of two, and buckets are small because a wave waits for its largest one: with
+// two writes and buckets of three elements 1.12 ms, and 1.17 by workgroups of
+// 1,024 threads.
+template <int NT, int CAP, int BITS, int R>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_sort_bins(
+    sd::PartOut in, const uint64_t* __restrict__ off, uint64_t* __restrict__ out,
+    uint64_t* __restrict__ big, unsigned long long* __restrict__ nbig,
+    unsigned long long* __restrict__ repeats) {
+  constexpr int NBK = 1 << BITS, BPT = NBK / NT;
+  static_assert(BPT * NT == NBK && NT >= 512, "buckets per thread, waves per region");
+  extern __shared__ __align__(16) unsigned char lds[];
+  uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
+  uint32_t* s_bk = reinterpret_cast<uint32_t*>(s_e + CAP);  // NBK + 1
+  uint32_t* s_tmp = s_bk + NBK + 1;
+  const uint32_t bin = blockIdx.x, nx = 1u << in.nxl;
+  // the waves share the bin's regions out: one lane's elements are its strip's
+  // every `stride` in one region
+  const uint32_t wave = threadIdx.x >> 6, mine = wave & (nx - 1);
+  const uint32_t strip = (wave >> in.nxl) * 64 + (threadIdx.x & 63);
+  const uint32_t stride = (NT / 64 >> in.nxl) * 64;
+  uint32_t m = 0, c = 0;
+  bool over = false;
+  for (uint32_t x = 0; x < nx; ++x) {
+    const uint32_t v = in.cursor[x * in.nbins + bin];
+    m += v;
+    over |= v > in.region || v > R * stride;
+    if (x == mine) c = v;
+  }
+  if (over || m > (uint32_t)CAP) {
+    if (threadIdx.x < nx) {
+      const uint32_t x = threadIdx.x, cu = x * in.nbins + bin;
+      const uint64_t a = (uint64_t)((bin << in.nxl) + x) * in.region;
+      const uint64_t w = atomicAdd(nbig, 1ull);
+      big[2 * w] = a;
+      big[2 * w + 1] = a + (in.cursor[cu] > in.region ? in.fill[cu] : in.cursor[cu]);
+    }
+    return;
+  }
+  const uint64_t* __restrict__ src = in.elem + (uint64_t)((bin << in.nxl) + mine) * in.region;
+  uint64_t e[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = strip + r * stride;
+    e[r] = i < c ? src[i] : 0;
+  }
+  for (uint32_t i = threadIdx.x; i < (uint32_t)NBK; i += NT) s_bk[i] = 0;
+  __syncthreads();
+  const int shift = 64 - in.lb - BITS;
+  uint32_t at[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (strip + r * stride < c) at[r] = atomicAdd(&s_bk[(uint32_t)(e[r] >> shift) & (NBK - 1)], 1u);
+  __syncthreads();
+  {
+    uint32_t n[BPT], sum = 0, tot;
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) sum += n[q] = s_bk[threadIdx.x * BPT + q];
+    uint32_t ex = block_excl_scan<NT>(sum, s_tmp, &tot);
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) {
+      s_bk[threadIdx.x * BPT + q] = ex;
+      ex += n[q];
+    }
+    if (threadIdx.x == 0) s_bk[NBK] = m;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (strip + r * stride < c) s_e[s_bk[(uint32_t)(e[r] >> shift) & (NBK - 1)] + at[r]] = e[r];
+  __syncthreads();
+  uint64_t* __restrict__ dst = out + off[bin];
+  uint32_t same = 0;
+  for (uint32_t i = threadIdx.x; i < m; i += NT) {
+    const uint64_t a = s_e[i];
+    const uint32_t bk = (uint32_t)(a >> shift) & (NBK - 1);
+    const uint32_t s = s_bk[bk], end = s_bk[bk + 1];
+    uint32_t p = s;
+    for (uint32_t y = s; y < end; ++y) {
+      const uint64_t b = s_e[y];
+      const bool rep = b == a && y < i;
+      same += rep;
+      p += b < a || rep;
+    }
+    dst[p] = a;
+  }
+  if (same) atomicAdd(repeats, (unsigned long long)same);
+}
+
+// The m elements of the bins that were left out, in order, to their places.
+__global__ __launch_bounds__(256) void k_place_bins(const uint64_t* __restrict__ X, uint64_t m,
+                                                    int lb, const uint64_t* __restrict__ off,
+                                                    uint64_t* __restrict__ out,
+                                                    unsigned long long* __restrict__ repeats) {
+  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= m) return;
+  const uint64_t e = X[i], first = e >> (64 - lb) << (64 - lb);
+  uint64_t lo = 0, hi = i;  // the bin's first element
+  while (lo < hi) {
+    const uint64_t mid = (lo + hi) / 2;
+    if (X[mid] < first)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  out[off[e >> (64 - lb)] + (i - lo)] = e;
+  if (i && X[i - 1] == e) atomicAdd(repeats, 1ull);
 }
 
 // ------------------------------------------------------------------ queries against an index
@@ -1196,6 +1331,7 @@ static size_t gen_lds(int lb) {
 template <int NT, int TILE>
 static void gen_t(const u128* seq, const uint32_t* vcnt, uint32_t n, int k, uint32_t idbits,
                   uint32_t spb, const PartOut& o, hipStream_t s) {
+  if (o.lb > sdk::tile_max_lb(NT)) throw Error{SD_E_HIP, "internal error: too many bins"};
   const unsigned g = (n + spb - 1) / spb;
   if (k == 3) {
     const size_t lds = gen_lds<NT, TILE>(o.lb);
@@ -1238,6 +1374,7 @@ void launch_paired_distinct(const u128* pa, const u128* pb, uint64_t n, int k, u
 template <int NT, int TILE>
 static void gen_paired_t(const u128* sa, const u128* sb, const uint32_t* vcnt, uint32_t n, int k,
                          uint32_t idbits, uint32_t spb, const PartOut& o, hipStream_t s) {
+  if (o.lb > sdk::tile_max_lb(NT)) throw Error{SD_E_HIP, "internal error: too many bins"};
   const size_t lds = (size_t)TILE * 8 + 96 * 8 + ((size_t)4 << o.lb) + (NT + 1) * 4 + NT / 64 * 4;
   allow_lds(&sdk::k_gen_part_paired<NT, TILE>, lds);
   hipLaunchKernelGGL((sdk::k_gen_part_paired<NT, TILE>), dim3((n + spb - 1) / spb), dim3(NT), lds,
@@ -1262,11 +1399,34 @@ void launch_gen_part_paired(const u128* sa, const u128* sb, const uint32_t* vcnt
 
 void launch_part_split(const PartOut& in, const PartOut& o, hipStream_t s) {
   constexpr int NT = 512, TILE = 8192;
+  if (o.lb - in.lb > PART_MAX_SPLIT) throw Error{SD_E_HIP, "internal error: split too fine"};
   const size_t lds = (size_t)TILE * 8 + ((size_t)4 << (o.lb - in.lb)) + NT / 64 * 4;
   allow_lds(&sdk::k_part_split<NT, TILE>, lds);
   const uint32_t tiles = (in.region + TILE - 1) / TILE;
   hipLaunchKernelGGL((sdk::k_part_split<NT, TILE>), dim3(tiles * (in.nbins << in.nxl)), dim3(NT),
                      lds, s, in, o, tiles);
+}
+
+void launch_bin_offsets(const PartOut& in, uint32_t* cnt, uint64_t* off, uint64_t* status,
+                        uint32_t* tile_counter, uint32_t epoch, uint32_t* err, hipStream_t s) {
+  hipLaunchKernelGGL(sdk::k_bin_totals, dim3((in.nbins + 255) / 256), dim3(256), 0, s, in, cnt);
+  launch_scan_excl(cnt, off, in.nbins, status, tile_counter, epoch, err, s);
+}
+
+void launch_sort_bins(const PartOut& in, const uint64_t* off, uint64_t* out, uint64_t* big,
+                      unsigned long long* nbig, unsigned long long* repeats, hipStream_t s) {
+  constexpr int NT = 512, CAP = 4032, BITS = 11, R = 9;
+  const size_t lds = CAP * 8 + ((4 << BITS) + 4) + NT / 64 * 4;
+  allow_lds(&sdk::k_sort_bins<NT, CAP, BITS, R>, lds);
+  hipLaunchKernelGGL((sdk::k_sort_bins<NT, CAP, BITS, R>), dim3(in.nbins), dim3(NT), lds, s, in, off,
+                     out, big, nbig, repeats);
+}
+
+void launch_place_bins(const uint64_t* X, uint64_t m, int lb, const uint64_t* off, uint64_t* out,
+                       unsigned long long* repeats, hipStream_t s) {
+  if (!m) return;
+  hipLaunchKernelGGL(sdk::k_place_bins, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, X, m, lb,
+                     off, out, repeats);
 }
 
 template <int NT, int SB>

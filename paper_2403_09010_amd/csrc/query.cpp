@@ -395,6 +395,146 @@ void index_free(sd_index* idx) {
   delete idx;
 }
 
+namespace {
+
+// The nk variants of n packed sequences, in order, to E, by a partition into
+// bins of their top hash bits and a sort of each bin in LDS. Bins too large for
+// that (single variants shared by thousands of sequences) are sorted together
+// by digit passes and put in their places. Returns the distinct elements, or 0
+// if an overflow area was too small or those bins hold over a quarter of the
+// elements: digit passes over everything do as well then.
+//
+// Bins of at most SORT_BIN_MEAN elements: small inputs take 2^8 bins of 512 or
+// more, so that every CU has one. Beyond 2^11 bins the partition takes two
+// levels, as a search's does beyond 2^12. Against one histogram, five digit passes over
+// everything and a copy: 2M sequences, k = 2 (202M elements), 14.5 and 2.4
+// ms of kernels.
+uint64_t sorted_bins(Call& cl0, const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nk,
+                     int k, uint32_t idbits, uint64_t* E) {
+  sd_ctx* c = cl0.c;
+  hipStream_t s = cl0.s;
+  Scratch sc(c);
+  Call cl{c, s, sc, cl0.tm, cl0.counters};
+  int lb = 1;
+  while ((nk >> lb) > SORT_BIN_MEAN || (lb < 8 && (nk >> lb) > 512)) ++lb;
+  const int nxl = nk >= (2u << 20) ? 3 : 0;
+  const int lb1 = lb > 11 ? std::max(8, lb - PART_MAX_SPLIT) : lb;
+  const uint64_t over_cap = nk / 16 + 65536;
+  uint32_t* over = cl.counters + CNT_OVER;
+  PartOut p = part_out(cl, nk, lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
+  launch_gen_part(seq, vcnt, n, nk, k, idbits, p, s);
+  if (lb1 < lb) {
+    const PartOut p2 = part_out(cl, nk, lb, nxl, over_cap, over);
+    launch_part_split(p, p2, s);
+    p = p2;
+  }
+  uint64_t* off = sc.get<uint64_t>(p.nbins + 1);
+  const uint64_t tiles = (p.nbins + scan_tile() - 1) / scan_tile();
+  const uint32_t epoch = next_epoch(c, tiles, s);
+  launch_bin_offsets(p, sc.get<uint32_t>(p.nbins), off, c->status, cl.tile_counter(), epoch,
+                     cl.lb_err(), s);
+  const uint64_t big_cap = ((uint64_t)p.nbins << nxl) + 1;
+  uint64_t* big = sc.get<uint64_t>(2 * big_cap);
+  auto* nbig = reinterpret_cast<unsigned long long*>(cl.counters + CNT_NBIG);
+  auto* repeats = reinterpret_cast<unsigned long long*>(cl.counters + CNT_CAND);
+  launch_sort_bins(p, off, E, big, nbig, repeats, s);
+  auto counters = [&] {
+    const uint32_t* h = static_cast<const uint32_t*>(readback(c, cl.counters, CNT_TOTAL * 4, s));
+    if (h[CNT_LBERR] & SD_ERRBIT_LOOKBACK)
+      throw Error{SD_E_HIP, "internal error: a look-back wait timed out"};
+    return h;
+  };
+  const uint32_t* h = counters();
+  if (h[CNT_OVER1] || h[CNT_OVER] > over_cap) return 0;
+  uint64_t nb, rep;
+  std::memcpy(&nb, h + CNT_NBIG, 8);
+  std::memcpy(&rep, h + CNT_CAND, 8);
+  if (nb) {
+    std::vector<uint64_t> hb(2 * (nb + 1)), start(nb + 1);
+    hip_check(hipMemcpyAsync(hb.data(), big, nb * 16, hipMemcpyDeviceToHost, s), "D2H big");
+    const uint64_t n_over = h[CNT_OVER];
+    hip_check(hipStreamSynchronize(s), "synchronise");
+    hb[2 * nb] = p.slots;
+    hb[2 * nb + 1] = p.slots + n_over;
+    uint64_t tot = 0;
+    for (uint64_t x = 0; x <= nb; ++x) {
+      start[x] = tot;
+      tot += hb[2 * x + 1] - hb[2 * x];
+    }
+    if (tot > nk / 4 + 65536) return 0;
+    uint64_t* dstart = sc.get<uint64_t>(nb + 1);
+    hip_check(hipMemcpyAsync(big, hb.data(), (nb + 1) * 16, hipMemcpyHostToDevice, s), "H2D big");
+    hip_check(hipMemcpyAsync(dstart, start.data(), (nb + 1) * 8, hipMemcpyHostToDevice, s),
+              "H2D starts");
+    uint64_t* g1 = sc.get<uint64_t>(tot);
+    uint64_t* g2 = sc.get<uint64_t>(tot);
+    launch_gather_big(p.elem, big, dstart, (uint32_t)(nb + 1), g1, s);
+    uint32_t* hist = sc.get<uint32_t>(8 * 256);
+    launch_fill_u32(hist, 0, 8 * 256, s);
+    launch_radix_hist(g1, nullptr, 1, tot, hist, s);
+    const std::vector<Digit> digits = top_digits(0);
+    std::vector<const uint32_t*> hists;
+    for (const Digit& d : digits) hists.push_back(hist + (d.shift / 8) * 256);
+    const bool flip = radix_sort(cl, g1, nullptr, nullptr, g2, nullptr, nullptr, 1, false,
+                                 (uint32_t)tot, digits, hists);
+    launch_place_bins(flip ? g2 : g1, tot, p.lb, off, E, repeats, s);
+    h = counters();
+    std::memcpy(&rep, h + CNT_CAND, 8);
+  }
+  if (!rep) return nk;
+  // two variants of one sequence share a hash: rare, dropped by a pass over all
+  uint64_t* uniq = sc.get<uint64_t>(nk);
+  const uint64_t utiles = (nk + unique_tile() - 1) / unique_tile();
+  const uint32_t uepoch = next_epoch(c, utiles, s);
+  launch_fill_u64(reinterpret_cast<uint64_t*>(repeats), 0, 1, s);
+  launch_unique_compact(E, nk, uniq, c->status, cl.tile_counter(), uepoch, repeats, cl.lb_err(), s);
+  h = counters();
+  uint64_t left;
+  std::memcpy(&left, h + CNT_CAND, 8);
+  hip_check(hipMemcpyAsync(E, uniq, left * 8, hipMemcpyDeviceToDevice, s), "copy index");
+  return left;
+}
+
+// The same by digit passes over all elements; idx->E is taken here if it is not yet.
+uint64_t sorted_passes(Call& cl, sd_index* idx, const u128* seq, const uint32_t* vcnt, uint64_t n,
+                       uint64_t nk, int k) {
+  sd_ctx* c = cl.c;
+  hipStream_t s = cl.s;
+  uint64_t* voff = cl.sc.get<uint64_t>(n + 1);
+  const uint64_t stiles = (n + scan_tile() - 1) / scan_tile();
+  const uint32_t sepoch = next_epoch(c, stiles, s);
+  launch_scan_excl(vcnt, voff, n, c->status, cl.tile_counter(), sepoch, cl.lb_err(), s);
+  uint64_t* e1 = cl.sc.get<uint64_t>(nk);
+  uint64_t* e2 = cl.sc.get<uint64_t>(nk);
+  uint32_t* unused = cl.sc.get<uint32_t>(3 * 256);
+  const uint32_t z[3] = {0, 0, 0};
+  launch_vargen_hash(seq, voff, n, k, true, e1, idx->idbits, 0, z, z, unused, nullptr,
+                     VG_MAX_SEQS_PER_BLOCK, s);
+  uint32_t* hist = cl.sc.get<uint32_t>(8 * 256);
+  launch_fill_u32(hist, 0, 8 * 256, s);
+  launch_radix_hist(e1, nullptr, 1, nk, hist, s);
+  const std::vector<Digit> digits = top_digits((int)idx->idbits);
+  std::vector<const uint32_t*> hists;
+  for (const Digit& d : digits) hists.push_back(hist + (d.shift / 8) * 256);
+  const bool flip = radix_sort(cl, e1, nullptr, nullptr, e2, nullptr, nullptr, 1, false,
+                               (uint32_t)nk, digits, hists);
+  uint64_t* sorted = flip ? e2 : e1;
+  uint64_t* uniq = flip ? e1 : e2;
+  unsigned long long* ucount = reinterpret_cast<unsigned long long*>(cl.counters + CNT_CAND);
+  const uint64_t tiles = (nk + unique_tile() - 1) / unique_tile();
+  const uint32_t epoch = next_epoch(c, tiles, s);
+  launch_fill_u64(reinterpret_cast<uint64_t*>(ucount), 0, 1, s);
+  launch_unique_compact(sorted, nk, uniq, c->status, cl.tile_counter(), epoch, ucount,
+                        cl.lb_err(), s);
+  const uint64_t left = *static_cast<const uint64_t*>(readback(c, ucount, 8, s));
+  check_lookback(cl);
+  if (!idx->E) idx->E = static_cast<uint64_t*>(index_alloc(c, idx, std::max<uint64_t>(left, 1) * 8));
+  hip_check(hipMemcpyAsync(idx->E, uniq, left * 8, hipMemcpyDeviceToDevice, s), "copy index");
+  return left;
+}
+
+}  // namespace
+
 sd_index* index_build(sd_ctx* c, const sd_seqs* ref, int k, hipStream_t s) {
   check_seqs(ref);
   if (k < 0 || k > 3) throw Error{SD_E_INVAL, "k must be 0, 1, 2 or 3"};
@@ -410,44 +550,34 @@ sd_index* index_build(sd_ctx* c, const sd_seqs* ref, int k, hipStream_t s) {
     const DevSeqs in = stage_seqs(c, sc, ref, s);
     idx->ref_seq = static_cast<u128*>(index_alloc(c, idx, std::max<uint64_t>(in.n, 1) * 16));
     uint64_t nk = 0;
-    const uint64_t* E = nullptr;
     if (in.n) {
-      const Packed p = pack_and_count(cl, in, k, true);
-      hip_check(hipMemcpyAsync(idx->ref_seq, p.seq, in.n * 16, hipMemcpyDeviceToDevice, s), "copy");
-      nk = p.nkeys;
-      uint64_t* e1 = sc.get<uint64_t>(nk);
-      uint64_t* e2 = sc.get<uint64_t>(nk);
-      uint32_t* unused = sc.get<uint32_t>(3 * 256);
-      const uint32_t z[3] = {0, 0, 0};
-      launch_vargen_hash(p.seq, p.voff, in.n, k, true, e1, idx->idbits, 0, z, z, unused, nullptr,
-                         VG_MAX_SEQS_PER_BLOCK, s);
-      uint32_t* hist = sc.get<uint32_t>(8 * 256);
-      launch_fill_u32(hist, 0, 8 * 256, s);
-      launch_radix_hist(e1, nullptr, 1, nk, hist, s);
-      const std::vector<Digit> digits = top_digits((int)idx->idbits);
-      std::vector<const uint32_t*> hists;
-      for (const Digit& d : digits) hists.push_back(hist + (d.shift / 8) * 256);
-      const bool flip = radix_sort(cl, e1, nullptr, nullptr, e2, nullptr, nullptr, 1, false,
-                                   (uint32_t)nk, digits, hists);
-      uint64_t* sorted = flip ? e2 : e1;
-      uint64_t* uniq = flip ? e1 : e2;
-      unsigned long long* ucount = reinterpret_cast<unsigned long long*>(cl.counters + CNT_CAND);
-      const uint64_t tiles = (nk + unique_tile() - 1) / unique_tile();
-      const uint32_t epoch = next_epoch(c, tiles, s);
-      launch_unique_compact(sorted, nk, uniq, c->status, cl.tile_counter(), epoch, ucount,
-                            cl.lb_err(), s);
-      nk = *static_cast<const uint64_t*>(readback(c, ucount, 8, s));
-      check_lookback(cl);
-      E = uniq;
+      uint32_t* vcnt = sc.get<uint32_t>(in.n);
+      launch_pack(in.codes, in.offs, in.n, k, true, idx->ref_seq, sc.get<u128>(in.n), vcnt,
+                  cl.counters + CNT_ERR, s,
+                  reinterpret_cast<unsigned long long*>(cl.counters + CNT_SUMS));
+      const uint32_t* h =
+          static_cast<const uint32_t*>(readback(c, cl.counters, CNT_TOTAL * 4, s));
+      raise_validation(h[CNT_ERR]);
+      nk = pack_total(h);
+      if (nk >= 0xFFFFFFFFull)
+        throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 deletion variants"};
+      uint64_t kept = 0;
+      // (positions of up to 2^31 elements and their regions' slack take 32 bits;
+      // the digit passes' knob chooses them)
+      if (nk < (1ull << 31) && !c->sort_items)
+        if_memory_suffices(c, [&] {
+          idx->E = static_cast<uint64_t*>(index_alloc(c, idx, nk * 8));
+          return (kept = sorted_bins(cl, idx->ref_seq, vcnt, in.n, nk, k, idx->idbits, idx->E)) > 0;
+        });
+      if (!kept) kept = sorted_passes(cl, idx, idx->ref_seq, vcnt, in.n, nk, k);
+      nk = kept;
     }
     idx->n_keys = nk;
     idx->bits = index_bits(nk);
     const uint32_t nseg = 1u << idx->bits;
-    idx->E = static_cast<uint64_t*>(index_alloc(c, idx, std::max<uint64_t>(nk, 1) * 8));
+    if (!idx->E) idx->E = static_cast<uint64_t*>(index_alloc(c, idx, 8));
     idx->seg_start = static_cast<uint32_t*>(index_alloc(c, idx, (size_t)nseg * 4));
     idx->seg_end = static_cast<uint32_t*>(index_alloc(c, idx, (size_t)nseg * 4));
-    if (nk)
-      hip_check(hipMemcpyAsync(idx->E, E, nk * 8, hipMemcpyDeviceToDevice, s), "copy index");
     launch_seg_bounds(idx->E, nk, 64u - (uint32_t)idx->bits, idx->seg_start, idx->seg_end, s);
     hip_check(hipStreamSynchronize(s), "synchronise");
     idx->bytes = idx->n_ref * 16 + nk * 8 + (uint64_t)nseg * 8;

@@ -247,6 +247,8 @@ struct PartOut {
 constexpr uint64_t PART_BIG_KEYS = 16ull << 20;
 // most bins (log2) one kernel partitions into
 constexpr int PART_MAX_LB = 12;
+// most bits of one split of a first partition's bins
+constexpr int PART_MAX_SPLIT = 9;
 // every distinct <= k-deletion variant of n packed sequences (vcnt: their
 // counts, nkeys in all), partitioned
 void launch_gen_part(const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nkeys, int k,
@@ -338,6 +340,19 @@ constexpr double JOIN_QUERY_MAX = 20000, JOIN_SURVIVORS = 2600, JOIN_BITMAP = 1 
 void launch_join_bins(const PartOut& in, const uint64_t* E, const uint32_t* seg_start,
                       const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
                       const PairBins& out, hipStream_t s);
+// The bins' starts (off: nbins + 1 entries; cnt: nbins of scratch).
+void launch_bin_offsets(const PartOut& in, uint32_t* cnt, uint64_t* off, uint64_t* status,
+                        uint32_t* tile_counter, uint32_t epoch, uint32_t* err, hipStream_t s);
+// The elements of every bin in order of the whole word to out; the regions of
+// bins too large for a workgroup (SORT_BIN_MEAN is a safe mean) are listed in
+// big instead (at most nbins << nxl ranges). *repeats counts repeated elements,
+// which stay, next to each other. Both counters are zeroed by the caller.
+constexpr uint32_t SORT_BIN_MEAN = 3200;
+void launch_sort_bins(const PartOut& in, const uint64_t* off, uint64_t* out, uint64_t* big,
+                      unsigned long long* nbig, unsigned long long* repeats, hipStream_t s);
+// m sorted elements, all there are of their bins, to the bins' places
+void launch_place_bins(const uint64_t* X, uint64_t m, int lb, const uint64_t* off, uint64_t* out,
+                       unsigned long long* repeats, hipStream_t s);
 // id pairs of equal hashes in every bin; big receives element ranges that
 // take the sort-and-runs path instead (at most (nbins << nxl) + 1)
 void launch_filter_group(const PartOut& in, uint64_t nkeys, uint32_t idbits, const PairBins& out,

@@ -172,3 +172,47 @@ def test_query_copies(query_paths):
         for q in queries:
             same_query(query_paths, idx, q, 1)
         idx.free()
+
+
+@pytest.fixture(scope="module")
+def build_paths():
+    from paper_2403_09010_amd import Context
+    from paper_2403_09010_amd.symdel import OPT_SORT_ITEMS
+    a, b = Context(0), Context(0)
+    b.set_option(OPT_SORT_ITEMS, 16)
+    yield a, b
+    a.close()
+    b.close()
+
+
+def same_index(paths, ref, k, queries):
+    """Indexes built bin by bin and by digit passes: the same sizes and answers."""
+    print(f"[index] {len(ref[1]) - 1} references k={k}", flush=True)
+    a, b = (c.build_index(*ref, k) for c in paths)
+    assert a.info() == b.info()
+    for q in queries:
+        x, y = paths[0].query(a, *q, k), paths[0].query(b, *q, k)
+        assert len(x) == len(y)
+        assert np.array_equal(x.i, y.i) and np.array_equal(x.j, y.j) and np.array_equal(x.d, y.d)
+    a.free()
+    b.free()
+
+
+# 2^1 to 2^8 bins, one level up to 2^12 bins, two levels, every radius; queries
+# that look their variants up, and that join whole bins
+@pytest.mark.parametrize("n,k", [(1, 2), (65, 0), (700, 3), (9_000, 1), (60_000, 2), (300_000, 2),
+                                 (100_000, 3), (900_000, 2)])
+def test_index_sizes(build_paths, n, k):
+    ref = cdr3gen.generate(n % 89, n)
+    same_index(build_paths, ref, k, [cdr3gen.generate_query(3, min(n, 3_000), *ref, ref_mut_frac=0.5),
+                                     cdr3gen.generate_query(4, min(n, 40_000), *ref, ref_mut_frac=0.9)])
+
+
+# variants shared by so many references that bins hold more than a workgroup
+# sorts, that a region overflows, and that most elements are in such bins
+@pytest.mark.parametrize("copies,rest", [(7_000, 60_000), (9_000, 3_000), (30_000, 300_000),
+                                         (50_000, 10)])
+def test_index_copies(build_paths, copies, rest):
+    s = strings_of(19, rest)
+    ref = csr(s[:rest // 2] + [s[0]] * copies + [s[1][:1]] * 3 + s[rest // 2:])
+    same_index(build_paths, ref, 2, [csr(s[:3] + s[-500:]), csr(s[-min(rest, 30_000):])])
