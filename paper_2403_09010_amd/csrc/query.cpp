@@ -26,6 +26,26 @@
 
 namespace sd {
 
+namespace {
+
+void pack(Call& cl, const DevSeqs& in, int k, bool distinct, u128* seq, u128* planes,
+          uint32_t* vcnt, unsigned long long* sums) {
+  if (in.sets)
+    launch_pack_sets(in.sets, in.nsets, in.n, k, distinct, seq, planes, vcnt, cl.counters + CNT_ERR,
+                     cl.s, sums);
+  else
+    launch_pack(in.codes, in.offs, in.n, k, distinct, seq, planes, vcnt, cl.counters + CNT_ERR,
+                cl.s, sums);
+}
+
+// bad offsets come first, as in sets that are checked on the host
+void raise_packed(const DevSeqs& in, uint32_t err) {
+  if (in.sets && (err & SD_ERRBIT_OFFSETS)) err = SD_ERRBIT_OFFSETS;
+  raise_validation(err);
+}
+
+}  // namespace
+
 Packed pack_and_count(Call& cl, const DevSeqs& in, int k, bool distinct) {
   Packed p;
   p.seq = cl.sc.get<u128>(in.n);
@@ -33,8 +53,7 @@ Packed pack_and_count(Call& cl, const DevSeqs& in, int k, bool distinct) {
   uint32_t* vcnt = cl.sc.get<uint32_t>(in.n);
   p.voff = cl.sc.get<uint64_t>(in.n + 1);
   launch_fill_u32(cl.counters + CNT_ERR, 0, 1, cl.s);
-  launch_pack(in.codes, in.offs, in.n, k, distinct, p.seq, p.planes, vcnt, cl.counters + CNT_ERR,
-              cl.s);
+  pack(cl, in, k, distinct, p.seq, p.planes, vcnt, nullptr);
   const uint64_t tiles = (in.n + scan_tile() - 1) / scan_tile();
   const uint32_t epoch = next_epoch(cl.c, tiles, cl.s);
   launch_scan_excl(vcnt, p.voff, in.n, cl.c->status, cl.tile_counter(), epoch, cl.lb_err(), cl.s);
@@ -42,7 +61,7 @@ Packed pack_and_count(Call& cl, const DevSeqs& in, int k, bool distinct) {
             "copy");
   const uint32_t* h =
       static_cast<const uint32_t*>(readback(cl.c, cl.counters, (CNT_NKEYS + 2) * 4, cl.s));
-  raise_validation(h[CNT_ERR]);
+  raise_packed(in, h[CNT_ERR]);
   std::memcpy(&p.nkeys, h + CNT_NKEYS, 8);
   if (p.nkeys >= 0xFFFFFFFFull) throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 deletion variants"};
   return p;
@@ -103,8 +122,8 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
   u128* seq = sc.get<u128>(q.n);
   u128* planes = sc.get<u128>(q.n);
   uint32_t* vcnt = sc.get<uint32_t>(q.n);
-  launch_pack(q.codes, q.offs, q.n, k, true, seq, planes, vcnt, cl.counters + CNT_ERR, s,
-              reinterpret_cast<unsigned long long*>(cl.counters + CNT_SUMS));
+  pack(cl, q, k, true, seq, planes, vcnt,
+       reinterpret_cast<unsigned long long*>(cl.counters + CNT_SUMS));
   cl.tm.mark("q_pack_scan", (double)q.n * 48, 1);
   // small sets are not waited for here: their variants are looked up whatever
   // their number, and the flags are read with the result
@@ -113,7 +132,7 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
   const bool known = nk > (1u << 20) || nk * PROBE_RATIO > idx->n_keys;
   if (known) {
     const uint32_t* h = static_cast<const uint32_t*>(readback(c, cl.counters, CNT_TOTAL * 4, s));
-    raise_validation(h[CNT_ERR]);
+    raise_packed(q, h[CNT_ERR]);
     nk = pack_total(h);
     if (nk >= 0xFFFFFFFFull) throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 deletion variants"};
   }
@@ -161,7 +180,7 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
                            idx->idbits, bins, s);
       },
       [&](const uint32_t* h, uint64_t*) {
-        if (!known) raise_validation(h[CNT_ERR]);
+        if (!known) raise_packed(q, h[CNT_ERR]);
         nk = pack_total(h);
         if (!join || !h[CNT_OVER]) return PairNext::done;
         join = false;  // copies of single variants overflow their bins: look them up
@@ -641,11 +660,27 @@ void query_sets(sd_ctx* c, const sd_index* idx, int nsets, const sd_seqs* sets, 
       }
       base[last - first] = (uint32_t)qpos;
     }
+    std::vector<SetRef> refs;  // the tile's sets, if all are on the device
+    bool on_device = true;
+    for (int x = first; x < last; ++x)
+      if (sets[x].n) {
+        on_device = on_device && sets[x].on_device;
+        refs.push_back(SetRef{sets[x].codes, sets[x].offsets, base[x - first]});
+      }
     if (last - first == 1 && sets[first].on_device) {
       q = DevSeqs{sets[first].codes, sets[first].offsets, (uint64_t)sets[first].n};
+    } else if (on_device && !refs.empty()) {
+      SetRef* table = sc.get<SetRef>(refs.size());
+      SetRef* host = reinterpret_cast<SetRef*>(stage_area(c, refs.size() * sizeof(SetRef)));
+      std::copy(refs.begin(), refs.end(), host);
+      hip_check(hipMemcpyAsync(table, host, refs.size() * sizeof(SetRef), hipMemcpyHostToDevice, s),
+                "copy set table");
+      stage_done(c, s);
+      q.sets = table;
+      q.nsets = (uint32_t)refs.size();
     } else {
-      // the sets' offsets on the host (device sets read into pinned memory
-      // with one wait), checked and rebased on host threads into pinned
+      // sets on the host (or on both): their offsets on the host (device sets
+      // read into pinned memory with one wait), checked and rebased on host threads into pinned
       // memory, one copy of the tile's offsets; codes one copy per device
       // set and one per run of host sets (through pinned memory)
       size_t dev_words = 0;

@@ -17,6 +17,9 @@ struct DevSeqs {
   const uint8_t* codes;
   const int64_t* offs;
   uint64_t n;
+  // or several device sets, read where they are (device table)
+  const SetRef* sets = nullptr;
+  uint32_t nsets = 0;
 };
 
 inline void check_seqs(const sd_seqs* s) {

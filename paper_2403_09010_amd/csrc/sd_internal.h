@@ -130,6 +130,16 @@ constexpr uint32_t PACK_SUMS = 64;
 void launch_pack(const uint8_t* codes, const int64_t* offs, uint64_t n, int k, bool distinct,
                  u128* seq, u128* planes, uint32_t* vcnt, uint32_t* err, hipStream_t s,
                  unsigned long long* sums = nullptr);
+// The same for the sequences of nsets device sets, one after the other. An offset
+// that decreases or a set that does not start at 0 sets SD_ERRBIT_OFFSETS.
+struct SetRef {
+  const uint8_t* codes;
+  const int64_t* offs;
+  uint64_t base;  // sequences before it
+};
+void launch_pack_sets(const SetRef* sets, uint32_t nsets, uint64_t n, int k, bool distinct,
+                      u128* seq, u128* planes, uint32_t* vcnt, uint32_t* err, hipStream_t s,
+                      unsigned long long* sums = nullptr);
 void launch_vargen(const u128* seq, const uint64_t* voff, uint64_t nseq, int k,
                    uint64_t* key_lo, uint64_t* key_hi, uint32_t* id, hipStream_t s);
 void launch_emit_runs(const uint64_t* key_lo, const uint64_t* key_hi, const uint32_t* id,

@@ -20,9 +20,14 @@ constexpr int NT = 256;
 // ------------------------------------------------------------------ pack
 
 // One thread per sequence; the total of vcnt goes to one of PACK_SUMS counters
-// per workgroup.
+// per workgroup. With SETS, the sequences of nsets device sets, one after the
+// other: read where they are, which spares a batch the copy of its sets into one
+// (20 sets, 750K sequences: 33 us for 1.1 ms of staging through the host).
+template <bool SETS>
 __global__ __launch_bounds__(NT) void k_pack(const uint8_t* __restrict__ codes,
-                                             const int64_t* __restrict__ offs, uint64_t n, int k,
+                                             const int64_t* __restrict__ offs,
+                                             const sd::SetRef* __restrict__ sets, uint32_t nsets,
+                                             uint64_t n, int k,
                                              int distinct, u128* __restrict__ seq,
                                              u128* __restrict__ planes,
                                              uint32_t* __restrict__ vcnt,
@@ -32,10 +37,28 @@ __global__ __launch_bounds__(NT) void k_pack(const uint8_t* __restrict__ codes,
   const uint64_t i = (uint64_t)blockIdx.x * NT + threadIdx.x;
   uint32_t c = 0;
   if (i < n) {
-    const int64_t a = offs[i], b = offs[i + 1];
+    uint64_t at = i;  // in its set
+    if (SETS) {
+      uint32_t lo = 0, hi = nsets - 1;  // last set that starts at or before i
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if (sets[mid].base <= i)
+          lo = mid;
+        else
+          hi = mid - 1;
+      }
+      codes = sets[lo].codes;
+      offs = sets[lo].offs;
+      at -= sets[lo].base;
+    }
+    const int64_t a = offs[at], b = offs[at + 1];
     const int64_t L = b - a;
-    if (L < 1 || L > KEY_MAX_LEN) {
-      atomicOr(err, SD_ERRBIT_LENGTH);
+    // (a sequence that starts below 0 or beyond what the ones before it can take
+    // follows one that is flagged: it is not read)
+    const bool lost = SETS && (a < 0 || a > (int64_t)at * KEY_MAX_LEN);
+    if (SETS && (L < 0 || (at == 0 && a != 0))) atomicOr(err, SD_ERRBIT_OFFSETS);
+    if (L < 1 || L > KEY_MAX_LEN || lost) {
+      if (!lost) atomicOr(err, SD_ERRBIT_LENGTH);
       seq[i] = 0;
       if (planes) planes[i] = 0;
     } else {
@@ -614,8 +637,16 @@ void launch_pack(const uint8_t* codes, const int64_t* offs, uint64_t n, int k, b
                  u128* seq, u128* planes, uint32_t* vcnt, uint32_t* err, hipStream_t s,
                  unsigned long long* sums) {
   if (!n) return;
-  hipLaunchKernelGGL(sdk::k_pack, dim3(blocks_for(n, sdk::NT)), dim3(sdk::NT), 0, s, codes, offs,
-                     n, k, distinct ? 1 : 0, seq, planes, vcnt, err, sums);
+  hipLaunchKernelGGL(sdk::k_pack<false>, dim3(blocks_for(n, sdk::NT)), dim3(sdk::NT), 0, s, codes,
+                     offs, nullptr, 0u, n, k, distinct ? 1 : 0, seq, planes, vcnt, err, sums);
+}
+
+void launch_pack_sets(const SetRef* sets, uint32_t nsets, uint64_t n, int k, bool distinct,
+                      u128* seq, u128* planes, uint32_t* vcnt, uint32_t* err, hipStream_t s,
+                      unsigned long long* sums) {
+  if (!n) return;
+  hipLaunchKernelGGL(sdk::k_pack<true>, dim3(blocks_for(n, sdk::NT)), dim3(sdk::NT), 0, s, nullptr,
+                     nullptr, sets, nsets, n, k, distinct ? 1 : 0, seq, planes, vcnt, err, sums);
 }
 
 void launch_vargen(const u128* seq, const uint64_t* voff, uint64_t nseq, int k, uint64_t* key_lo,

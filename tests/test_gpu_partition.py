@@ -216,3 +216,45 @@ def test_index_copies(build_paths, copies, rest):
     s = strings_of(19, rest)
     ref = csr(s[:rest // 2] + [s[0]] * copies + [s[1][:1]] * 3 + s[rest // 2:])
     same_index(build_paths, ref, 2, [csr(s[:3] + s[-500:]), csr(s[-min(rest, 30_000):])])
+
+
+# batches of device sets are packed where they lie: set sizes around a
+# workgroup's 256 sequences, empty sets, one set, tiles of several sets
+@pytest.mark.parametrize("sizes", [(0, 1, 255, 0, 256, 257, 1, 0), (700,), (0, 0), (1,) * 70,
+                                   (3_000, 40_000, 900)])
+def test_batch_device_sets(query_paths, sizes):
+    import torch
+    ctx = query_paths[0]
+    ref = cdr3gen.generate(29, 8_000)
+    idx = ctx.build_index(*ref, 2)
+    none = (np.zeros(0, np.uint8), np.zeros(1, np.int64))
+    sets = [cdr3gen.generate_query(600 + x, n, *ref, ref_mut_frac=0.4) if n else none
+            for x, n in enumerate(sizes)]
+    dev = [tuple(torch.from_numpy(a).cuda() for a in q) for q in sets]
+    for q, r in zip(sets, ctx.query_batch(idx, dev, 2)):
+        want = ctx.query(idx, *q, 2)
+        assert len(r) == len(want)
+        for a, b in zip(r.numpy(), want.numpy()):
+            assert np.array_equal(a, b)
+    idx.free()
+
+
+# offsets of a device set that the kernel must refuse without reading past them
+@pytest.mark.parametrize("at,value,name", [(0, 3, "SD_E_INVAL"), (5, -9, "SD_E_INVAL"),
+                                           (40, 1 << 40, "SD_E_INVAL"),
+                                           (-1, 1 << 40, "SD_E_LENGTH")])
+def test_batch_device_offsets_refused(query_paths, at, value, name):
+    import torch
+    from paper_2403_09010_amd import SymdelError
+    ctx = query_paths[0]
+    ref = cdr3gen.generate(29, 3_000)
+    idx = ctx.build_index(*ref, 1)
+    good = cdr3gen.generate_query(7, 300, *ref)
+    bad = good[1].copy()
+    bad[at] = value
+    sets = [tuple(torch.from_numpy(a).cuda() for a in q) for q in (good, (good[0], bad), good)]
+    with pytest.raises(SymdelError) as e:
+        ctx.query_batch(idx, sets, 1)
+    assert e.value.name == name
+    assert len(ctx.query_batch(idx, sets[::2], 1)) == 2
+    idx.free()
