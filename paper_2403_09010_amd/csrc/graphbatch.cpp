@@ -590,20 +590,22 @@ void query_sets_graph(sd_ctx* c, const sd_index* idx, int nsets, const sd_seqs* 
         sj[x] = dalloc_t<uint32_t>(c, total[x]);
         sd[x] = dalloc_t<uint8_t>(c, total[x]);
       }
+      std::vector<PairSlice> slices;
       for (size_t x = 0; x < plan->tiles.size(); ++x) {
         const TileBufs& t = plan->tiles[x];
         uint32_t q = 0;
         for (size_t p = 0; p < t.pieces.size(); ++p) {
           const Piece& pc = t.pieces[p];
           const uint64_t lo = res[x].bounds[p], n = res[x].bounds[p + 1] - lo;
-          launch_slice_rebase(res[x].i, res[x].j, res[x].d, lo, n, pc.first - (int64_t)q,
-                              si[pc.set] + at[pc.set], sj[pc.set] + at[pc.set],
-                              sd[pc.set] + at[pc.set], s);
+          slices.push_back(PairSlice{res[x].i + lo, res[x].j + lo, res[x].d + lo, n,
+                                     pc.first - (int64_t)q, si[pc.set] + at[pc.set],
+                                     sj[pc.set] + at[pc.set], sd[pc.set] + at[pc.set]});
           at[pc.set] += n;
           npairs += n;
           q += (uint32_t)pc.count;
         }
       }
+      launch_copy_slices(slices.data(), (int)slices.size(), s);
       for (int x = 0; x < nsets; ++x) finish_output(c, si[x], sj[x], sd[x], total[x], &outs[x], s);
       hip_check(hipStreamSynchronize(s), "synchronise");
     }

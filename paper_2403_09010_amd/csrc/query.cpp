@@ -736,14 +736,18 @@ void query_sets(sd_ctx* c, const sd_index* idx, int nsets, const sd_seqs* sets, 
           }
           fill_host_slices(c, r.i, r.j, r.d, r.n, sl, outs, s);
         }
+        std::vector<PairSlice> slices;
         for (int x = 0; x < ns && !host_out; ++x) {
           const uint64_t lo = hb[x], n = hb[x + 1] - hb[x];
           uint32_t* oi = dalloc_t<uint32_t>(c, n);
           uint32_t* oj = dalloc_t<uint32_t>(c, n);
           uint8_t* od = dalloc_t<uint8_t>(c, n);
-          launch_slice_rebase(r.i, r.j, r.d, lo, n, -(int64_t)base[x], oi, oj, od, s);
-          finish_output(c, oi, oj, od, n, &outs[first + x], s);
+          slices.push_back(
+              PairSlice{r.i + lo, r.j + lo, r.d + lo, n, -(int64_t)base[x], oi, oj, od});
         }
+        launch_copy_slices(slices.data(), (int)slices.size(), s);
+        for (size_t x = 0; x < slices.size(); ++x)
+          finish_output(c, slices[x].oi, slices[x].oj, slices[x].od, slices[x].n, &outs[first + x], s);
       } catch (...) {
         dfree(c, r.i);
         dfree(c, r.j);

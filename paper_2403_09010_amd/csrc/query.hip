@@ -16,7 +16,7 @@
 //                     followed by a finer metric), kept when both the unit
 //                     distance is <= k and the score is <= max_score
 //   k_set_ranges      per-set slices of a (q, r)-sorted result
-//   k_slice_rebase    copy one set's slice with query ids made set-local
+//   k_copy_slices     copy sets' slices with query ids made set-local
 #include "distance.h"
 #include "sd_device.h"
 #include "sd_internal.h"
@@ -285,15 +285,19 @@ __global__ void k_set_ranges(const uint32_t* __restrict__ qi, uint64_t n,
   bounds[s] = lo;
 }
 
-__global__ void k_slice_rebase(const uint32_t* __restrict__ qi, const uint32_t* __restrict__ rj,
-                               const uint8_t* __restrict__ d, uint64_t lo, uint64_t n,
-                               int64_t shift, uint32_t* __restrict__ oi,
-                               uint32_t* __restrict__ oj, uint8_t* __restrict__ od) {
-  for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n;
-       t += (uint64_t)gridDim.x * blockDim.x) {
-    oi[t] = (uint32_t)((int64_t)qi[lo + t] + shift);
-    oj[t] = rj[lo + t];
-    od[t] = d[lo + t];
+// Slices of results, each to its own arrays (blockIdx.y): one launch for up to
+// PAIR_SLICES sets, whose own launches took 4 us of host time each.
+struct PairSliceArgs {
+  sd::PairSlice s[sd::PAIR_SLICES];
+};
+
+__global__ __launch_bounds__(QNT) void k_copy_slices(PairSliceArgs a) {
+  const sd::PairSlice& p = a.s[blockIdx.y];
+  for (uint64_t t = (uint64_t)blockIdx.x * QNT + threadIdx.x; t < p.n;
+       t += (uint64_t)gridDim.x * QNT) {
+    p.oi[t] = (uint32_t)((int64_t)p.i[t] + p.shift);
+    p.oj[t] = p.j[t];
+    p.od[t] = p.d[t];
   }
 }
 
@@ -345,14 +349,19 @@ void launch_set_ranges(const uint32_t* qi, uint64_t n, const uint32_t* set_base,
                      set_base, nb, bounds);
 }
 
-void launch_slice_rebase(const uint32_t* qi, const uint32_t* rj, const uint8_t* d, uint64_t lo,
-                         uint64_t n, int64_t shift, uint32_t* oi, uint32_t* oj, uint8_t* od,
-                         hipStream_t s) {
-  if (!n) return;
-  uint64_t g = (n + 255) / 256;
-  if (g > 4096) g = 4096;
-  hipLaunchKernelGGL(sdk::k_slice_rebase, dim3((unsigned)g), dim3(256), 0, s, qi, rj, d, lo, n,
-                     shift, oi, oj, od);
+void launch_copy_slices(const PairSlice* slices, int count, hipStream_t s) {
+  for (int x = 0; x < count; x += PAIR_SLICES) {
+    sdk::PairSliceArgs a{};
+    const int m = std::min(count - x, PAIR_SLICES);
+    uint64_t longest = 0;
+    for (int y = 0; y < m; ++y) {
+      a.s[y] = slices[x + y];
+      longest = std::max(longest, a.s[y].n);
+    }
+    if (!longest) continue;
+    const uint64_t g = std::min<uint64_t>((longest + 1023) / 1024, 4096);
+    hipLaunchKernelGGL(sdk::k_copy_slices, dim3((unsigned)g, (unsigned)m), dim3(sdk::QNT), 0, s, a);
+  }
 }
 
 }  // namespace sd

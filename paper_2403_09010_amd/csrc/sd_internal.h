@@ -395,9 +395,19 @@ void launch_verify_weighted(const uint64_t* cand, uint64_t c, const u128* sa, co
 void launch_set_ranges(const uint32_t* qi, uint64_t n, const uint32_t* set_base, uint32_t nb,
                        uint64_t* bounds, hipStream_t s, const unsigned long long* n_dev = nullptr);
 // oi[t] = qi[lo + t] + shift, oj[t] = rj[lo + t], od[t] = d[lo + t] for t < n
-void launch_slice_rebase(const uint32_t* qi, const uint32_t* rj, const uint8_t* d, uint64_t lo,
-                         uint64_t n, int64_t shift, uint32_t* oi, uint32_t* oj, uint8_t* od,
-                         hipStream_t s);
+// slices of results copied to arrays of their own, i shifted on the way
+struct PairSlice {
+  const uint32_t* i;
+  const uint32_t* j;
+  const uint8_t* d;
+  uint64_t n;
+  int64_t shift;
+  uint32_t* oi;
+  uint32_t* oj;
+  uint8_t* od;
+};
+constexpr int PAIR_SLICES = 32;  // of one launch
+void launch_copy_slices(const PairSlice* slices, int count, hipStream_t s);
 // learned index
 size_t leaf_bytes();
 size_t coord_bytes();
