@@ -38,8 +38,7 @@ struct Shape {
 };
 
 // Bins of one level (2^lb bins, 2^nxl regions each).
-PairBins level(Scratch& sc, uint64_t guess, int lb, int nxl, double var, uint32_t most,
-               hipStream_t s) {
+PairBins level(Scratch& sc, uint64_t guess, int lb, int nxl, double var, uint32_t most) {
   PairBins b{};
   b.lb = lb;
   b.nbins = 1u << lb;
@@ -49,11 +48,12 @@ PairBins level(Scratch& sc, uint64_t guess, int lb, int nxl, double var, uint32_
   b.region =
       (uint32_t)std::min<double>(most, mean * 1.25 + 6.0 * std::sqrt(var * mean) + 32);
   b.cursor = sc.get<uint32_t>(nc);
-  launch_fill_u32(b.cursor, 0, nc, s);
   return b;
 }
 
-Shape shape(Scratch& sc, uint64_t guess, int k, int spread, hipStream_t s) {
+ZeroRange cursors(const PairBins& b) { return {b.cursor, (uint64_t)b.nbins << b.nxl}; }
+
+Shape shape(Scratch& sc, uint64_t guess, int k, int spread) {
   Shape sh;
   sh.split = guess >= (8ull << 20);
   sh.wide = sh.split || k >= 3;
@@ -62,16 +62,16 @@ Shape shape(Scratch& sc, uint64_t guess, int k, int spread, hipStream_t s) {
   while ((guess >> lb) > mean_max) ++lb;
   const int nxl = sh.split ? 3 : 0;
   const uint32_t most = pair_bin_max(sh.wide) >> nxl;
-  sh.b = level(sc, guess, lb, nxl, spread ? 1e6 : 32, most, s);
+  sh.b = level(sc, guess, lb, nxl, spread ? 1e6 : 32, most);
   sh.slots = ((uint64_t)sh.b.nbins << nxl) * sh.b.region;
   sh.fits = sh.slots < 0xFFFFFFFFull && guess < 3000000000ull && lb <= 18;
   if (!sh.fits) return sh;
   sh.b.base = sc.get<uint64_t>(sh.slots);
   if (sh.split) {
     const uint32_t all = (uint32_t)guess;
-    sh.l0 = level(sc, std::min<uint64_t>(guess << spread, 8 * guess), 0, 3, 4096, all, s);
+    sh.l0 = level(sc, std::min<uint64_t>(guess << spread, 8 * guess), 0, 3, 4096, all);
     sh.l0.base = sc.get<uint64_t>((uint64_t)sh.l0.region << 3);
-    sh.l1 = level(sc, guess, (lb + 1) / 2, 3, spread ? 16384 : 1024, all, s);
+    sh.l1 = level(sc, guess, (lb + 1) / 2, 3, spread ? 16384 : 1024, all);
     sh.l1.base = sc.get<uint64_t>(((uint64_t)sh.l1.nbins << 3) * sh.l1.region);
   }
   return sh;
@@ -102,7 +102,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
   for (int attempt = 0; attempt < 8; ++attempt) {
     Scratch sc(c);
     Call cl{c, s, sc, cl0.tm, cl0.counters};
-    Shape sh = shape(sc, guess, q.k, spread, s);
+    Shape sh = shape(sc, guess, q.k, spread);
     if (!sh.fits) return false;
     PairBufs b{};
     b.icnt = sc.get<uint32_t>(q.na);
@@ -118,8 +118,12 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     b.longs = sc.get<uint32_t>(b.long_cap);
     b.state = sc.get<PairState>(1);
     b.err = cl.lb_err();
-    launch_fill_u32(b.icnt, 0, q.na, s);
-    launch_fill_u32(reinterpret_cast<uint32_t*>(b.state), 0, sizeof(PairState) / 4, s);
+    launch_zero({{b.icnt, q.na},
+                 {reinterpret_cast<uint32_t*>(b.state), sizeof(PairState) / 4},
+                 cursors(sh.b),
+                 cursors(sh.l0),
+                 cursors(sh.l1)},
+                s);
     produce(sh.split ? sh.l0 : sh.b);
     cl.tm.mark(stage, (double)nkeys * 8 + (double)guess * 8, 1);
     if (sh.split) {

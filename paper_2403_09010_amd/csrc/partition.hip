@@ -1356,9 +1356,13 @@ static uint32_t seqs_per_tile(uint64_t n, uint64_t nkeys, uint32_t tile, uint32_
 void launch_gen_part(const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nkeys,
                      int k, uint32_t idbits, const PartOut& o, hipStream_t s) {
   if (!n) return;
-  if (nkeys < PART_BIG_KEYS)
-    gen_t<256, 4096>(seq, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 4096, 256), o, s);
-  else if (o.lb <= 11)  // two workgroups on a CU
+  if (nkeys < PART_BIG_KEYS) {
+    // inputs of fewer tiles than CUs: a part of a tile for each CU (10K sequences,
+    // k = 1, in 37 full tiles: 21 us; more and smaller parts than CUs queue for
+    // the bins' cursors instead)
+    const uint32_t most = (uint32_t)std::min<uint64_t>(256, std::max<uint64_t>(8, n / 256));
+    gen_t<256, 4096>(seq, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 4096, most), o, s);
+  } else if (o.lb <= 11)  // two workgroups on a CU
     gen_t<512, 7680>(seq, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 7680, 512), o, s);
   else
     gen_t<1024, 14336>(seq, vcnt, (uint32_t)n, k, idbits, seqs_per_tile(n, nkeys, 14336, 1024), o, s);

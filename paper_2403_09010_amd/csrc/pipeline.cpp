@@ -506,8 +506,13 @@ Verified sort_and_verify(Call& cl, uint64_t* cand, uint64_t nc, uint64_t n, int 
 // comes from the L2): scattering 100M elements into 2^13 bins at once takes
 // 0.92 ms, two levels of 2^8 and 2^5 0.43 + 0.33; 1G elements group in 6.9 ms
 // in bins of 31K elements and in 2.8 in bins of 15K.
-bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, const PairSeqs& q, const char* hint,
+//
+// nk may be an estimate; there are at most `most` variants. check sees the
+// call's counters as soon as they are read.
+bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const PairSeqs& q,
+                        const char* hint,
                         const std::function<void(const PartOut&, uint32_t)>& generate,
+                        const std::function<void(const uint32_t*)>& check,
                         const std::function<Verified(Call&, uint64_t*, uint64_t)>& sort_pairs,
                         Verified* v) {
   sd_ctx* c = cl0.c;
@@ -527,8 +532,8 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, const PairSeqs& q, c
   const int lb1 = lb > PART_MAX_LB ? 8 : lb;
   const uint64_t over_cap = nk / 16 + 65536;
   uint32_t* over = cl.counters + CNT_OVER;
-  launch_fill_u32(over, 0, 2, s);
-  PartOut p = part_out(cl, nk, lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
+  // (regions of an estimate hold 1.2 times the most)
+  PartOut p = part_out(cl, std::max(nk, most / 5 * 3), lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
   generate(p, idbits);
   cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
   if (lb1 < lb) {
@@ -542,15 +547,18 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, const PairSeqs& q, c
   unsigned long long* nbig = reinterpret_cast<unsigned long long*>(cl.counters + CNT_NBIG);
   Cands extra;  // candidates of the listed ranges
   uint64_t listed = 0;
+  bool again = false;  // (a call's counters start as zeros)
   TileOut out;
   const bool done = binned_pairs(
       cl, hint, nk, q,
       [&](const PairBins& bins) {
-        launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
+        if (again) launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
+        again = true;
         launch_filter_group(p, nk, idbits, bins, big, nbig, s);
         launch_pair_scatter(extra.p, extra.n, bins, s);
       },
       [&](const uint32_t* h, uint64_t* more) {
+        check(h);
         if (h[CNT_OVER1] || h[CNT_OVER] > over_cap)
           return PairNext::give_up;
         uint64_t nb;
@@ -804,10 +812,11 @@ void paired_self_search(sd_ctx* c, const sd_seqs* a, const sd_seqs* b, int k, sd
     // verification reads the second chains' planes and keys: a2 = planes
     done = partition_applies(c, nkeys) && if_memory_suffices(c, [&] {
              return partitioned_search(
-                 cl, n, nkeys, q, "pairs/paired",
+                 cl, n, nkeys, nkeys, q, "pairs/paired",
                  [&](const PartOut& p, uint32_t idbits) {
                    launch_gen_part_paired(sa, sb, vcnt, n, nkeys, k, idbits, p, s);
                  },
+                 [](const uint32_t*) {},
                  [&](Call& c2, uint64_t* cand_, uint64_t m) {
                    return sort_and_verify(c2, cand_, m, n, k, sa, pa, sb, pb);
                  },
@@ -883,14 +892,19 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
   launch_pack(in.codes, in.offs, n, k, c->path != 1, seq, planes, vcnt, counters + CNT_ERR, s,
               reinterpret_cast<unsigned long long*>(counters + CNT_SUMS));
   tm.mark("pack", (double)n * (16 + 16 + 16 + 8 + 4), 1);
-  uint64_t nkeys = 0;
-  {
-    // one read-back: validation flags and the key total
-    const uint32_t* h = static_cast<const uint32_t*>(readback(c, counters, CNT_TOTAL * 4, s));
+  uint64_t nkeys = n * TYPICAL_VARIANTS[k];
+  // validation flags and the key total: with the result if that can be
+  auto take_counters = [&](const uint32_t* h) {
     raise_validation(h[CNT_ERR]);
     nkeys = pack_total(h);
-  }
-  c->stats.n_keys = (int64_t)nkeys;
+    c->stats.n_keys = (int64_t)nkeys;
+  };
+  const bool unread = nkeys <= UNREAD_KEYS && partition_applies(c, nkeys) && !c->arena &&
+                      !c->budget && c->stream != 2;
+  auto read_counters = [&] {
+    take_counters(static_cast<const uint32_t*>(readback(c, counters, CNT_TOTAL * 4, s)));
+  };
+  if (!unread) read_counters();
   // the sorted, streamed and full-key paths write variants at scanned offsets
   auto scan_offsets = [&] {
     const uint64_t tiles = (n + scan_tile() - 1) / scan_tile();
@@ -900,13 +914,12 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
   };
 
   Verified v;
-  const uint64_t group_elems = stream_group_elems(c, n, nkeys);
+  const uint64_t group_elems = unread ? 0 : stream_group_elems(c, n, nkeys);
   if (group_elems) {
     scan_offsets();
     v = streamed_search(cl, seq, planes, voff, n, k, nkeys, group_elems);
   } else {
     // 3-5: grouping and in-group emission
-    const uint32_t nk = (uint32_t)nkeys;
     Cands cand;
     int passes = 0;
     const bool hamming = c->metric == SD_METRIC_HAMMING;
@@ -915,15 +928,20 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
     const bool done =
         partition_applies(c, nkeys) && if_memory_suffices(c, [&] {
           return partitioned_search(
-              cl, n, nkeys, q, "pairs/self",
+              cl, n, nkeys, unread ? n * MOST_VARIANTS[k] : nkeys, q, "pairs/self",
               [&](const PartOut& p, uint32_t idbits) {
                 launch_gen_part(seq, vcnt, n, nkeys, k, idbits, p, s);
+              },
+              [&](const uint32_t* h) {
+                if (unread) take_counters(h);
               },
               [&](Call& c2, uint64_t* cand_, uint64_t m) {
                 return sort_and_verify(c2, cand_, m, n, k, seq, planes);
               },
               &v);
         });
+    if (!done && unread) read_counters();
+    const uint32_t nk = (uint32_t)nkeys;
     if (done) {
       // 3-7 in one
     } else if (c->path == 1) {

@@ -127,9 +127,8 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
   cl.tm.mark("q_pack_scan", (double)q.n * 48, 1);
   // small sets are not waited for here: their variants are looked up whatever
   // their number, and the flags are read with the result
-  static const uint32_t typical[4] = {1, 16, 110, 500};  // variants of 15 residues
-  uint64_t nk = q.n * typical[k];
-  const bool known = nk > (1u << 20) || nk * PROBE_RATIO > idx->n_keys;
+  uint64_t nk = q.n * TYPICAL_VARIANTS[k];
+  const bool known = nk > UNREAD_KEYS || nk * PROBE_RATIO > idx->n_keys;
   if (known) {
     const uint32_t* h = static_cast<const uint32_t*>(readback(c, cl.counters, CNT_TOTAL * 4, s));
     raise_packed(q, h[CNT_ERR]);

@@ -537,6 +537,18 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t v, uint64_t n) {
     p[e] = v;
 }
 
+// several arrays in one launch (blockIdx.y)
+struct ZeroArgs {
+  sd::ZeroRange r[sd::ZERO_RANGES];
+};
+
+__global__ void k_zero(ZeroArgs a) {
+  const sd::ZeroRange r = a.r[blockIdx.y];
+  for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < r.n;
+       e += (uint64_t)gridDim.x * blockDim.x)
+    r.p[e] = 0;
+}
+
 __global__ void k_fill_u64(uint64_t* p, uint64_t v, uint64_t n) {
   for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
        e += (uint64_t)gridDim.x * blockDim.x)
@@ -559,6 +571,19 @@ static unsigned grid_for(uint64_t n, unsigned per_block, unsigned cap) {
 void launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s) {
   if (!n) return;
   hipLaunchKernelGGL(sdk::k_fill_u32, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, p, v, n);
+}
+
+void launch_zero(std::initializer_list<ZeroRange> ranges, hipStream_t s) {
+  sdk::ZeroArgs a{};
+  unsigned m = 0;
+  uint64_t longest = 0;
+  for (const ZeroRange& r : ranges) {
+    if (!r.n || m >= (unsigned)ZERO_RANGES) continue;
+    a.r[m++] = r;
+    longest = std::max(longest, r.n);
+  }
+  if (!m) return;
+  hipLaunchKernelGGL(sdk::k_zero, dim3(grid_for(longest, 256, 4096), m), dim3(256), 0, s, a);
 }
 
 uint32_t out_shards() { return OUT_SHARDS; }

@@ -356,6 +356,13 @@ bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, const PairSeqs& q,
                   const char* stage, TileOut* out);
 
 // Regions of one partition level, cursors zeroed (pipeline.cpp).
+// Sequences of the usual lengths have about this many distinct variants, and no
+// sequence has more than the second number.
+constexpr uint32_t TYPICAL_VARIANTS[4] = {1, 16, 110, 500}, MOST_VARIANTS[4] = {1, 25, 301, 2325};
+// Inputs of fewer variants (by that estimate) are not waited for after the
+// packing kernel: their searches size everything for the estimate, and read the
+// flags and the total with the result.
+constexpr uint64_t UNREAD_KEYS = 1ull << 20;
 PartOut part_out(Call& cl, uint64_t nk, int lb, int nxl, uint64_t over_cap, uint32_t* over_count);
 
 // Runs a path that needs more scratch than the sorted one; where the memory

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <initializer_list>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -29,6 +30,13 @@ namespace sd {
 
 // ------------------------------------------------------------------ launchers
 void launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s);
+// up to ZERO_RANGES arrays of 32-bit words set to zero
+struct ZeroRange {
+  uint32_t* p;
+  uint64_t n;
+};
+constexpr int ZERO_RANGES = 5;
+void launch_zero(std::initializer_list<ZeroRange> ranges, hipStream_t s);
 void launch_fill_u64(uint64_t* p, uint64_t v, uint64_t n, hipStream_t s);
 uint32_t out_shards();
 // (writes stop at cap elements of out; off[] receives the shard offsets and,

@@ -59,8 +59,10 @@ __global__ __launch_bounds__(NT) void k_pack(const uint8_t* __restrict__ codes,
     if (SETS && (L < 0 || (at == 0 && a != 0))) atomicOr(err, SD_ERRBIT_OFFSETS);
     if (L < 1 || L > KEY_MAX_LEN || lost) {
       if (!lost) atomicOr(err, SD_ERRBIT_LENGTH);
-      seq[i] = 0;
-      if (planes) planes[i] = 0;
+      // (one residue, so that what runs before the flag is read has a sequence)
+      seq[i] = (u128)1 << 120;
+      if (planes) planes[i] = (u128)1 << 120;
+      if (vcnt) c = k >= 1 ? 2u : 1u;
     } else {
       u128 key = (u128)L << 120;
       uint32_t pl[5] = {0, 0, 0, 0, 0};

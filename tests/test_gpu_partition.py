@@ -62,6 +62,24 @@ def test_lengths(paths, length):
         same(paths, *csr([bytes(x) for x in pick]), k)
 
 
+# small inputs are sized by an estimate: the most variants a sequence can have,
+# and sequences that are refused in between
+@pytest.mark.parametrize("n,k", [(1, 3), (40, 3), (2_000, 2), (9_000, 2), (30_000, 1)])
+def test_estimated_sizes(paths, n, k):
+    from paper_2403_09010_amd import SymdelError
+    rng = np.random.default_rng(n)
+    rows = np.argsort(rng.random((n, 20)), axis=1).astype(np.uint8)
+    rows = np.concatenate([rows, rows[:, :4]], axis=1)  # 24 residues, no two neighbours alike
+    rows[n // 2:, 3] = rows[:n - n // 2, 7]
+    c, o = csr([bytes(x) for x in rows])
+    same(paths, c, o, k)
+    for bad, name in ((np.full(1, 20, np.uint8), "SD_E_ALPHABET"), (np.zeros(0, np.uint8), "SD_E_LENGTH"),
+                      (np.zeros(25, np.uint8), "SD_E_LENGTH")):
+        with pytest.raises(SymdelError) as e:
+            paths[0].self_search(np.concatenate([c, bad]), np.append(o, o[-1] + len(bad)), k)
+        assert e.value.name == name
+
+
 def test_sequences_sorted_by_length(paths):
     # consecutive long sequences: workgroups hold more variants than the mean
     s = sorted(strings_of(9, 30_000), key=len)
