@@ -85,6 +85,66 @@ __device__ __forceinline__ uint32_t lev_planes(u128 pa, u128 b) {
   return score;
 }
 
+// The same distance where only a value of at most K matters, both strings as bit
+// planes: K + 1 or more for pairs further apart. The furthest rows of the
+// diagonals -K..K for 0..K edits (Ukkonen 1985; Myers 1986), where a run of
+// equal residues is one count of trailing zeros in the diagonal's mismatch mask
+// (bit t: residue t of a differs from residue t + d of b). About 65 operations for
+// the masks and 60 for the rows at K = 2, the same for every length; lev_planes
+// takes about 25 per residue.
+template <int K>
+__device__ __forceinline__ uint32_t lev_within(u128 pa, u128 pb) {
+  const int m = (int)(pa >> 120), n = (int)(pb >> 120);
+  uint32_t A[5], B[5];
+  {
+    const uint64_t lo = (uint64_t)pa, hi = (uint64_t)(pa >> 64);
+    const uint64_t lo2 = (uint64_t)pb, hi2 = (uint64_t)(pb >> 64);
+    A[0] = (uint32_t)lo & 0xFFFFFFu;
+    A[1] = (uint32_t)(lo >> 24) & 0xFFFFFFu;
+    A[2] = (uint32_t)((lo >> 48) | (hi << 16)) & 0xFFFFFFu;
+    A[3] = (uint32_t)(hi >> 8) & 0xFFFFFFu;
+    A[4] = (uint32_t)(hi >> 32) & 0xFFFFFFu;
+    B[0] = (uint32_t)lo2 & 0xFFFFFFu;
+    B[1] = (uint32_t)(lo2 >> 24) & 0xFFFFFFu;
+    B[2] = (uint32_t)((lo2 >> 48) | (hi2 << 16)) & 0xFFFFFFu;
+    B[3] = (uint32_t)(hi2 >> 8) & 0xFFFFFFu;
+    B[4] = (uint32_t)(hi2 >> 32) & 0xFFFFFFu;
+  }
+  // per diagonal d: where it ends, its mismatches (all ones from there on), and
+  // the furthest row with the edits so far
+  int end[2 * K + 1], row[2 * K + 1] = {};
+  uint32_t miss[2 * K + 1];
+#pragma unroll
+  for (int d = -K; d <= K; ++d) {
+    uint32_t x = 0;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) x |= A[q] ^ (d >= 0 ? B[q] >> (d >= 0 ? d : 0) : B[q] << (d < 0 ? -d : 0));
+    end[d + K] = max(min(m, n - d), 0);
+    miss[d + K] = x | (~0u << end[d + K]);
+  }
+  uint32_t dist = K + 1;
+#pragma unroll
+  for (int e = 0; e <= K; ++e) {
+    int left = 0;  // the row of diagonal d - 1 before this edit
+#pragma unroll
+    for (int d = -e; d <= e; ++d) {
+      const int old = row[d + K];
+      int t = 0;
+      if (e > 0) {
+        t = d > -e && d < e ? old + 1 : 0;                       // substitution
+        if (d - 1 >= -(e - 1) && d - 1 <= e - 1) t = max(t, left);              // b's residue added
+        if (d + 1 <= e - 1 && d + 1 >= -(e - 1)) t = max(t, row[d + 1 + K] + 1);  // a's deleted
+        t = min(t, end[d + K]);
+      }
+      t += __builtin_ctz(miss[d + K] >> t);
+      left = old;
+      row[d + K] = t;
+      if (d == n - m && t >= m && dist > (uint32_t)e) dist = (uint32_t)e;
+    }
+  }
+  return dist;
+}
+
 // Hamming distance of two packed keys of equal length (Section III C's
 // filter): residues sit in 5-bit fields at bits [5 g, 5 g + 5), so a field of
 // a XOR b is non-zero exactly where the residues differ; OR-ing each field's
@@ -139,6 +199,36 @@ __device__ __forceinline__ uint8_t pair_verdict(const u128* __restrict__ pa,
     if (dd <= (uint32_t)k) return (uint8_t)dd;
   }
   return DROP;
+}
+
+// The same for two sequences that both have bit planes (PAIRED: records, pa2 the
+// second chains' planes): half the random reads of pair_verdict, from arrays that
+// the Infinity Cache can hold.
+template <bool PAIRED, int K>
+__device__ __forceinline__ uint8_t planes_verdict_k(const u128* __restrict__ pa,
+                                                    const u128* __restrict__ pa2, uint32_t i,
+                                                    uint32_t j) {
+  const u128 a = pa[i], b = pa[j];
+  u128 a2 = 0, b2 = 0;
+  if (PAIRED) {
+    a2 = pa2[i];
+    b2 = pa2[j];
+  }
+  uint32_t d = lev_within<K>(a, b);
+  if (PAIRED && d <= (uint32_t)K) d += lev_within<K>(a2, b2);
+  return d <= (uint32_t)K ? (uint8_t)d : DROP;
+}
+
+template <bool PAIRED>
+__device__ __forceinline__ uint8_t planes_verdict(const u128* __restrict__ pa,
+                                                  const u128* __restrict__ pa2, uint32_t i,
+                                                  uint32_t j, int k) {
+  switch (k) {
+    case 0: return planes_verdict_k<PAIRED, 0>(pa, pa2, i, j);
+    case 1: return planes_verdict_k<PAIRED, 1>(pa, pa2, i, j);
+    case 2: return planes_verdict_k<PAIRED, 2>(pa, pa2, i, j);
+    default: return planes_verdict_k<PAIRED, 3>(pa, pa2, i, j);
+  }
 }
 
 // Minimum-cost global alignment of a and b with substitution costs sub[20][20]

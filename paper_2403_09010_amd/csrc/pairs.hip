@@ -27,7 +27,7 @@ namespace sdk {
 constexpr int PR_ROWS = 8;          // rows of candidates in flight per wave
 constexpr uint32_t PR_LONG = 64;    // ranges with more pairs are ordered by k_pair_long
 constexpr uint32_t PR_MAX = 4096;   // longest range it orders in LDS
-enum : int { PM_LEV = 0, PM_HAMMING = 1, PM_PAIRED = 2, PM_WEIGHTED = 3 };
+enum : int { PM_LEV = 0, PM_HAMMING = 1, PM_PAIRED = 2, PM_WEIGHTED = 3, PM_SELF = 4 };
 
 // Candidates from the regions of one level to those of the next, a tile at a
 // time. Consecutive workgroups take consecutive regions (the region of XCD x is
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
 template <int NT, int TSLOG, int MODE>
 __global__ __launch_bounds__(NT) void k_pair_verify(
     sd::PairBins in, const u128* __restrict__ pa, const u128* __restrict__ sb,
-    const u128* __restrict__ pa2, const u128* __restrict__ sb2, uint32_t na, uint32_t nb, int k,
+    const u128* __restrict__ pa2, uint32_t na, uint32_t nb, int k,
     int self_pairs, const uint8_t* __restrict__ subst, uint32_t indel, uint32_t max_score,
     sd::PairBufs out) {
   constexpr uint32_t TS = 1u << TSLOG;
@@ -184,8 +184,11 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
             keep = d <= max_score;
             d = d > 255u ? 255u : d;
           }
+        } else if (MODE == PM_SELF || MODE == PM_PAIRED) {
+          d = planes_verdict<MODE == PM_PAIRED>(pa, pa2, i, j, k);
+          keep = d != DROP;
         } else {
-          d = pair_verdict<MODE>(pa, sb, pa2, sb2, i, j, k);
+          d = pair_verdict<MODE>(pa, sb, nullptr, nullptr, i, j, k);
           keep = d != DROP;
         }
       } else {  // an id out of range is an internal error: flagged, never read
@@ -317,7 +320,7 @@ static void verify_t(const PairBins& in, const PairSeqs& q, const PairBufs& b, h
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     (void)hipGetLastError();  // the launch reports any real problem
   hipLaunchKernelGGL((sdk::k_pair_verify<NT, TSLOG, MODE>), dim3(in.nbins), dim3(NT), lds, s, in,
-                     q.a, q.b, q.a2, q.b2, (uint32_t)q.na, (uint32_t)q.nb, q.k, q.self_pairs,
+                     q.a, q.b, q.a2, (uint32_t)q.na, (uint32_t)q.nb, q.k, q.self_pairs,
                      q.subst, q.indel, q.max_score, b);
 }
 
@@ -327,6 +330,7 @@ static void verify_mode(const PairBins& in, const PairSeqs& q, const PairBufs& b
     case sdk::PM_LEV: verify_t<NT, TSLOG, sdk::PM_LEV>(in, q, b, s); break;
     case sdk::PM_HAMMING: verify_t<NT, TSLOG, sdk::PM_HAMMING>(in, q, b, s); break;
     case sdk::PM_PAIRED: verify_t<NT, TSLOG, sdk::PM_PAIRED>(in, q, b, s); break;
+    case sdk::PM_SELF: verify_t<NT, TSLOG, sdk::PM_SELF>(in, q, b, s); break;
     default: verify_t<NT, TSLOG, sdk::PM_WEIGHTED>(in, q, b, s); break;
   }
 }

@@ -808,8 +808,7 @@ void paired_self_search(sd_ctx* c, const sd_seqs* a, const sd_seqs* b, int k, sd
     tm.mark("pack", (double)n * 2 * (16 + 16 + 16 + 8) + (double)n * 4, 3);
     read_counters(&nkeys);
     c->stats.n_keys = (int64_t)nkeys;
-    const PairSeqs q{pa, sa, pb, sb, n, n, k, 2, 1, nullptr, 0, 0};
-    // verification reads the second chains' planes and keys: a2 = planes
+    const PairSeqs q{pa, nullptr, pb, n, n, k, 2, 1, nullptr, 0, 0};
     done = partition_applies(c, nkeys) && if_memory_suffices(c, [&] {
              return partitioned_search(
                  cl, n, nkeys, nkeys, q, "pairs/paired",
@@ -923,8 +922,8 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
     Cands cand;
     int passes = 0;
     const bool hamming = c->metric == SD_METRIC_HAMMING;
-    const PairSeqs q{hamming ? seq : planes, seq, nullptr, nullptr, n, n, k, hamming ? 1 : 0, 1,
-                     nullptr, 0, 0};
+    const PairSeqs q{hamming ? seq : planes, seq, nullptr, n, n, k, hamming ? 1 : 4, 1, nullptr, 0,
+                     0};
     const bool done =
         partition_applies(c, nkeys) && if_memory_suffices(c, [&] {
           return partitioned_search(

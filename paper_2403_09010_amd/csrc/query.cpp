@@ -159,7 +159,6 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
   const PairSeqs ps{w ? planes : hamming ? seq : planes,
                     idx->ref_seq,
                     w ? seq : nullptr,
-                    nullptr,
                     q.n,
                     idx->n_ref,
                     k,

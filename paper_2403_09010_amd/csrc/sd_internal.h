@@ -295,12 +295,12 @@ struct PairBins {
 };
 // Verification of binned candidates (pairs.hip). mode 0: Levenshtein distance
 // of a = bit planes of the first sequences and b = packed keys of the second;
-// 1: Hamming distance, a = packed keys; 2: the sum over both chains (a, b, a2,
-// b2); 3: Levenshtein within k, then the weighted score (a2 = packed keys of
-// the first). First ids are below na, second ids below nb. self_pairs: pairs
-// with i >= j are dropped.
+// 1: Hamming distance, both packed keys; 2: the sum over both chains' bit planes
+// a and a2; 3: Levenshtein within k, then the weighted score (a2 = packed keys of
+// the first); 4: Levenshtein distance, a = bit planes of both. First ids are below
+// na, second ids below nb. self_pairs: pairs with i >= j are dropped.
 struct PairSeqs {
-  const u128 *a, *b, *a2, *b2;
+  const u128 *a, *b, *a2;
   uint64_t na, nb;
   int k, mode, self_pairs;
   const uint8_t* subst;
