@@ -567,16 +567,20 @@ __global__ __launch_bounds__(NT) void k_part_split(sd::PartOut in, sd::PartOut o
 
 // ------------------------------------------------------------------ filter and group
 
-// Elements a round groups in LDS at once, and the buckets it sorts them into.
-template <int SB>
+// Sizes of a shape of k_filter_group with a bitmap of 2^SB bits in `LDS` bytes (as
+// many as leave room for the shape's workgroups on a CU): a round groups FULL
+// elements of at most CAP at once (pairs take the rest) and sorts them into NBK
+// buckets. The elements and buckets lie where the first bitmap was.
+template <int SB, int LDS>
 struct FilterShape {
-  // the bitmap of 2^SB bits holds, once it is no longer read, the candidates
-  // (7/8 of it) and their bucket table (1/8)
-  static constexpr int BYTES = (1 << SB) / 8;
-  static constexpr int CAP = BYTES / 8 * 7 / 8;
-  static constexpr int FULL = CAP - CAP / 8;  // candidates of a round: the rest holds pairs
-  static constexpr int NBK = BYTES / 8 / 4;
-  static constexpr int TB = SB - 3;  // bits of the second bitmap (log2)
+  static constexpr int SEEN = (1 << SB) / 8;   // bytes of the first bitmap
+  static constexpr int TWICE = SEEN / 8;       // and of the second
+  static constexpr int NBK = SEEN / 8 / 4;     // 4 bytes each
+  static constexpr int CAP = (LDS - TWICE - NBK * 4) / 64 * 8;
+  static constexpr int FULL = CAP - CAP / 8;
+  static constexpr int BK_AT = CAP * 8;
+  static constexpr int TWICE_AT = BK_AT + NBK * 4;
+  static_assert(TWICE_AT >= SEEN && TWICE_AT + TWICE <= LDS, "layout");
 };
 constexpr int FG_LOADS = 8;      // elements in flight per thread
 constexpr int FG_MAX_ROUNDS = 64;
@@ -593,20 +597,27 @@ constexpr int FG_MAX_ROUNDS = 64;
 // regions, or whose round still does not fit (thousands of elements of one
 // hash), is listed in big[] for the sort-and-runs path.
 //
-// Bound: the two reads of the elements (the second mostly from the Infinity
-// Cache) and LDS atomics. 100M random elements in 2048 bins: 0.28 ms.
-template <int NT, int SB>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_filter_group(sd::PartOut in, uint32_t idbits, sd::PairBins out,
-                                                     uint64_t* __restrict__ big,
-                                                     unsigned long long* __restrict__ nbig) {
-  using F = FilterShape<SB>;
+// Bound: the two reads of the elements, the second backwards, so that it begins
+// with what the caches still hold; then LDS accesses, of which a wave has eight in
+// flight where its rows are full. An element's two marks lie in one word: one
+// access, for a few more false marks than two words would give. 1G elements in
+// 2^17 bins: 2.59 ms (2.80 with a bounds check and a wait per access and marks in
+// two words); 101M in 2^11 bins: 0.41 (0.43). Elements kept in registers between
+// the two reads cost more than they save, since half as many waves fit: 2.96 and
+// 0.58 ms.
+template <int NT, int SB, int LDS, bool WIDE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_filter_group(
+    sd::PartOut in, sd::PairBins out, uint64_t* __restrict__ big,
+    unsigned long long* __restrict__ nbig) {
+  constexpr uint32_t idbits = WIDE ? 32 : 24;
+  using F = FilterShape<SB, LDS>;
   constexpr int PER = (F::FULL + NT - 1) / NT;
   static_assert(F::NBK <= 4 * NT, "bucket scan");
   extern __shared__ __align__(16) unsigned char lds[];
   uint32_t* s_seen = reinterpret_cast<uint32_t*>(lds);
-  uint32_t* s_tw = reinterpret_cast<uint32_t*>(lds + F::BYTES);
+  uint32_t* s_tw = reinterpret_cast<uint32_t*>(lds + F::TWICE_AT);
   uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
-  uint32_t* s_bk = reinterpret_cast<uint32_t*>(lds + F::CAP * 8);
+  uint32_t* s_bk = reinterpret_cast<uint32_t*>(lds + F::BK_AT);
   __shared__ uint32_t s_n, s_np;
   __shared__ uint32_t s_tmp[NT / 64];
   const uint32_t bin = blockIdx.x, nx = 1u << in.nxl;
@@ -638,8 +649,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     }
     return;
   }
-  for (uint32_t i = threadIdx.x; i < (uint32_t)(F::BYTES + (1 << F::TB) / 8) / 4; i += NT)
-    s_seen[i] = 0;
+  for (uint32_t i = threadIdx.x; i < (uint32_t)F::SEEN / 4; i += NT) s_seen[i] = 0;
+  for (uint32_t i = threadIdx.x; i < (uint32_t)F::TWICE / 4; i += NT) s_tw[i] = 0;
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
   // every element of the bin: waves share out the regions, and each takes
@@ -647,53 +658,68 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   constexpr uint32_t NW = NT / 64, ROW = 64 * FG_LOADS;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t parts = NW > nx ? NW / nx : 1u;
-  auto stream = [&](auto&& f) {
+  // (full: all of them are there, and no operation waits for a bounds check)
+  auto stream = [&](bool back, auto&& f) {
     for (uint32_t x = w & (nx - 1); x < nx; x += NW) {
       const uint32_t c = in.cursor[x * in.nbins + bin];
       const uint64_t* __restrict__ p = in.elem + base + (uint64_t)x * in.region;
-      for (uint32_t t0 = (w >> in.nxl) * ROW; t0 < c; t0 += parts * ROW) {
+      const uint32_t first = (w >> in.nxl) * ROW, step = parts * ROW;
+      if (first >= c) continue;
+      const uint32_t steps = (c - first + step - 1) / step;
+      for (uint32_t q = 0; q < steps; ++q) {
+        const uint32_t t0 = first + (back ? steps - 1 - q : q) * step;
         uint64_t e[FG_LOADS];
+        if (t0 + ROW <= c) {
 #pragma unroll
-        for (int u = 0; u < FG_LOADS; ++u) {
-          const uint32_t i = t0 + u * 64 + lane;
-          e[u] = i < c ? p[i] : 0;
+          for (int u = 0; u < FG_LOADS; ++u) e[u] = p[t0 + u * 64 + lane];
+          f(e, ROW, std::true_type{});
+        } else {
+#pragma unroll
+          for (int u = 0; u < FG_LOADS; ++u) {
+            const uint32_t i = t0 + u * 64 + lane;
+            e[u] = i < c ? p[i] : 0;
+          }
+          f(e, c - t0, std::false_type{});
         }
-        f(e, c - t0);
       }
     }
   };
-  // two marks per element in the second bitmap
-  auto mark = [&](uint64_t e) { return (uint32_t)(e >> idbits) * 0x9E3779B1u; };
-  constexpr uint32_t TM = (1u << F::TB) - 1;
-  stream([&](const uint64_t(&e)[FG_LOADS], uint32_t left) {
+  auto hash = [](uint64_t e) { return (uint32_t)(e >> idbits); };
+  // an element's two marks: bits of one word of the second bitmap, which its
+  // topmost free hash bits choose (the first bitmap goes by the lowest ones)
+  constexpr int TWBITS = SB - 8;  // log2 of its words
+  const int twshift = max(64 - (int)idbits - in.lb - TWBITS, 0);
+  auto mark_word = [&](uint32_t h) { return (h >> twshift) & ((1u << TWBITS) - 1); };
+  auto marks = [](uint32_t h) { return 1u << (h & 31u) | 1u << ((h >> 5) & 31u); };
+  stream(false, [&](const uint64_t(&e)[FG_LOADS], uint32_t left, auto full) {
     uint32_t old[FG_LOADS];
 #pragma unroll
     for (int u = 0; u < FG_LOADS; ++u) {
-      const uint32_t i = (uint32_t)(e[u] >> idbits) & ((1u << SB) - 1);
+      const uint32_t h = hash(e[u]);
       old[u] = 0;
-      if (u * 64 + lane < left) old[u] = atomicOr(&s_seen[i >> 5], 1u << (i & 31u)) >> (i & 31u);
+      if (full || u * 64 + lane < left)
+        old[u] = atomicOr(&s_seen[(h >> 5) & ((1u << (SB - 5)) - 1)], 1u << (h & 31u));
     }
 #pragma unroll
-    for (int u = 0; u < FG_LOADS; ++u)
-      if (old[u] & 1u) {
-        const uint32_t j = mark(e[u]), j1 = j >> (32 - F::TB), j2 = (j >> 3) & TM;
-        atomicOr(&s_tw[j1 >> 5], 1u << (j1 & 31u));
-        atomicOr(&s_tw[j2 >> 5], 1u << (j2 & 31u));
-      }
+    for (int u = 0; u < FG_LOADS; ++u) {
+      const uint32_t h = hash(e[u]);
+      if ((old[u] >> (h & 31u)) & 1u) atomicOr(&s_tw[mark_word(h)], marks(h));
+    }
   });
   __syncthreads();
   const uint64_t idmask = (1ull << idbits) - 1;
   const int bkshift = 64 - in.lb - __builtin_ctz(F::NBK);  // bucket: the bits below the bin's
   uint32_t rounds = 1;
   for (uint32_t round = 0; round < rounds; ++round) {
-    stream([&](const uint64_t(&e)[FG_LOADS], uint32_t left) {
+    stream(true, [&](const uint64_t(&e)[FG_LOADS], uint32_t left, auto full) {
       uint64_t bal[FG_LOADS];
-      uint32_t tot = 0;
+      uint32_t tw[FG_LOADS], tot = 0;
+#pragma unroll
+      for (int u = 0; u < FG_LOADS; ++u) tw[u] = s_tw[mark_word(hash(e[u]))];
 #pragma unroll
       for (int u = 0; u < FG_LOADS; ++u) {
-        const uint32_t j = mark(e[u]), j1 = j >> (32 - F::TB), j2 = (j >> 3) & TM;
-        bool keep = u * 64 + lane < left && ((s_tw[j1 >> 5] >> (j1 & 31u)) & 1u);
-        if (keep) keep = (s_tw[j2 >> 5] >> (j2 & 31u)) & 1u;
+        const uint32_t need = marks(hash(e[u]));
+        bool keep = (tw[u] & need) == need && (full || u * 64 + lane < left);
         if (rounds > 1) keep = keep && ((uint32_t)(e[u] >> (bkshift - 6)) & (rounds - 1)) == round;
         bal[u] = __ballot(keep);
         tot += (uint32_t)__popcll(bal[u]);
@@ -1433,22 +1459,31 @@ void launch_place_bins(const uint64_t* X, uint64_t m, int lb, const uint64_t* of
                      off, out, repeats);
 }
 
-template <int NT, int SB>
-static void filter_t(const PartOut& in, uint32_t idbits, const PairBins& out, uint64_t* big,
+template <int NT, int SB, int LDS, bool WIDE>
+static void filter_t(const PartOut& in, const PairBins& out, uint64_t* big,
                      unsigned long long* nbig, hipStream_t s) {
-  const size_t lds = (size_t)sdk::FilterShape<SB>::BYTES + (1 << sdk::FilterShape<SB>::TB) / 8;
-  allow_lds(&sdk::k_filter_group<NT, SB>, lds);
-  hipLaunchKernelGGL((sdk::k_filter_group<NT, SB>), dim3(in.nbins), dim3(NT), lds, s, in, idbits,
+  allow_lds(&sdk::k_filter_group<NT, SB, LDS, WIDE>, LDS);
+  hipLaunchKernelGGL((sdk::k_filter_group<NT, SB, LDS, WIDE>), dim3(in.nbins), dim3(NT), LDS, s, in,
                      out, big, nbig);
+}
+
+template <bool WIDE>
+static void filter_shape(bool small, const PartOut& in, const PairBins& out, uint64_t* big,
+                         unsigned long long* nbig, hipStream_t s) {
+  if (small)
+    filter_t<256, 17, 20352, WIDE>(in, out, big, nbig, s);  // eight on a CU
+  else
+    filter_t<1024, 19, 81664, WIDE>(in, out, big, nbig, s);  // two
 }
 
 void launch_filter_group(const PartOut& in, uint64_t nkeys, uint32_t idbits, const PairBins& out,
                          uint64_t* big, unsigned long long* nbig, hipStream_t s) {
   // bins of up to 10K elements fill a small bitmap to a twelfth
-  if (nkeys >> in.lb <= 10240)
-    filter_t<256, 17>(in, idbits, out, big, nbig, s);
+  const bool small = nkeys >> in.lb <= 10240;
+  if (idbits == 32)
+    filter_shape<true>(small, in, out, big, nbig, s);
   else
-    filter_t<1024, 19>(in, idbits, out, big, nbig, s);
+    filter_shape<false>(small, in, out, big, nbig, s);
 }
 
 void launch_gen_probe(const u128* seq, uint64_t n, int k, const uint64_t* E, uint32_t nkeys,

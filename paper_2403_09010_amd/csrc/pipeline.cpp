@@ -498,14 +498,14 @@ Verified sort_and_verify(Call& cl, uint64_t* cand, uint64_t nc, uint64_t n, int 
 //
 // The bins. Small inputs take 2^8 bins of 512 elements or more, so that every
 // CU has one, and more bins only to keep them under 10K elements (what the
-// small bitmap filters well). Large inputs take bins of 27K to 53K elements:
+// small bitmap filters well). Large inputs take bins of 26K to 51K elements:
 // with fewer a tile's runs get short (100M elements of 1M sequences: 0.52 ms
 // into 2^11 bins, 0.60 into 2^12), with more the filter lets too many through.
 // Beyond 2^12 bins of that size the partition takes a second level, into bins
 // a quarter as large since more bins cost little there (and their second read
 // comes from the L2): scattering 100M elements into 2^13 bins at once takes
 // 0.92 ms, two levels of 2^8 and 2^5 0.43 + 0.33; 1G elements group in 6.9 ms
-// in bins of 31K elements and in 2.8 in bins of 15K.
+// in bins of 31K elements and in 2.6 in bins of 15K.
 //
 // nk may be an estimate; there are at most `most` variants. check sees the
 // call's counters as soon as they are read.
@@ -525,7 +525,7 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
     while (lb < 11 && ((nk >> lb) > 10240 || (lb < 8 && (nk >> lb) > 512))) ++lb;
   } else {
     lb = 11;
-    while ((nk >> lb) > 53248) ++lb;
+    while ((nk >> lb) > 51200) ++lb;
     if (lb > PART_MAX_LB) lb += 2;
   }
   const int nxl = nk >= (2u << 20) ? 3 : 0;
