@@ -582,7 +582,7 @@ struct FilterShape {
   static constexpr int TWICE_AT = BK_AT + NBK * 4;
   static_assert(TWICE_AT >= SEEN && TWICE_AT + TWICE <= LDS, "layout");
 };
-constexpr int FG_LOADS = 8;      // elements in flight per thread
+constexpr int FG_ROWS = 8;      // elements in flight per thread
 constexpr int FG_MAX_ROUNDS = 64;
 
 // One workgroup per bin. First pass over the bin's elements: each sets the bit
@@ -654,8 +654,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
   // every element of the bin: waves share out the regions, and each takes
-  // FG_LOADS rows of 64 elements at a time
-  constexpr uint32_t NW = NT / 64, ROW = 64 * FG_LOADS;
+  // FG_ROWS rows of 64 elements at a time
+  constexpr uint32_t NW = NT / 64, ROW = 64 * FG_ROWS;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t parts = NW > nx ? NW / nx : 1u;
   // (full: all of them are there, and no operation waits for a bounds check)
@@ -668,14 +668,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
       const uint32_t steps = (c - first + step - 1) / step;
       for (uint32_t q = 0; q < steps; ++q) {
         const uint32_t t0 = first + (back ? steps - 1 - q : q) * step;
-        uint64_t e[FG_LOADS];
+        uint64_t e[FG_ROWS];
         if (t0 + ROW <= c) {
 #pragma unroll
-          for (int u = 0; u < FG_LOADS; ++u) e[u] = p[t0 + u * 64 + lane];
+          for (int u = 0; u < FG_ROWS; ++u) e[u] = p[t0 + u * 64 + lane];
           f(e, ROW, std::true_type{});
         } else {
 #pragma unroll
-          for (int u = 0; u < FG_LOADS; ++u) {
+          for (int u = 0; u < FG_ROWS; ++u) {
             const uint32_t i = t0 + u * 64 + lane;
             e[u] = i < c ? p[i] : 0;
           }
@@ -691,17 +691,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   const int twshift = max(64 - (int)idbits - in.lb - TWBITS, 0);
   auto mark_word = [&](uint32_t h) { return (h >> twshift) & ((1u << TWBITS) - 1); };
   auto marks = [](uint32_t h) { return 1u << (h & 31u) | 1u << ((h >> 5) & 31u); };
-  stream(false, [&](const uint64_t(&e)[FG_LOADS], uint32_t left, auto full) {
-    uint32_t old[FG_LOADS];
+  stream(false, [&](const uint64_t(&e)[FG_ROWS], uint32_t left, auto full) {
+    uint32_t old[FG_ROWS];
 #pragma unroll
-    for (int u = 0; u < FG_LOADS; ++u) {
+    for (int u = 0; u < FG_ROWS; ++u) {
       const uint32_t h = hash(e[u]);
       old[u] = 0;
       if (full || u * 64 + lane < left)
         old[u] = atomicOr(&s_seen[(h >> 5) & ((1u << (SB - 5)) - 1)], 1u << (h & 31u));
     }
 #pragma unroll
-    for (int u = 0; u < FG_LOADS; ++u) {
+    for (int u = 0; u < FG_ROWS; ++u) {
       const uint32_t h = hash(e[u]);
       if ((old[u] >> (h & 31u)) & 1u) atomicOr(&s_tw[mark_word(h)], marks(h));
     }
@@ -711,13 +711,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   const int bkshift = 64 - in.lb - __builtin_ctz(F::NBK);  // bucket: the bits below the bin's
   uint32_t rounds = 1;
   for (uint32_t round = 0; round < rounds; ++round) {
-    stream(true, [&](const uint64_t(&e)[FG_LOADS], uint32_t left, auto full) {
-      uint64_t bal[FG_LOADS];
-      uint32_t tw[FG_LOADS], tot = 0;
+    stream(true, [&](const uint64_t(&e)[FG_ROWS], uint32_t left, auto full) {
+      uint64_t bal[FG_ROWS];
+      uint32_t tw[FG_ROWS], tot = 0;
 #pragma unroll
-      for (int u = 0; u < FG_LOADS; ++u) tw[u] = s_tw[mark_word(hash(e[u]))];
+      for (int u = 0; u < FG_ROWS; ++u) tw[u] = s_tw[mark_word(hash(e[u]))];
 #pragma unroll
-      for (int u = 0; u < FG_LOADS; ++u) {
+      for (int u = 0; u < FG_ROWS; ++u) {
         const uint32_t need = marks(hash(e[u]));
         bool keep = (tw[u] & need) == need && (full || u * 64 + lane < left);
         if (rounds > 1) keep = keep && ((uint32_t)(e[u] >> (bkshift - 6)) & (rounds - 1)) == round;
@@ -730,7 +730,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
         at = __builtin_amdgcn_readfirstlane(at);
         if (at + tot <= (uint32_t)F::FULL) {
 #pragma unroll
-          for (int u = 0; u < FG_LOADS; ++u) {
+          for (int u = 0; u < FG_ROWS; ++u) {
             if ((bal[u] >> lane) & 1u) s_e[at + mask_rank(bal[u])] = e[u];
             at += (uint32_t)__popcll(bal[u]);
           }
@@ -1119,11 +1119,12 @@ constexpr uint32_t JB_QCAP = (1u << JB_SB) / 64;  // query survivors
 constexpr int JB_NBK = 1024;
 constexpr size_t JB_LDS = (1 << JB_SB) / 8 + (1 << JB_TB) / 8 + JB_CAP * 8 + JB_NBK * 4;
 
-template <int NT>
+template <int NT, bool WIDE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_join_bins(
     sd::PartOut in, const uint64_t* __restrict__ E, const uint32_t* __restrict__ seg_start,
-    const uint32_t* __restrict__ seg_end, int bits, int sub, uint32_t idbits, sd::PairBins out) {
-  constexpr uint32_t NW = NT / 64, ROW = 64 * FG_LOADS;
+    const uint32_t* __restrict__ seg_end, int bits, int sub, sd::PairBins out) {
+  constexpr uint32_t idbits = WIDE ? 32 : 24;
+  constexpr uint32_t NW = NT / 64, ROW = 64 * FG_ROWS;
   constexpr uint32_t PER = (JB_CAP + NT - 1) / NT;
   extern __shared__ __align__(16) unsigned char lds[];
   uint32_t* s_bq = reinterpret_cast<uint32_t*>(lds);
@@ -1148,27 +1149,33 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   if (r0 >= r1) return;
   const uint64_t base = (uint64_t)(bin << in.nxl) * in.region;
   const uint32_t parts = NW > nx ? NW / nx : 1u;
-  // the segment's query elements: f(element, whether it is one)
+  // the segment's query elements: f(rows, whether each lane has one)
   auto queries = [&](auto&& f) {
     for (uint32_t x = w & (nx - 1); x < nx; x += NW) {
       const uint32_t c = min(in.cursor[x * in.nbins + bin], in.region);
       const uint64_t* __restrict__ p = in.elem + base + (uint64_t)x * in.region;
       for (uint32_t t0 = (w >> in.nxl) * ROW; t0 < c; t0 += parts * ROW) {
-        uint64_t e[FG_LOADS];
+        uint64_t e[FG_ROWS];
 #pragma unroll
-        for (int u = 0; u < FG_LOADS; ++u) {
+        for (int u = 0; u < FG_ROWS; ++u) {
           const uint32_t i = t0 + u * 64 + lane;
           e[u] = i < c ? p[i] : 0;
         }
+        bool valid[FG_ROWS];
 #pragma unroll
-        for (int u = 0; u < FG_LOADS; ++u)
-          if (t0 + u * 64 < c)
-            f(e[u], t0 + u * 64 + lane < c && (uint32_t)(e[u] >> (64 - segbits)) == seg);
+        for (int u = 0; u < FG_ROWS; ++u)
+          valid[u] = t0 + u * 64 + lane < c && (uint32_t)(e[u] >> 32) >> (32 - segbits) == seg;
+        f(e, valid);
       }
     }
   };
-  auto mark = [&](uint64_t e) { return (uint32_t)(e >> idbits) * 0x9E3779B1u; };
-  constexpr uint32_t TM = (1u << JB_TB) - 1;
+  // marks as in k_filter_group: two bits of one word
+  constexpr int TWBITS = JB_TB - 5;
+  const int twshift = max(64 - (int)idbits - segbits - TWBITS, 0);
+  auto hash = [](uint64_t e) { return (uint32_t)(e >> idbits); };
+  auto mark_word = [&](uint32_t h) { return (h >> twshift) & ((1u << TWBITS) - 1); };
+  auto marks = [](uint32_t h) { return 1u << (h & 31u) | 1u << ((h >> 5) & 31u); };
+  auto bq_word = [](uint32_t h) { return (h >> 5) & ((1u << (JB_SB - 5)) - 1); };
   const uint64_t idmask = (1ull << idbits) - 1;
   const int bkshift = 64 - segbits - __builtin_ctz(JB_NBK);
   uint32_t rounds = 1;
@@ -1182,30 +1189,27 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
       s_nq = 0;
     }
     __syncthreads();
-    queries([&](uint64_t e, bool valid) {
-      const uint32_t i = (uint32_t)(e >> idbits) & ((1u << JB_SB) - 1);
-      if (valid && mine(e)) atomicOr(&s_bq[i >> 5], 1u << (i & 31u));
+    queries([&](const uint64_t(&e)[FG_ROWS], const bool(&valid)[FG_ROWS]) {
+#pragma unroll
+      for (int u = 0; u < FG_ROWS; ++u) {
+        const uint32_t h = hash(e[u]);
+        if (valid[u] && mine(e[u])) atomicOr(&s_bq[bq_word(h)], 1u << (h & 31u));
+      }
     });
     __syncthreads();
-    for (uint32_t t0 = r0 + w * ROW; t0 < r1; t0 += NW * ROW) {
-      uint64_t e[FG_LOADS], bal[FG_LOADS];
+    // the index elements whose bit is set (full: all rows of 64 are there)
+    auto look = [&](const uint64_t(&e)[FG_ROWS], uint32_t left, auto full) {
+      uint64_t bal[FG_ROWS];
+      uint32_t bq[FG_ROWS], tot = 0;
 #pragma unroll
-      for (int u = 0; u < FG_LOADS; ++u) {
-        const uint32_t i = t0 + u * 64 + lane;
-        e[u] = i < r1 ? E[i] : 0;
-      }
-      uint32_t tot = 0;
+      for (int u = 0; u < FG_ROWS; ++u) bq[u] = s_bq[bq_word(hash(e[u]))];
 #pragma unroll
-      for (int u = 0; u < FG_LOADS; ++u) {
-        const uint32_t i = (uint32_t)(e[u] >> idbits) & ((1u << JB_SB) - 1);
-        const bool keep = t0 + u * 64 + lane < r1 && ((s_bq[i >> 5] >> (i & 31u)) & 1u) && mine(e[u]);
+      for (int u = 0; u < FG_ROWS; ++u) {
+        const uint32_t h = hash(e[u]);
+        const bool keep = ((bq[u] >> (h & 31u)) & 1u) && (full || u * 64 + lane < left) && mine(e[u]);
         bal[u] = __ballot(keep);
         tot += (uint32_t)__popcll(bal[u]);
-        if (keep) {
-          const uint32_t j = mark(e[u]), j1 = j >> (32 - JB_TB), j2 = (j >> 2) & TM;
-          atomicOr(&s_br[j1 >> 5], 1u << (j1 & 31u));
-          atomicOr(&s_br[j2 >> 5], 1u << (j2 & 31u));
-        }
+        if (keep) atomicOr(&s_br[mark_word(h)], marks(h));
       }
       if (tot) {
         uint32_t at = 0;
@@ -1213,11 +1217,26 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
         at = __builtin_amdgcn_readfirstlane(at);
         if (at + tot <= JB_CAP) {
 #pragma unroll
-          for (int u = 0; u < FG_LOADS; ++u) {
+          for (int u = 0; u < FG_ROWS; ++u) {
             if ((bal[u] >> lane) & 1u) s_e[at + mask_rank(bal[u])] = e[u];
             at += (uint32_t)__popcll(bal[u]);
           }
         }
+      }
+    };
+    for (uint32_t t0 = r0 + w * ROW; t0 < r1; t0 += NW * ROW) {
+      uint64_t e[FG_ROWS];
+      if (t0 + ROW <= r1) {
+#pragma unroll
+        for (int u = 0; u < FG_ROWS; ++u) e[u] = E[t0 + u * 64 + lane];
+        look(e, ROW, std::true_type{});
+      } else {
+#pragma unroll
+        for (int u = 0; u < FG_ROWS; ++u) {
+          const uint32_t i = t0 + u * 64 + lane;
+          e[u] = i < r1 ? E[i] : 0;
+        }
+        look(e, r1 - t0, std::false_type{});
       }
     }
     __syncthreads();
@@ -1238,16 +1257,28 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
       continue;
     }
     // query survivors
-    queries([&](uint64_t e, bool valid) {
-      const uint32_t j = mark(e), j1 = j >> (32 - JB_TB), j2 = (j >> 2) & TM;
-      bool keep = valid && mine(e) && ((s_br[j1 >> 5] >> (j1 & 31u)) & 1u);
-      if (keep) keep = (s_br[j2 >> 5] >> (j2 & 31u)) & 1u;
-      const uint64_t bal = __ballot(keep);
-      if (bal) {
+    queries([&](const uint64_t(&e)[FG_ROWS], const bool(&valid)[FG_ROWS]) {
+      uint64_t bal[FG_ROWS];
+      uint32_t br[FG_ROWS], tot = 0;
+#pragma unroll
+      for (int u = 0; u < FG_ROWS; ++u) br[u] = s_br[mark_word(hash(e[u]))];
+#pragma unroll
+      for (int u = 0; u < FG_ROWS; ++u) {
+        const uint32_t need = marks(hash(e[u]));
+        bal[u] = __ballot((br[u] & need) == need && valid[u] && mine(e[u]));
+        tot += (uint32_t)__popcll(bal[u]);
+      }
+      if (tot) {
         uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(&s_nq, (uint32_t)__popcll(bal));
-        at = __builtin_amdgcn_readfirstlane(at) + mask_rank(bal);
-        if (keep && at < JB_QCAP) s_qe[at] = e;
+        if (lane == 0) at = atomicAdd(&s_nq, tot);
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (at + tot <= JB_QCAP) {
+#pragma unroll
+          for (int u = 0; u < FG_ROWS; ++u) {
+            if ((bal[u] >> lane) & 1u) s_qe[at + mask_rank(bal[u])] = e[u];
+            at += (uint32_t)__popcll(bal[u]);
+          }
+        }
       }
     });
     __syncthreads();
@@ -1255,21 +1286,32 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     if (m > JB_CAP || nq > JB_QCAP) {
       // one variant shared by thousands: every query element of the round
       // against the sorted index segment
-      queries([&](uint64_t e, bool valid) {
-        if (!valid || !mine(e)) return;
-        uint32_t lo = r0, hi = r1;
-        const uint64_t h = e >> idbits;
-        while (lo < hi) {
-          const uint32_t mid = lo + ((hi - lo) >> 1);
-          if ((E[mid] >> idbits) < h)
-            lo = mid + 1;
-          else
-            hi = mid;
-        }
-        for (; lo < r1; ++lo) {
-          const uint64_t r = E[lo];
-          if ((r >> idbits) != h) break;
-          pair_put(out, (e & idmask) << 32 | (r & idmask));
+      queries([&](const uint64_t(&es)[FG_ROWS], const bool(&valid)[FG_ROWS]) {
+#pragma unroll 1
+        for (int u = 0; u < FG_ROWS; ++u) {
+          uint64_t e = 0;
+          bool on = false;
+#pragma unroll
+          for (int q = 0; q < FG_ROWS; ++q)
+            if (q == u) {
+              e = es[q];
+              on = valid[q];
+            }
+          if (!on || !mine(e)) continue;
+          uint32_t lo = r0, hi = r1;
+          const uint64_t h = e >> idbits;
+          while (lo < hi) {
+            const uint32_t mid = lo + ((hi - lo) >> 1);
+            if ((E[mid] >> idbits) < h)
+              lo = mid + 1;
+            else
+              hi = mid;
+          }
+          for (; lo < r1; ++lo) {
+            const uint64_t r = E[lo];
+            if ((r >> idbits) != h) break;
+            pair_put(out, (e & idmask) << 32 | (r & idmask));
+          }
         }
       });
       __syncthreads();
@@ -1503,9 +1545,15 @@ void launch_join_bins(const PartOut& in, const uint64_t* E, const uint32_t* seg_
                       const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
                       const PairBins& out, hipStream_t s) {
   if (in.lb + sub > bits) throw Error{SD_E_HIP, "internal error: join segments finer than the index"};
-  allow_lds(&sdk::k_join_bins<1024>, sdk::JB_LDS);
-  hipLaunchKernelGGL((sdk::k_join_bins<1024>), dim3(in.nbins << sub), dim3(1024), sdk::JB_LDS, s, in,
-                     E, seg_start, seg_end, bits, sub, idbits, out);
+  auto launch = [&](auto kernel) {
+    allow_lds(kernel, sdk::JB_LDS);
+    hipLaunchKernelGGL(kernel, dim3(in.nbins << sub), dim3(1024), sdk::JB_LDS, s, in, E, seg_start,
+                       seg_end, bits, sub, out);
+  };
+  if (idbits == 32)
+    launch(&sdk::k_join_bins<1024, true>);
+  else
+    launch(&sdk::k_join_bins<1024, false>);
 }
 
 }  // namespace sd
