@@ -560,7 +560,7 @@ __global__ __launch_bounds__(NT) void k_part_split(sd::PartOut in, sd::PartOut o
     }
   }
   __syncthreads();
-  partition_tail<NT, TILE, sd::PART_MAX_SPLIT, false>(
+  partition_tail<NT, TILE, sd::PART_MAX_SPLIT, false, true>(
       s_e, m, s_cnt, s_tmp, (int)lb, [&](uint64_t v) { return (uint32_t)(v >> shift) & (nb - 1); },
       bin << lb, o.elem, o.cursor, o.region, o.nbins, o.nxl, o.slots, o.fill, o.cap, o.over_count);
 }

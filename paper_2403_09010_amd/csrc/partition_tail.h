@@ -21,8 +21,11 @@ namespace sdk {
 // the same XCD wrote them, so with one region per XCD its L2 completes the
 // cache lines at its own frontiers. Ordering the tile in LDS first beats
 // scattering it from registers (100M random elements into 2^10 and 2^11 bins:
-// 0.39 and 0.42 ms against 0.57 and 0.60).
-template <int NT, int TILE, int MAXLB, bool DROP, class Digit>
+// 0.39 and 0.42 ms against 0.57 and 0.60). With TOGETHER all of a thread's
+// elements are looked up before the first is written: 1G elements split in 3.34
+// ms instead of 3.52; a generator, whose other workgroups use the waits, gets
+// slower (4.66 instead of 4.36 ms).
+template <int NT, int TILE, int MAXLB, bool DROP, bool TOGETHER = false, class Digit>
 __device__ __forceinline__ void partition_tail(uint64_t* s_e, uint32_t m, uint32_t* s_cnt,
                                                uint32_t* s_tmp, int lb, const Digit& digit,
                                                uint32_t bin0, uint64_t* __restrict__ elem,
@@ -95,13 +98,30 @@ __device__ __forceinline__ void partition_tail(uint64_t* s_e, uint32_t m, uint32
     ex += c[q];
   }
   __syncthreads();
+  const auto write = [&](uint64_t v, uint32_t to, uint32_t t) {
+    const uint32_t p = to + t;
+    if (DROP ? (to != 0xFFFFFFFFu && p < slots) : p < cap) elem[p] = v;
+  };
+  if (TOGETHER) {
+    uint32_t to[PER];
 #pragma unroll
-  for (int r = 0; r < PER; ++r) {
-    const uint32_t t = threadIdx.x + r * NT;
-    if (t < m) {
-      const uint64_t v = s_e[t];
-      const uint32_t s = s_cnt[digit(v)], p = s + t;
-      if (DROP ? (s != 0xFFFFFFFFu && p < slots) : p < cap) elem[p] = v;
+    for (int r = 0; r < PER; ++r) {
+      const uint32_t t = threadIdx.x + r * NT;
+      e[r] = t < m ? s_e[t] : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < PER; ++r) to[r] = s_cnt[digit(e[r])];
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+      if (threadIdx.x + r * NT < m) write(e[r], to[r], threadIdx.x + r * NT);
+  } else {
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const uint32_t t = threadIdx.x + r * NT;
+      if (t < m) {
+        const uint64_t v = s_e[t];
+        write(v, s_cnt[digit(v)], t);
+      }
     }
   }
 }
