@@ -65,6 +65,18 @@ __device__ __forceinline__ uint32_t residue_at(u128 key, uint32_t t) {
   return (uint32_t)((s >= 56 ? top : lo) >> (s >= 56 ? s - 56 : s)) & 31u;
 }
 
+// What lane t of a half wave needs of its sequence: the two bytes of the packed key
+// that hold residue t, and the length.
+struct SeqLane {
+  uint32_t field, length;
+};
+__device__ __forceinline__ SeqLane load_lane(const u128* __restrict__ seq, uint32_t x, uint32_t t) {
+  const unsigned char* p = reinterpret_cast<const unsigned char*>(seq + x);
+  uint16_t f;
+  __builtin_memcpy(&f, p + ((115 - 5 * min(t, 23u)) >> 3), 2);
+  return SeqLane{f, p[15]};
+}
+
 // The end of the chunk of sequences from xa on whose variants fit the tile.
 template <int TILE>
 __device__ __forceinline__ uint32_t chunk_end(const uint32_t* s_pref, uint32_t xa, uint32_t ns) {
@@ -149,13 +161,13 @@ struct LanePairs {
 // from its lanes' at0 on, the upper half's id0 + 1 and its own at0. rows: the
 // wave's 4 GP_ROW words of LDS.
 template <bool K3, class Put>
-__device__ __forceinline__ void gen_step(u128 key, uint32_t id0, bool two, uint32_t at0, int k,
+__device__ __forceinline__ void gen_step(SeqLane key, uint32_t id0, bool two, uint32_t at0, int k,
                                          uint64_t* rows, const uint64_t* s_b, const uint64_t* s_c,
                                          const LanePairs& lp, Put&& put) {
   constexpr int QS = GP_ROW;
   const uint32_t lane = threadIdx.x & 63u, half = lane >> 5, t = lane & 31u;
-  const uint32_t L = key_len(key);
-  const uint32_t r = t < L ? residue_at(key, t < 24u ? t : 0u) : 31u;
+  const uint32_t L = key.length;
+  const uint32_t r = t < L ? __builtin_amdgcn_ubfe(key.field, (115 - 5 * min(t, 23u)) & 7u, 5) : 31u;
   W2 term = rotr_w2(w2(s_b[r]), t);
   if (t >= L) term = W2{0, 0};
   const W2 incl{half_xor_scan(term.lo), half_xor_scan(term.hi)};
@@ -167,7 +179,7 @@ __device__ __forceinline__ void gen_step(u128 key, uint32_t id0, bool two, uint3
   // as 31, which no residue equals)
   const uint32_t r1 = next_lane(r);
   const bool c1 = t < L && (r != r1 || t + 1 == L);
-  const uint64_t n1 = __ballot(c1);
+  const uint64_t n1 = __builtin_amdgcn_ballot_w64(c1);
   if (k >= 2 && t < (uint32_t)QS) {
     const W2 base2 = w2(s_c[L >= 2 ? L - 2 : 0]) ^ rotl_w2(pl, 2);
     uint64_t* row = rows + half * 2 * QS;
@@ -180,7 +192,7 @@ __device__ __forceinline__ void gen_step(u128 key, uint32_t id0, bool two, uint3
     // none (lane L, where q = P[L] ^ rotl(P[L], 1)) and one deletion
     const bool keep = ((k >= 1 && c1) || t == L) && (!half || two);
     const W2 h = w2(s_c[t < L ? L - 1 : L & 31u]) ^ rotl_w2(pl, 1) ^ q;
-    const uint64_t bal = __ballot(keep);
+    const uint64_t bal = __builtin_amdgcn_ballot_w64(keep);
     const uint32_t na = (uint32_t)__popc((uint32_t)bal);
     const uint32_t rank = mask_rank(bal) - (half ? na : 0u);
     if (keep) put(h, id0 + half, at0 + rank);
@@ -189,42 +201,55 @@ __device__ __forceinline__ void gen_step(u128 key, uint32_t id0, bool two, uint3
   }
   if (k < 2) return;
   const uint32_t r2 = next_lane(r1);
-  const uint64_t n2 = __ballot(t < L && (r != r2 || t + 2 >= L));
+  const uint64_t n2 = __builtin_amdgcn_ballot_w64(t < L && (r != r2 || t + 2 >= L));
   uint64_t n3 = 0;
-  if (K3) n3 = __ballot(t < L && (r != next_lane(r2) || t + 3 >= L));
+  if (K3) n3 = __builtin_amdgcn_ballot_w64(t < L && (r != next_lane(r2) || t + 3 >= L));
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  for (uint32_t sI = 0; sI < (two ? 2u : 1u); ++sI) {
+  // the words of two chunks of both sequences are read at once: most lengths have
+  // two (the empty asm keeps the compiler from moving the reads to their uses,
+  // each with its own wait)
+  auto pair_word = [&](uint32_t sI, int c) {
+    const unsigned char* Q = reinterpret_cast<const unsigned char*>(rows + sI * 2 * QS);
+    return w2(*reinterpret_cast<const uint64_t*>(Q + lp.pa[c])) ^
+           w2(*reinterpret_cast<const uint64_t*>(Q + lp.pb[c]));
+  };
+  W2 first[2][2];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) first[x >> 1][x & 1] = pair_word(x >> 1, x & 1);
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+    asm volatile("" : "+v"(first[x >> 1][x & 1].lo), "+v"(first[x >> 1][x & 1].hi));
+#pragma unroll
+  for (uint32_t sI = 0; sI < 2; ++sI) {
+    if (sI && !two) break;
     const uint32_t SL = read_lane(L, sI ? 32 : 0);
     const uint32_t m1 = (uint32_t)(n1 >> (sI * 32)), m2 = (uint32_t)(n2 >> (sI * 32));
     const unsigned char* Q = reinterpret_cast<const unsigned char*>(rows + sI * 2 * QS);
-    const uint32_t id = id0 + sI;
+    // (in a vector register: one AND-OR with the hash's mask in a scalar one)
+    uint32_t id = id0 + sI;
+    asm volatile("" : "+v"(id));
     uint32_t at = sI ? atB : atA;
     const uint32_t np = SL * (SL - 1) / 2;
     W2 pw[GP_CHUNKS];
     uint64_t kp[GP_CHUNKS], kq[GP_CHUNKS];
     const uint32_t m3 = (uint32_t)(n3 >> (sI * 32));
-    // (the words of two chunks are read at once: most lengths have two)
-    auto pair_word = [&](int c) {
-      return w2(*reinterpret_cast<const uint64_t*>(Q + lp.pa[c])) ^
-             w2(*reinterpret_cast<const uint64_t*>(Q + lp.pb[c]));
-    };
-    pw[0] = pair_word(0);
-    pw[1] = pair_word(1);
+    pw[0] = first[sI][0];
+    pw[1] = first[sI][1];
 #pragma unroll
     for (int c = 0; c < GP_CHUNKS; ++c) {
       if ((uint32_t)c * 64 >= np) break;  // uniform
-      if (c >= 2) pw[c] = pair_word(c);
+      if (c >= 2) pw[c] = pair_word(sI, c);
       const W2 h = pw[c];
       const bool keep = ((lp.need1[c] & ~m1) | (lp.need2[c] & ~m2)) == 0;
-      const uint64_t bal = __ballot(keep);
+      const uint64_t bal = __builtin_amdgcn_ballot_w64(keep);
       if (keep) put(h, id, at + mask_rank(bal));
       at += (uint32_t)__popcll(bal);
       if (K3) {
         kp[c] = bal;
         // with p3 = p2 + 1: p2 needs n2, p1 needs n1, or n3 if p1, p2, p3 adjoin
         const uint32_t b2 = 1u << ((lp.pb[c] >> 3) - QS), b1 = lp.need1[c] & ~b2;
-        kq[c] = __ballot(((b2 & ~m2) | (b1 & ~m1) | (lp.need2[c] & ~m3)) == 0 &&
+        kq[c] = __builtin_amdgcn_ballot_w64(((b2 & ~m2) | (b1 & ~m1) | (lp.need2[c] & ~m3)) == 0 &&
                          (lp.need1[c] >> 31) == 0);
       }
     }
@@ -260,9 +285,10 @@ constexpr int tile_max_lb(int threads) { return threads >= 1024 ? sd::PART_MAX_L
 // gen_step over a block's sequences, into an LDS tile that partition_tail
 // orders and writes.
 //
-// Bound: vector instructions and LDS operations, then the element writes.
-// 100M variants of 1M sequences (k = 2): 0.47-0.52 ms, of which the generation
-// alone is 0.26; two workgroups of 512 threads on a CU, so that one generates
+// Bound: vector instructions and LDS operations (about half of what either can
+// issue, with four waves per SIMD; eight, in half the registers, take 30% longer),
+// then the element writes. 101M variants of 1M sequences (k = 2): 0.46 ms, of
+// which the generation alone is 0.26; 454M (k = 3) 2.57 ms; two workgroups of 512 threads on a CU, so that one generates
 // while the other writes (one of 1,024: 0.55). Generating them in sequence
 // order took 0.40 and the first radix pass another 0.39.
 template <int NT, int TILE, bool K3>
@@ -273,13 +299,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   constexpr int NW = NT / 64;
   extern __shared__ __align__(16) unsigned char lds[];
   const uint32_t nb = 1u << o.lb;
-  uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
-  uint64_t* s_q = s_e + TILE;   // [NW][2][2][GP_ROW]: per sequence Q, then rotl(Q, 1) ^ base
+  // (the tile last: what lies within 64 KiB needs no address arithmetic)
+  // s_q: [NW][2][2][GP_ROW], per sequence Q, then rotl(Q, 1) ^ base
+  uint64_t* s_q = reinterpret_cast<uint64_t*>(lds);
   uint64_t* s_b = s_q + NW * 4 * GP_ROW;               // [32]
   uint64_t* s_c = s_b + 32;                          // [32]
-  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_c + 32);
-  uint32_t* s_pref = s_cnt + nb;                      // [NT + 1]
-  uint32_t* s_tmp = s_pref + NT + 1;                 // [NW]
+  uint32_t* s_pref = reinterpret_cast<uint32_t*>(s_c + 32);  // [NT + 2]
+  uint32_t* s_tmp = s_pref + NT + 2;                 // [NW]
+  uint32_t* s_cnt = s_tmp + NW;                      // [nb]
+  uint64_t* s_e = reinterpret_cast<uint64_t*>(s_cnt + nb);
   const uint32_t s0 = blockIdx.x * spb;
   const uint32_t ns = min(spb, nseq - s0);
   const uint32_t lane = threadIdx.x & 63u, half = lane >> 5;
@@ -316,13 +344,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     lp.load(pl_lane);
     uint32_t x = xa + 2 * w;
     // each half's sequence, loaded one step ahead
-    u128 key = x < xb ? seq[s0 + min(x + half, xb - 1)] : (u128)0;
+    SeqLane key{0, 0};
+    if (x < xb) key = load_lane(seq, s0 + min(x + half, xb - 1), lane & 31u);
     for (uint32_t i = threadIdx.x; i < nb; i += NT) s_cnt[i] = 0;
     __syncthreads();
     for (; x < xb; x += 2 * NW) {
       const bool two = x + 1 < xb;
-      const u128 cur = key;
-      key = seq[s0 + min(x + 2 * NW + half, xb - 1)];
+      const SeqLane cur = key;
+      key = load_lane(seq, s0 + min(x + 2 * NW + half, xb - 1), lane & 31u);
       const uint32_t at0 = s_pref[min(x + half, xb)] - p0;
       gen_step<K3>(cur, s0 + x, two, at0, k, s_q + w * 4 * GP_ROW, s_b, s_c, lp, put);
     }
@@ -1076,7 +1105,7 @@ __global__ __launch_bounds__(256) void k_gen_probe(const u128* __restrict__ seq,
   {
     const uint32_t x = (blockIdx.x * 4 + w) * 2;
     if (x < nseq) {
-      const u128 key = seq[min(x + (lane >> 5), nseq - 1)];
+      const SeqLane key = load_lane(seq, min(x + (lane >> 5), nseq - 1), lane & 31u);
       gen_step<K3>(key, x, x + 1 < nseq, 0, k, s_q + w * 4 * GP_ROW, s_b, s_c, lp, put);
     }
   }
@@ -1393,7 +1422,7 @@ static void allow_lds(F* f, size_t bytes) {
 template <int NT, int TILE>
 static size_t gen_lds(int lb) {
   return (size_t)TILE * 8 + (NT / 64) * 4 * KEY_MAX_LEN * 8 + 64 * 8 + ((size_t)4 << lb) +
-         (NT + 1) * 4 + (NT / 64) * 4;
+         (NT + 2) * 4 + (NT / 64) * 4;
 }
 
 template <int NT, int TILE>
