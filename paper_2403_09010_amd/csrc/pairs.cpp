@@ -110,15 +110,18 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     b.rank = sc.get<uint32_t>(sh.slots);
     b.kd = sc.get<uint8_t>(sh.slots);
     b.kept = sc.get<uint32_t>(sh.b.nbins);
-    b.off = sc.get<uint64_t>(q.na + 1);
-    b.ti = sc.get<uint32_t>(sh.slots);
-    b.tj = sc.get<uint32_t>(sh.slots);
+    const uint64_t tiles = pair_tiles(q.na), groups = (tiles + PAIR_GROUP - 1) / PAIR_GROUP;
+    b.sums = sc.get<uint32_t>(tiles);
+    b.groups = sc.get<uint32_t>(groups);
+    b.off = sc.get<uint32_t>(q.na + 1);
+    b.t = sc.get<uint64_t>(sh.slots);
     b.td = sc.get<uint8_t>(sh.slots);
     b.long_cap = (uint32_t)std::min<uint64_t>(sh.slots / 64 + 1, q.na);
     b.longs = sc.get<uint32_t>(b.long_cap);
     b.state = sc.get<PairState>(1);
     b.err = cl.lb_err();
     launch_zero({{b.icnt, q.na},
+                 {b.groups, groups},
                  {reinterpret_cast<uint32_t*>(b.state), sizeof(PairState) / 4},
                  cursors(sh.b),
                  cursors(sh.l0),
@@ -133,9 +136,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     }
     launch_pair_verify(sh.b, sh.wide, q, b, s);
     cl.tm.mark("pair_verify", (double)guess * (8 + 32), 1);
-    const uint64_t tiles = (q.na + scan_tile() - 1) / scan_tile();
-    const uint32_t epoch = next_epoch(c, tiles, s);
-    launch_scan_excl(b.icnt, b.off, q.na, c->status, cl.tile_counter(), epoch, cl.lb_err(), s);
+    launch_pair_scan(b, q.na, s);
     launch_pair_place(sh.b, b, s);
     Scratch res(c);  // the result arrays, handed over at the end
     uint32_t* oi = res.get<uint32_t>(cap);
@@ -148,8 +149,6 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     uint64_t raw = 0, more = 0;
     for (uint64_t x : st.raw) raw += x;
     const uint64_t kept = st.count;
-    if (st.counters[CNT_LBERR] & SD_ERRBIT_LOOKBACK)
-      throw Error{SD_E_HIP, "internal error: a look-back wait timed out"};
     const bool overflow = st.flags & PF_OVERFLOW;
     if (overflow)  // (a split reads slots that lost candidates never filled)
       launch_fill_u32(cl.lb_err(), 0, 1, s);
@@ -173,9 +172,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     out->ncand = raw;
     if (st.flags & PF_LONG) {
       // a first id with thousands of pairs: the kept pairs take the radix sort
-      uint64_t* cand = sc.get<uint64_t>(kept);
-      launch_join_pairs(b.ti, b.tj, kept, cand, s);
-      *out = sort_pairs(cand, kept);
+      *out = sort_pairs(b.t, kept);
       out->ncand = raw;
       return true;
     }

@@ -6,10 +6,10 @@
 //   k_pair_verify     one workgroup per bin: an LDS hash set drops the
 //                     repeats, the distinct candidates are verified, and every
 //                     kept pair takes a rank among its first id's pairs
-//   (scan)            kept pairs per first id -> output offsets
+//   k_pair_sums,      kept pairs per first id -> output offsets
+//   k_pair_scan
 //   k_pair_place      kept pairs to their first id's range of the output
 //   k_pair_order      order inside each range by second id, final arrays
-//   k_pair_long       the same for the few long ranges
 //
 // About nine raw candidates per reported pair (1M sequences, k = 2) leave
 // after one write and one read this way, instead of a sort of six passes:
@@ -25,8 +25,8 @@
 namespace sdk {
 
 constexpr int PR_ROWS = 8;          // rows of candidates in flight per wave
-constexpr uint32_t PR_LONG = 64;    // ranges with more pairs are ordered by k_pair_long
-constexpr uint32_t PR_MAX = 4096;   // longest range it orders in LDS
+constexpr uint32_t PR_LONG = 64;    // ranges with more pairs are ordered in LDS
+constexpr uint32_t PR_MAX = 4096;   // the longest of them
 enum : int { PM_LEV = 0, PM_HAMMING = 1, PM_PAIRED = 2, PM_WEIGHTED = 3, PM_SELF = 4 };
 
 // Candidates from the regions of one level to those of the next, a tile at a
@@ -218,65 +218,116 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
   if (threadIdx.x == 0) out.kept[bin] = s_k;
 }
 
-// Kept pairs to off[i] + rank.
+// Exclusive scan of the pairs kept per first id (fewer than 2^32 in all), in two
+// launches: the sums of tiles and groups of tiles, then each tile's own part, with
+// the sums before it. One launch with a look-back from tile to tile took longer: 19 us for
+// 1M ids and 100 for 10M, where these take 10 and 37.
+constexpr int PS_NT = 256, PS_ROWS = 4, PS_TILE = PS_NT * 4 * PS_ROWS;
+
+// lane's four counts of each row of its wave (the wave has PS_ROWS rows of 256 ids)
+__device__ __forceinline__ void tile_counts(const uint32_t* __restrict__ icnt, uint64_t n,
+                                            uint64_t first, uint4 (&c)[PS_ROWS]) {
+#pragma unroll
+  for (int r = 0; r < PS_ROWS; ++r) {
+    const uint64_t i = first + r * 256;
+    if (i + 4 <= n) {
+      c[r] = *reinterpret_cast<const uint4*>(icnt + i);
+    } else {
+      c[r].x = i < n ? icnt[i] : 0u;
+      c[r].y = i + 1 < n ? icnt[i + 1] : 0u;
+      c[r].z = i + 2 < n ? icnt[i + 2] : 0u;
+      c[r].w = 0u;
+    }
+  }
+}
+
+__device__ __forceinline__ uint64_t tile_first() {
+  return (uint64_t)blockIdx.x * PS_TILE + (threadIdx.x >> 6) * (256 * PS_ROWS) +
+         (threadIdx.x & 63u) * 4;
+}
+
+__global__ __launch_bounds__(PS_NT) void k_pair_sums(sd::PairBufs b, uint64_t n) {
+  __shared__ uint32_t s_tmp[PS_NT / 64];
+  uint4 c[PS_ROWS];
+  tile_counts(b.icnt, n, tile_first(), c);
+  uint32_t sum = 0, total;
+#pragma unroll
+  for (int r = 0; r < PS_ROWS; ++r) sum += c[r].x + c[r].y + c[r].z + c[r].w;
+  block_excl_scan<PS_NT>(sum, s_tmp, &total);
+  if (threadIdx.x == 0) {
+    b.sums[blockIdx.x] = total;
+    if (total) atomicAdd(&b.groups[blockIdx.x / sd::PAIR_GROUP], total);
+  }
+}
+
+__global__ __launch_bounds__(PS_NT) void k_pair_scan(sd::PairBufs b, uint64_t n) {
+  __shared__ uint32_t s_tmp[PS_NT / 64], s_wave[PS_NT / 64];
+  const uint64_t first = tile_first();
+  uint4 c[PS_ROWS];
+  tile_counts(b.icnt, n, first, c);
+  uint32_t sum = 0, before;
+  const uint32_t g = blockIdx.x / sd::PAIR_GROUP;
+  for (uint32_t x = threadIdx.x; x < g; x += PS_NT) sum += b.groups[x];
+  for (uint32_t x = g * sd::PAIR_GROUP + threadIdx.x; x < blockIdx.x; x += PS_NT) sum += b.sums[x];
+  block_excl_scan<PS_NT>(sum, s_tmp, &before);
+  // the rows of a wave one after the other, the waves likewise
+  uint32_t ex[PS_ROWS], run = 0;
+#pragma unroll
+  for (int r = 0; r < PS_ROWS; ++r) {
+    const uint32_t v = c[r].x + c[r].y + c[r].z + c[r].w, incl = wave_incl_scan(v);
+    ex[r] = run + incl - v;
+    run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+  }
+  if ((threadIdx.x & 63u) == 0) s_wave[threadIdx.x >> 6] = run;
+  __syncthreads();
+  for (uint32_t w = 0; w < threadIdx.x >> 6; ++w) before += s_wave[w];
+#pragma unroll
+  for (int r = 0; r < PS_ROWS; ++r) {
+    const uint64_t i = first + r * 256;
+    uint4 o;
+    o.x = before + ex[r];
+    o.y = o.x + c[r].x;
+    o.z = o.y + c[r].y;
+    o.w = o.z + c[r].z;
+    if (i + 4 <= n) {
+      *reinterpret_cast<uint4*>(b.off + i) = o;
+      if (i + 4 == n) b.off[n] = o.w + c[r].w;
+    } else if (i < n) {
+      const uint32_t v[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        if (i + x <= n) b.off[i + x] = v[x];
+    }
+  }
+}
+
+// Kept pairs to off[i] + rank. Bound: the random writes, a word and a byte per
+// pair (8.6M pairs of 10M sequences: 0.47 ms; with the two ids in words of
+// their own 0.66).
 __global__ __launch_bounds__(64) void k_pair_place(sd::PairBins in, sd::PairBufs b) {
   const uint32_t n = b.kept[blockIdx.x];
   const uint64_t base = (uint64_t)(blockIdx.x << in.nxl) * in.region;
   for (uint32_t x = threadIdx.x; x < n; x += 64) {
     const uint64_t v = b.kv[base + x];
-    const uint64_t p = b.off[v >> 32] + b.rank[base + x];
-    b.ti[p] = (uint32_t)(v >> 32);
-    b.tj[p] = (uint32_t)v;
+    const uint32_t p = b.off[v >> 32] + b.rank[base + x];
+    b.t[p] = v;
     b.td[p] = b.kd[base + x];
-  }
-}
-
-// Position p's pair goes to the start of its first id's range plus the number
-// of smaller second ids there: most ranges hold one to three pairs, neighbours
-// in the same cache lines. The last kernel of a search also copies the call's
-// counters beside its own, so that one read-back gets both.
-__global__ __launch_bounds__(256) void k_pair_order(sd::PairBufs b, uint64_t n,
-                                                    uint32_t* __restrict__ oi,
-                                                    uint32_t* __restrict__ oj,
-                                                    uint8_t* __restrict__ od, uint64_t cap,
-                                                    const uint32_t* __restrict__ counters) {
-  const uint64_t total = b.off[n];
-  if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) b.state->count = total;
-    if (threadIdx.x < sd::PAIR_COUNTERS) b.state->counters[threadIdx.x] = counters[threadIdx.x];
-  }
-  for (uint64_t p = (uint64_t)blockIdx.x * 256 + threadIdx.x; p < total;
-       p += (uint64_t)gridDim.x * 256) {
-    const uint32_t i = b.ti[p], j = b.tj[p];
-    const uint64_t s = b.off[i], e = b.off[i + 1];
-    if (e - s > PR_LONG) continue;
-    uint64_t at = s;
-    for (uint64_t q = s; q < e; ++q) at += b.tj[q] < j;
-    if (at < cap) {
-      oi[at] = i;
-      oj[at] = j;
-      od[at] = b.td[p];
-    }
   }
 }
 
 // Ranges of PR_LONG + 1 to PR_MAX pairs: a bitonic sort in LDS, one workgroup
 // per range in turn.
-__global__ __launch_bounds__(256) void k_pair_long(sd::PairBufs b, uint32_t* __restrict__ oi,
-                                                   uint32_t* __restrict__ oj,
-                                                   uint8_t* __restrict__ od, uint64_t cap) {
-  __shared__ uint64_t s_v[PR_MAX];
+__device__ __forceinline__ void order_long(const sd::PairBufs& b, uint64_t* s_v,
+                                           uint32_t* __restrict__ oi, uint32_t* __restrict__ oj,
+                                           uint8_t* __restrict__ od, uint64_t cap) {
   const uint32_t nl = min(b.state->nlong, b.long_cap);
   for (uint32_t l = blockIdx.x; l < nl; l += gridDim.x) {
-    const uint32_t i = b.longs[l];
-    const uint64_t s = b.off[i];
-    const uint64_t m64 = b.off[i + 1] - s;
-    if (m64 > PR_MAX) continue;  // flagged by k_pair_verify
-    const uint32_t m = (uint32_t)m64;
+    const uint32_t i = b.longs[l], s = b.off[i], m = b.off[i + 1] - s;
+    if (m > PR_MAX) continue;  // flagged by k_pair_verify
     uint32_t pw = 128;
     while (pw < m) pw <<= 1;
     for (uint32_t x = threadIdx.x; x < pw; x += 256)
-      s_v[x] = x < m ? ((uint64_t)b.tj[s + x] << 8) | b.td[s + x] : ~0ull;
+      s_v[x] = x < m ? (b.t[s + x] << 8 & 0xFFFFFFFF00ull) | b.td[s + x] : ~0ull;
     __syncthreads();
     for (uint32_t a = 2; a <= pw; a <<= 1)
       for (uint32_t h = a >> 1; h > 0; h >>= 1) {
@@ -297,6 +348,40 @@ __global__ __launch_bounds__(256) void k_pair_long(sd::PairBufs b, uint32_t* __r
         od[s + x] = (uint8_t)s_v[x];
       }
     __syncthreads();
+  }
+}
+
+// Position p's pair goes to the start of its first id's range plus the number
+// of smaller second ids there: most ranges hold one to three pairs, neighbours
+// in the same cache lines. The first workgroups order the few long ranges
+// before, while the others are at work (10M sequences: 0.28 ms, where they took 0.23
+// in a kernel of their own and the rest 0.14). The last kernel of a search also copies
+// the call's counters beside its own, so that one read-back gets both.
+__global__ __launch_bounds__(256) void k_pair_order(sd::PairBufs b, uint64_t n,
+                                                    uint32_t* __restrict__ oi,
+                                                    uint32_t* __restrict__ oj,
+                                                    uint8_t* __restrict__ od, uint64_t cap,
+                                                    const uint32_t* __restrict__ counters) {
+  __shared__ uint64_t s_v[PR_MAX];
+  const uint64_t total = b.off[n];
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) b.state->count = total;
+    if (threadIdx.x < sd::PAIR_COUNTERS) b.state->counters[threadIdx.x] = counters[threadIdx.x];
+  }
+  order_long(b, s_v, oi, oj, od, cap);
+  for (uint64_t p = (uint64_t)blockIdx.x * 256 + threadIdx.x; p < total;
+       p += (uint64_t)gridDim.x * 256) {
+    const uint64_t v = b.t[p];
+    const uint32_t i = (uint32_t)(v >> 32), j = (uint32_t)v;
+    const uint32_t s = b.off[i], e = b.off[i + 1];
+    if (e - s > PR_LONG) continue;
+    uint64_t at = s;
+    for (uint32_t q = s; q < e; ++q) at += (uint32_t)b.t[q] < j;
+    if (at < cap) {
+      oi[at] = i;
+      oj[at] = j;
+      od[at] = b.td[p];
+    }
   }
 }
 
@@ -358,6 +443,14 @@ void launch_pair_split(const PairBins& in, const PairBins& o, PairState* state, 
                      lds, s, in, o, state, tiles);
 }
 
+uint64_t pair_tiles(uint64_t na) { return (na + sdk::PS_TILE - 1) / sdk::PS_TILE; }
+
+void launch_pair_scan(const PairBufs& b, uint64_t na, hipStream_t s) {
+  const dim3 g((unsigned)pair_tiles(na));
+  hipLaunchKernelGGL(sdk::k_pair_sums, g, dim3(sdk::PS_NT), 0, s, b, na);
+  hipLaunchKernelGGL(sdk::k_pair_scan, g, dim3(sdk::PS_NT), 0, s, b, na);
+}
+
 void launch_pair_place(const PairBins& in, const PairBufs& b, hipStream_t s) {
   hipLaunchKernelGGL(sdk::k_pair_place, dim3(in.nbins), dim3(64), 0, s, in, b);
 }
@@ -365,8 +458,6 @@ void launch_pair_place(const PairBins& in, const PairBufs& b, hipStream_t s) {
 void launch_pair_order(const PairBufs& b, uint64_t n, uint32_t* oi, uint32_t* oj, uint8_t* od,
                        uint64_t cap, const uint32_t* counters, hipStream_t s) {
   const unsigned g = (unsigned)std::min<uint64_t>(std::max<uint64_t>((cap + 255) / 256, 1), 4096);
-  hipLaunchKernelGGL(sdk::k_pair_long, dim3(std::min(512u, g)), dim3(256), 0, s, b, oi, oj, od,
-                     cap);
   hipLaunchKernelGGL(sdk::k_pair_order, dim3(g), dim3(256), 0, s, b, n, oi, oj, od, cap, counters);
 }
 

@@ -35,7 +35,7 @@ struct ZeroRange {
   uint32_t* p;
   uint64_t n;
 };
-constexpr int ZERO_RANGES = 5;
+constexpr int ZERO_RANGES = 6;
 void launch_zero(std::initializer_list<ZeroRange> ranges, hipStream_t s);
 void launch_fill_u64(uint64_t* p, uint64_t v, uint64_t n, hipStream_t s);
 uint32_t out_shards();
@@ -321,9 +321,10 @@ struct PairBufs {
   uint8_t* kd;      // ... and distance
   uint32_t* kept;   // nbins: how many
   uint32_t* icnt;   // na, zeroed: pairs kept per first id
-  uint64_t* off;    // na + 1: exclusive scan of icnt
-  uint32_t* ti;     // slots: kept pairs by first id
-  uint32_t* tj;
+  uint32_t* sums;   // pair_tiles(na): pairs kept per tile of first ids, ...
+  uint32_t* groups; // ... and per PAIR_GROUP tiles, zeroed
+  uint32_t* off;    // na + 1: exclusive scan of icnt
+  uint64_t* t;      // slots: kept pairs by first id
   uint8_t* td;
   uint32_t* longs;  // first ids with many pairs
   uint32_t long_cap;
@@ -338,7 +339,11 @@ void launch_pair_verify(const PairBins& in, bool large, const PairSeqs& q, const
 // the candidates of one level of bins to the next (o.lb > in.lb); what in's
 // regions lost is counted in state
 void launch_pair_split(const PairBins& in, const PairBins& o, PairState* state, hipStream_t s);
-// ti, tj, td from those and off
+// off from icnt
+constexpr uint32_t PAIR_GROUP = 64;
+uint64_t pair_tiles(uint64_t na);
+void launch_pair_scan(const PairBufs& b, uint64_t na, hipStream_t s);
+// t, td from kv, rank, kd and off
 void launch_pair_place(const PairBins& in, const PairBufs& b, hipStream_t s);
 // the placed pairs in order to o*[0, cap), their number and PAIR_COUNTERS words
 // of counters to b.state
