@@ -401,11 +401,10 @@ __global__ __launch_bounds__(256) void k_paired_distinct(const u128* __restrict_
     const uint64_t n2 = ((d2 & low_bits(L - 2)) | 1ull << (L - 2)) & keep;
     c = 1;
     if (k >= 1) c += (uint32_t)__popcll(n1);
-    if (k >= 2)
-      for (uint64_t m = n1 & ~1ull; m; m &= m - 1) {
-        const uint32_t p2 = (uint32_t)__builtin_ctzll(m);
-        c += (uint32_t)__popcll(n1 & low_bits(p2 - 1)) + (uint32_t)((n2 >> (p2 - 1)) & 1u);
-      }
+    if (k >= 2) {
+      const uint32_t m = (uint32_t)__popcll(n1);
+      c += m * (m - 1) / 2 - (uint32_t)__popcll(n1 & (n1 >> 1)) + (uint32_t)__popcll(n2 & (n1 >> 1));
+    }
     vcnt[i] = c;
   }
   uint32_t total;

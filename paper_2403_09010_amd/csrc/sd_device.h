@@ -86,17 +86,16 @@ __device__ __forceinline__ bool variant_canonical_ext(uint32_t n1x, uint32_t n2x
   return ((sel >> p1) & (n1x >> p2) & 1u) != 0;
 }
 
-// Number of distinct strings among the deletion variants with at most k
-// deletions: the canonical sets above, counted in O(L) from the same masks
-// (the run count is the number of canonical first deletions p1 <= p2 - 2).
-__device__ __forceinline__ uint32_t num_distinct_variants(uint32_t n1, uint32_t n2, uint32_t L,
-                                                          int k) {
+// Number of distinct strings among the deletion variants with at most k <= 2
+// deletions: the canonical sets above, counted from the same masks. Of the m
+// positions in n1 every two that do not adjoin are a canonical pair, and of two
+// that do, the second one in n1, those whose first is in n2.
+__device__ __forceinline__ uint32_t num_distinct_variants(uint32_t n1, uint32_t n2, int k) {
+  const uint32_t m = (uint32_t)__popc(n1), next = n1 >> 1;
   uint32_t c = 1;
-  if (k >= 1) c += (uint32_t)__popc(n1);
+  if (k >= 1) c += m;
   if (k >= 2)
-    for (uint32_t p2 = 1; p2 < L; ++p2)
-      if ((n1 >> p2) & 1u)
-        c += (uint32_t)__popc(n1 & ((1u << (p2 - 1)) - 1u)) + ((n2 >> (p2 - 1)) & 1u);
+    c += m * (m - 1) / 2 - (uint32_t)__popc(n1 & next) + (uint32_t)__popc(n2 & next);
   return c;
 }
 
@@ -133,19 +132,17 @@ __device__ __forceinline__ bool variant_canonical3(uint32_t n1x, uint32_t n2x, u
   return c1 && c2 && c3;
 }
 
-// Canonical sets of exactly three deletions, in O(L^2) from the masks: for
-// every canonical last two deletions (p2, p3), first deletions p1 <= p2 - 2
-// need n1, and p1 = p2 - 1 needs n2 (p3 > p2 + 1) or n3 (p3 = p2 + 1).
+// Canonical sets of exactly three deletions, in O(L) from the masks: by the
+// middle one p2, which needs n1 with the p3 >= p2 + 2 in n1, or n2 with p3 =
+// p2 + 1 in n1; first deletions p1 <= p2 - 2 need n1, and p1 = p2 - 1 needs n2 or,
+// with p3 = p2 + 1, n3.
 __device__ __forceinline__ uint32_t num_distinct_triples(uint32_t n1, uint32_t n2, uint32_t n3,
                                                          uint32_t L) {
   uint32_t c = 0;
-  for (uint32_t p3 = 2; p3 < L; ++p3) {
-    if (!((n1 >> p3) & 1u)) continue;
-    for (uint32_t p2 = 1; p2 < p3; ++p2) {
-      const bool adj = p3 == p2 + 1;
-      if (!(((adj ? n2 : n1) >> p2) & 1u)) continue;
-      c += (uint32_t)__popc(n1 & ((1u << (p2 - 1)) - 1u)) + (((adj ? n3 : n2) >> (p2 - 1)) & 1u);
-    }
+  for (uint32_t p2 = 1; p2 + 1 < L; ++p2) {
+    const uint32_t far = (uint32_t)__popc(n1 & ((1u << (p2 - 1)) - 1u));
+    if ((n1 >> p2) & 1u) c += (uint32_t)__popc(n1 >> (p2 + 2)) * (far + ((n2 >> (p2 - 1)) & 1u));
+    if ((n2 >> p2) & (n1 >> (p2 + 1)) & 1u) c += far + ((n3 >> (p2 - 1)) & 1u);
   }
   return c;
 }

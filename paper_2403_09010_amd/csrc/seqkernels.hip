@@ -19,10 +19,34 @@ constexpr int NT = 256;
 
 // ------------------------------------------------------------------ pack
 
+// Bit q of eight residues (bytes) to byte q: an 8 x 8 bit transposition.
+__device__ __forceinline__ void transpose8(uint32_t& lo, uint32_t& hi) {
+  uint32_t t = (lo ^ (lo >> 7)) & 0x00AA00AAu;
+  lo ^= t ^ (t << 7);
+  t = (hi ^ (hi >> 7)) & 0x00AA00AAu;
+  hi ^= t ^ (t << 7);
+  t = (lo ^ (lo >> 14)) & 0x0000CCCCu;
+  lo ^= t ^ (t << 14);
+  t = (hi ^ (hi >> 14)) & 0x0000CCCCu;
+  hi ^= t ^ (t << 14);
+  t = (lo ^ (hi << 4)) & 0xF0F0F0F0u;
+  lo ^= t;
+  hi ^= t >> 4;
+}
+
 // One thread per sequence; the total of vcnt goes to one of PACK_SUMS counters
 // per workgroup. With SETS, the sequences of nsets device sets, one after the
 // other: read where they are, which spares a batch the copy of its sets into one
-// (20 sets, 750K sequences: 33 us for 1.1 ms of staging through the host).
+// (20 sets, 750K sequences: about 30 us for 1.1 ms of staging through the host).
+//
+// The codes of a workgroup's sequences follow each other: they come through LDS,
+// 16 bytes a lane (if a length is refused, or the workgroup spans two sets, each
+// lane reads its own bytes). The fields and bit planes are formed four and eight
+// residues at a time. Bound: vector instructions, then the 64 bytes a sequence
+// that it reads and writes. 2M sequences, k = 1: 39 us (57 with a byte at a time);
+// 1M, k = 3: 31 (92 with the sets counted in O(L^2)).
+constexpr int PK_BYTES = NT * KEY_MAX_LEN;
+
 template <bool SETS>
 __global__ __launch_bounds__(NT) void k_pack(const uint8_t* __restrict__ codes,
                                              const int64_t* __restrict__ offs,
@@ -34,10 +58,16 @@ __global__ __launch_bounds__(NT) void k_pack(const uint8_t* __restrict__ codes,
                                              uint32_t* __restrict__ err,
                                              unsigned long long* __restrict__ sums) {
   __shared__ uint32_t s_tmp[NT / 64];
+  __shared__ uint4 s_codes[PK_BYTES / 16 + 4];
+  __shared__ const uint8_t* s_from;
+  __shared__ const uint8_t* s_to;
+  __shared__ uint32_t s_set[2];
   const uint64_t i = (uint64_t)blockIdx.x * NT + threadIdx.x;
-  uint32_t c = 0;
+  uint32_t c = 0, set = 0;
+  uint64_t at = i;  // in its set
+  int64_t a = 0, L = 0;
+  bool good = true;
   if (i < n) {
-    uint64_t at = i;  // in its set
     if (SETS) {
       uint32_t lo = 0, hi = nsets - 1;  // last set that starts at or before i
       while (lo < hi) {
@@ -47,53 +77,108 @@ __global__ __launch_bounds__(NT) void k_pack(const uint8_t* __restrict__ codes,
         else
           hi = mid - 1;
       }
+      set = lo;
       codes = sets[lo].codes;
       offs = sets[lo].offs;
       at -= sets[lo].base;
     }
-    const int64_t a = offs[at], b = offs[at + 1];
-    const int64_t L = b - a;
+    a = offs[at];
+    L = offs[at + 1] - a;
     // (a sequence that starts below 0 or beyond what the ones before it can take
     // follows one that is flagged: it is not read)
     const bool lost = SETS && (a < 0 || a > (int64_t)at * KEY_MAX_LEN);
     if (SETS && (L < 0 || (at == 0 && a != 0))) atomicOr(err, SD_ERRBIT_OFFSETS);
-    if (L < 1 || L > KEY_MAX_LEN || lost) {
-      if (!lost) atomicOr(err, SD_ERRBIT_LENGTH);
-      // (one residue, so that what runs before the flag is read has a sequence)
-      seq[i] = (u128)1 << 120;
-      if (planes) planes[i] = (u128)1 << 120;
-      if (vcnt) c = k >= 1 ? 2u : 1u;
-    } else {
-      u128 key = (u128)L << 120;
-      uint32_t pl[5] = {0, 0, 0, 0, 0};
-      bool bad = false;
-      for (int t = 0; t < (int)L; ++t) {
-        const uint32_t r = codes[a + t];
-        bad |= r >= 20u;
-        key |= (u128)(r & 31u) << (115 - 5 * t);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) pl[q] |= ((r >> q) & 1u) << t;
-      }
-      if (bad) atomicOr(err, SD_ERRBIT_ALPHABET);
-      seq[i] = key;
-      if (planes) {
-        const uint64_t lo = (uint64_t)pl[0] | ((uint64_t)pl[1] << 24) | ((uint64_t)pl[2] << 48);
-        const uint64_t hi = ((uint64_t)pl[2] >> 16) | ((uint64_t)pl[3] << 8) |
-                            ((uint64_t)pl[4] << 32) | ((uint64_t)L << 56);
-        planes[i] = ((u128)hi << 64) | lo;
-      }
-      if (vcnt) {
-        c = num_variants((uint32_t)L, k);
-        if (distinct) {
-          uint32_t n1, n2;
-          canonical_masks(pl, (uint32_t)L, n1, n2);
-          c = num_distinct_variants(n1, n2, (uint32_t)L, k);
-          if (k >= 3)
-            c += num_distinct_triples(n1, n2, canonical_mask3(pl, (uint32_t)L), (uint32_t)L);
-        }
+    good = L >= 1 && L <= KEY_MAX_LEN && !lost;
+    if (!good && !lost) atomicOr(err, SD_ERRBIT_LENGTH);
+    const bool last = threadIdx.x == NT - 1 || i + 1 == n;
+    if (threadIdx.x == 0) {
+      s_from = codes + a;
+      s_set[0] = set;
+    }
+    if (last) {
+      s_to = codes + a + L;
+      s_set[1] = set;
+    }
+  }
+  // (with every length good, a sequence of one set begins where the one before ends)
+  const bool together = __syncthreads_and(good) && s_set[0] == s_set[1];
+  uint32_t w[6] = {0, 0, 0, 0, 0, 0};  // the residues, a byte each
+  if (together) {
+    const uint8_t* const from = s_from;
+    const uint8_t* const to = s_to;
+    const uint32_t skew = (uint32_t)(reinterpret_cast<uintptr_t>(from) & 15u);
+    uint8_t* const buf = reinterpret_cast<uint8_t*>(s_codes);  // byte x: from[x - skew]
+    const uint32_t len = (uint32_t)(to - from) + skew;  // at most PK_BYTES + 15
+    for (uint32_t x = threadIdx.x * 16; x < len; x += NT * 16) {
+      if (x >= skew && x + 16 <= len) {
+        s_codes[x / 16] = *reinterpret_cast<const uint4*>(from + x - skew);
+      } else {
+        for (uint32_t y = x < skew ? skew : x; y < x + 16 && y < len; ++y) buf[y] = from[y - skew];
       }
     }
-    if (vcnt) vcnt[i] = c;
+    __syncthreads();
+    if (i < n) {
+      const uint32_t o = (uint32_t)(codes + a - from) + skew;
+      const uint32_t* const word = reinterpret_cast<const uint32_t*>(s_codes) + (o >> 2);
+      uint32_t v[7];
+#pragma unroll
+      for (int d = 0; d < 7; ++d) v[d] = word[d];
+#pragma unroll
+      for (int d = 0; d < 6; ++d) {
+        const int left = (int)L - 4 * d;  // of the word's bytes
+        const uint32_t x = __builtin_amdgcn_alignbit(v[d + 1], v[d], (o & 3u) * 8);
+        w[d] = left >= 4 ? x : left <= 0 ? 0u : x & ((1u << (8 * left)) - 1u);
+      }
+    }
+  } else if (i < n && good) {
+#pragma unroll
+    for (int t = 0; t < KEY_MAX_LEN; ++t)
+      if (t < (int)L) w[t / 4] |= (uint32_t)codes[a + t] << (8 * (t % 4));
+  }
+  if (i < n && !good) L = 1;  // (residue 0, so that what runs before the flag is read has a sequence)
+  if (i < n) {
+    uint32_t bad = 0, f[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      // a residue of 20 or more: a bit above the fifth, or 16 and 4 or 8
+      bad |= (w[d] & 0xE0E0E0E0u) | (w[d] & 0x10101010u & (w[d] << 1 | w[d] << 2));
+      w[d] &= 0x1F1F1F1Fu;
+      // four 5-bit fields, the first residue topmost
+      const uint32_t y = __builtin_bswap32(w[d]);
+      const uint32_t t = (y & 0x001F001Fu) | ((y >> 3) & 0x03E003E0u);
+      f[d] = (t & 0x3FFu) | ((t >> 6) & 0xFFC00u);
+    }
+    if (bad) atomicOr(err, SD_ERRBIT_ALPHABET);
+    const uint64_t klo = (uint64_t)f[5] | (uint64_t)f[4] << 20 | (uint64_t)f[3] << 40 | (uint64_t)f[2] << 60;
+    const uint64_t khi = (uint64_t)(f[2] >> 4) | (uint64_t)f[1] << 16 | (uint64_t)f[0] << 36 |
+                         (uint64_t)L << 56;
+    seq[i] = ((u128)khi << 64) | klo;
+    transpose8(w[0], w[1]);
+    transpose8(w[2], w[3]);
+    transpose8(w[4], w[5]);
+    uint32_t pl[5];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+      const int h = q / 4, s = 8 * (q % 4);
+      pl[q] = ((w[h] >> s) & 255u) | ((w[2 + h] >> s) & 255u) << 8 | ((w[4 + h] >> s) & 255u) << 16;
+    }
+    if (planes) {
+      const uint64_t lo = (uint64_t)pl[0] | ((uint64_t)pl[1] << 24) | ((uint64_t)pl[2] << 48);
+      const uint64_t hi = ((uint64_t)pl[2] >> 16) | ((uint64_t)pl[3] << 8) |
+                          ((uint64_t)pl[4] << 32) | ((uint64_t)L << 56);
+      planes[i] = ((u128)hi << 64) | lo;
+    }
+    if (vcnt) {
+      c = num_variants((uint32_t)L, k);
+      if (distinct) {
+        uint32_t n1, n2;
+        canonical_masks(pl, (uint32_t)L, n1, n2);
+        c = num_distinct_variants(n1, n2, k);
+        if (k >= 3)
+          c += num_distinct_triples(n1, n2, canonical_mask3(pl, (uint32_t)L), (uint32_t)L);
+      }
+      vcnt[i] = c;
+    }
   }
   if (sums) {
     uint32_t total;

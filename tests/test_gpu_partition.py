@@ -276,3 +276,21 @@ def test_batch_device_offsets_refused(query_paths, at, value, name):
     assert e.value.name == name
     assert len(ctx.query_batch(idx, sets[::2], 1)) == 2
     idx.free()
+
+
+# codes at any alignment, part of a workgroup and whole ones, against the host's
+# own copy of the same sequences
+@pytest.mark.parametrize("n,shift", [(1, 3), (255, 1), (256, 15), (257, 8), (1_000, 7)])
+def test_unaligned_codes(paths, n, shift):
+    import torch
+    c, o = cdr3gen.generate(n, n)
+    c = c.copy()
+    c[o[n // 2]:o[n // 2] + 2] = (0, 19)  # the residue codes' ends
+    dev = torch.zeros(len(c) + shift, dtype=torch.uint8, device="cuda")
+    dev[shift:] = torch.from_numpy(c).cuda()
+    for k in (0, 2):
+        a = paths[0].self_search(dev[shift:], torch.from_numpy(o).cuda(), k)
+        b = paths[1].self_search(c, o, k)
+        assert len(a) == len(b)
+        for x, y in zip(a.numpy(), b.numpy()):
+            assert np.array_equal(x, y)
