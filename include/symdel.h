@@ -448,10 +448,11 @@ void sd_server_destroy(sd_server* server);
  * SD_OPT_GROUP_BITS (the radix width of the grouping sort: the automatic
  * count plus one or two bits), SD_OPT_PAIR_SORT and SD_OPT_GROUP_SHAPE. With
  * an index it tunes sd_query_batch over the nsets sets: a grid over
- * SD_OPT_BATCH_TILE and SD_OPT_SORT_ITEMS, then SD_OPT_BATCH_GRAPH. Each
+ * SD_OPT_BATCH_TILE and SD_OPT_SORT_ITEMS (0 and 32), then SD_OPT_BATCH_GRAPH. Each
  * candidate runs once to warm up and then `reps` times (1..100); the score
- * is the mean wall time of the call. On error the context keeps its
- * previous options.
+ * is the mean wall time of the call. The context keeps the options it had
+ * before if they were faster than every candidate (default_s < best_s; the
+ * result then names the fastest candidate), and on error.
  * With a cache file set by sd_autotune_cache, a choice stored under the same
  * key (device architecture; self, or query with floor(log2) of the
  * reference count; floor(log2) of the sequence count and of the set count;

@@ -8,8 +8,11 @@
 // width of the grouping sort: the automatic choice, one bit more, two bits
 // more, which can add an 8-bit pass), the candidate pair sort (one-sweep or
 // counted passes) and the grouping kernel's shape. Query batches (index
-// given): a grid over the query tile size and the radix items per thread,
-// then the captured-graph batch on or off. Every candidate runs once to warm
+// given): a grid over the query tile size, each with the automatic join and with
+// the radix passes of the general path, then the captured-graph batch on or off.
+// The context keeps the options it had if they were faster than every candidate
+// (a self search's automatic path usually is: 1M sequences, k = 2, 1.06 ms, the
+// best of the grid 2.2). Every candidate runs once to warm
 // the memory pool, then `reps` times; the score is the mean host wall time
 // of the synchronous call, so allocation and read-back costs count too.
 // Results are identical for every configuration; only speed changes.
@@ -223,7 +226,8 @@ void autotune(sd_ctx* c, const sd_index* idx, int nsets, const sd_seqs* sets, in
     auto it = cache.find(key);
     Knobs kb;
     if (it != cache.end() && from_entry(it->second, kb)) {
-      set_knobs(c, kb);
+      const auto kept = it->second.find("kept");
+      if (kept == it->second.end() || !kept->second) set_knobs(c, kb);
       out->path = kb.path;
       out->group_cap = kb.group_cap;
       out->sort_items = kb.sort_items;
@@ -284,7 +288,7 @@ void autotune(sd_ctx* c, const sd_index* idx, int nsets, const sd_seqs* sets, in
         trial(kb);
       }
     } else {
-      for (int items : {16, 32})
+      for (int items : {0, 32})
         for (int64_t tile : {1ll << 20, 1ll << 21, 1ll << 22, 1ll << 23}) {
           Knobs kb = start;
           kb.sort_items = items;
@@ -339,18 +343,20 @@ void autotune(sd_ctx* c, const sd_index* idx, int nsets, const sd_seqs* sets, in
     set_knobs(c, start);
     throw;
   }
-  set_knobs(c, best_k);
-  out->path = c->path;
-  out->group_cap = c->group_cap;
-  out->sort_items = c->sort_items;
-  out->batch_tile = c->batch_tile_seqs;
-  out->group_bits = c->group_bits;
-  out->pair_sort = c->pair_sort;
-  out->group_shape = c->group_shape;
-  out->batch_graph = c->batch_graph;
+  const bool kept = out->default_s < best;  // (the context has those options now)
+  if (!kept) set_knobs(c, best_k);
+  out->path = best_k.path;
+  out->group_cap = best_k.group_cap;
+  out->sort_items = best_k.sort_items;
+  out->batch_tile = best_k.tile;
+  out->group_bits = best_k.group_bits;
+  out->pair_sort = best_k.pair_sort;
+  out->group_shape = best_k.group_shape;
+  out->batch_graph = best_k.batch_graph;
   out->best_s = best;
   if (!c->tune_cache.empty()) {
     cache[key] = to_entry(best_k);
+    if (kept) cache[key]["kept"] = 1;
     write_cache(c->tune_cache, cache);
   }
 }
