@@ -42,9 +42,11 @@ HBM_PEAK_GBS = 8000.0
 # are a stored profile, not a measurement of this run: TRAFFIC_SOURCE names it.
 # (both hash passes run over the same fixed tiles, so the counters give one
 # mean over their 14 dispatches)
-TRAFFIC_PER_LAUNCH = {("plain_1m_k2", "hash_counted_pass"): 1.6594e9,
+TRAFFIC_PER_LAUNCH = {("plain_1m_k2", "vargen_part"): 1.1152e9,
+                      ("plain_1m_k2", "hash_counted_pass"): 1.6594e9,
                       ("plain_1m_k2", "hash_passes"): 1.6594e9}
-TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of k_scatter_counted, "
+TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE: k_gen_part in "
+                  "profiles/binned_path_plain_1m_k2.md, k_scatter_counted in "
                   "profiles/traffic_hashed_path_plain_1m_k2.md (kernel and tiles unchanged since)")
 # method floor of the end-to-end fraction: every deletion variant written once,
 # read and written by one grouping pass and read once more (20-byte key records)
