@@ -14,7 +14,7 @@ namespace sd {
 namespace {
 
 // Bins for an expected number of candidates. A bin's hash set lies in LDS:
-// 2,048 slots for a mean of up to 768 candidates; from 8M candidates on, and
+// 2,048 slots for a mean of up to 768 candidates; from 2^20 candidates on, and
 // with three deletions (a pair can repeat 2,325 times), 8,192 slots for a mean
 // of up to 4,096. Regions hold the mean, a quarter more and room for its
 // deviation: bins are as even as the pair hash, but a pair comes with all its
@@ -22,10 +22,12 @@ namespace {
 // is taken as 32 times the mean). spread > 0, after a bin overflowed all the
 // same: half as many candidates per bin each time, and whole hash sets.
 //
-// Few candidates go straight to their bins. From 8M on, the scattered 8-byte
-// writes would leave the L2 as partial lines (85M candidates into 2^15 bins
-// from the grouping kernel: 2.2 ms); they are appended to one list per XCD and
-// split in two levels instead, a coalesced read and write each (0.65 ms). A
+// Few candidates go straight to their bins. More would leave the L2 as partial
+// lines, ten times their bytes at 4M (85M candidates into 2^15 bins from the
+// grouping kernel: 2.2 ms); they are appended to one list per XCD and split in
+// two levels instead, a coalesced read and write each (0.65 ms). Whole searches,
+// straight / split: 1.3M candidates 0.51 / 0.49 ms, 3.6M 1.10 / 1.04, 1.3M of
+// weighted queries 1.41 / 1.24; below 1M the two launches cost what they save. A
 // list may get more than its share, since all pairs of a group of equal
 // variants come from one XCD: with spread it is twice as long each time.
 struct Shape {
@@ -55,7 +57,7 @@ ZeroRange cursors(const PairBins& b) { return {b.cursor, (uint64_t)b.nbins << b.
 
 Shape shape(Scratch& sc, uint64_t guess, int k, int spread) {
   Shape sh;
-  sh.split = guess >= (8ull << 20);
+  sh.split = guess >= (1ull << 20);
   sh.wide = sh.split || k >= 3;
   const uint64_t mean_max = (sh.wide ? 4096u : 768u) >> spread;
   int lb = 6;
