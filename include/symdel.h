@@ -79,13 +79,14 @@ typedef struct {
 #define SD_MAX_STAGES 16
 typedef struct {
   int64_t n_seqs;         /* sequences searched */
-  int64_t n_keys;         /* deletion variants generated (with multiplicity) */
+  int64_t n_keys;         /* deletion variants generated (distinct per sequence where the path
+                             generates each once, else with multiplicity) */
   int64_t n_cand_raw;     /* candidate pairs emitted inside groups (with multiplicity) */
   int64_t n_cand_unique;  /* distinct candidate pairs */
   int64_t n_pairs;        /* pairs returned */
   int32_t n_stages;       /* valid entries below (0 unless SD_OPT_TIMING is on) */
-  int32_t n_sort_passes;  /* radix passes run by the grouping sort */
-  int64_t n_big_segments; /* hashed path: ranges neither grouping kernel could hold in LDS,
+  int32_t n_sort_passes;  /* radix passes run by the grouping sort (0: variants generated into bins) */
+  int64_t n_big_segments; /* hashed paths: ranges the grouping kernels could not hold in LDS,
                              grouped by a sort on the full hash instead */
   int64_t n_probe_steps;  /* learned indexes: comparisons made by the lookups' searches */
   int64_t n_stream_groups; /* streamed self search: column groups processed (0: in memory) */
@@ -103,17 +104,20 @@ typedef struct {
 
 /* Options for sd_set_option. */
 #define SD_OPT_TIMING 1  /* 1: record per-stage HIP events (adds no host synchronisation) */
-#define SD_OPT_PATH 2       /* grouping path: 0 = automatic, 1 = full-key LSD sort, 2 = hashed segments */
+#define SD_OPT_PATH 2       /* grouping path: 0 = automatic (variants generated into hash bins, unless
+                               one of SD_OPT_GROUP_CAP, _BITS, _BATCHES and _SHAPE, SD_OPT_SORT_ITEMS
+                               or SD_OPT_PAIR_SORT is set), 1 = full-key LSD sort, 2 = hashed segments */
 #define SD_OPT_GROUP_CAP 3  /* hashed path: LDS batch capacity, 0 (automatic), 256, 1024, 2048 or 4096 */
 #define SD_OPT_GROUP_BITS 4 /* hashed path: hash bits sorted by LSD passes, 0 (automatic) .. 23 */
-#define SD_OPT_SORT_ITEMS 5 /* keys-only radix passes: items per thread, 0 (automatic), 16 or 32 */
+#define SD_OPT_SORT_ITEMS 5 /* keys-only radix passes: items per thread, 0 (automatic), 16 or 32; not 0
+                               chooses the paths with such passes (searches, queries, index builds) */
 #define SD_OPT_BATCH_TILE 6 /* query batches: at most this many query sequences per tile (0: 4Mi) */
 #define SD_OPT_PROBE 7      /* learned indexes: 0 = search the model's window, 1 = binary search over the whole index */
 #define SD_OPT_GROUP_BATCHES 8 /* hashed path: LDS batches each workgroup groups in sequence, 0 (automatic: 4) .. 64 */
-#define SD_OPT_PAIR_SORT 9  /* candidate pair sort of self searches: 0 automatic (buckets by the
-                               top bits of i, each sorted and verified in LDS, up to 2^22
-                               sequences; else global passes), 1 one-sweep LSD passes,
-                               2 counted LSD passes */
+#define SD_OPT_PAIR_SORT 9  /* candidate pair sort: 0 automatic (candidates in bins by a hash of the
+                               pair, repeats dropped in LDS; only kept pairs are ordered), 1
+                               one-sweep LSD passes, 2 counted LSD passes (1 and 2 choose the
+                               paths that sort their candidates) */
 #define SD_OPT_METRIC 10    /* distance of the final filter of every search on the context:
                                SD_METRIC_LEVENSHTEIN (default) or SD_METRIC_HAMMING */
 #define SD_OPT_STREAM 11    /* self search in column groups of hash bins (bounded memory):
@@ -122,8 +126,9 @@ typedef struct {
 #define SD_OPT_JOIN_ELEMS 15 /* query tiles (eager): query elements a join segment aims at; a
                                 tile with fewer than that per index segment joins over coarser
                                 segments (unions of index segments); 0 = automatic (the cube
-                                root of the tile's element count, at least 64), 1 keeps the
-                                index's own segments for any tile */
+                                root of the tile's element count, at least 64, on the path
+                                with join segments; most tiles look their variants up or are
+                                joined by bins), 1 keeps the index's own segments for any tile */
 #define SD_OPT_BATCH_GRAPH 14 /* sd_query_batch as one captured HIP graph: 0 off (tiles with host
                                  synchronisations), 1 on (capture once per batch shape, then replay) */
 #define SD_OPT_GROUP_SHAPE 13 /* hashed path grouping kernel at LDS capacity 2048: 0 (256 threads,

@@ -463,7 +463,7 @@ struct Error {
 
 namespace sd {
 // Device blocks of freed indexes, kept for the next index of the context that
-// built them: memory given back to the driver is cleared before it can be
+// built them: memory given back to the system is cleared before it can be
 // handed out again, at about 35 GB/s, so a program that rebuilds an index over
 // and over waits for that once the card's clean memory is used up (2M
 // sequences, 1.6 GB: 45 ms a build, whatever the build takes). It keeps at most
