@@ -1142,7 +1142,7 @@ __global__ __launch_bounds__(256) void k_gen_probe(const u128* __restrict__ seq,
 // passes over the queries.
 constexpr int JB_SB = 18;                      // query bitmap, bits (32 KiB)
 constexpr int JB_TB = 15;                      // mark bitmap, bits
-constexpr uint32_t JB_CAP = 4608;              // index survivors in LDS
+constexpr uint32_t JB_CAP = 5056;              // index survivors in LDS (two workgroups on a CU)
 constexpr uint32_t JB_QCAP = (1u << JB_SB) / 64;  // query survivors
 constexpr int JB_NBK = 1024;
 constexpr size_t JB_LDS = (1 << JB_SB) / 8 + (1 << JB_TB) / 8 + JB_CAP * 8 + JB_NBK * 4;

@@ -358,8 +358,11 @@ void launch_pair_scatter(const uint64_t* cand, uint64_t n, const PairBins& o, hi
 void launch_gen_probe(const u128* seq, uint64_t n, int k, const uint64_t* E, uint32_t nkeys,
                       const uint32_t* seg_start, const uint32_t* seg_end, int bits, uint32_t idbits,
                       const PairBins& out, hipStream_t s);
-// most query elements and (expected) index survivors a join workgroup takes well
-constexpr double JOIN_QUERY_MAX = 20000, JOIN_SURVIVORS = 2600, JOIN_BITMAP = 1 << 18;
+// most query elements and (expected) index survivors a join workgroup takes well:
+// LDS has room for 5,056, and more workgroups per bin read its query elements more
+// often (71M query elements against 500M: 1.05 ms with two for a bin, 1.25 with
+// the four that 2,600 asked for)
+constexpr double JOIN_QUERY_MAX = 20000, JOIN_SURVIVORS = 3900, JOIN_BITMAP = 1 << 18;
 void launch_join_bins(const PartOut& in, const uint64_t* E, const uint32_t* seg_start,
                       const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
                       const PairBins& out, hipStream_t s);
