@@ -230,7 +230,12 @@ void index_release(sd_index* idx, void* const* p, int n) {
     return;
   }
   for (int x = 0; x < m; ++x) size[x] = idx->sizes[own[x]];
-  if (idx->pool && hipDeviceSynchronize() == hipSuccess && idx->pool->put(own, size, m)) return;
+  if (idx->pool) {
+    if (hipDeviceSynchronize() != hipSuccess)
+      (void)hipGetLastError();
+    else if (idx->pool->put(own, size, m))
+      return;
+  }
   for (int x = 0; x < m; ++x) (void)hipFree(own[x]);
 }
 

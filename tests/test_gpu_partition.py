@@ -294,3 +294,30 @@ def test_unaligned_codes(paths, n, shift):
         assert len(a) == len(b)
         for x, y in zip(a.numpy(), b.numpy()):
             assert np.array_equal(x, y)
+
+
+# blocks of freed indexes serve the next ones: sizes that fit, nearly fit and do
+# not, two indexes at a time, and one that outlives its context
+@pytest.mark.parametrize("sizes", [(40_000, 40_100, 39_000), (60_000, 500, 60_000), (1, 30_000, 1)])
+def test_index_memory_kept(sizes):
+    from paper_2403_09010_amd import Context
+    ctx, fresh = Context(0), Context(0)
+    for n in sizes:
+        ref = cdr3gen.generate(31, n)
+        q = cdr3gen.generate_query(5, 2_000, *ref, ref_mut_frac=0.6)
+        a, b = ctx.build_index(*ref, 2), ctx.build_index(*ref, 1)
+        c = fresh.build_index(*ref, 2)
+        assert a.info() == c.info()
+        x, y = ctx.query(a, *q, 2), fresh.query(c, *q, 2)
+        assert np.array_equal(x.i, y.i) and np.array_equal(x.j, y.j) and np.array_equal(x.d, y.d)
+        a.free()
+        z = ctx.query(b, *q, 1)
+        keep = y.d <= 1
+        assert np.array_equal(z.i, y.i[keep]) and np.array_equal(z.j, y.j[keep])
+        b.free()
+    ctx.close()
+    x = fresh.query(c, *q, 2)
+    assert np.array_equal(x.i, y.i) and np.array_equal(x.j, y.j)
+    last = fresh
+    last.close()
+    c.free()
