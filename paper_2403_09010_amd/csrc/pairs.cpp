@@ -185,6 +185,8 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
       oj = res.get<uint32_t>(kept);
       od = res.get<uint8_t>(kept);
       launch_pair_order(b, q.na, oi, oj, od, kept, cl.counters, s);
+      // (a call returns after its work)
+      hip_check(hipStreamSynchronize(s), "synchronise");
     }
     res.blocks.clear();
     out->i = oi;

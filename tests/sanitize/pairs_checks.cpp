@@ -1,0 +1,161 @@
+// The host side of the binned candidate pairs (csrc/pairs.cpp) on the CPU under
+// AddressSanitizer and UBSan, built by tests/test_pair_host.py. The launches
+// are counted and otherwise do nothing, device blocks come from malloc, and
+// each read-back answers with the next of a list of states: what the search
+// makes of them is checked. Exits 0 and prints "ok" when every check holds.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "sd_host.h"
+
+namespace {
+
+int pending = 0;  // launches since the stream was waited for
+std::vector<sd::PairState> answers;
+size_t answered = 0;
+std::vector<std::string> log_;  // launches, in order
+
+void launched(const char* what) {
+  ++pending;
+  log_.push_back(what);
+}
+int launches(const char* what) {
+  int n = 0;
+  for (const auto& x : log_) n += x == what;
+  return n;
+}
+
+}  // namespace
+
+namespace sd {
+void* dalloc(sd_ctx*, size_t bytes) { return std::malloc(bytes < 4096 ? bytes : 4096); }
+void dfree(sd_ctx*, void* p) { std::free(p); }
+void hip_check(hipError_t e, const char* what) {
+  if (e != hipSuccess) throw Error{SD_E_HIP, what};
+}
+void* readback(sd_ctx*, const void*, size_t bytes, hipStream_t) {
+  pending = 0;
+  if (answered >= answers.size()) throw Error{SD_E_STATE, "one read-back too many"};
+  if (bytes != sizeof(PairState)) throw Error{SD_E_STATE, "a read-back of another size"};
+  return &answers[answered++];
+}
+StageTimer::StageTimer(sd_ctx* ctx, hipStream_t st) : c(ctx), s(st), on(false) {}
+void StageTimer::mark(const char*, double, int) {}
+void launch_zero(std::initializer_list<ZeroRange>, hipStream_t) { launched("zero"); }
+void launch_fill_u32(uint32_t*, uint32_t, uint64_t, hipStream_t) { launched("fill"); }
+void launch_pair_split(const PairBins&, const PairBins&, PairState*, hipStream_t) {
+  launched("split");
+}
+uint32_t pair_bin_max(bool large) { return (large ? 8192u : 2048u) / 8 * 7; }
+void launch_pair_verify(const PairBins&, bool, const PairSeqs&, const PairBufs&, hipStream_t) {
+  launched("verify");
+}
+uint64_t pair_tiles(uint64_t na) { return (na + 4095) / 4096; }
+void launch_pair_scan(const PairBufs&, uint64_t, hipStream_t) { launched("scan"); }
+void launch_pair_place(const PairBins&, const PairBufs&, hipStream_t) { launched("place"); }
+void launch_pair_order(const PairBufs&, uint64_t, uint32_t*, uint32_t*, uint8_t*, uint64_t,
+                       const uint32_t*, hipStream_t) {
+  launched("order");
+}
+}  // namespace sd
+
+extern "C" {
+hipError_t hipStreamSynchronize(hipStream_t) {
+  pending = 0;
+  return hipSuccess;
+}
+}
+
+namespace {
+
+int failures = 0;
+void check(bool ok, const char* what) {
+  std::printf("%-66s %s\n", what, ok ? "ok" : "FAILED");
+  failures += !ok;
+}
+
+// a read-back: pairs kept, candidates put, flags, the call's error word
+sd::PairState answer(uint64_t kept, uint64_t raw, uint32_t flags = 0, uint32_t err = 0) {
+  sd::PairState s;
+  std::memset(&s, 0, sizeof(s));
+  s.count = kept;
+  s.flags = flags;
+  s.raw[3] = raw / 2;
+  s.raw[40] = raw - raw / 2;
+  s.counters[sd::CNT_LBERR] = err;
+  return s;
+}
+
+struct Outcome {
+  bool found = false;
+  int code = SD_OK;
+  sd::TileOut out;
+  int produced = 0, checked = 0;
+};
+
+// one search of nkeys variants, k = 2, answered by `a` in turn; `next` is what
+// its check says each time (done when it has run out)
+Outcome search(uint64_t nkeys, std::vector<sd::PairState> a,
+               std::vector<sd::PairNext> next = {}, sd_ctx* ctx = nullptr) {
+  static sd_ctx fresh;
+  sd_ctx* c = ctx ? ctx : &fresh;
+  if (!ctx) c->out_hint.clear();
+  answers = std::move(a);
+  answered = 0;
+  log_.clear();
+  pending = 0;
+  Outcome o;
+  uint32_t counters[sd::CNT_TOTAL] = {};
+  sd::Scratch sc(c);
+  sd::StageTimer tm(c, nullptr);
+  sd::Call cl{c, nullptr, sc, tm, counters};
+  const sd::PairSeqs q{nullptr, nullptr, nullptr, 1000, 1000, 2, 4, 1, nullptr, 0, 0};
+  try {
+    o.found = sd::binned_pairs(
+        cl, "pairs/test", nkeys, q,
+        [&](const sd::PairBins&) {
+          ++o.produced;
+          launched("produce");
+        },
+        [&](const uint32_t*, uint64_t*) {
+          const size_t x = (size_t)o.checked++;
+          return x < next.size() ? next[x] : sd::PairNext::done;
+        },
+        [&](uint64_t*, uint64_t m) {
+          sd::TileOut t;
+          t.n = m;
+          return t;
+        },
+        "group", &o.out);
+  } catch (const sd::Error& e) {
+    o.code = e.code;
+  }
+  if (o.found) {
+    for (void* p : {(void*)o.out.i, (void*)o.out.j, (void*)o.out.d}) sd::dfree(c, p);
+  }
+  return o;
+}
+
+}  // namespace
+
+int main() {
+  {
+    const Outcome o = search(100000, {answer(500, 3000)});
+    check(o.found && o.out.n == 500 && o.out.ncand == 3000 && o.produced == 1 && pending == 0,
+          "a search that fits runs once");
+  }
+  {
+    // 100,000 / 22 + 1,024 candidates were expected: the bins held the 9,000 that
+    // came, the result arrays did not
+    const Outcome o = search(100000, {answer(9000, 9000)});
+    check(o.found && o.out.n == 9000 && launches("order") == 2, "larger result arrays: ordered again");
+    check(pending == 0, "larger result arrays: nothing in flight at the return");
+  }
+  std::printf(failures ? "%d checks failed\n" : "ok\n", failures);
+  return failures ? 1 : 0;
+}

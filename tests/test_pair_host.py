@@ -1,0 +1,20 @@
+"""The host side of the binned candidate pairs (csrc/pairs.cpp) on the CPU under
+AddressSanitizer and UBSan, with launches that are only counted and scripted
+read-backs (tests/sanitize/pairs_checks.cpp)."""
+import os
+import shutil
+
+import pytest
+
+from test_sanitizers import ROOT, build_and_run
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="needs g++ and the ROCm headers")
+def test_pair_host(tmp_path):
+    csrc = os.path.join(ROOT, "paper_2403_09010_amd", "csrc")
+    build_and_run(tmp_path, "pairs_checks",
+                  [os.path.join(csrc, "pairs.cpp"),
+                   os.path.join(ROOT, "tests", "sanitize", "pairs_checks.cpp")],
+                  ["-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                   "-I" + os.path.join(ROOT, "include"), "-I" + csrc])
