@@ -21,6 +21,19 @@ __device__ __forceinline__ uint32_t pair_hash_below(uint64_t v, int lb, int bits
   return (uint32_t)(pair_hash(v) >> (64 - lb - bits)) & ((1u << bits) - 1);
 }
 
+// The place of n candidates in list x (taken by one lane).
+__device__ __forceinline__ unsigned long long list_reserve(const sd::PairBins& o, uint32_t x,
+                                                           uint32_t n) {
+  return atomicAdd(&o.lists[x * sd::PAIR_LIST_STRIDE], (unsigned long long)n);
+}
+
+// The first active lane's value.
+__device__ __forceinline__ unsigned long long first_lane(unsigned long long v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (unsigned long long)hi << 32 | lo;
+}
+
 // Adds a candidate to its bin (or, with lb = 0, to its XCD's list, one
 // reservation for the active lanes); one that finds its region full is only
 // counted.
@@ -30,10 +43,11 @@ __device__ __forceinline__ void pair_put(const sd::PairBins& o, uint64_t v) {
   const uint32_t x = o.nxl ? blockIdx.x & 7u : 0u;
   if (o.lb == 0) {
     const uint64_t act = __ballot(true);
-    uint32_t at = 0;
-    if (mask_rank(act) == 0) at = atomicAdd(&o.cursor[x], (uint32_t)__popcll(act));
-    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + mask_rank(act);
-    if (at < o.region) o.base[(uint64_t)x * o.region + at] = v;
+    const uint32_t n = (uint32_t)__popcll(act), rank = mask_rank(act);
+    unsigned long long at = 0;
+    if (rank == 0) at = list_reserve(o, x, n);
+    at = first_lane(at);
+    if (rank < sd::list_room(at, n, o.region)) o.base[(uint64_t)x * o.region + at + rank] = v;
     return;
   }
   const uint32_t b = (uint32_t)(pair_hash(v) >> (64 - o.lb));

@@ -49,11 +49,17 @@ PairBins level(Scratch& sc, uint64_t guess, int lb, int nxl, double var, uint32_
   const double mean = (double)guess / (double)nc;
   b.region =
       (uint32_t)std::min<double>(most, mean * 1.25 + 6.0 * std::sqrt(var * mean) + 32);
-  b.cursor = sc.get<uint32_t>(nc);
+  if (lb)
+    b.cursor = sc.get<uint32_t>(nc);
+  else
+    b.lists = sc.get<unsigned long long>((uint64_t)PAIR_LIST_STRIDE << nxl);
   return b;
 }
 
-ZeroRange cursors(const PairBins& b) { return {b.cursor, (uint64_t)b.nbins << b.nxl}; }
+ZeroRange cursors(const PairBins& b) {
+  if (b.lists) return {reinterpret_cast<uint32_t*>(b.lists), (uint64_t)(2 * PAIR_LIST_STRIDE) << b.nxl};
+  return {b.cursor, (uint64_t)b.nbins << b.nxl};
+}
 
 Shape shape(Scratch& sc, uint64_t guess, int k, int spread) {
   Shape sh;
@@ -156,10 +162,11 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
       launch_fill_u32(cl.lb_err(), 0, 1, s);
     else if (st.counters[CNT_LBERR] & SD_ERRBIT_INDEX)
       throw Error{SD_E_HIP, "internal error: a candidate id out of range"};
+    // more candidates than a search answers, or than it would without the repeats
+    // of a bin that was grouped twice: the path that counts them once decides
+    if (raw >= 0xFFFFFFFFull) return false;
     const PairNext next = check(st.counters, &more);
-    if (next == PairNext::give_up) return false;
-    if (raw + more >= 0xFFFFFFFFull)
-      throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 candidate pairs"};
+    if (next == PairNext::give_up || raw + more >= 0xFFFFFFFFull) return false;
     if (overflow || next == PairNext::again) {
       // more room: what was counted and what comes; where the room was there
       // but pairs have very many repeats, fewer of them per bin

@@ -50,12 +50,13 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
   const uint32_t sub = tiles < 64 ? blockIdx.x % nsub : blockIdx.x / tiles;
   const uint32_t tile = tiles < 64 ? blockIdx.x / nsub : blockIdx.x - sub * tiles;
   const uint32_t bin = sub >> in.nxl, x = in.nxl ? sub & 7u : 0u;
-  const uint32_t put = in.cursor[x * in.nbins + bin];
+  const unsigned long long put =
+      in.lists ? in.lists[x * sd::PAIR_LIST_STRIDE] : in.cursor[x * in.nbins + bin];
   if (put > in.region && tile == 0 && threadIdx.x == 0) {
     atomicOr(&state->flags, sd::PF_OVERFLOW);
-    atomicAdd(&state->raw[sub % sd::PACK_SUMS], (unsigned long long)(put - in.region));
+    atomicAdd(&state->raw[sub % sd::PACK_SUMS], put - in.region);
   }
-  const uint32_t c = min(put, in.region), t0 = tile * TILE;
+  const uint32_t c = (uint32_t)min(put, (unsigned long long)in.region), t0 = tile * TILE;
   if (t0 >= c) return;
   const uint32_t m = min((uint32_t)TILE, c - t0);
   const uint64_t* __restrict__ src = in.base + (uint64_t)((bin << in.nxl) + x) * in.region + t0;

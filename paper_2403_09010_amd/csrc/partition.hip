@@ -647,6 +647,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
   uint32_t* s_bk = reinterpret_cast<uint32_t*>(lds + F::BK_AT);
   __shared__ uint32_t s_n, s_np;
+  __shared__ unsigned long long s_at;
   __shared__ uint32_t s_tmp[NT / 64];
   const uint32_t bin = blockIdx.x, nx = 1u << in.nxl;
   const uint32_t lane = threadIdx.x & 63u;
@@ -850,12 +851,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
       // its write)
       uint32_t cnt = 0, tot;
       each_pair([&](uint64_t) { ++cnt; });
-      uint32_t at = block_excl_scan<NT>(cnt, s_tmp, &tot);
+      unsigned long long at = block_excl_scan<NT>(cnt, s_tmp, &tot);
       const uint32_t x = blockIdx.x & ((1u << out.nxl) - 1);
-      if (threadIdx.x == 0 && tot) s_np = atomicAdd(&out.cursor[x], tot);
+      if (threadIdx.x == 0 && tot) s_at = list_reserve(out, x, tot);
       __syncthreads();
       if (cnt) {
-        at += s_np;
+        at += s_at;
         uint64_t* dst = out.base + (uint64_t)x * out.region;
         each_pair([&](uint64_t v) {
           if (at < out.region) dst[at] = v;
@@ -1161,6 +1162,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   uint64_t* s_e = reinterpret_cast<uint64_t*>(s_br + (1 << JB_TB) / 32);
   uint32_t* s_bk = reinterpret_cast<uint32_t*>(s_e + JB_CAP);
   __shared__ uint32_t s_n, s_nq;
+  __shared__ unsigned long long s_at;
   __shared__ uint32_t s_tmp[NW];
   // the workgroups of a query bin follow each other on one XCD, whose L2 then
   // has the bin's elements
@@ -1387,12 +1389,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     if (out.lb == 0) {  // a list per XCD, one reservation (see k_filter_group)
       uint32_t cnt = 0, tot;
       each_pair([&](uint64_t) { ++cnt; });
-      uint32_t at = block_excl_scan<NT>(cnt, s_tmp, &tot);
+      unsigned long long at = block_excl_scan<NT>(cnt, s_tmp, &tot);
       const uint32_t x = blockIdx.x & ((1u << out.nxl) - 1);
-      if (threadIdx.x == 0 && tot) s_n = atomicAdd(&out.cursor[x], tot);
+      if (threadIdx.x == 0 && tot) s_at = list_reserve(out, x, tot);
       __syncthreads();
       if (cnt) {
-        at += s_n;
+        at += s_at;
         uint64_t* dst = out.base + (uint64_t)x * out.region;
         each_pair([&](uint64_t v) {
           if (at < out.region) dst[at] = v;

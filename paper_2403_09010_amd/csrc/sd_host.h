@@ -345,8 +345,8 @@ enum class PairNext {
   give_up   // the search takes another path
 };
 struct TileOut;
-// Returns false if check gave up, or if no shape of the bins held the
-// candidates. out: pairs sorted by (i, j), in pool blocks. sort_pairs orders a
+// Returns false if check gave up, if there were 2^32 - 1 candidates or more, or
+// if no shape of the bins held them. out: pairs sorted by (i, j), in pool blocks. sort_pairs orders a
 // dense array of distinct verified pairs instead, where one first id has
 // thousands of them.
 bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, const PairSeqs& q,

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/symdel.h"
+#include "pair_list.h"
 
 typedef unsigned __int128 u128;
 
@@ -286,12 +287,13 @@ void launch_part_split(const PartOut& in, const PartOut& o, hipStream_t s);
 // (pair_put.h): bin b's lie in 2^nxl regions of `region` slots from
 // base[(b << nxl) * region]; region x of it received cursor[x * nbins + b] of
 // them (those past the region are lost and counted). lb = 0: plain lists, one
-// per region.
+// per region, counted in lists (pair_list.h) instead.
 struct PairBins {
   uint64_t* base;
   uint32_t* cursor;  // nbins << nxl, zeroed before the producer
   uint32_t region, nbins;
   int lb, nxl;
+  unsigned long long* lists = nullptr;  // PAIR_LIST_STRIDE << nxl, zeroed too
 };
 // Verification of binned candidates (pairs.hip). mode 0: Levenshtein distance
 // of a = bit planes of the first sequences and b = packed keys of the second;

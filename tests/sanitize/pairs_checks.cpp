@@ -156,6 +156,23 @@ int main() {
     check(o.found && o.out.n == 9000 && launches("order") == 2, "larger result arrays: ordered again");
     check(pending == 0, "larger result arrays: nothing in flight at the return");
   }
+  {
+    // a list keeps what it has room for, however many it was sent
+    constexpr uint64_t past = (1ull << 32) + 5;
+    static_assert(sd::list_room(0, 10, 100) == 10 && sd::list_room(95, 10, 100) == 5 &&
+                      sd::list_room(100, 10, 100) == 0 && sd::list_room(past, 10, 100) == 0 &&
+                      sd::list_room(past, 10, ~0u) == 0 && sd::list_room(~0u - 3ull, 10, ~0u) == 3,
+                  "places past a list's room");
+    static_assert(sizeof(*sd::PairBins{}.lists) == 8, "64-bit counts");
+    const uint64_t limit = 0xFFFFFFFFull;
+    Outcome o = search(100000000, {answer(0, limit, sd::PF_OVERFLOW)});
+    check(!o.found && o.code == SD_OK && o.produced == 1 && o.checked == 0,
+          "2^32 - 1 candidates: left to the path that counts each once");
+    o = search(100000000, {answer(0, (9ull << 32) + 77, sd::PF_OVERFLOW)});
+    check(!o.found && o.code == SD_OK && o.produced == 1, "far more than 2^32 candidates: the same");
+    o = search(100000000, {answer(0, limit - 1, sd::PF_OVERFLOW)});
+    check(!o.found && o.code == SD_OK && o.checked == 1, "one less: no shape of the bins holds them");
+  }
   std::printf(failures ? "%d checks failed\n" : "ok\n", failures);
   return failures ? 1 : 0;
 }
