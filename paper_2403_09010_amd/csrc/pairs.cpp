@@ -158,9 +158,13 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     for (uint64_t x : st.raw) raw += x;
     const uint64_t kept = st.count;
     const bool overflow = st.flags & PF_OVERFLOW;
-    if (overflow)  // (a split reads slots that lost candidates never filled)
+    // (the sorts of `check` report here too, in the read-back after them)
+    const uint32_t err = st.counters[CNT_LBERR];
+    if (err & SD_ERRBIT_LOOKBACK) throw Error{SD_E_HIP, "internal error: a look-back wait timed out"};
+    if (err & SD_ERRBIT_PLACEMENT) throw Error{SD_E_HIP, "internal error: a counted pass misplaced"};
+    if (overflow)  // (a split reads slots that lost candidates never filled: ids out of range)
       launch_fill_u32(cl.lb_err(), 0, 1, s);
-    else if (st.counters[CNT_LBERR] & SD_ERRBIT_INDEX)
+    else if (err & SD_ERRBIT_INDEX)
       throw Error{SD_E_HIP, "internal error: a candidate id out of range"};
     // more candidates than a search answers, or than it would without the repeats
     // of a bin that was grouped twice: the path that counts them once decides

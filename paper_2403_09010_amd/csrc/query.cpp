@@ -462,6 +462,8 @@ uint64_t sorted_bins(Call& cl0, const u128* seq, const uint32_t* vcnt, uint64_t 
     const uint32_t* h = static_cast<const uint32_t*>(readback(c, cl.counters, CNT_TOTAL * 4, s));
     if (h[CNT_LBERR] & SD_ERRBIT_LOOKBACK)
       throw Error{SD_E_HIP, "internal error: a look-back wait timed out"};
+    if (h[CNT_LBERR] & SD_ERRBIT_PLACEMENT)
+      throw Error{SD_E_HIP, "internal error: a counted pass misplaced"};
     return h;
   };
   const uint32_t* h = counters();

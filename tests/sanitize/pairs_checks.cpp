@@ -173,6 +173,17 @@ int main() {
     o = search(100000000, {answer(0, limit - 1, sd::PF_OVERFLOW)});
     check(!o.found && o.code == SD_OK && o.checked == 1, "one less: no shape of the bins holds them");
   }
+  for (const uint32_t bit : {SD_ERRBIT_LOOKBACK, SD_ERRBIT_PLACEMENT, SD_ERRBIT_INDEX}) {
+    // an error of the sorts that `check` ran shows in the read-back after them
+    Outcome o = search(100000, {answer(5, 3000), answer(5, 3500, 0, bit)}, {sd::PairNext::again});
+    check(!o.found && o.code == SD_E_HIP && o.produced == 2, "an error bit fails the search");
+    // only ids out of range are what an overflow leaves behind
+    o = search(100000, {answer(5, 30000, sd::PF_OVERFLOW, bit), answer(5, 30000)});
+    if (bit == SD_ERRBIT_INDEX)
+      check(o.found && o.produced == 2 && launches("fill") == 1, "an overflow's ids are forgotten");
+    else
+      check(!o.found && o.code == SD_E_HIP && o.produced == 1, "an error bit beside an overflow too");
+  }
   std::printf(failures ? "%d checks failed\n" : "ok\n", failures);
   return failures ? 1 : 0;
 }
