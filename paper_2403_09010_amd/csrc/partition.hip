@@ -1182,7 +1182,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   // the segment's query elements: f(rows, whether each lane has one)
   auto queries = [&](auto&& f) {
     for (uint32_t x = w & (nx - 1); x < nx; x += NW) {
-      const uint32_t c = min(in.cursor[x * in.nbins + bin], in.region);
+      const uint32_t cu = x * in.nbins + bin;
+      uint32_t c = in.cursor[cu];
+      if (c > in.region) c = in.fill[cu];
       const uint64_t* __restrict__ p = in.elem + base + (uint64_t)x * in.region;
       for (uint32_t t0 = (w >> in.nxl) * ROW; t0 < c; t0 += parts * ROW) {
         uint64_t e[FG_ROWS];

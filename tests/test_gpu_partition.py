@@ -321,3 +321,22 @@ def test_index_memory_kept(sizes):
     last = fresh
     last.close()
     c.free()
+
+
+def test_query_copies_after_a_larger_set(query_paths):
+    # copies overflow their bins' regions; the slots that a cut run leaves behind
+    # hold elements of the larger set before, whose last ids the smaller one has not
+    rng = np.random.default_rng(41)
+    pick = [bytes(x) for x in rng.integers(0, 20, (80_000, 11)).astype(np.uint8)]
+    long = bytes(rng.permutation(20).astype(np.uint8)) + b"\1\5\3\7"
+    ctx = query_paths[0]
+    idx = ctx.build_index(*csr(pick[60_000:] + [long]), 2)
+    large = csr(pick[:60_000] + [long] * 5_000)
+    small = csr([long] * 5_000 + pick[:59_000])
+    want = query_paths[1].query(idx, *small, 2)
+    for turn in range(4):
+        print(f"[partition] copies after a larger set, turn {turn}", flush=True)
+        ctx.query(idx, *large, 2)
+        got = ctx.query(idx, *small, 2)
+        assert np.array_equal(got.i, want.i) and np.array_equal(got.j, want.j)
+    idx.free()
