@@ -279,9 +279,6 @@ __device__ __forceinline__ void gen_step(SeqLane key, uint32_t id0, bool two, ui
   __builtin_amdgcn_wave_barrier();
 }
 
-// most bins (log2) that a workgroup's threads reserve runs of
-constexpr int tile_max_lb(int threads) { return threads >= 1024 ? sd::PART_MAX_LB : 11; }
-
 // gen_step over a block's sequences, into an LDS tile that partition_tail
 // orders and writes.
 //
@@ -357,7 +354,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
     __syncthreads();
     const int shift = 64 - o.lb;
-    partition_tail<NT, TILE, tile_max_lb(NT), false>(
+    partition_tail<NT, TILE, sd::tile_max_lb(NT), false>(
         s_e, s_pref[xb] - p0, s_cnt, s_tmp, o.lb,
         [&](uint64_t v) { return (uint32_t)(v >> shift); }, 0, o.elem, o.cursor, o.region, o.nbins,
         o.nxl, o.slots, o.fill, o.cap, o.over_count);
@@ -537,7 +534,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
     __syncthreads();
     const int shift = 64 - o.lb;
-    partition_tail<NT, TILE, tile_max_lb(NT), false>(
+    partition_tail<NT, TILE, sd::tile_max_lb(NT), false>(
         s_e, s_pref[xb] - p0, s_cnt, s_tmp, o.lb,
         [&](uint64_t v) { return (uint32_t)(v >> shift); }, 0, o.elem, o.cursor, o.region, o.nbins,
         o.nxl, o.slots, o.fill, o.cap, o.over_count);
@@ -737,7 +734,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   });
   __syncthreads();
   const uint64_t idmask = (1ull << idbits) - 1;
-  const int bkshift = 64 - in.lb - __builtin_ctz(F::NBK);  // bucket: the bits below the bin's
+  // bucket: the bits below the bin's; round: the next six
+  constexpr int NBKLOG = __builtin_ctz(F::NBK);
+  const int bkshift = sd::hash_shift(in.lb, NBKLOG, idbits);
+  const int rdshift = sd::hash_shift(in.lb, NBKLOG + 6, idbits);
   uint32_t rounds = 1;
   for (uint32_t round = 0; round < rounds; ++round) {
     stream(true, [&](const uint64_t(&e)[FG_ROWS], uint32_t left, auto full) {
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
       for (int u = 0; u < FG_ROWS; ++u) {
         const uint32_t need = marks(hash(e[u]));
         bool keep = (tw[u] & need) == need && (full || u * 64 + lane < left);
-        if (rounds > 1) keep = keep && ((uint32_t)(e[u] >> (bkshift - 6)) & (rounds - 1)) == round;
+        if (rounds > 1) keep = keep && ((uint32_t)(e[u] >> rdshift) & (rounds - 1)) == round;
         bal[u] = __ballot(keep);
         tot += (uint32_t)__popcll(bal[u]);
       }
@@ -1209,11 +1209,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   auto marks = [](uint32_t h) { return 1u << (h & 31u) | 1u << ((h >> 5) & 31u); };
   auto bq_word = [](uint32_t h) { return (h >> 5) & ((1u << (JB_SB - 5)) - 1); };
   const uint64_t idmask = (1ull << idbits) - 1;
-  const int bkshift = 64 - segbits - __builtin_ctz(JB_NBK);
+  constexpr int NBKLOG = __builtin_ctz(JB_NBK);
+  const int bkshift = sd::hash_shift(segbits, NBKLOG, idbits);
+  const int rdshift = sd::hash_shift(segbits, NBKLOG + 6, idbits);
   uint32_t rounds = 1;
   for (uint32_t round = 0; round < rounds; ++round) {
     auto mine = [&](uint64_t e) {
-      return rounds == 1 || ((uint32_t)(e >> (bkshift - 6)) & (rounds - 1)) == round;
+      return rounds == 1 || ((uint32_t)(e >> rdshift) & (rounds - 1)) == round;
     };
     for (uint32_t i = threadIdx.x; i < ((1 << JB_SB) + (1 << JB_TB)) / 32; i += NT) s_bq[i] = 0;
     if (threadIdx.x == 0) {
@@ -1431,7 +1433,7 @@ static size_t gen_lds(int lb) {
 template <int NT, int TILE>
 static void gen_t(const u128* seq, const uint32_t* vcnt, uint32_t n, int k, uint32_t idbits,
                   uint32_t spb, const PartOut& o, hipStream_t s) {
-  if (o.lb > sdk::tile_max_lb(NT)) throw Error{SD_E_HIP, "internal error: too many bins"};
+  if (o.lb > tile_max_lb(NT)) throw Error{SD_E_HIP, "internal error: too many bins"};
   const unsigned g = (n + spb - 1) / spb;
   if (k == 3) {
     const size_t lds = gen_lds<NT, TILE>(o.lb);
@@ -1478,7 +1480,7 @@ void launch_paired_distinct(const u128* pa, const u128* pb, uint64_t n, int k, u
 template <int NT, int TILE>
 static void gen_paired_t(const u128* sa, const u128* sb, const uint32_t* vcnt, uint32_t n, int k,
                          uint32_t idbits, uint32_t spb, const PartOut& o, hipStream_t s) {
-  if (o.lb > sdk::tile_max_lb(NT)) throw Error{SD_E_HIP, "internal error: too many bins"};
+  if (o.lb > tile_max_lb(NT)) throw Error{SD_E_HIP, "internal error: too many bins"};
   const size_t lds = (size_t)TILE * 8 + 96 * 8 + ((size_t)4 << o.lb) + (NT + 1) * 4 + NT / 64 * 4;
   allow_lds(&sdk::k_gen_part_paired<NT, TILE>, lds);
   hipLaunchKernelGGL((sdk::k_gen_part_paired<NT, TILE>), dim3((n + spb - 1) / spb), dim3(NT), lds,

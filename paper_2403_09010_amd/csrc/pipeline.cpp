@@ -289,17 +289,17 @@ bool partition_applies(const sd_ctx* c, uint64_t nk) {
 
 }  // namespace
 
-// Bins and regions of one partition level. Regions hold an eighth more than
-// their mean share (small inputs: twice it) and six standard deviations of
-// it: bins are even, since the hash is, unless single variants are shared by
-// thousands of sequences (such bins overflow and are grouped by a sort).
+// Bins and regions of one partition level. Bins are even, since the hash is,
+// unless single variants are shared by thousands of sequences (such bins
+// overflow their regions and are grouped by a sort).
 PartOut part_out(Call& cl, uint64_t nk, int lb, int nxl, uint64_t over_cap, uint32_t* over_count) {
   PartOut o{};
   o.lb = lb;
   o.nxl = nxl;
   o.nbins = 1u << lb;
-  const double mean = (double)nk / (double)((uint64_t)o.nbins << nxl);
-  o.region = ((uint32_t)(mean * (nxl ? 1.125 : 2.0) + 6.0 * std::sqrt(mean)) + 64 + 15) / 16 * 16;
+  if (!part_fits(nk, lb, nxl, over_cap))
+    throw Error{SD_E_HIP, "internal error: a partition's positions exceed 32 bits"};
+  o.region = (uint32_t)part_region(nk, lb, nxl);
   o.slots = (o.region * o.nbins) << nxl;
   o.cap = o.slots + (uint32_t)over_cap;
   o.elem = cl.sc.get<uint64_t>(o.cap);
@@ -491,21 +491,10 @@ Verified sort_and_verify(Call& cl, uint64_t* cand, uint64_t nc, uint64_t n, int 
 
 // Partitioned grouping: `generate` (given the regions and the id bits) writes
 // the nk variants of n sequences straight into bins of their top hash bits, and
-// one workgroup per bin filters and groups them.
+// one workgroup per bin filters and groups them (search_plan says which bins).
 // The id pairs go through the pair bins (pairs.cpp). Returns false if the input
 // has so many copies of single variants that even the overflow area was too
-// small (the sorted path then takes it).
-//
-// The bins. Small inputs take 2^8 bins of 512 elements or more, so that every
-// CU has one, and more bins only to keep them under 10K elements (what the
-// small bitmap filters well). Large inputs take bins of 26K to 51K elements:
-// with fewer a tile's runs get short (100M elements of 1M sequences: 0.52 ms
-// into 2^11 bins, 0.60 into 2^12), with more the filter lets too many through.
-// Beyond 2^12 bins of that size the partition takes a second level, into bins
-// a quarter as large since more bins cost little there (and their second read
-// comes from the L2): scattering 100M elements into 2^13 bins at once takes
-// 0.92 ms, two levels of 2^8 and 2^5 0.43 + 0.33; 1G elements group in 6.9 ms
-// in bins of 31K elements and in 2.6 in bins of 15K.
+// small, or no plan for it fits the kernels (the sorted path then takes it).
 //
 // nk may be an estimate; there are at most `most` variants. check sees the
 // call's counters as soon as they are read.
@@ -520,17 +509,10 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   Scratch sc(c);
   Call cl{c, s, sc, cl0.tm, cl0.counters};
   const uint32_t idbits = n <= (1ull << 24) ? 24u : 32u;
-  int lb = 1;
-  if (nk < PART_BIG_KEYS) {
-    while (lb < 11 && ((nk >> lb) > 10240 || (lb < 8 && (nk >> lb) > 512))) ++lb;
-  } else {
-    lb = 11;
-    while ((nk >> lb) > 51200) ++lb;
-    if (lb > PART_MAX_LB) lb += 2;
-  }
-  const int nxl = nk >= (2u << 20) ? 3 : 0;
-  const int lb1 = lb > PART_MAX_LB ? 8 : lb;
+  const PartPlan plan = search_plan(nk);
+  const int lb = plan.lb, lb1 = plan.lb1, nxl = plan.nxl;
   const uint64_t over_cap = nk / 16 + 65536;
+  if (!plan_fits(plan, nk, over_cap)) return false;
   uint32_t* over = cl.counters + CNT_OVER;
   // (regions of an estimate hold 1.2 times the most)
   PartOut p = part_out(cl, std::max(nk, most / 5 * 3), lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);

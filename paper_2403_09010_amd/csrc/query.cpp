@@ -424,22 +424,18 @@ namespace {
 // if an overflow area was too small or those bins hold over a quarter of the
 // elements: digit passes over everything do as well then.
 //
-// Bins of at most SORT_BIN_MEAN elements: small inputs take 2^8 bins of 512 or
-// more, so that every CU has one. Beyond 2^11 bins the partition takes two
-// levels, as a search's does beyond 2^12. Against one histogram, five digit passes over
-// everything and a copy: 2M sequences, k = 2 (202M elements), 14.5 and 2.4
-// ms of kernels.
+// Against one histogram, five digit passes over everything and a copy: 2M
+// sequences, k = 2 (202M elements), 14.5 and 2.4 ms of kernels.
 uint64_t sorted_bins(Call& cl0, const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nk,
                      int k, uint32_t idbits, uint64_t* E) {
   sd_ctx* c = cl0.c;
   hipStream_t s = cl0.s;
   Scratch sc(c);
   Call cl{c, s, sc, cl0.tm, cl0.counters};
-  int lb = 1;
-  while ((nk >> lb) > SORT_BIN_MEAN || (lb < 8 && (nk >> lb) > 512)) ++lb;
-  const int nxl = nk >= (2u << 20) ? 3 : 0;
-  const int lb1 = lb > 11 ? std::max(8, lb - PART_MAX_SPLIT) : lb;
+  const PartPlan plan = sort_plan(nk);
+  const int lb = plan.lb, lb1 = plan.lb1, nxl = plan.nxl;
   const uint64_t over_cap = nk / 16 + 65536;
+  if (!plan_fits(plan, nk, over_cap)) return 0;
   uint32_t* over = cl.counters + CNT_OVER;
   PartOut p = part_out(cl, nk, lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
   launch_gen_part(seq, vcnt, n, nk, k, idbits, p, s);

@@ -15,6 +15,7 @@
 
 #include "../../include/symdel.h"
 #include "pair_list.h"
+#include "part_plan.h"
 
 typedef unsigned __int128 u128;
 
@@ -261,13 +262,6 @@ struct PartOut {
   uint32_t region, slots, cap, nbins;
   int lb, nxl;
 };
-// Inputs of at least this many variants are generated and grouped by the
-// large workgroups (1,024 threads, one or two on a CU).
-constexpr uint64_t PART_BIG_KEYS = 16ull << 20;
-// most bins (log2) one kernel partitions into
-constexpr int PART_MAX_LB = 12;
-// most bits of one split of a first partition's bins
-constexpr int PART_MAX_SPLIT = 9;
 // every distinct <= k-deletion variant of n packed sequences (vcnt: their
 // counts, nkeys in all), partitioned
 void launch_gen_part(const u128* seq, const uint32_t* vcnt, uint64_t n, uint64_t nkeys, int k,
@@ -375,7 +369,6 @@ void launch_bin_offsets(const PartOut& in, uint32_t* cnt, uint64_t* off, uint64_
 // bins too large for a workgroup (SORT_BIN_MEAN is a safe mean) are listed in
 // big instead (at most nbins << nxl ranges). *repeats counts repeated elements,
 // which stay, next to each other. Both counters are zeroed by the caller.
-constexpr uint32_t SORT_BIN_MEAN = 3200;
 void launch_sort_bins(const PartOut& in, const uint64_t* off, uint64_t* out, uint64_t* big,
                       unsigned long long* nbig, unsigned long long* repeats, hipStream_t s);
 // m sorted elements, all there are of their bins, to the bins' places

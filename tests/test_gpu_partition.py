@@ -116,6 +116,16 @@ def test_wide_ids(paths):
     same(paths, *cdr3gen.generate(13, (1 << 24) + 3), 0)
 
 
+# 32 id bits on two levels; 2^18 bins, which the first level shares out further
+@pytest.mark.parametrize("n,k,least", [((1 << 24) + 5, 1, 51_200 << 12), (3_850_000, 3, 51_200 << 15)])
+def test_large_plans(n, k, least):
+    from paper_2403_09010_amd import Context
+    from paper_2403_09010_amd.symdel import OPT_PATH
+    with Context(0) as a, Context(0) as b:
+        b.set_option(OPT_PATH, 2)
+        assert same((a, b), *cdr3gen.generate(15, n), k)["n_keys"] > least
+
+
 def same_paired(paths, a, b, k):
     print(f"[partition] {len(a[1]) - 1} paired records k={k}", flush=True)
     x = paths[0].paired_self_search(a, b, k)

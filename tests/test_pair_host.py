@@ -18,3 +18,11 @@ def test_pair_host(tmp_path):
                    os.path.join(ROOT, "tests", "sanitize", "pairs_checks.cpp")],
                   ["-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                    "-I" + os.path.join(ROOT, "include"), "-I" + csrc])
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_partition_plans(tmp_path):
+    """Every plan of a partition fits the kernels that take it."""
+    build_and_run(tmp_path, "plan_checks",
+                  [os.path.join(ROOT, "tests", "sanitize", "plan_checks.cpp")],
+                  ["-I" + os.path.join(ROOT, "paper_2403_09010_amd", "csrc")])
