@@ -664,7 +664,8 @@ void query_sets(sd_ctx* c, const sd_index* idx, int nsets, const sd_seqs* sets, 
     for (int x = first; x < last; ++x)
       if (sets[x].n) {
         on_device = on_device && sets[x].on_device;
-        refs.push_back(SetRef{sets[x].codes, sets[x].offsets, base[x - first]});
+        refs.push_back(
+            SetRef{sets[x].codes, sets[x].offsets, base[x - first], (uint64_t)sets[x].n});
       }
     if (last - first == 1 && sets[first].on_device) {
       q = DevSeqs{sets[first].codes, sets[first].offsets, (uint64_t)sets[first].n};

@@ -141,11 +141,13 @@ void launch_pack(const uint8_t* codes, const int64_t* offs, uint64_t n, int k, b
                  u128* seq, u128* planes, uint32_t* vcnt, uint32_t* err, hipStream_t s,
                  unsigned long long* sums = nullptr);
 // The same for the sequences of nsets device sets, one after the other. An offset
-// that decreases or a set that does not start at 0 sets SD_ERRBIT_OFFSETS.
+// that decreases or a set that does not start at 0 sets SD_ERRBIT_OFFSETS; no codes
+// outside [0, a set's last offset) are read.
 struct SetRef {
   const uint8_t* codes;
   const int64_t* offs;
   uint64_t base;  // sequences before it
+  uint64_t n;     // its own, at least 1
 };
 void launch_pack_sets(const SetRef* sets, uint32_t nsets, uint64_t n, int k, bool distinct,
                       u128* seq, u128* planes, uint32_t* vcnt, uint32_t* err, hipStream_t s,

@@ -12,6 +12,7 @@
 #include "distance.h"
 #include "sd_device.h"
 #include "sd_internal.h"
+#include "set_check.h"
 
 namespace sdk {
 
@@ -84,10 +85,9 @@ __global__ __launch_bounds__(NT) void k_pack(const uint8_t* __restrict__ codes,
     }
     a = offs[at];
     L = offs[at + 1] - a;
-    // (a sequence that starts below 0 or beyond what the ones before it can take
-    // follows one that is flagged: it is not read)
-    const bool lost = SETS && (a < 0 || a > (int64_t)at * KEY_MAX_LEN);
-    if (SETS && (L < 0 || (at == 0 && a != 0))) atomicOr(err, SD_ERRBIT_OFFSETS);
+    // (a sequence outside its set's codes is flagged, not read)
+    const bool lost = SETS && !sd::inside_set(at, a, offs[at + 1], offs[sets[set].n]);
+    if (lost) atomicOr(err, SD_ERRBIT_OFFSETS);
     good = L >= 1 && L <= KEY_MAX_LEN && !lost;
     if (!good && !lost) atomicOr(err, SD_ERRBIT_LENGTH);
     const bool last = threadIdx.x == NT - 1 || i + 1 == n;

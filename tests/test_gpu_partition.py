@@ -288,6 +288,24 @@ def test_batch_device_offsets_refused(query_paths, at, value, name):
     idx.free()
 
 
+# two offsets that agree with each other, past the codes' end
+@pytest.mark.parametrize("at", [60, 1, 253, 256])
+def test_batch_device_offsets_beyond_the_codes(query_paths, at):
+    import torch
+    from paper_2403_09010_amd import SymdelError
+    ctx = query_paths[0]
+    ref = cdr3gen.generate(29, 3_000)
+    idx = ctx.build_index(*ref, 1)
+    good = csr([bytes([x % 20] * 10) for x in range(300)])
+    bad = good[1].copy()
+    bad[at], bad[at + 1] = 3_400, 3_410
+    sets = [tuple(torch.from_numpy(a).cuda() for a in q) for q in (good, (good[0], bad), good)]
+    with pytest.raises(SymdelError) as e:
+        ctx.query_batch(idx, sets, 1)
+    assert e.value.name == "SD_E_INVAL"
+    idx.free()
+
+
 # codes at any alignment, part of a workgroup and whole ones, against the host's
 # own copy of the same sequences
 @pytest.mark.parametrize("n,shift", [(1, 3), (255, 1), (256, 15), (257, 8), (1_000, 7)])

@@ -26,3 +26,11 @@ def test_partition_plans(tmp_path):
     build_and_run(tmp_path, "plan_checks",
                   [os.path.join(ROOT, "tests", "sanitize", "plan_checks.cpp")],
                   ["-I" + os.path.join(ROOT, "paper_2403_09010_amd", "csrc")])
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_device_set_offsets(tmp_path):
+    """No offsets of a device set have the packing kernel read outside its codes."""
+    build_and_run(tmp_path, "set_checks",
+                  [os.path.join(ROOT, "tests", "sanitize", "set_checks.cpp")],
+                  ["-I" + os.path.join(ROOT, "paper_2403_09010_amd", "csrc")])
