@@ -128,6 +128,12 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     b.longs = sc.get<uint32_t>(b.long_cap);
     b.state = sc.get<PairState>(1);
     b.err = cl.lb_err();
+    Scratch res(c);  // the result arrays, handed over at the end
+    uint32_t* oi = res.get<uint32_t>(cap);
+    uint32_t* oj = res.get<uint32_t>(cap);
+    uint8_t* od = res.get<uint8_t>(cap);
+    // (everything is taken before anything runs: where the memory does not suffice,
+    // no work was for nothing)
     launch_zero({{b.icnt, q.na},
                  {b.groups, groups},
                  {reinterpret_cast<uint32_t*>(b.state), sizeof(PairState) / 4},
@@ -146,10 +152,6 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     cl.tm.mark("pair_verify", (double)guess * (8 + 32), 1);
     launch_pair_scan(b, q.na, s);
     launch_pair_place(sh.b, b, s);
-    Scratch res(c);  // the result arrays, handed over at the end
-    uint32_t* oi = res.get<uint32_t>(cap);
-    uint32_t* oj = res.get<uint32_t>(cap);
-    uint8_t* od = res.get<uint8_t>(cap);
     launch_pair_order(b, q.na, oi, oj, od, cap, cl.counters, s);
     cl.tm.mark("pair_order", (double)q.na * 20, 4);
     PairState st;

@@ -515,15 +515,9 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   if (!plan_fits(plan, nk, over_cap)) return false;
   uint32_t* over = cl.counters + CNT_OVER;
   // (regions of an estimate hold 1.2 times the most)
-  PartOut p = part_out(cl, std::max(nk, most / 5 * 3), lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
-  generate(p, idbits);
-  cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
-  if (lb1 < lb) {
-    const PartOut p2 = part_out(cl, nk, lb, nxl, over_cap, over);
-    launch_part_split(p, p2, s);
-    cl.tm.mark("part_split", (double)nk * 16, 1);
-    p = p2;
-  }
+  const PartOut p1 = part_out(cl, std::max(nk, most / 5 * 3), lb1, nxl, over_cap,
+                              lb1 < lb ? over + 1 : over);
+  const PartOut p = lb1 < lb ? part_out(cl, nk, lb, nxl, over_cap, over) : p1;
   const uint64_t nbig_cap = ((uint64_t)p.nbins << nxl) + 1;
   uint64_t* big = cl.sc.get<uint64_t>(2 * nbig_cap);
   unsigned long long* nbig = reinterpret_cast<unsigned long long*>(cl.counters + CNT_NBIG);
@@ -534,7 +528,16 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   const bool done = binned_pairs(
       cl, hint, nk, q,
       [&](const PairBins& bins) {
-        if (again) launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
+        if (again) {
+          launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
+        } else {
+          generate(p1, idbits);
+          cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
+          if (lb1 < lb) {
+            launch_part_split(p1, p, s);
+            cl.tm.mark("part_split", (double)nk * 16, 1);
+          }
+        }
         again = true;
         launch_filter_group(p, nk, idbits, bins, big, nbig, s);
         launch_pair_scatter(extra.p, extra.n, bins, s);

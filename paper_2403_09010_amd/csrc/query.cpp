@@ -155,9 +155,8 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
     };
     while (lb + sub < idx->bits && too_many()) ++sub;
     p = part_out(cl, nk, lb, nk >= (2u << 20) ? 3 : 0, 4096, cl.counters + CNT_OVER);
-    launch_gen_part(seq, vcnt, q.n, nk, k, idx->idbits, p, s);
-    cl.tm.mark("q_vargen_part", (double)nk * 8 + (double)q.n * 20, 1);
   }
+  bool again = false;
   const bool hamming = c->metric == SD_METRIC_HAMMING;
   const PairSeqs ps{w ? planes : hamming ? seq : planes,
                     idx->ref_seq,
@@ -173,6 +172,11 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
   const bool done = binned_pairs(
       cl, join ? "pairs/join" : "pairs/probe", nk, ps,
       [&](const PairBins& bins) {
+        if (join && !again) {
+          launch_gen_part(seq, vcnt, q.n, nk, k, idx->idbits, p, s);
+          cl.tm.mark("q_vargen_part", (double)nk * 8 + (double)q.n * 20, 1);
+        }
+        again = true;
         if (join)
           launch_join_bins(p, idx->E, idx->seg_start, idx->seg_end, idx->bits, sub, idx->idbits,
                            bins, s);
@@ -437,20 +441,18 @@ uint64_t sorted_bins(Call& cl0, const u128* seq, const uint32_t* vcnt, uint64_t 
   const uint64_t over_cap = nk / 16 + 65536;
   if (!plan_fits(plan, nk, over_cap)) return 0;
   uint32_t* over = cl.counters + CNT_OVER;
-  PartOut p = part_out(cl, nk, lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
-  launch_gen_part(seq, vcnt, n, nk, k, idbits, p, s);
-  if (lb1 < lb) {
-    const PartOut p2 = part_out(cl, nk, lb, nxl, over_cap, over);
-    launch_part_split(p, p2, s);
-    p = p2;
-  }
+  const PartOut p1 = part_out(cl, nk, lb1, nxl, over_cap, lb1 < lb ? over + 1 : over);
+  const PartOut p = lb1 < lb ? part_out(cl, nk, lb, nxl, over_cap, over) : p1;
   uint64_t* off = sc.get<uint64_t>(p.nbins + 1);
-  const uint64_t tiles = (p.nbins + scan_tile() - 1) / scan_tile();
-  const uint32_t epoch = next_epoch(c, tiles, s);
-  launch_bin_offsets(p, sc.get<uint32_t>(p.nbins), off, c->status, cl.tile_counter(), epoch,
-                     cl.lb_err(), s);
+  uint32_t* cnt = sc.get<uint32_t>(p.nbins);
   const uint64_t big_cap = ((uint64_t)p.nbins << nxl) + 1;
   uint64_t* big = sc.get<uint64_t>(2 * big_cap);
+  // (all memory is taken before the first launch)
+  launch_gen_part(seq, vcnt, n, nk, k, idbits, p1, s);
+  if (lb1 < lb) launch_part_split(p1, p, s);
+  const uint64_t tiles = (p.nbins + scan_tile() - 1) / scan_tile();
+  const uint32_t epoch = next_epoch(c, tiles, s);
+  launch_bin_offsets(p, cnt, off, c->status, cl.tile_counter(), epoch, cl.lb_err(), s);
   auto* nbig = reinterpret_cast<unsigned long long*>(cl.counters + CNT_NBIG);
   auto* repeats = reinterpret_cast<unsigned long long*>(cl.counters + CNT_CAND);
   launch_sort_bins(p, off, E, big, nbig, repeats, s);

@@ -336,8 +336,8 @@ void fill_host_slices(sd_ctx* c, const uint32_t* di, const uint32_t* dj, const u
                       hipStream_t s);
 
 // Candidates of a search through the bins of pairs.hip (pairs.cpp).
-// `produce` enqueues the kernels that put every candidate; it may run again,
-// with more room, after `check` looked at the call's counters. nkeys: about how
+// `produce` enqueues the kernels that put every candidate, once all memory is taken;
+// it may run again, with more room, after `check` looked at the call's counters. nkeys: about how
 // many variants produce the candidates.
 enum class PairNext {
   done,     // every candidate was put

@@ -19,6 +19,7 @@ int pending = 0;  // launches since the stream was waited for
 std::vector<sd::PairState> answers;
 size_t answered = 0;
 std::vector<std::string> log_;  // launches, in order
+int allocations = 0;            // the last of them fails (0: none does)
 
 void launched(const char* what) {
   ++pending;
@@ -33,7 +34,10 @@ int launches(const char* what) {
 }  // namespace
 
 namespace sd {
-void* dalloc(sd_ctx*, size_t bytes) { return std::malloc(bytes < 4096 ? bytes : 4096); }
+void* dalloc(sd_ctx*, size_t bytes) {
+  if (--allocations == 0) throw Error{SD_E_NOMEM, "no memory"};
+  return std::malloc(bytes < 4096 ? bytes : 4096);
+}
 void dfree(sd_ctx*, void* p) { std::free(p); }
 void hip_check(hipError_t e, const char* what) {
   if (e != hipSuccess) throw Error{SD_E_HIP, what};
@@ -183,6 +187,19 @@ int main() {
       check(o.found && o.produced == 2 && launches("fill") == 1, "an overflow's ids are forgotten");
     else
       check(!o.found && o.code == SD_E_HIP && o.produced == 1, "an error bit beside an overflow too");
+  }
+  {
+    // memory that ends anywhere in the first attempt: nothing has run
+    int at = 0;
+    bool idle = true;
+    Outcome o;
+    do {
+      allocations = ++at;
+      o = search(40000000, {answer(500, 3000)});
+      idle = idle && (o.found || (o.code == SD_E_NOMEM && log_.empty()));
+    } while (!o.found && at < 100);
+    allocations = 0;
+    check(o.found && at > 15 && idle, "all memory is taken before the first launch");
   }
   std::printf(failures ? "%d checks failed\n" : "ok\n", failures);
   return failures ? 1 : 0;

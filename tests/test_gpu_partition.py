@@ -126,6 +126,23 @@ def test_large_plans(n, k, least):
         assert same((a, b), *cdr3gen.generate(15, n), k)["n_keys"] > least
 
 
+def test_budget_without_room_for_two_levels(paths):
+    # the sorted path fits, two levels do not: their generator does not run for nothing
+    from paper_2403_09010_amd import Context
+    from paper_2403_09010_amd.symdel import OPT_TIMING
+    c, o = cdr3gen.generate(16, 2_300_000)
+    want = paths[0].self_search(c, o, 2)
+    nk = paths[0].stats()["n_keys"]
+    assert nk > 51_200 << 12
+    print(f"[partition] a budget of 22 bytes for each of {nk} variants", flush=True)
+    with Context(0, hbm_budget=22 * nk) as ctx:
+        ctx.set_option(OPT_TIMING, 1)
+        got = ctx.self_search(c, o, 2)
+        names = [s["name"] for s in ctx.stats()["stages"]]
+    assert np.array_equal(got.i, want.i) and np.array_equal(got.j, want.j)
+    assert "vargen_hash" in names and "vargen_part" not in names
+
+
 def same_paired(paths, a, b, k):
     print(f"[partition] {len(a[1]) - 1} paired records k={k}", flush=True)
     x = paths[0].paired_self_search(a, b, k)
