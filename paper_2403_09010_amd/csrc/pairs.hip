@@ -386,11 +386,31 @@ __global__ __launch_bounds__(256) void k_pair_order(sd::PairBufs b, uint64_t n,
   }
 }
 
-// A dense candidate array into the bins.
+// A dense candidate array into the bins, or, PC_CHUNK at a time, to the lists in turn
+// (612M candidates of 3,000 equal sequences: 108 ms with a reservation for each
+// wave's 64, 1.9 with one for each chunk).
+constexpr uint32_t PC_CHUNK = 8192;
+
 __global__ __launch_bounds__(256) void k_pair_scatter(const uint64_t* __restrict__ cand,
                                                       uint64_t n, sd::PairBins o) {
-  for (uint64_t p = (uint64_t)blockIdx.x * 256 + threadIdx.x; p < n; p += (uint64_t)gridDim.x * 256)
-    pair_put(o, cand[p]);
+  __shared__ unsigned long long s_at;
+  if (o.lb > 0) {
+    for (uint64_t p = (uint64_t)blockIdx.x * 256 + threadIdx.x; p < n; p += (uint64_t)gridDim.x * 256)
+      pair_put(o, cand[p]);
+    return;
+  }
+  for (uint64_t c = blockIdx.x; c * PC_CHUNK < n; c += gridDim.x) {
+    const uint32_t x = (uint32_t)c & ((1u << o.nxl) - 1);
+    const uint64_t* __restrict__ src = cand + c * PC_CHUNK;
+    const uint32_t m = (uint32_t)min((uint64_t)PC_CHUNK, n - c * PC_CHUNK);
+    if (threadIdx.x == 0) s_at = list_reserve(o, x, m);
+    __syncthreads();
+    const unsigned long long at = s_at;
+    const uint32_t room = sd::list_room(at, m, o.region);
+    uint64_t* __restrict__ dst = o.base + (uint64_t)x * o.region + at;
+    for (uint32_t i = threadIdx.x; i < room; i += 256) dst[i] = src[i];
+    __syncthreads();  // the next chunk's place
+  }
 }
 
 }  // namespace sdk
@@ -464,7 +484,8 @@ void launch_pair_order(const PairBufs& b, uint64_t n, uint32_t* oi, uint32_t* oj
 
 void launch_pair_scatter(const uint64_t* cand, uint64_t n, const PairBins& o, hipStream_t s) {
   if (!n) return;
-  const unsigned g = (unsigned)std::min<uint64_t>((n + 255) / 256, 16384);
+  const uint64_t per = o.lb > 0 ? 256 : sdk::PC_CHUNK;
+  const unsigned g = (unsigned)std::min<uint64_t>((n + per - 1) / per, 16384);
   hipLaunchKernelGGL(sdk::k_pair_scatter, dim3(g), dim3(256), 0, s, cand, n, o);
 }
 

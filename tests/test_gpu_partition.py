@@ -385,3 +385,36 @@ def test_query_copies_after_a_larger_set(query_paths):
         got = ctx.query(idx, *small, 2)
         assert np.array_equal(got.i, want.i) and np.array_equal(got.j, want.j)
     idx.free()
+
+
+def not_slower(binned, general, call, check):
+    """Median times of call(ctx) on two contexts in turn, after one call of each."""
+    import time
+    import torch
+    check(call(binned), call(general))
+    times = {binned: [], general: []}
+    for _ in range(7):
+        for ctx in times:
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            call(ctx)
+            torch.cuda.synchronize()
+            times[ctx].append(time.perf_counter() - t)
+    a, b = (float(np.median(t)) for t in times.values())
+    print(f"[partition] {a * 1e3:.3f} ms, the path that sorts {b * 1e3:.3f}", flush=True)
+    assert a < 1.25 * b
+
+
+def equal(a, b):
+    for x, y in zip(a.numpy(), b.numpy()):
+        assert np.array_equal(x, y)
+
+
+# copies that bins, lists and hash sets were not sized for take no longer than where
+# all candidates are sorted
+@pytest.mark.parametrize("n,clones,copies,k", [(100_000, 1, 3_000, 2)])
+def test_copies_take_no_longer(paths, n, clones, copies, k):
+    import torch
+    s = strings_of(23, n)
+    q = [torch.from_numpy(a).cuda() for a in csr(s + [x for x in s[:clones] for _ in range(copies)])]
+    not_slower(*paths, lambda ctx: ctx.self_search(*q, k), equal)
