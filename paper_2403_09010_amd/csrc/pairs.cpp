@@ -29,10 +29,10 @@ namespace {
 // straight / split: 1.3M candidates 0.51 / 0.49 ms, 3.6M 1.10 / 1.04, 1.3M of
 // weighted queries 1.41 / 1.24; below 1M the two launches cost what they save. A
 // list may get more than its share, since all pairs of a group of equal
-// variants come from one XCD: with spread it is twice as long each time.
+// variants come from one XCD: the next attempt gives each what the fullest was sent.
 struct Shape {
   PairBins b{};           // the final bins
-  PairBins l0{}, l1{};    // split: the lists the producer appends to, the first level
+  PairBins l1{};          // split: the first level
   bool wide = false;      // 8,192 slots
   bool split = false;
   bool fits = true;       // positions fit 32 bits
@@ -77,8 +77,6 @@ Shape shape(Scratch& sc, uint64_t guess, int k, int spread) {
   sh.b.base = sc.get<uint64_t>(sh.slots);
   if (sh.split) {
     const uint32_t all = (uint32_t)guess;
-    sh.l0 = level(sc, std::min<uint64_t>(guess << spread, 8 * guess), 0, 3, 4096, all);
-    sh.l0.base = sc.get<uint64_t>((uint64_t)sh.l0.region << 3);
     sh.l1 = level(sc, guess, (lb + 1) / 2, 3, spread ? 16384 : 1024, all);
     sh.l1.base = sc.get<uint64_t>(((uint64_t)sh.l1.nbins << 3) * sh.l1.region);
   }
@@ -107,11 +105,24 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
   uint64_t guess = (uint64_t)expect + 1024;
   uint64_t cap = guess;
   int spread = 0;
+  // the lists that a large search's producer appends to; while they hold every
+  // candidate, an attempt begins with the levels after them
+  Scratch lists_sc(c);
+  PairBins lists{};
+  uint64_t list_room = 0;  // 0: from the guess
+  bool held = false;
   for (int attempt = 0; attempt < 8; ++attempt) {
     Scratch sc(c);
     Call cl{c, s, sc, cl0.tm, cl0.counters};
     Shape sh = shape(sc, guess, q.k, spread);
     if (!sh.fits) return false;
+    if (sh.split && !held) {
+      while (!lists_sc.blocks.empty()) lists_sc.release(lists_sc.blocks.back());
+      lists = level(lists_sc, guess, 0, 3, 4096, (uint32_t)guess);
+      if (list_room) lists.region = (uint32_t)list_room;
+      lists.base = lists_sc.get<uint64_t>((uint64_t)lists.region << 3);
+    }
+    const bool run = !sh.split || !held;
     PairBufs b{};
     b.icnt = sc.get<uint32_t>(q.na);
     b.kv = sc.get<uint64_t>(sh.slots);
@@ -138,13 +149,15 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
                  {b.groups, groups},
                  {reinterpret_cast<uint32_t*>(b.state), sizeof(PairState) / 4},
                  cursors(sh.b),
-                 cursors(sh.l0),
+                 sh.split && run ? cursors(lists) : ZeroRange{},
                  cursors(sh.l1)},
                 s);
-    produce(sh.split ? sh.l0 : sh.b);
-    cl.tm.mark(stage, (double)nkeys * 8 + (double)guess * 8, 1);
+    if (run) {
+      produce(sh.split ? lists : sh.b);
+      cl.tm.mark(stage, (double)nkeys * 8 + (double)guess * 8, 1);
+    }
     if (sh.split) {
-      launch_pair_split(sh.l0, sh.l1, b.state, s);
+      launch_pair_split(lists, sh.l1, b.state, s);
       launch_pair_split(sh.l1, sh.b, b.state, s);
       cl.tm.mark("pair_split", (double)guess * 32, 2);
     }
@@ -177,7 +190,15 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
       // more room: what was counted and what comes; where the room was there
       // but pairs have very many repeats, fewer of them per bin
       const uint64_t want = raw + more + raw / 16 + 1024;
-      if (overflow && want <= guess) ++spread;
+      const bool full = st.flags & PF_LISTS;
+      held = sh.split && !full && next != PairNext::again;
+      if (overflow && !full && want <= guess) ++spread;
+      // (what a producer sends each list does not change; `more` is shared out in
+      // chunks)
+      list_room = 0;
+      if (sh.split && (more || next != PairNext::again))
+        for (uint64_t n : st.lists) list_room = std::max(list_room, n + more / 8 + 16384);
+      list_room = std::min<uint64_t>(list_room, 0xFFFFFFFFull);
       guess = std::max(guess, want);
       cap = guess;
       continue;

@@ -52,9 +52,12 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
   const uint32_t bin = sub >> in.nxl, x = in.nxl ? sub & 7u : 0u;
   const unsigned long long put =
       in.lists ? in.lists[x * sd::PAIR_LIST_STRIDE] : in.cursor[x * in.nbins + bin];
-  if (put > in.region && tile == 0 && threadIdx.x == 0) {
-    atomicOr(&state->flags, sd::PF_OVERFLOW);
-    atomicAdd(&state->raw[sub % sd::PACK_SUMS], put - in.region);
+  if (tile == 0 && threadIdx.x == 0) {
+    if (in.lists) state->lists[x] = put;
+    if (put > in.region) {
+      atomicOr(&state->flags, sd::PF_OVERFLOW | (in.lists ? sd::PF_LISTS : 0u));
+      atomicAdd(&state->raw[sub % sd::PACK_SUMS], put - in.region);
+    }
   }
   const uint32_t c = (uint32_t)min(put, (unsigned long long)in.region), t0 = tile * TILE;
   if (t0 >= c) return;

@@ -306,11 +306,13 @@ struct PairSeqs {
 };
 constexpr uint32_t PF_OVERFLOW = 1;  // a region was full: candidates were lost
 constexpr uint32_t PF_LONG = 2;      // one first id has too many pairs to order in LDS
+constexpr uint32_t PF_LISTS = 4;     // with PF_OVERFLOW: a list was full
 constexpr uint32_t PAIR_COUNTERS = 256;
 struct PairState {  // zeroed before the producer; read back when the search is done
   uint32_t flags, nlong;
   unsigned long long count;           // pairs kept
   unsigned long long raw[PACK_SUMS];  // candidates put, in parts
+  unsigned long long lists[8];        // with lists: candidates sent to each
   uint32_t counters[PAIR_COUNTERS];   // a copy of the call's counters
 };
 struct PairBufs {
@@ -335,7 +337,7 @@ uint32_t pair_bin_max(bool large);
 void launch_pair_verify(const PairBins& in, bool large, const PairSeqs& q, const PairBufs& b,
                         hipStream_t s);
 // the candidates of one level of bins to the next (o.lb > in.lb); what in's
-// regions lost is counted in state
+// regions lost is counted in state, and what each list was sent
 void launch_pair_split(const PairBins& in, const PairBins& o, PairState* state, hipStream_t s);
 // off from icnt
 constexpr uint32_t PAIR_GROUP = 64;

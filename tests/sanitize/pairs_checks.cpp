@@ -19,6 +19,7 @@ int pending = 0;  // launches since the stream was waited for
 std::vector<sd::PairState> answers;
 size_t answered = 0;
 std::vector<std::string> log_;  // launches, in order
+std::vector<uint32_t> rooms;    // of what each producer was given
 int allocations = 0;            // the last of them fails (0: none does)
 
 void launched(const char* what) {
@@ -112,6 +113,7 @@ Outcome search(uint64_t nkeys, std::vector<sd::PairState> a,
   answers = std::move(a);
   answered = 0;
   log_.clear();
+  rooms.clear();
   pending = 0;
   Outcome o;
   uint32_t counters[sd::CNT_TOTAL] = {};
@@ -122,8 +124,9 @@ Outcome search(uint64_t nkeys, std::vector<sd::PairState> a,
   try {
     o.found = sd::binned_pairs(
         cl, "pairs/test", nkeys, q,
-        [&](const sd::PairBins&) {
+        [&](const sd::PairBins& b) {
           ++o.produced;
+          rooms.push_back(b.region);
           launched("produce");
         },
         [&](const uint32_t*, uint64_t*) {
@@ -200,6 +203,29 @@ int main() {
     } while (!o.found && at < 100);
     allocations = 0;
     check(o.found && at > 15 && idle, "all memory is taken before the first launch");
+  }
+  {
+    // a large search: lists, two levels of bins after them
+    Outcome o = search(100000000, {answer(500, 4000000)});
+    check(o.found && o.produced == 1 && launches("split") == 2, "lists are split in two levels");
+    // a later level was full: the lists are split again, not produced
+    o = search(100000000, {answer(500, 4000000, sd::PF_OVERFLOW), answer(500, 4000000)});
+    check(o.found && o.produced == 1 && launches("split") == 4, "full bins: the lists are split again");
+    o = search(100000000, {answer(500, 9000000, sd::PF_OVERFLOW), answer(500, 9000000)});
+    check(o.found && o.produced == 1 && launches("split") == 4, "the same with more than expected");
+    // a list was full: produced again, with room for what the fullest was sent
+    const uint32_t full = sd::PF_OVERFLOW | sd::PF_LISTS;
+    sd::PairState one = answer(500, 4000000, full);
+    one.lists[5] = 3900000;
+    o = search(100000000, {one, answer(500, 4000000)});
+    check(o.found && o.produced == 2 && rooms.back() == 3900000 + 16384, "a full list: more room");
+    // and both in turn
+    o = search(100000000, {one, answer(500, 4000000, sd::PF_OVERFLOW), answer(500, 4000000)});
+    check(o.found && o.produced == 2 && launches("split") == 6, "a full list, then full bins");
+    // more candidates come: produced again even if the bins were full too
+    o = search(100000000, {answer(500, 4000000, sd::PF_OVERFLOW), answer(500, 4000000)},
+               {sd::PairNext::again});
+    check(o.found && o.produced == 2, "more candidates: produced again");
   }
   std::printf(failures ? "%d checks failed\n" : "ok\n", failures);
   return failures ? 1 : 0;
