@@ -19,8 +19,11 @@ namespace {
 // of up to 4,096. Regions hold the mean, a quarter more and room for its
 // deviation: bins are as even as the pair hash, but a pair comes with all its
 // repeats (about 9 on average; up to 100 for equal sequences, so the variance
-// is taken as 32 times the mean). spread > 0, after a bin overflowed all the
-// same: half as many candidates per bin each time, and whole hash sets.
+// is taken as 32 times the mean), and four to eight hash sets where that is
+// little memory. A set is bounded by the distinct candidates only. spread > 0,
+// after a bin overflowed all the same (equal sequences and three deletions: 500
+// repeats, an eighth of them from each XCD): first regions for that, then half
+// as many candidates per bin each time.
 //
 // Few candidates go straight to their bins. More would leave the L2 as partial
 // lines, ten times their bytes at 4M (85M candidates into 2^15 bins from the
@@ -61,23 +64,27 @@ ZeroRange cursors(const PairBins& b) {
   return {b.cursor, (uint64_t)b.nbins << b.nxl};
 }
 
-Shape shape(Scratch& sc, uint64_t guess, int k, int spread) {
+Shape shape(Scratch& sc, uint64_t guess, int k, int spread, bool uneven) {
   Shape sh;
   sh.split = guess >= (1ull << 20);
   sh.wide = sh.split || k >= 3;
-  const uint64_t mean_max = (sh.wide ? 4096u : 768u) >> spread;
+  const uint64_t mean_max = (sh.wide ? 4096u : 768u) >> std::max(spread - 1, 0);
   int lb = 6;
   while ((guess >> lb) > mean_max) ++lb;
   const int nxl = sh.split ? 3 : 0;
-  const uint32_t most = pair_bin_max(sh.wide) >> nxl;
-  sh.b = level(sc, guess, lb, nxl, spread ? 1e6 : 32, most);
+  const uint32_t most = pair_set_max(sh.wide) >> nxl;
+  sh.b = level(sc, guess, lb, nxl, spread ? 64 : 32, spread ? 3 * most : most);
+  // (a budget's or a fixed area's memory is not spent on room)
+  if (!sh.split && !sc.c->budget && !sc.c->arena)
+    for (uint32_t sets = 8; sets >= 4; sets /= 2)
+      if (((uint64_t)sets * most << lb) <= (1u << 22)) sh.b.region = std::max(sh.b.region, sets * most);
   sh.slots = ((uint64_t)sh.b.nbins << nxl) * sh.b.region;
   sh.fits = sh.slots < 0xFFFFFFFFull && guess < 3000000000ull && lb <= 18;
   if (!sh.fits) return sh;
   sh.b.base = sc.get<uint64_t>(sh.slots);
   if (sh.split) {
     const uint32_t all = (uint32_t)guess;
-    sh.l1 = level(sc, guess, (lb + 1) / 2, 3, spread ? 16384 : 1024, all);
+    sh.l1 = level(sc, guess, (lb + 1) / 2, 3, uneven ? 16384 : 1024, all);
     sh.l1.base = sc.get<uint64_t>(((uint64_t)sh.l1.nbins << 3) * sh.l1.region);
   }
   return sh;
@@ -105,6 +112,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
   uint64_t guess = (uint64_t)expect + 1024;
   uint64_t cap = guess;
   int spread = 0;
+  bool uneven = false;  // the level between overflowed
   // the lists that a large search's producer appends to; while they hold every
   // candidate, an attempt begins with the levels after them
   Scratch lists_sc(c);
@@ -114,7 +122,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
   for (int attempt = 0; attempt < 8; ++attempt) {
     Scratch sc(c);
     Call cl{c, s, sc, cl0.tm, cl0.counters};
-    Shape sh = shape(sc, guess, q.k, spread);
+    Shape sh = shape(sc, guess, q.k, spread, uneven);
     if (!sh.fits) return false;
     if (sh.split && !held) {
       while (!lists_sc.blocks.empty()) lists_sc.release(lists_sc.blocks.back());
@@ -125,7 +133,6 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     const bool run = !sh.split || !held;
     PairBufs b{};
     b.icnt = sc.get<uint32_t>(q.na);
-    b.kv = sc.get<uint64_t>(sh.slots);
     b.rank = sc.get<uint32_t>(sh.slots);
     b.kd = sc.get<uint8_t>(sh.slots);
     b.kept = sc.get<uint32_t>(sh.b.nbins);
@@ -192,7 +199,11 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
       const uint64_t want = raw + more + raw / 16 + 1024;
       const bool full = st.flags & PF_LISTS;
       held = sh.split && !full && next != PairNext::again;
-      if (overflow && !full && want <= guess) ++spread;
+      const bool mid = st.flags & PF_MID;
+      if (overflow && !full && want <= guess) {
+        uneven = uneven || mid;
+        if (!mid) ++spread;
+      }
       // (what a producer sends each list does not change; `more` is shared out in
       // chunks)
       list_room = 0;

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
   if (tile == 0 && threadIdx.x == 0) {
     if (in.lists) state->lists[x] = put;
     if (put > in.region) {
-      atomicOr(&state->flags, sd::PF_OVERFLOW | (in.lists ? sd::PF_LISTS : 0u));
+      atomicOr(&state->flags, sd::PF_OVERFLOW | (in.lists ? sd::PF_LISTS : sd::PF_MID));
       atomicAdd(&state->raw[sub % sd::PACK_SUMS], put - in.region);
     }
   }
@@ -87,9 +87,10 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
                                     o.region, o.nbins, o.nxl, slots, nullptr, 0, nullptr);
 }
 
-// One workgroup per bin, its hash set in LDS (TS slots; the bin's regions hold
-// at most 7/8 of that). Kept pairs go to the front of the bin's slots of the
-// kept arrays, with their rank and distance.
+// One workgroup per bin, its hash set in LDS (TS slots for at most 7/8 as many
+// distinct candidates; with more the bin is over, as with a full region). Kept
+// pairs go to the front of the bin's own slots, with their rank and distance in
+// arrays of as many.
 //
 // Bound: LDS latency of the set's inserts and the gathers of two packed
 // sequences per distinct candidate.
@@ -106,6 +107,9 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
   __shared__ uint32_t s_n, s_k;
   __shared__ uint8_t s_sub[MODE == PM_WEIGHTED ? 400 : 1];
   const uint32_t bin = blockIdx.x, nx = 1u << in.nxl, lane = threadIdx.x & 63u;
+  constexpr uint32_t MOST = TS / 8 * 7;
+  // (each thread inserts at most one candidate past MOST before it sees the count)
+  static_assert(MOST - 1 + NT < TS, "the set always has a free slot");
   uint32_t total = 0;
   bool over = false;
   for (uint32_t x = 0; x < nx; ++x) {
@@ -132,7 +136,7 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
   const uint32_t parts = NW > nx ? NW / nx : 1u;
   for (uint32_t x = w & (nx - 1); x < nx; x += NW) {
     const uint32_t c = in.cursor[x * in.nbins + bin];
-    const uint64_t* __restrict__ p = in.base + base + (uint64_t)x * in.region;
+    const uint64_t* p = in.base + base + (uint64_t)x * in.region;
     for (uint32_t t0 = (w >> in.nxl) * 64; t0 < c; t0 += parts * 64 * PR_ROWS) {
       uint64_t e[PR_ROWS];
 #pragma unroll
@@ -144,13 +148,14 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
       for (int u = 0; u < PR_ROWS; ++u) {
         const uint32_t t = t0 + u * parts * 64;
         if (t >= c) break;
+        if (*(volatile uint32_t*)&s_n >= MOST) break;
         const uint64_t v = e[u];
         // a self search pairs i < j only (a candidate of one sequence with
         // itself can come from two of its variants that share a hash)
         bool fresh = t + lane < c && (!self_pairs || (uint32_t)(v >> 32) < (uint32_t)v);
         uint32_t slot = pair_hash_below(v, in.lb, TSLOG);
         if (fresh) {
-          while (true) {  // ends: the set has more slots than the bin candidates
+          while (true) {  // ends: the set has a free slot
             const unsigned long long old = atomicCAS(&s_tab[slot], 0ull, (unsigned long long)v + 1);
             if (old == 0) break;
             if (old == v + 1) {
@@ -172,6 +177,13 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
   }
   __syncthreads();
   const uint32_t n = s_n;
+  if (n >= MOST) {
+    if (threadIdx.x == 0) {
+      atomicOr(&out.state->flags, sd::PF_OVERFLOW);
+      out.kept[bin] = 0;
+    }
+    return;
+  }
   for (uint32_t l0 = 0; l0 < n; l0 += NT) {
     const uint32_t l = l0 + threadIdx.x;
     bool keep = false;
@@ -212,7 +224,7 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
           if (q < out.long_cap) out.longs[q] = i;
         }
         if (r == PR_MAX) atomicOr(&out.state->flags, sd::PF_LONG);
-        out.kv[base + at] = v;
+        in.base[base + at] = v;
         out.rank[base + at] = r;
         out.kd[base + at] = (uint8_t)d;
       }
@@ -312,7 +324,7 @@ __global__ __launch_bounds__(64) void k_pair_place(sd::PairBins in, sd::PairBufs
   const uint32_t n = b.kept[blockIdx.x];
   const uint64_t base = (uint64_t)(blockIdx.x << in.nxl) * in.region;
   for (uint32_t x = threadIdx.x; x < n; x += 64) {
-    const uint64_t v = b.kv[base + x];
+    const uint64_t v = in.base[base + x];
     const uint32_t p = b.off[v >> 32] + b.rank[base + x];
     b.t[p] = v;
     b.td[p] = b.kd[base + x];
@@ -420,11 +432,11 @@ __global__ __launch_bounds__(256) void k_pair_scatter(const uint64_t* __restrict
 
 namespace sd {
 
-uint32_t pair_bin_max(bool large) { return (large ? 8192u : 2048u) / 8 * 7; }
+uint32_t pair_set_max(bool large) { return (large ? 8192u : 2048u) / 8 * 7; }
 
 template <int NT, int TSLOG, int MODE>
 static void verify_t(const PairBins& in, const PairSeqs& q, const PairBufs& b, hipStream_t s) {
-  const size_t lds = ((size_t)8 << TSLOG) + ((size_t)in.region << in.nxl) * 2;
+  const size_t lds = ((size_t)8 << TSLOG) + ((7u << TSLOG) / 8 + NT) * 2;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(&sdk::k_pair_verify<NT, TSLOG, MODE>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     (void)hipGetLastError();  // the launch reports any real problem
@@ -446,8 +458,6 @@ static void verify_mode(const PairBins& in, const PairSeqs& q, const PairBufs& b
 
 void launch_pair_verify(const PairBins& in, bool large, const PairSeqs& q, const PairBufs& b,
                         hipStream_t s) {
-  if ((in.region << in.nxl) > pair_bin_max(large))
-    throw Error{SD_E_HIP, "internal error: a pair bin exceeds its hash set"};
   if (large)
     verify_mode<512, 13>(in, q, b, s);
   else

@@ -306,7 +306,8 @@ struct PairSeqs {
 };
 constexpr uint32_t PF_OVERFLOW = 1;  // a region was full: candidates were lost
 constexpr uint32_t PF_LONG = 2;      // one first id has too many pairs to order in LDS
-constexpr uint32_t PF_LISTS = 4;     // with PF_OVERFLOW: a list was full
+constexpr uint32_t PF_LISTS = 4;     // with PF_OVERFLOW: a list was full, ...
+constexpr uint32_t PF_MID = 8;       // ... a region of the level after the lists
 constexpr uint32_t PAIR_COUNTERS = 256;
 struct PairState {  // zeroed before the producer; read back when the search is done
   uint32_t flags, nlong;
@@ -316,9 +317,8 @@ struct PairState {  // zeroed before the producer; read back when the search is 
   uint32_t counters[PAIR_COUNTERS];   // a copy of the call's counters
 };
 struct PairBufs {
-  uint64_t* kv;     // slots of the bins: kept pairs, ...
-  uint32_t* rank;   // ... their rank among their first id's pairs
-  uint8_t* kd;      // ... and distance
+  uint32_t* rank;   // slots of the bins: kept pairs' rank among their first id's, ...
+  uint8_t* kd;      // ... and distance (the pairs are where the candidates were)
   uint32_t* kept;   // nbins: how many
   uint32_t* icnt;   // na, zeroed: pairs kept per first id
   uint32_t* sums;   // pair_tiles(na): pairs kept per tile of first ids, ...
@@ -331,9 +331,9 @@ struct PairBufs {
   PairState* state;
   uint32_t* err;
 };
-// most candidates a bin may hold
-uint32_t pair_bin_max(bool large);
-// kv, rank, kd, kept, icnt, longs from the binned candidates
+// most distinct candidates a bin may hold
+uint32_t pair_set_max(bool large);
+// kept pairs over the binned candidates, rank, kd, kept, icnt, longs
 void launch_pair_verify(const PairBins& in, bool large, const PairSeqs& q, const PairBufs& b,
                         hipStream_t s);
 // the candidates of one level of bins to the next (o.lb > in.lb); what in's
@@ -343,7 +343,7 @@ void launch_pair_split(const PairBins& in, const PairBins& o, PairState* state, 
 constexpr uint32_t PAIR_GROUP = 64;
 uint64_t pair_tiles(uint64_t na);
 void launch_pair_scan(const PairBufs& b, uint64_t na, hipStream_t s);
-// t, td from kv, rank, kd and off
+// t, td from the kept pairs, rank, kd and off
 void launch_pair_place(const PairBins& in, const PairBufs& b, hipStream_t s);
 // the placed pairs in order to o*[0, cap), their number and PAIR_COUNTERS words
 // of counters to b.state

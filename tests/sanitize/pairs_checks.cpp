@@ -56,7 +56,7 @@ void launch_fill_u32(uint32_t*, uint32_t, uint64_t, hipStream_t) { launched("fil
 void launch_pair_split(const PairBins&, const PairBins&, PairState*, hipStream_t) {
   launched("split");
 }
-uint32_t pair_bin_max(bool large) { return (large ? 8192u : 2048u) / 8 * 7; }
+uint32_t pair_set_max(bool large) { return (large ? 8192u : 2048u) / 8 * 7; }
 void launch_pair_verify(const PairBins&, bool, const PairSeqs&, const PairBufs&, hipStream_t) {
   launched("verify");
 }

@@ -412,7 +412,7 @@ def equal(a, b):
 
 # copies that bins, lists and hash sets were not sized for take no longer than where
 # all candidates are sorted
-@pytest.mark.parametrize("n,clones,copies,k", [(100_000, 1, 3_000, 2)])
+@pytest.mark.parametrize("n,clones,copies,k", [(100_000, 1, 3_000, 2), (300_000, 20, 300, 3)])
 def test_copies_take_no_longer(paths, n, clones, copies, k):
     import torch
     s = strings_of(23, n)
