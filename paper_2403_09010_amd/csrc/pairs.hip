@@ -321,6 +321,7 @@ __global__ __launch_bounds__(PS_NT) void k_pair_scan(sd::PairBufs b, uint64_t n)
 // pair (8.6M pairs of 10M sequences: 0.47 ms; with the two ids in words of
 // their own 0.66).
 __global__ __launch_bounds__(64) void k_pair_place(sd::PairBins in, sd::PairBufs b) {
+  if (b.state->flags & sd::PF_OVERFLOW) return;  // (the attempt is not answered)
   const uint32_t n = b.kept[blockIdx.x];
   const uint64_t base = (uint64_t)(blockIdx.x << in.nxl) * in.region;
   for (uint32_t x = threadIdx.x; x < n; x += 64) {
@@ -384,6 +385,8 @@ __global__ __launch_bounds__(256) void k_pair_order(sd::PairBufs b, uint64_t n,
     if (threadIdx.x == 0) b.state->count = total;
     if (threadIdx.x < sd::PAIR_COUNTERS) b.state->counters[threadIdx.x] = counters[threadIdx.x];
   }
+  // (nothing to order: the attempt is not answered, or the placed pairs are sorted)
+  if (b.state->flags & (sd::PF_OVERFLOW | sd::PF_LONG)) return;
   order_long(b, s_v, oi, oj, od, cap);
   for (uint64_t p = (uint64_t)blockIdx.x * 256 + threadIdx.x; p < total;
        p += (uint64_t)gridDim.x * 256) {

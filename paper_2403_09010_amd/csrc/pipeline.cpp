@@ -115,10 +115,15 @@ Cands oversized_group(Call& cl, const uint64_t* E, const uint64_t* big, uint64_t
   const bool flip =
       radix_sort(cl, g1, nullptr, nullptr, g2, nullptr, nullptr, 1, false, (uint32_t)tot, digits, hists);
   const uint64_t* sorted = flip ? g2 : g1;
-  uint64_t cap = tot / 8 + 65536;
+  // room for what the runs can give (unless that is very much: repeated elements give
+  // less), so that the pairs are walked once
+  unsigned long long* ccount = reinterpret_cast<unsigned long long*>(cl.counters + CNT_CAND2);
+  launch_fill_u64(reinterpret_cast<uint64_t*>(ccount), 0, 1, s);
+  launch_count_hash_runs(sorted, tot, idbits, ccount, s);
+  uint64_t cap = *static_cast<const uint64_t*>(readback(c, ccount, 8, s));
+  if (cap > (1ull << 30)) cap = tot / 8 + 65536;
   Cands out;
   out.p = dalloc_t<uint64_t>(c, cap);
-  unsigned long long* ccount = reinterpret_cast<unsigned long long*>(cl.counters + CNT_CAND2);
   launch_fill_u64(reinterpret_cast<uint64_t*>(ccount), 0, 1, s);
   launch_emit_hash_runs(sorted, tot, idbits, out.p, cap, ccount, s);
   const uint64_t nc = *static_cast<const uint64_t*>(readback(c, ccount, 8, s));

@@ -384,6 +384,9 @@ void launch_filter_group(const PartOut& in, uint64_t nkeys, uint32_t idbits, con
                          uint64_t* big, unsigned long long* nbig, hipStream_t s);
 void launch_gather_big(const uint64_t* E, const uint64_t* big, const uint64_t* out_off,
                        uint32_t nseg, uint64_t* out, hipStream_t s);
+// no fewer than the pairs that the emission below finds, added to *pairs
+void launch_count_hash_runs(const uint64_t* E, uint64_t n, uint32_t idbits,
+                            unsigned long long* pairs, hipStream_t s);
 void launch_emit_hash_runs(const uint64_t* E, uint64_t n, uint32_t idbits, uint64_t* cand,
                            uint64_t cap, unsigned long long* counter, hipStream_t s);
 void launch_pair_distance(const u128* seq_a, uint64_t na, const u128* seq_b, uint64_t nb,
