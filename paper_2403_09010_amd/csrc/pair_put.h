@@ -38,7 +38,10 @@ __device__ __forceinline__ unsigned long long first_lane(unsigned long long v) {
 // reservation for the active lanes); one that finds its region full is only
 // counted.
 // Each bin has a region per XCD (nxl = 3), so that an XCD's L2 completes the
-// lines of its own regions.
+// lines of its own regions. With ALIKE, lanes with the first active lane's pair
+// reserve together: the variants of two equal sequences all give one pair, and an
+// atomic takes its line 10 ns whichever lane it comes from.
+template <bool ALIKE = false>
 __device__ __forceinline__ void pair_put(const sd::PairBins& o, uint64_t v) {
   const uint32_t x = o.nxl ? blockIdx.x & 7u : 0u;
   if (o.lb == 0) {
@@ -51,8 +54,42 @@ __device__ __forceinline__ void pair_put(const sd::PairBins& o, uint64_t v) {
     return;
   }
   const uint32_t b = (uint32_t)(pair_hash(v) >> (64 - o.lb));
-  const uint32_t slot = atomicAdd(&o.cursor[x * o.nbins + b], 1u);
+  uint32_t* const cursor = &o.cursor[(x * o.nbins + b) << o.pad];
+  uint32_t slot = 0;
+  if (ALIKE) {
+    const bool same = v == first_lane(v);
+    const uint64_t peers = __ballot(same);
+    const uint32_t rank = mask_rank(peers);
+    if (!same || rank == 0) slot = atomicAdd(cursor, same ? (uint32_t)__popcll(peers) : 1u);
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
+    if (same) slot = first + rank;
+  } else {
+    slot = atomicAdd(cursor, 1u);
+  }
   if (slot < o.region) o.base[(uint64_t)((b << o.nxl) + x) * o.region + slot] = v;
+}
+
+// The lane's candidates v[u] with on[u], their reservations in flight together.
+template <int N>
+__device__ __forceinline__ void pair_put_rows(const sd::PairBins& o, const uint64_t (&v)[N],
+                                              const bool (&on)[N]) {
+  if (o.lb == 0) {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (on[u]) pair_put(o, v[u]);
+    return;
+  }
+  const uint32_t x = o.nxl ? blockIdx.x & 7u : 0u;
+  uint32_t b[N], slot[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    b[u] = (uint32_t)(pair_hash(v[u]) >> (64 - o.lb));
+    slot[u] = o.region;
+    if (on[u]) slot[u] = atomicAdd(&o.cursor[(x * o.nbins + b[u]) << o.pad], 1u);
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+    if (slot[u] < o.region) o.base[(uint64_t)((b[u] << o.nxl) + x) * o.region + slot[u]] = v[u];
 }
 
 }  // namespace sdk

@@ -18,19 +18,21 @@ namespace {
 // with three deletions (a pair can repeat 2,325 times), 8,192 slots for a mean
 // of up to 4,096. Regions hold the mean, a quarter more and room for its
 // deviation: bins are as even as the pair hash, but a pair comes with all its
-// repeats (about 9 on average; up to 100 for equal sequences, so the variance
-// is taken as 32 times the mean), and four to eight hash sets where that is
-// little memory. A set is bounded by the distinct candidates only. spread > 0,
-// after a bin overflowed all the same (equal sequences and three deletions: 500
-// repeats, an eighth of them from each XCD): first regions for that, then half
-// as many candidates per bin each time.
+// repeats, about 9 on average, 120 (k = 3: 500) for equal sequences, an eighth of them
+// from each XCD. So the variance is taken as that many times the mean, where a
+// first attempt that overflows costs the producer's work again, and as 32 times where
+// it does not; and regions have four to eight hash sets' room where that is little
+// memory. A set is bounded by the distinct candidates only. spread > 0, after a
+// bin overflowed all the same: more room, then half as many candidates per bin
+// each time.
 //
 // Few candidates go straight to their bins. More would leave the L2 as partial
 // lines, ten times their bytes at 4M (85M candidates into 2^15 bins from the
 // grouping kernel: 2.2 ms); they are appended to one list per XCD and split in
 // two levels instead, a coalesced read and write each (0.65 ms). Whole searches,
 // straight / split: 1.3M candidates 0.51 / 0.49 ms, 3.6M 1.10 / 1.04, 1.3M of
-// weighted queries 1.41 / 1.24; below 1M the two launches cost what they save. A
+// weighted queries 1.41 / 1.24; below 1M the two launches cost what they save,
+// unless a few workgroups put most of the candidates (`lists`). A
 // list may get more than its share, since all pairs of a group of equal
 // variants come from one XCD: the next attempt gives each what the fullest was sent.
 struct Shape {
@@ -43,50 +45,54 @@ struct Shape {
 };
 
 // Bins of one level (2^lb bins, 2^nxl regions each).
-PairBins level(Scratch& sc, uint64_t guess, int lb, int nxl, double var, uint32_t most) {
+PairBins level(uint64_t guess, int lb, int nxl, double var, uint32_t most) {
   PairBins b{};
   b.lb = lb;
   b.nbins = 1u << lb;
   b.nxl = nxl;
-  const uint64_t nc = (uint64_t)b.nbins << nxl;
-  const double mean = (double)guess / (double)nc;
+  const double mean = (double)guess / (double)((uint64_t)b.nbins << nxl);
   b.region =
       (uint32_t)std::min<double>(most, mean * 1.25 + 6.0 * std::sqrt(var * mean) + 32);
-  if (lb)
-    b.cursor = sc.get<uint32_t>(nc);
-  else
-    b.lists = sc.get<unsigned long long>((uint64_t)PAIR_LIST_STRIDE << nxl);
+  // (one region per bin: counted by single atomics, which queue for their line, so
+  // few bins have a line each)
+  if (!nxl) b.pad = lb <= 9 ? 5 : lb <= 12 ? 2 : 0;
   return b;
+}
+
+uint64_t slots(const PairBins& b) { return ((uint64_t)b.nbins << b.nxl) * b.region; }
+
+void take(Scratch& sc, PairBins& b) {
+  if (b.lb)
+    b.cursor = sc.get<uint32_t>((uint64_t)b.nbins << b.nxl << b.pad);
+  else
+    b.lists = sc.get<unsigned long long>((uint64_t)PAIR_LIST_STRIDE << b.nxl);
+  b.base = sc.get<uint64_t>(slots(b));
 }
 
 ZeroRange cursors(const PairBins& b) {
   if (b.lists) return {reinterpret_cast<uint32_t*>(b.lists), (uint64_t)(2 * PAIR_LIST_STRIDE) << b.nxl};
-  return {b.cursor, (uint64_t)b.nbins << b.nxl};
+  return {b.cursor, (uint64_t)b.nbins << b.nxl << b.pad};
 }
 
-Shape shape(Scratch& sc, uint64_t guess, int k, int spread, bool uneven) {
+// most candidates: beyond them the bins would take more memory than a sort
+constexpr uint64_t PAIR_MOST = 750000000;
+
+Shape shape(uint64_t guess, int k, int spread, bool uneven, bool lists) {
   Shape sh;
-  sh.split = guess >= (1ull << 20);
+  sh.split = lists || guess >= (1ull << 20);
   sh.wide = sh.split || k >= 3;
   const uint64_t mean_max = (sh.wide ? 4096u : 768u) >> std::max(spread - 1, 0);
   int lb = 6;
   while ((guess >> lb) > mean_max) ++lb;
-  const int nxl = sh.split ? 3 : 0;
-  const uint32_t most = pair_set_max(sh.wide) >> nxl;
-  sh.b = level(sc, guess, lb, nxl, spread ? 64 : 32, spread ? 3 * most : most);
-  // (a budget's or a fixed area's memory is not spent on room)
-  if (!sh.split && !sc.c->budget && !sc.c->arena)
-    for (uint32_t sets = 8; sets >= 4; sets /= 2)
-      if (((uint64_t)sets * most << lb) <= (1u << 22)) sh.b.region = std::max(sh.b.region, sets * most);
-  sh.slots = ((uint64_t)sh.b.nbins << nxl) * sh.b.region;
-  sh.fits = sh.slots < 0xFFFFFFFFull && guess < 3000000000ull && lb <= 18;
-  if (!sh.fits) return sh;
-  sh.b.base = sc.get<uint64_t>(sh.slots);
-  if (sh.split) {
-    const uint32_t all = (uint32_t)guess;
-    sh.l1 = level(sc, guess, (lb + 1) / 2, 3, uneven ? 16384 : 1024, all);
-    sh.l1.base = sc.get<uint64_t>(((uint64_t)sh.l1.nbins << 3) * sh.l1.region);
-  }
+  const uint32_t most = pair_set_max(sh.wide) >> (sh.split ? 3 : 0);
+  if (sh.split)
+    sh.b = level(guess, lb, 3, spread ? 64 : 32, spread ? 3 * most : most);
+  else
+    sh.b = level(guess, lb, 0, k >= 3 ? 512 : 128, k >= 3 || spread ? 3 * most : 2 * most);
+  sh.slots = slots(sh.b);
+  sh.fits = sh.slots < 0xFFFFFFFFull && guess <= PAIR_MOST && lb <= 18;
+  if (sh.fits && sh.split)
+    sh.l1 = level(guess, (lb + 1) / 2, 3, uneven ? 16384 : 1024, (uint32_t)guess);
   return sh;
 }
 
@@ -103,7 +109,8 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
   // search of this kind on the context made, scaled down to this one's
   // variants (never up: one input of many copies must not size the next)
   constexpr double first[4] = {1.0 / 64, 1.0 / 48, 1.0 / 22, 1.0 / 9};
-  const std::string hint_raw(hint), hint_keys = hint_raw + "/variants";
+  const std::string hint_raw(hint), hint_keys = hint_raw + "/variants",
+                    hint_lists = hint_raw + "/lists";
   double expect = (double)nkeys * first[q.k & 3];
   if (c->out_hint.count(hint_raw)) {
     const double last = (double)c->out_hint[hint_raw], keys = (double)c->out_hint[hint_keys];
@@ -113,6 +120,8 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
   uint64_t cap = guess;
   int spread = 0;
   bool uneven = false;  // the level between overflowed
+  auto crowded = c->out_hint.find(hint_lists);
+  bool to_lists = crowded != c->out_hint.end() && crowded->second;
   // the lists that a large search's producer appends to; while they hold every
   // candidate, an attempt begins with the levels after them
   Scratch lists_sc(c);
@@ -122,29 +131,34 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
   for (int attempt = 0; attempt < 8; ++attempt) {
     Scratch sc(c);
     Call cl{c, s, sc, cl0.tm, cl0.counters};
-    Shape sh = shape(sc, guess, q.k, spread, uneven);
+    Shape sh = shape(guess, q.k, spread, uneven, to_lists);
     if (!sh.fits) return false;
     if (sh.split && !held) {
       while (!lists_sc.blocks.empty()) lists_sc.release(lists_sc.blocks.back());
-      lists = level(lists_sc, guess, 0, 3, 4096, (uint32_t)guess);
+      lists = level(guess, 0, 3, 4096, (uint32_t)guess);
       if (list_room) lists.region = (uint32_t)list_room;
-      lists.base = lists_sc.get<uint64_t>((uint64_t)lists.region << 3);
+      take(lists_sc, lists);
     }
     const bool run = !sh.split || !held;
     PairBufs b{};
-    b.icnt = sc.get<uint32_t>(q.na);
+    const uint64_t tiles = pair_tiles(q.na), groups = (tiles + PAIR_GROUP - 1) / PAIR_GROUP;
+    b.long_cap = (uint32_t)std::min<uint64_t>(sh.slots / 64 + 1, q.na);
+    take(sc, sh.b);
+    if (sh.split) take(sc, sh.l1);
+    // (the pairs are placed where the level between was: no more than went through it)
+    const uint64_t placed = sh.split ? std::min(sh.slots, slots(sh.l1)) : sh.slots;
+    b.t = sh.split ? sh.l1.base : sc.get<uint64_t>(placed);
+    b.td = sc.get<uint8_t>(placed);
     b.rank = sc.get<uint32_t>(sh.slots);
     b.kd = sc.get<uint8_t>(sh.slots);
     b.kept = sc.get<uint32_t>(sh.b.nbins);
-    const uint64_t tiles = pair_tiles(q.na), groups = (tiles + PAIR_GROUP - 1) / PAIR_GROUP;
+    b.icnt = sc.get<uint32_t>(q.na);
     b.sums = sc.get<uint32_t>(tiles);
     b.groups = sc.get<uint32_t>(groups);
     b.off = sc.get<uint32_t>(q.na + 1);
-    b.t = sc.get<uint64_t>(sh.slots);
-    b.td = sc.get<uint8_t>(sh.slots);
-    b.long_cap = (uint32_t)std::min<uint64_t>(sh.slots / 64 + 1, q.na);
     b.longs = sc.get<uint32_t>(b.long_cap);
     b.state = sc.get<PairState>(1);
+    b.missed = sc.get<unsigned long long>(1);
     b.err = cl.lb_err();
     Scratch res(c);  // the result arrays, handed over at the end
     uint32_t* oi = res.get<uint32_t>(cap);
@@ -155,12 +169,16 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     launch_zero({{b.icnt, q.na},
                  {b.groups, groups},
                  {reinterpret_cast<uint32_t*>(b.state), sizeof(PairState) / 4},
+                 {reinterpret_cast<uint32_t*>(b.missed), 2},
                  cursors(sh.b),
                  sh.split && run ? cursors(lists) : ZeroRange{},
                  cursors(sh.l1)},
                 s);
     if (run) {
-      produce(sh.split ? lists : sh.b);
+      PairBins& to = sh.split ? lists : sh.b;
+      to.expect = (uint32_t)std::min<uint64_t>(guess, 0xFFFFFFFFull);
+      to.missed = b.missed;
+      produce(to);
       cl.tm.mark(stage, (double)nkeys * 8 + (double)guess * 8, 1);
     }
     if (sh.split) {
@@ -179,7 +197,10 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     uint64_t raw = 0, more = 0;
     for (uint64_t x : st.raw) raw += x;
     const uint64_t kept = st.count;
-    const bool overflow = st.flags & PF_OVERFLOW;
+    const bool missed = !sh.split && st.missed;
+    if (missed) raw += st.missed;
+    const bool overflow = (st.flags & PF_OVERFLOW) || missed;
+    if (run) to_lists = st.missed != 0;
     // (the sorts of `check` report here too, in the read-back after them)
     const uint32_t err = st.counters[CNT_LBERR];
     if (err & SD_ERRBIT_LOOKBACK) throw Error{SD_E_HIP, "internal error: a look-back wait timed out"};
@@ -200,7 +221,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
       const bool full = st.flags & PF_LISTS;
       held = sh.split && !full && next != PairNext::again;
       const bool mid = st.flags & PF_MID;
-      if (overflow && !full && want <= guess) {
+      if (overflow && !full && !missed && want <= guess) {
         uneven = uneven || mid;
         if (!mid) ++spread;
       }
@@ -216,6 +237,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     }
     c->out_hint[hint_raw] = raw;
     c->out_hint[hint_keys] = nkeys;
+    c->out_hint[hint_lists] = to_lists;
     out->ncand = raw;
     if (st.flags & PF_LONG) {
       // a first id with thousands of pairs: the kept pairs take the radix sort

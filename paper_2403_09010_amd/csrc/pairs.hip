@@ -51,7 +51,7 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
   const uint32_t tile = tiles < 64 ? blockIdx.x / nsub : blockIdx.x - sub * tiles;
   const uint32_t bin = sub >> in.nxl, x = in.nxl ? sub & 7u : 0u;
   const unsigned long long put =
-      in.lists ? in.lists[x * sd::PAIR_LIST_STRIDE] : in.cursor[x * in.nbins + bin];
+      in.lists ? in.lists[x * sd::PAIR_LIST_STRIDE] : in.cursor[(x * in.nbins + bin) << in.pad];
   if (tile == 0 && threadIdx.x == 0) {
     if (in.lists) state->lists[x] = put;
     if (put > in.region) {
@@ -59,7 +59,11 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
       atomicAdd(&state->raw[sub % sd::PACK_SUMS], put - in.region);
     }
   }
-  const uint32_t c = (uint32_t)min(put, (unsigned long long)in.region), t0 = tile * TILE;
+  // (a 64-bit minimum is a vector operation: the tile's bounds would follow it out of
+  // the scalar registers)
+  const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane(
+      (int)(uint32_t)min(put, (unsigned long long)in.region));
+  const uint32_t t0 = tile * TILE;
   if (t0 >= c) return;
   const uint32_t m = min((uint32_t)TILE, c - t0);
   const uint64_t* __restrict__ src = in.base + (uint64_t)((bin << in.nxl) + x) * in.region + t0;
@@ -83,7 +87,7 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
   }
   __syncthreads();
   const uint32_t slots = (o.nbins << o.nxl) * o.region;
-  partition_tail<NT, TILE, 9, true>(s_e, m, s_cnt, s_tmp, lb, digit, bin << lb, o.base, o.cursor,
+  partition_tail<NT, TILE, 9, true, true>(s_e, m, s_cnt, s_tmp, lb, digit, bin << lb, o.base, o.cursor,
                                     o.region, o.nbins, o.nxl, slots, nullptr, 0, nullptr);
 }
 
@@ -113,7 +117,7 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
   uint32_t total = 0;
   bool over = false;
   for (uint32_t x = 0; x < nx; ++x) {
-    const uint32_t c = in.cursor[x * in.nbins + bin];
+    const uint32_t c = in.cursor[(x * in.nbins + bin) << in.pad];
     total += c;
     over |= c > in.region;
   }
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(NT) void k_pair_verify(
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t parts = NW > nx ? NW / nx : 1u;
   for (uint32_t x = w & (nx - 1); x < nx; x += NW) {
-    const uint32_t c = in.cursor[x * in.nbins + bin];
+    const uint32_t c = in.cursor[(x * in.nbins + bin) << in.pad];
     const uint64_t* p = in.base + base + (uint64_t)x * in.region;
     for (uint32_t t0 = (w >> in.nxl) * 64; t0 < c; t0 += parts * 64 * PR_ROWS) {
       uint64_t e[PR_ROWS];
@@ -321,7 +325,6 @@ __global__ __launch_bounds__(PS_NT) void k_pair_scan(sd::PairBufs b, uint64_t n)
 // pair (8.6M pairs of 10M sequences: 0.47 ms; with the two ids in words of
 // their own 0.66).
 __global__ __launch_bounds__(64) void k_pair_place(sd::PairBins in, sd::PairBufs b) {
-  if (b.state->flags & sd::PF_OVERFLOW) return;  // (the attempt is not answered)
   const uint32_t n = b.kept[blockIdx.x];
   const uint64_t base = (uint64_t)(blockIdx.x << in.nxl) * in.region;
   for (uint32_t x = threadIdx.x; x < n; x += 64) {
@@ -382,7 +385,10 @@ __global__ __launch_bounds__(256) void k_pair_order(sd::PairBufs b, uint64_t n,
   __shared__ uint64_t s_v[PR_MAX];
   const uint64_t total = b.off[n];
   if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) b.state->count = total;
+    if (threadIdx.x == 0) {
+      b.state->count = total;
+      b.state->missed = *b.missed;
+    }
     if (threadIdx.x < sd::PAIR_COUNTERS) b.state->counters[threadIdx.x] = counters[threadIdx.x];
   }
   // (nothing to order: the attempt is not answered, or the placed pairs are sorted)

@@ -643,7 +643,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   uint32_t* s_tw = reinterpret_cast<uint32_t*>(lds + F::TWICE_AT);
   uint64_t* s_e = reinterpret_cast<uint64_t*>(lds);
   uint32_t* s_bk = reinterpret_cast<uint32_t*>(lds + F::BK_AT);
-  __shared__ uint32_t s_n, s_np;
+  __shared__ uint32_t s_n;
   __shared__ unsigned long long s_at;
   __shared__ uint32_t s_tmp[NT / 64];
   const uint32_t bin = blockIdx.x, nx = 1u << in.nxl;
@@ -769,10 +769,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     __syncthreads();
     const uint32_t m = s_n;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      s_n = 0;
-      s_np = 0;
-    }
+    if (threadIdx.x == 0) s_n = 0;
     if (m > (uint32_t)F::FULL) {
       if (rounds == 1) {
         // again in rounds of about half a capacity
@@ -829,11 +826,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     __syncthreads();
     // (every bucket's entry is its end now)
     // each element pairs with the later ones of its bucket that share its hash
+    // (not unrolled: three copies of seven times the loop took registers from the
+    // passes over the elements)
     auto each_pair = [&](auto&& f) {
-#pragma unroll
-      for (int r = 0; r < PER; ++r) {
-        const uint32_t i = threadIdx.x + r * NT;
-        if (i >= m) break;
+#pragma unroll 1
+      for (uint32_t i = threadIdx.x; i < m; i += NT) {
         const uint64_t a = s_e[i];
         const uint32_t end = s_bk[(uint32_t)(a >> bkshift) & (F::NBK - 1)];
         for (uint32_t y = i + 1; y < end; ++y) {
@@ -845,39 +842,44 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
         }
       }
     };
-    if (out.lb == 0) {
-      // a list per XCD: the pairs are counted, reserved together and written
-      // (a few bins hold groups of thousands: nothing here is per pair but
-      // its write)
-      uint32_t cnt = 0, tot;
-      each_pair([&](uint64_t) { ++cnt; });
-      unsigned long long at = block_excl_scan<NT>(cnt, s_tmp, &tot);
+    // the pairs are counted first: a list per XCD takes them with one reservation
+    // (a few bins hold groups of thousands: nothing here is per pair but its write),
+    // and where they go to their bins they collect behind the candidates, so that
+    // their reservations are in flight side by side
+    uint32_t cnt = 0, tot;
+    each_pair([&](uint64_t) { ++cnt; });
+    const uint32_t at0 = block_excl_scan<NT>(cnt, s_tmp, &tot);
+    if (tot > out.limit && threadIdx.x == 0)
+      atomicAdd(out.missed, out.lb == 0 ? 1ull : (unsigned long long)tot);
+    if (tot == 0 || (tot > out.limit && out.lb > 0)) {
+      // (uniform: on to the barrier)
+    } else if (out.lb == 0) {
       const uint32_t x = blockIdx.x & ((1u << out.nxl) - 1);
-      if (threadIdx.x == 0 && tot) s_at = list_reserve(out, x, tot);
+      if (threadIdx.x == 0) s_at = list_reserve(out, x, tot);
       __syncthreads();
       if (cnt) {
-        at += s_at;
-        uint64_t* dst = out.base + (uint64_t)x * out.region;
+        const uint32_t room = sd::list_room(s_at, tot, out.region);
+        uint64_t* dst = out.base + (uint64_t)x * out.region + s_at;
+        uint32_t at = at0;
         each_pair([&](uint64_t v) {
-          if (at < out.region) dst[at] = v;
+          if (at < room) dst[at] = v;
           ++at;
         });
       }
     } else {
-      // to their bins: pairs collect behind the candidates and leave together,
-      // so that their reservations are in flight side by side
       uint64_t* s_pair = s_e + m;
       const uint32_t room = F::CAP - m;
-      each_pair([&](uint64_t v) {
-        const uint32_t at = atomicAdd(&s_np, 1u);
-        if (at < room)
-          s_pair[at] = v;
-        else
-          pair_put(out, v);
-      });
-      __syncthreads();
-      const uint32_t np = min(s_np, room);
-      for (uint32_t i = threadIdx.x; i < np; i += NT) pair_put(out, s_pair[i]);
+      for (uint32_t w = 0; w < tot; w += room) {
+        uint32_t at = at0 - w;  // (below 0: a large number)
+        each_pair([&](uint64_t v) {
+          if (at < room) s_pair[at] = v;
+          ++at;
+        });
+        __syncthreads();
+        const uint32_t np = min(tot - w, room);
+        for (uint32_t i = threadIdx.x; i < np; i += NT) pair_put(out, s_pair[i]);
+        __syncthreads();
+      }
     }
     __syncthreads();  // the next round rewrites the LDS
   }
@@ -1448,6 +1450,17 @@ static void gen_t(const u128* seq, const uint32_t* vcnt, uint32_t n, int k, uint
   }
 }
 
+// The bins as a producer's workgroups see them. One with a sixteenth of all expected
+// candidates holds copies: far more pairs than bins were sized for, which would queue
+// one by one for their counters (10,000 sequences with 300 copies of one, k = 2,
+// 5.4M candidates: 10 ms). They are only counted then, and go to lists in the next
+// attempt.
+static PairBins with_limit(const PairBins& out) {
+  PairBins o = out;
+  o.limit = std::max(4096u, out.expect / 16);
+  return o;
+}
+
 // Sequences per workgroup (at most `most`): their variants fill 15/16 of the
 // tile on average.
 static uint32_t seqs_per_tile(uint64_t n, uint64_t nkeys, uint32_t tile, uint32_t most) {
@@ -1540,7 +1553,7 @@ static void filter_t(const PartOut& in, const PairBins& out, uint64_t* big,
                      unsigned long long* nbig, hipStream_t s) {
   allow_lds(&sdk::k_filter_group<NT, SB, LDS, WIDE>, LDS);
   hipLaunchKernelGGL((sdk::k_filter_group<NT, SB, LDS, WIDE>), dim3(in.nbins), dim3(NT), LDS, s, in,
-                     out, big, nbig);
+                     with_limit(out), big, nbig);
 }
 
 template <bool WIDE>

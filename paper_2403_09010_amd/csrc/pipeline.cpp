@@ -529,20 +529,23 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   Cands extra;  // candidates of the listed ranges
   uint64_t listed = 0;
   bool again = false;  // (a call's counters start as zeros)
+  bool generated = false;
+  auto partition = [&] {
+    generated = true;
+    generate(p1, idbits);
+    cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
+    if (lb1 < lb) {
+      launch_part_split(p1, p, s);
+      cl.tm.mark("part_split", (double)nk * 16, 1);
+    }
+  };
+  if (!memory_bounded(c)) partition();
   TileOut out;
   const bool done = binned_pairs(
       cl, hint, nk, q,
       [&](const PairBins& bins) {
-        if (again) {
-          launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
-        } else {
-          generate(p1, idbits);
-          cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
-          if (lb1 < lb) {
-            launch_part_split(p1, p, s);
-            cl.tm.mark("part_split", (double)nk * 16, 1);
-          }
-        }
+        if (again) launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
+        if (!generated) partition();
         again = true;
         launch_filter_group(p, nk, idbits, bins, big, nbig, s);
         launch_pair_scatter(extra.p, extra.n, bins, s);

@@ -365,6 +365,11 @@ constexpr uint32_t TYPICAL_VARIANTS[4] = {1, 16, 110, 500}, MOST_VARIANTS[4] = {
 constexpr uint64_t UNREAD_KEYS = 1ull << 20;
 PartOut part_out(Call& cl, uint64_t nk, int lb, int nxl, uint64_t over_cap, uint32_t* over_count);
 
+// Under a budget or in a fixed area a search takes all its memory before its first
+// launch, so that one that does not fit has done nothing for nothing; otherwise the
+// generator runs while the host takes the rest (8 us), and room is not saved.
+inline bool memory_bounded(const sd_ctx* c) { return c->budget || c->arena; }
+
 // Runs a path that needs more scratch than the sorted one; where the memory
 // does not suffice (a budget, a fixed area), everything it took is given back
 // and the sorted path runs instead.

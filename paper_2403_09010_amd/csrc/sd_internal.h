@@ -37,7 +37,7 @@ struct ZeroRange {
   uint32_t* p;
   uint64_t n;
 };
-constexpr int ZERO_RANGES = 6;
+constexpr int ZERO_RANGES = 7;
 void launch_zero(std::initializer_list<ZeroRange> ranges, hipStream_t s);
 void launch_fill_u64(uint64_t* p, uint64_t v, uint64_t n, hipStream_t s);
 uint32_t out_shards();
@@ -286,9 +286,14 @@ void launch_part_split(const PartOut& in, const PartOut& o, hipStream_t s);
 // per region, counted in lists (pair_list.h) instead.
 struct PairBins {
   uint64_t* base;
-  uint32_t* cursor;  // nbins << nxl, zeroed before the producer
+  uint32_t* cursor;  // (nbins << nxl) << pad (word (x * nbins + b) << pad), zeroed before the producer
   uint32_t region, nbins;
   int lb, nxl;
+  int pad = 0;
+  // a workgroup with more pairs than `limit` puts none and adds them to *missed, or,
+  // with lists, puts them and adds 1
+  uint32_t expect = 0, limit = ~0u;
+  unsigned long long* missed = nullptr;
   unsigned long long* lists = nullptr;  // PAIR_LIST_STRIDE << nxl, zeroed too
 };
 // Verification of binned candidates (pairs.hip). mode 0: Levenshtein distance
@@ -314,6 +319,7 @@ struct PairState {  // zeroed before the producer; read back when the search is 
   unsigned long long count;           // pairs kept
   unsigned long long raw[PACK_SUMS];  // candidates put, in parts
   unsigned long long lists[8];        // with lists: candidates sent to each
+  unsigned long long missed;          // a copy of the producer's
   uint32_t counters[PAIR_COUNTERS];   // a copy of the call's counters
 };
 struct PairBufs {
@@ -329,6 +335,7 @@ struct PairBufs {
   uint32_t* longs;  // first ids with many pairs
   uint32_t long_cap;
   PairState* state;
+  unsigned long long* missed;  // zeroed: the producer's, on a line that no other kernel adds to
   uint32_t* err;
 };
 // most distinct candidates a bin may hold

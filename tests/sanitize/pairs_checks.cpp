@@ -202,7 +202,7 @@ int main() {
       idle = idle && (o.found || (o.code == SD_E_NOMEM && log_.empty()));
     } while (!o.found && at < 100);
     allocations = 0;
-    check(o.found && at > 15 && idle, "all memory is taken before the first launch");
+    check(o.found && at > 12 && idle, "all memory is taken before the first launch");
   }
   {
     // a large search: lists, two levels of bins after them
@@ -226,6 +226,24 @@ int main() {
     o = search(100000000, {answer(500, 4000000, sd::PF_OVERFLOW), answer(500, 4000000)},
                {sd::PairNext::again});
     check(o.found && o.produced == 2, "more candidates: produced again");
+  }
+  {
+    // workgroups that only counted: their candidates go to lists, now and as long as
+    // there are such workgroups
+    sd_ctx ctx;
+    sd::PairState few = answer(500, 2000), counted = answer(500, 90000);
+    few.missed = 70000;
+    counted.missed = 3;
+    Outcome o = search(100000, {few, counted}, {}, &ctx);
+    check(o.found && o.produced == 2 && launches("split") == 2 && o.out.ncand == 90000,
+          "counted only: lists take them");
+    o = search(100000, {counted}, {}, &ctx);
+    check(o.found && o.produced == 1 && launches("split") == 2, "lists from the start");
+    counted.missed = 0;
+    o = search(100000, {counted}, {}, &ctx);
+    check(o.found && launches("split") == 2, "lists once more");
+    o = search(100000, {answer(500, 2000)}, {}, &ctx);
+    check(o.found && launches("split") == 0, "bins again");
   }
   std::printf(failures ? "%d checks failed\n" : "ok\n", failures);
   return failures ? 1 : 0;

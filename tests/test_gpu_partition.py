@@ -418,3 +418,15 @@ def test_copies_take_no_longer(paths, n, clones, copies, k):
     s = strings_of(23, n)
     q = [torch.from_numpy(a).cuda() for a in csr(s + [x for x in s[:clones] for _ in range(copies)])]
     not_slower(*paths, lambda ctx: ctx.self_search(*q, k), equal)
+
+
+# the first search of a context, whose bins are sized for sequences without copies
+@pytest.mark.parametrize("n,copies,k", [(10_000, 300, 2), (10_000, 1_000, 1), (3_000, 200, 3),
+                                        (40_000, 40, 2)])
+def test_first_search_with_copies(paths, n, copies, k):
+    from paper_2403_09010_amd import Context
+    s = strings_of(29, n)
+    c, o = csr(s + [s[9]] * copies)
+    print(f"[partition] the first search of a context: {n} sequences, {copies} copies, k={k}", flush=True)
+    with Context(0) as ctx:
+        equal(ctx.self_search(c, o, k), paths[1].self_search(c, o, k))
