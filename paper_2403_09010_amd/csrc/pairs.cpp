@@ -98,7 +98,8 @@ Shape shape(uint64_t guess, int k, int spread, bool uneven, bool lists) {
 
 }  // namespace
 
-bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q,
+bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
+                  const PairSeqs& q,
                   const std::function<void(const PairBins&)>& produce,
                   const std::function<PairNext(const uint32_t*, uint64_t*)>& check,
                   const std::function<TileOut(uint64_t*, uint64_t)>& sort_pairs,
@@ -116,6 +117,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, const PairSeqs& q
     const double last = (double)c->out_hint[hint_raw], keys = (double)c->out_hint[hint_keys];
     expect = std::max(expect, 1.1 * last * std::min(1.0, (double)nkeys / std::max(keys, 1.0)));
   }
+  expect = std::max(expect, (double)least);
   uint64_t guess = (uint64_t)expect + 1024;
   uint64_t cap = guess;
   int spread = 0;

@@ -59,6 +59,17 @@ __global__ __launch_bounds__(NT) void k_pair_split(sd::PairBins in, sd::PairBins
       atomicAdd(&state->raw[sub % sd::PACK_SUMS], put - in.region);
     }
   }
+  // (with a full list the attempt is not answered: the candidates that it has are
+  // counted, and nothing is split)
+  if (in.lists) {
+    bool full = false;
+    for (uint32_t y = 0; y < nsub; ++y) full |= in.lists[y * sd::PAIR_LIST_STRIDE] > in.region;
+    if (full) {
+      if (tile == 0 && threadIdx.x == 0)
+        atomicAdd(&state->raw[sub % sd::PACK_SUMS], min(put, (unsigned long long)in.region));
+      return;
+    }
+  }
   // (a 64-bit minimum is a vector operation: the tile's bounds would follow it out of
   // the scalar registers)
   const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane(

@@ -1052,28 +1052,67 @@ __device__ __forceinline__ uint32_t lower_bound_near(const uint64_t* __restrict_
   return lo;
 }
 
+constexpr int PB_ROWS = 4;
+
 // Few queries: each variant is looked up in the index as it is generated, from
 // its place by interpolation in its directory segment; no query element is
 // written, sorted or read.
 //
 // Bound: the latency of three to four dependent loads per variant. A variant
 // shared by many references would hold its wave up: beyond the first PB_SHORT
-// of a run, the rest is left to the whole workgroup.
-constexpr uint32_t PB_SHORT = 4, PB_QUEUE = 1024;
+// of a run, the rest is left to the waves of the workgroup, one run each; runs of more
+// than RUN_MOST, and of more than RUN_LONG beyond the first PB_LONGS (copies: a query's
+// every variant has one), are left to k_put_runs.
+constexpr uint32_t PB_SHORT = 4, PB_QUEUE = 1024, PB_LONGS = 16;
+constexpr uint32_t RUN_LONG = 256, RUN_MOST = 1024;
+
+// The end of the run that holds position p, by steps that double (E[p] >> idbits is h).
+__device__ __forceinline__ uint32_t run_end(const uint64_t* __restrict__ E, uint32_t p, uint32_t n,
+                                            uint64_t h, uint32_t idbits) {
+  uint64_t lo = (uint64_t)p + 1, step = 1;  // the end lies at lo or beyond
+  while (lo - 1 + step < n && (E[lo - 1 + step] >> idbits) == h) {
+    lo += step;
+    step *= 2;
+  }
+  uint64_t hi = min(lo - 1 + step, (uint64_t)n);
+  while (lo < hi) {
+    const uint64_t mid = (lo + hi) / 2;
+    if ((E[mid] >> idbits) == h)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return (uint32_t)lo;
+}
+
+// Adds the active lanes' runs to the queue (those past its room are only counted).
+__device__ __forceinline__ void push_run(const sd::RunQueue& q, uint32_t p, uint32_t n,
+                                         uint32_t id) {
+  const uint64_t act = __ballot(true);
+  uint32_t at = 0;
+  if (mask_rank(act) == 0) at = atomicAdd(q.count, (uint32_t)__popcll(act));
+  at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + mask_rank(act);
+  if (at < q.cap) q.runs[at] = sd::PairRun{p, n, id};
+}
+
 template <bool K3>
 __global__ __launch_bounds__(256) void k_gen_probe(const u128* __restrict__ seq, uint32_t nseq,
                                                    int k, const uint64_t* __restrict__ E,
                                                    uint32_t nkeys,
                                                    const uint32_t* __restrict__ seg_start,
                                                    const uint32_t* __restrict__ seg_end, int bits,
-                                                   uint32_t idbits, sd::PairBins out) {
+                                                   uint32_t idbits, sd::PairBins out,
+                                                   sd::RunQueue longs) {
   __shared__ uint64_t s_q[4 * 4 * GP_ROW];
   __shared__ uint64_t s_b[32], s_c[32];
   __shared__ uint32_t s_run[PB_QUEUE], s_id[PB_QUEUE];  // runs left over: position, query
-  __shared__ uint32_t s_runs;
+  __shared__ uint32_t s_runs, s_longs;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (threadIdx.x == 0) s_runs = 0;
+  if (threadIdx.x == 0) {
+    s_runs = 0;
+    s_longs = 0;
+  }
   if (threadIdx.x < 32) {
     s_b[threadIdx.x] = kHashTab.b[threadIdx.x];
     s_c[threadIdx.x] = kHashTab.c[threadIdx.x];
@@ -1100,8 +1139,12 @@ __global__ __launch_bounds__(256) void k_gen_probe(const u128* __restrict__ seq,
           s_id[x] = id;
           break;
         }
+        if (e - p > RUN_MOST && (E[p + RUN_MOST] >> idbits) == h) {
+          push_run(longs, p, run_end(E, p, e, h, idbits) - p, id);
+          break;
+        }
       }
-      pair_put(out, (uint64_t)id << 32 | (r & idmask));
+      pair_put<true>(out, (uint64_t)id << 32 | (r & idmask));
     }
   };
   {
@@ -1113,14 +1156,42 @@ __global__ __launch_bounds__(256) void k_gen_probe(const u128* __restrict__ seq,
   }
   __syncthreads();
   const uint32_t runs = min(s_runs, PB_QUEUE);
-  for (uint32_t q = w; q < runs; q += 4) {  // a wave per run, 64 references at a time
-    const uint32_t p0 = s_run[q];
-    const uint64_t id = (uint64_t)s_id[q] << 32, h = E[p0] >> idbits;
-    for (uint32_t p = p0 + lane;; p += 64) {
-      const uint64_t r = p < nkeys && p >= p0 ? E[p] : ~h << idbits;
-      const bool same = (r >> idbits) == h;
-      if (same) pair_put(out, id | (r & idmask));
-      if (__ballot(same) != ~0ull) break;
+  for (uint32_t q = w; q < runs; q += 4) {  // a wave per run
+    const uint32_t p0 = s_run[q], id = s_id[q];
+    const uint64_t h = E[p0] >> idbits;
+    auto at = [&](uint32_t i) {
+      const uint64_t p = (uint64_t)p0 + i + lane;
+      return p < nkeys ? E[p] : ~h << idbits;
+    };
+    const uint64_t r0 = at(0);
+    const bool same = (r0 >> idbits) == h;
+    if (__ballot(same) != ~0ull) {  // most runs end here
+      if (same) pair_put(out, (uint64_t)id << 32 | (r0 & idmask));
+      continue;
+    }
+    if (nkeys - p0 > RUN_LONG && (E[p0 + RUN_LONG] >> idbits) == h) {
+      uint32_t before = 0;
+      if (lane == 0) before = atomicAdd(&s_longs, 1u);
+      before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
+      if (before >= PB_LONGS ||
+          (nkeys - p0 > RUN_MOST && (E[p0 + RUN_MOST] >> idbits) == h)) {
+        if (lane == 0) push_run(longs, p0, run_end(E, p0, nkeys, h, idbits) - p0, id);
+        continue;
+      }
+    }
+    pair_put(out, (uint64_t)id << 32 | (r0 & idmask));
+    for (uint32_t i = 64;; i += 64 * PB_ROWS) {  // (PB_ROWS reads in flight together)
+      uint64_t r[PB_ROWS];
+      bool on[PB_ROWS];
+#pragma unroll
+      for (int u = 0; u < PB_ROWS; ++u) r[u] = at(i + u * 64);
+#pragma unroll
+      for (int u = 0; u < PB_ROWS; ++u) {
+        on[u] = (r[u] >> idbits) == h;
+        r[u] = (uint64_t)id << 32 | (r[u] & idmask);
+      }
+      pair_put_rows(out, r, on);
+      if (__ballot(on[PB_ROWS - 1]) != ~0ull) break;
     }
   }
 }
@@ -1134,10 +1205,9 @@ __global__ __launch_bounds__(256) void k_gen_probe(const u128* __restrict__ seq,
 //   3. the query elements with their marks collect in the first bitmap's place;
 //   4. the index survivors are put in order of a few more hash bits, and each
 //      query survivor is compared with its bucket.
-// If LDS does not hold the survivors, steps 2 to 4 run in rounds by further
-// hash bits; index survivors beyond any round (thousands of references sharing
-// a variant) are compared with every query survivor of the round piece by
-// piece.
+// If LDS does not hold the survivors, the steps run in rounds by further hash bits;
+// where it does not hold those of a round either, or would take too many rounds
+// (variants shared by thousands), the segment or the round is listed in `copies`.
 //
 // Bound: the one read of the index elements, at 8 bytes each. 200K queries
 // (20M variants) against 202M index elements: 0.48 ms (3.4 TB/s); looking each
@@ -1148,12 +1218,15 @@ constexpr int JB_TB = 15;                      // mark bitmap, bits
 constexpr uint32_t JB_CAP = 5056;              // index survivors in LDS (two workgroups on a CU)
 constexpr uint32_t JB_QCAP = (1u << JB_SB) / 64;  // query survivors
 constexpr int JB_NBK = 1024;
+constexpr uint32_t JB_SHARED = 48;  // index elements of one bucket: 4 on average
+constexpr uint32_t JB_ROUNDS = 16;  // most rounds
 constexpr size_t JB_LDS = (1 << JB_SB) / 8 + (1 << JB_TB) / 8 + JB_CAP * 8 + JB_NBK * 4;
 
 template <int NT, bool WIDE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_join_bins(
     sd::PartOut in, const uint64_t* __restrict__ E, const uint32_t* __restrict__ seg_start,
-    const uint32_t* __restrict__ seg_end, int bits, int sub, sd::PairBins out) {
+    const uint32_t* __restrict__ seg_end, int bits, int sub, sd::PairBins out,
+    sd::JoinParts copies) {
   constexpr uint32_t idbits = WIDE ? 32 : 24;
   constexpr uint32_t NW = NT / 64, ROW = 64 * FG_ROWS;
   constexpr uint32_t PER = (JB_CAP + NT - 1) / NT;
@@ -1163,7 +1236,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   uint32_t* s_br = s_bq + (1 << JB_SB) / 32;
   uint64_t* s_e = reinterpret_cast<uint64_t*>(s_br + (1 << JB_TB) / 32);
   uint32_t* s_bk = reinterpret_cast<uint32_t*>(s_e + JB_CAP);
-  __shared__ uint32_t s_n, s_nq;
+  __shared__ uint32_t s_n, s_nq, s_shared;
   __shared__ unsigned long long s_at;
   __shared__ uint32_t s_tmp[NW];
   // the workgroups of a query bin follow each other on one XCD, whose L2 then
@@ -1223,6 +1296,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     if (threadIdx.x == 0) {
       s_n = 0;
       s_nq = 0;
+      s_shared = 0;  // set where a bucket is large
     }
     __syncthreads();
     queries([&](const uint64_t(&e)[FG_ROWS], const bool(&valid)[FG_ROWS]) {
@@ -1281,17 +1355,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
       __syncthreads();
       continue;
     }
-    if (m > JB_CAP && rounds < (uint32_t)FG_MAX_ROUNDS) {
-      // again in rounds of about half the capacity (in twice as many, if a
-      // round was still too large: what it found before is found again and
-      // dropped with the repeats)
-      const uint32_t least = rounds * 2;
-      while (rounds < (uint32_t)FG_MAX_ROUNDS && (rounds < least || rounds * JB_CAP < 2 * m))
-        rounds <<= 1;
-      round = ~0u;
-      __syncthreads();
-      continue;
-    }
     // query survivors
     queries([&](const uint64_t(&e)[FG_ROWS], const bool(&valid)[FG_ROWS]) {
       uint64_t bal[FG_ROWS];
@@ -1320,37 +1383,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     __syncthreads();
     const uint32_t nq = s_nq;
     if (m > JB_CAP || nq > JB_QCAP) {
-      // one variant shared by thousands: every query element of the round
-      // against the sorted index segment
-      queries([&](const uint64_t(&es)[FG_ROWS], const bool(&valid)[FG_ROWS]) {
-#pragma unroll 1
-        for (int u = 0; u < FG_ROWS; ++u) {
-          uint64_t e = 0;
-          bool on = false;
-#pragma unroll
-          for (int q = 0; q < FG_ROWS; ++q)
-            if (q == u) {
-              e = es[q];
-              on = valid[q];
-            }
-          if (!on || !mine(e)) continue;
-          uint32_t lo = r0, hi = r1;
-          const uint64_t h = e >> idbits;
-          while (lo < hi) {
-            const uint32_t mid = lo + ((hi - lo) >> 1);
-            if ((E[mid] >> idbits) < h)
-              lo = mid + 1;
-            else
-              hi = mid;
-          }
-          for (; lo < r1; ++lo) {
-            const uint64_t r = E[lo];
-            if ((r >> idbits) != h) break;
-            pair_put(out, (e & idmask) << 32 | (r & idmask));
-          }
-        }
-      });
-      __syncthreads();
+      __syncthreads();  // (every thread has read the counts)
+      const uint32_t need = max(m / (JB_CAP / 5 * 4), nq / (JB_QCAP / 5 * 4)) + 1;
+      if (rounds == 1 && need <= JB_ROUNDS) {
+        while (rounds < need) rounds <<= 1;
+        round = ~0u;  // again, in rounds
+      } else if (threadIdx.x == 0) {
+        copies.at[atomicAdd(copies.count, 1u)] = sd::JoinPart{seg, round, rounds};
+      }
       continue;
     }
     // the index survivors by bucket
@@ -1370,6 +1410,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     {
       static_assert(JB_NBK <= NT, "one bucket per thread");
       const uint32_t c = threadIdx.x < (uint32_t)JB_NBK ? s_bk[threadIdx.x] : 0u;
+      if (c > JB_SHARED) s_shared = 1;
       uint32_t tot;
       const uint32_t ex = block_excl_scan<NT>(c, s_tmp, &tot);
       if (threadIdx.x < (uint32_t)JB_NBK) s_bk[threadIdx.x] = ex;
@@ -1392,18 +1433,26 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
         }
       }
     };
-    if (out.lb == 0) {  // a list per XCD, one reservation (see k_filter_group)
-      uint32_t cnt = 0, tot;
+    // counted first, as in k_filter_group, for a list or where there may be very many
+    uint32_t at = 0, cnt = 1, tot = 1;
+    if (out.lb == 0 || s_shared) {
+      cnt = 0;
       each_pair([&](uint64_t) { ++cnt; });
-      unsigned long long at = block_excl_scan<NT>(cnt, s_tmp, &tot);
+      at = block_excl_scan<NT>(cnt, s_tmp, &tot);
+    }
+    if (tot > out.limit && threadIdx.x == 0)
+      atomicAdd(out.missed, out.lb == 0 ? 1ull : (unsigned long long)tot);
+    if (tot == 0 || (tot > out.limit && out.lb > 0)) {
+      // (uniform: on to the barrier)
+    } else if (out.lb == 0) {
       const uint32_t x = blockIdx.x & ((1u << out.nxl) - 1);
-      if (threadIdx.x == 0 && tot) s_at = list_reserve(out, x, tot);
+      if (threadIdx.x == 0) s_at = list_reserve(out, x, tot);
       __syncthreads();
       if (cnt) {
-        at += s_at;
-        uint64_t* dst = out.base + (uint64_t)x * out.region;
+        const uint32_t room = sd::list_room(s_at, tot, out.region);
+        uint64_t* dst = out.base + (uint64_t)x * out.region + s_at;
         each_pair([&](uint64_t v) {
-          if (at < out.region) dst[at] = v;
+          if (at < room) dst[at] = v;
           ++at;
         });
       }
@@ -1411,6 +1460,137 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
       each_pair([&](uint64_t v) { pair_put(out, v); });
     }
     __syncthreads();  // the next round rewrites the LDS
+  }
+}
+
+// Query elements that a join left: those of the listed segments or rounds (a
+// workgroup takes one region of one of them) and, from the last gridDim.y - 1 on, those
+// of the overflow area. Each is looked up, and its run of equal hashes queued.
+__global__ __launch_bounds__(256) void k_join_runs(sd::PartOut in, const uint64_t* __restrict__ E,
+                                                   const uint32_t* __restrict__ seg_start,
+                                                   const uint32_t* __restrict__ seg_end, int bits,
+                                                   int sub, uint32_t idbits, sd::JoinParts parts,
+                                                   sd::RunQueue queue) {
+  const uint32_t idmask = (uint32_t)((1ull << idbits) - 1);
+  auto look_up = [&](uint64_t e, uint32_t r0, uint32_t r1) {
+    const uint64_t h = e >> idbits;
+    uint32_t lo = r0, hi = r1;
+    while (lo < hi) {
+      const uint32_t mid = lo + ((hi - lo) >> 1);
+      if ((E[mid] >> idbits) < h)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    if (lo < r1 && (E[lo] >> idbits) == h)
+      push_run(queue, lo, run_end(E, lo, r1, h, idbits) - lo, (uint32_t)e & idmask);
+  };
+  const uint32_t nx = 1u << in.nxl;
+  if (blockIdx.y == nx) {
+    const uint32_t n = min(*in.over_count, in.cap - in.slots);
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+      const uint64_t e = in.elem[in.slots + i];
+      const uint32_t seg = bits ? (uint32_t)(e >> 32) >> (32 - bits) : 0u;
+      look_up(e, seg_start[seg], seg_end[seg]);
+    }
+    return;
+  }
+  const int segbits = in.lb + sub;
+  const int rdshift = sd::hash_shift(segbits, __builtin_ctz(JB_NBK) + 6, (int)idbits);
+  const uint32_t np = *parts.count;
+  for (uint32_t y = blockIdx.x; y < np; y += gridDim.x) {
+    const sd::JoinPart part = parts.at[y];
+    const uint32_t cu = blockIdx.y * in.nbins + (part.seg >> sub);
+    uint32_t c = in.cursor[cu];
+    if (c > in.region) c = in.fill[cu];
+    const uint32_t r0 = seg_start[part.seg << (bits - segbits)];
+    const uint32_t r1 = seg_end[((part.seg + 1) << (bits - segbits)) - 1];
+    const uint64_t* __restrict__ p =
+        in.elem + (uint64_t)(((part.seg >> sub) << in.nxl) + blockIdx.y) * in.region;
+    for (uint32_t i = threadIdx.x; i < c; i += 256) {
+      const uint64_t e = p[i];
+      if ((uint32_t)(e >> 32) >> (32 - segbits) == part.seg &&
+          (part.rounds == 1 || ((uint32_t)(e >> rdshift) & (part.rounds - 1)) == part.round))
+        look_up(e, r0, r1);
+    }
+  }
+}
+
+constexpr uint32_t PUT_LONG = 256;
+
+// The candidates of the queued runs, `per` runs a workgroup: long ones one after the
+// other by all threads, the others by the wave that read them, one reservation for all
+// of a wave's and output positions shared out evenly (the owner of each by a search
+// in the wave's scanned lengths).
+//
+// Bound: the candidate writes. 369M candidates, nearly all of 33,000 runs of 9,000:
+// 1.4 ms together with the join before it; 350 when each query's lane walked its run.
+__global__ __launch_bounds__(256) void k_put_runs(const uint64_t* __restrict__ E, uint32_t idbits,
+                                                  sd::RunQueue q, uint32_t per, sd::PairBins out) {
+  __shared__ uint32_t s_long[256], s_nl;
+  __shared__ unsigned long long s_at;
+  const uint64_t idmask = (1ull << idbits) - 1;
+  const uint32_t n = min(*q.count, q.cap), lane = threadIdx.x & 63u;
+  for (uint64_t b0 = (uint64_t)blockIdx.x * per; b0 < n; b0 += (uint64_t)gridDim.x * per) {
+    const uint32_t m = (uint32_t)min((uint64_t)per, n - b0);
+    if (threadIdx.x == 0) s_nl = 0;
+    __syncthreads();
+    sd::PairRun r{0, 0, 0};
+    if (threadIdx.x < m) r = q.runs[b0 + threadIdx.x];
+    if (r.n >= PUT_LONG) {
+      s_long[atomicAdd(&s_nl, 1u)] = threadIdx.x;
+      r.n = 0;
+    }
+    const uint32_t incl = wave_incl_scan(r.n), tot = __shfl(incl, 63, 64), excl = incl - r.n;
+    if (tot) {
+      const uint32_t x = (blockIdx.x + (threadIdx.x >> 6)) & ((1u << out.nxl) - 1);
+      unsigned long long at = 0;
+      uint32_t room = 0;
+      if (out.lb == 0) {
+        if (lane == 0) at = list_reserve(out, x, tot);
+        at = first_lane(at);
+        room = sd::list_room(at, tot, out.region);
+      }
+      uint64_t* dst = out.base + (uint64_t)x * out.region + at;
+      for (uint32_t t0 = 0; t0 < tot; t0 += 64) {
+        const uint32_t t = t0 + lane;
+        uint32_t lo = 0, hi = 63;  // the first lane whose inclusive count exceeds t
+        while (lo < hi) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (__shfl(incl, (int)mid, 64) <= t)
+            lo = mid + 1;
+          else
+            hi = mid;
+        }
+        const uint32_t p = __shfl(r.p, (int)lo, 64) + t - __shfl(excl, (int)lo, 64);
+        const uint64_t id = __shfl(r.id, (int)lo, 64);
+        if (t < tot) {
+          const uint64_t v = id << 32 | (E[p] & idmask);
+          if (out.lb > 0)
+            pair_put(out, v);
+          else if (t < room)
+            dst[t] = v;
+        }
+      }
+    }
+    __syncthreads();
+    const uint32_t nl = s_nl;
+    for (uint32_t y = 0; y < nl; ++y) {
+      const sd::PairRun l = q.runs[b0 + s_long[y]];
+      const uint64_t id = (uint64_t)l.id << 32;
+      if (out.lb > 0) {
+        for (uint32_t i = threadIdx.x; i < l.n; i += 256) pair_put(out, id | (E[l.p + i] & idmask));
+        continue;
+      }
+      const uint32_t x = (blockIdx.x + y) & ((1u << out.nxl) - 1);
+      __syncthreads();  // (the place of the run before is read)
+      if (threadIdx.x == 0) s_at = list_reserve(out, x, l.n);
+      __syncthreads();
+      const uint32_t room = sd::list_room(s_at, l.n, out.region);
+      uint64_t* dst = out.base + (uint64_t)x * out.region + s_at;
+      for (uint32_t i = threadIdx.x; i < room; i += 256) dst[i] = id | (E[l.p + i] & idmask);
+    }
+    __syncthreads();
   }
 }
 
@@ -1454,7 +1634,8 @@ static void gen_t(const u128* seq, const uint32_t* vcnt, uint32_t n, int k, uint
 // candidates holds copies: far more pairs than bins were sized for, which would queue
 // one by one for their counters (10,000 sequences with 300 copies of one, k = 2,
 // 5.4M candidates: 10 ms). They are only counted then, and go to lists in the next
-// attempt.
+// attempt. (200,000 queries of 2M references without copies: 670,000 candidates, more
+// than 4,096 of them from some workgroups.)
 static PairBins with_limit(const PairBins& out) {
   PairBins o = out;
   o.limit = std::max(4096u, out.expect / 16);
@@ -1577,30 +1758,46 @@ void launch_filter_group(const PartOut& in, uint64_t nkeys, uint32_t idbits, con
 
 void launch_gen_probe(const u128* seq, uint64_t n, int k, const uint64_t* E, uint32_t nkeys,
                       const uint32_t* seg_start, const uint32_t* seg_end, int bits, uint32_t idbits,
-                      const PairBins& out, hipStream_t s) {
+                      const PairBins& out, const RunQueue& longs, hipStream_t s) {
   if (!n) return;
   const unsigned g = (unsigned)((n + 7) / 8);
   if (k == 3)
     hipLaunchKernelGGL((sdk::k_gen_probe<true>), dim3(g), dim3(256), 0, s, seq, (uint32_t)n, k, E, nkeys,
-                       seg_start, seg_end, bits, idbits, out);
+                       seg_start, seg_end, bits, idbits, out, longs);
   else
     hipLaunchKernelGGL((sdk::k_gen_probe<false>), dim3(g), dim3(256), 0, s, seq, (uint32_t)n, k, E, nkeys,
-                       seg_start, seg_end, bits, idbits, out);
+                       seg_start, seg_end, bits, idbits, out, longs);
 }
 
 void launch_join_bins(const PartOut& in, const uint64_t* E, const uint32_t* seg_start,
                       const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
-                      const PairBins& out, hipStream_t s) {
+                      const PairBins& out, const JoinParts& copies, hipStream_t s) {
   if (in.lb + sub > bits) throw Error{SD_E_HIP, "internal error: join segments finer than the index"};
   auto launch = [&](auto kernel) {
     allow_lds(kernel, sdk::JB_LDS);
     hipLaunchKernelGGL(kernel, dim3(in.nbins << sub), dim3(1024), sdk::JB_LDS, s, in, E, seg_start,
-                       seg_end, bits, sub, out);
+                       seg_end, bits, sub, with_limit(out), copies);
   };
   if (idbits == 32)
     launch(&sdk::k_join_bins<1024, true>);
   else
     launch(&sdk::k_join_bins<1024, false>);
+}
+
+uint32_t join_parts(const PartOut& in, int sub) { return (in.nbins << sub) * sdk::JB_ROUNDS; }
+
+void launch_join_runs(const PartOut& in, const uint64_t* E, const uint32_t* seg_start,
+                      const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
+                      const JoinParts& copies, const RunQueue& queue, hipStream_t s) {
+  hipLaunchKernelGGL(sdk::k_join_runs, dim3(256, (1u << in.nxl) + 1), dim3(256), 0, s, in, E,
+                     seg_start, seg_end, bits, sub, idbits, copies, queue);
+}
+
+void launch_put_runs(const uint64_t* E, uint32_t idbits, const RunQueue& queue, uint64_t expect,
+                     const PairBins& out, hipStream_t s) {
+  // runs a workgroup: fewer of few runs, which may be long
+  const uint32_t per = (uint32_t)std::min<uint64_t>(256, std::max<uint64_t>(8, expect / 2048));
+  hipLaunchKernelGGL(sdk::k_put_runs, dim3(2048), dim3(256), 0, s, E, idbits, queue, per, out);
 }
 
 }  // namespace sd

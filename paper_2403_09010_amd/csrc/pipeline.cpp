@@ -542,7 +542,7 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   if (!memory_bounded(c)) partition();
   TileOut out;
   const bool done = binned_pairs(
-      cl, hint, nk, q,
+      cl, hint, nk, 0, q,
       [&](const PairBins& bins) {
         if (again) launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
         if (!generated) partition();

@@ -112,7 +112,8 @@ constexpr uint64_t PROBE_RATIO = 64;
 // A tile of queries against a hashed index through the pair bins: few queries
 // look their variants up as they are generated, many are partitioned into bins
 // and joined with the index's segments. Returns false where the general path
-// has to run (positions beyond 32 bits, no shape of the pair bins that fits).
+// has to run (positions beyond 32 bits, no shape of the pair bins that fits, more
+// copies than the overflow area holds).
 bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
                        const WeightedSpec* w, TileOut* out) {
   sd_ctx* c = cl0.c;
@@ -143,6 +144,8 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
   // and of its index elements about 3% have a query of the same hash and as many
   // others pass as the bitmap is filled
   PartOut p{};
+  JoinParts parts{};
+  uint64_t over_cap = 0;
   int sub = 0;
   if (join) {
     int lb = 1;
@@ -154,9 +157,28 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
       return mq > JOIN_QUERY_MAX || mr * (mq / JOIN_BITMAP + 0.03) > JOIN_SURVIVORS;
     };
     while (lb + sub < idx->bits && too_many()) ++sub;
-    p = part_out(cl, nk, lb, nk >= (2u << 20) ? 3 : 0, 4096, cl.counters + CNT_OVER);
+    // (copies among the queries go to the overflow area: room for all elements where
+    // memory is not bounded)
+    const int nxl = nk >= (2u << 20) ? 3 : 0;
+    over_cap = !memory_bounded(c) && nk <= (1ull << 28) ? nk : nk / 16 + 65536;
+    p = part_out(cl, nk, lb, nxl, over_cap, cl.counters + CNT_OVER);
+    parts = JoinParts{sc.get<JoinPart>(join_parts(p, sub)), cl.counters + CNT_PARTS};
   }
-  bool again = false;
+  const char* const hint = join ? "pairs/join" : "pairs/probe";
+  const std::string hint_runs = std::string(hint) + "/runs";
+  // copies, if there are any: what the join left and long runs are followed up by
+  // kernels of their own (known from the attempt before, or the last search)
+  uint64_t runs = c->out_hint[hint_runs];
+  bool follow = runs > 0, again = false;
+  runs += runs / 4 + 4096;
+  RunQueue queue{nullptr, 0, cl.counters + CNT_RUNS};
+  bool generated = !join;
+  auto generate = [&] {
+    generated = true;
+    launch_gen_part(seq, vcnt, q.n, nk, k, idx->idbits, p, s);
+    cl.tm.mark("q_vargen_part", (double)nk * 8 + (double)q.n * 20, 1);
+  };
+  if (join && !memory_bounded(c)) generate();
   const bool hamming = c->metric == SD_METRIC_HAMMING;
   const PairSeqs ps{w ? planes : hamming ? seq : planes,
                     idx->ref_seq,
@@ -170,25 +192,42 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
                     w ? w->indel : 0,
                     w ? w->max_score : 0};
   const bool done = binned_pairs(
-      cl, join ? "pairs/join" : "pairs/probe", nk, ps,
+      // (queries that are in the index find each of their variants there: bins for that
+      // cost nothing, and their counters have lines of their own: 3,000 queries of 5M
+      // references 239 us, 233 with them)
+      cl, hint, nk, join ? 0 : std::min<uint64_t>(nk + nk / 4, 640 << 10), ps,
       [&](const PairBins& bins) {
-        if (join && !again) {
-          launch_gen_part(seq, vcnt, q.n, nk, k, idx->idbits, p, s);
-          cl.tm.mark("q_vargen_part", (double)nk * 8 + (double)q.n * 20, 1);
-        }
+        if (again) launch_fill_u32(cl.counters + CNT_PARTS, 0, 2, s);
+        if (!generated) generate();
         again = true;
+        if (follow && queue.cap < runs) {
+          queue.runs = sc.get<PairRun>(runs);
+          queue.cap = (uint32_t)runs;
+        }
         if (join)
           launch_join_bins(p, idx->E, idx->seg_start, idx->seg_end, idx->bits, sub, idx->idbits,
-                           bins, s);
+                           bins, parts, s);
         else
           launch_gen_probe(seq, q.n, k, idx->E, (uint32_t)idx->n_keys, idx->seg_start, idx->seg_end, idx->bits,
-                           idx->idbits, bins, s);
+                           idx->idbits, bins, queue, s);
+        if (!follow) return;
+        if (join)
+          launch_join_runs(p, idx->E, idx->seg_start, idx->seg_end, idx->bits, sub, idx->idbits,
+                           parts, queue, s);
+        launch_put_runs(idx->E, idx->idbits, queue, queue.cap, bins, s);
       },
       [&](const uint32_t* h, uint64_t*) {
         if (!known) raise_packed(q, h[CNT_ERR]);
         nk = pack_total(h);
-        if (!join || !h[CNT_OVER]) return PairNext::done;
-        join = false;  // copies of single variants overflow their bins: look them up
+        if (join && h[CNT_OVER] > over_cap) return PairNext::give_up;
+        const uint64_t over = join ? h[CNT_OVER] : 0, left = h[CNT_PARTS], queued = h[CNT_RUNS];
+        const bool copies = over || left || queued;
+        c->out_hint[hint_runs] = copies ? std::max<uint64_t>(queued, 1) : 0;
+        if (!copies || (follow && queued <= queue.cap)) return PairNext::done;
+        // what is queued, or about what the parts will queue
+        runs = std::max(queued, over + left * 4096) + 4096;
+        if (runs > (1ull << 30)) return PairNext::give_up;
+        follow = true;
         return PairNext::again;
       },
       [&](uint64_t* cand, uint64_t m) {

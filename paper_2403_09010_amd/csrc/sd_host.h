@@ -66,6 +66,8 @@ enum : int {
   CNT_STEPS = 108,    // u64 search comparisons of learned-index lookups
   CNT_OVER = 110,     // elements in the overflow area of a partition
   CNT_OVER1 = 111,    // the same of its first level
+  CNT_PARTS = 112,    // segments or rounds that a join left
+  CNT_RUNS = 113,     // queued runs of copies
   CNT_SUMS = 128,     // u64 partial sums of the variant counts
   CNT_TOTAL = CNT_SUMS + 2 * PACK_SUMS
 };
@@ -349,7 +351,9 @@ struct TileOut;
 // if no shape of the bins held them. out: pairs sorted by (i, j), in pool blocks. sort_pairs orders a
 // dense array of distinct verified pairs instead, where one first id has
 // thousands of them.
-bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, const PairSeqs& q,
+// least: the fewest candidates to expect, whatever came of the last search.
+bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, uint64_t least,
+                  const PairSeqs& q,
                   const std::function<void(const PairBins&)>& produce,
                   const std::function<PairNext(const uint32_t*, uint64_t*)>& check,
                   const std::function<TileOut(uint64_t*, uint64_t)>& sort_pairs,

@@ -360,19 +360,46 @@ void launch_pair_scatter(const uint64_t* cand, uint64_t n, const PairBins& o, hi
 // Query variants against a hashed index (E sorted by hash, a directory of
 // 2^bits segments), as (query << 32 | reference) candidates: looked up as they
 // are generated, or joined bin by bin from a partition of them (in.lb + sub <=
-// bits: 2^sub workgroups share a bin; elements in the overflow area are not
-// read).
+// bits: 2^sub workgroups share a bin).
+// A query's variant and the index elements [p, p + n) of its hash; runs of copies
+// wait in a queue (its counter, zeroed before, also counts those past its room).
+struct PairRun {
+  uint32_t p, n, id;
+};
+struct RunQueue {
+  PairRun* runs;
+  uint32_t cap;
+  uint32_t* count;
+};
+// (runs of more than a few hundred elements go to `longs`)
 void launch_gen_probe(const u128* seq, uint64_t n, int k, const uint64_t* E, uint32_t nkeys,
                       const uint32_t* seg_start, const uint32_t* seg_end, int bits, uint32_t idbits,
-                      const PairBins& out, hipStream_t s);
+                      const PairBins& out, const RunQueue& longs, hipStream_t s);
+// about `expect` queued runs' candidates
+void launch_put_runs(const uint64_t* E, uint32_t idbits, const RunQueue& queue, uint64_t expect,
+                     const PairBins& out, hipStream_t s);
 // most query elements and (expected) index survivors a join workgroup takes well:
 // LDS has room for 5,056, and more workgroups per bin read its query elements more
 // often (71M query elements against 500M: 1.05 ms with two for a bin, 1.25 with
 // the four that 2,600 asked for)
 constexpr double JOIN_QUERY_MAX = 20000, JOIN_SURVIVORS = 3900, JOIN_BITMAP = 1 << 18;
+// Segments, or one of their rounds, that a join leaves (join_parts of them at most;
+// the counter is zeroed before): launch_join_runs queues their runs, and those of the
+// overflow area.
+struct JoinPart {
+  uint32_t seg, round, rounds;
+};
+struct JoinParts {
+  JoinPart* at;
+  uint32_t* count;
+};
+uint32_t join_parts(const PartOut& in, int sub);
 void launch_join_bins(const PartOut& in, const uint64_t* E, const uint32_t* seg_start,
                       const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
-                      const PairBins& out, hipStream_t s);
+                      const PairBins& out, const JoinParts& copies, hipStream_t s);
+void launch_join_runs(const PartOut& in, const uint64_t* E, const uint32_t* seg_start,
+                      const uint32_t* seg_end, int bits, int sub, uint32_t idbits,
+                      const JoinParts& copies, const RunQueue& queue, hipStream_t s);
 // The bins' starts (off: nbins + 1 entries; cnt: nbins of scratch).
 void launch_bin_offsets(const PartOut& in, uint32_t* cnt, uint64_t* off, uint64_t* status,
                         uint32_t* tile_counter, uint32_t epoch, uint32_t* err, hipStream_t s);

@@ -123,7 +123,7 @@ Outcome search(uint64_t nkeys, std::vector<sd::PairState> a,
   const sd::PairSeqs q{nullptr, nullptr, nullptr, 1000, 1000, 2, 4, 1, nullptr, 0, 0};
   try {
     o.found = sd::binned_pairs(
-        cl, "pairs/test", nkeys, q,
+        cl, "pairs/test", nkeys, 0, q,
         [&](const sd::PairBins& b) {
           ++o.produced;
           rooms.push_back(b.region);

@@ -430,3 +430,34 @@ def test_first_search_with_copies(paths, n, copies, k):
     print(f"[partition] the first search of a context: {n} sequences, {copies} copies, k={k}", flush=True)
     with Context(0) as ctx:
         equal(ctx.self_search(c, o, k), paths[1].self_search(c, o, k))
+
+
+@pytest.fixture(scope="module")
+def sorting():
+    """The automatic path, and contexts whose candidates are sorted by either kind of passes."""
+    from paper_2403_09010_amd import Context
+    from paper_2403_09010_amd.symdel import OPT_PAIR_SORT
+    ctxs = [Context(0) for _ in range(3)]
+    for x in (1, 2):
+        ctxs[x].set_option(OPT_PAIR_SORT, x)
+    yield ctxs
+    for c in ctxs:
+        c.close()
+
+
+# references with thousands and hundreds of copies, copies among the queries, queries
+# that are all in the index, with three deletions too
+@pytest.mark.parametrize("nref,copies,k,queries,qcopies", [
+    (200_000, 9_000, 2, 50, 3), (200_000, 9_000, 2, 3_000, 300), (200_000, 9_000, 2, 200_000, 0),
+    (200_000, 500, 2, 3_000, 300), (300_000, 0, 2, 30_000, 3_000), (300_000, 0, 2, 30_000, 30_000),
+    (300_000, 0, 1, 100_000, 5_000), (100_000, 0, 3, 1_000, 0), (100_000, 0, 3, 20_000, 0)])
+def test_query_copies_take_no_longer(sorting, nref, copies, k, queries, qcopies):
+    import torch
+    s = strings_of(23, nref)
+    idx = sorting[0].build_index(*csr([s[5]] * copies + s), k)
+    q = [torch.from_numpy(a).cuda() for a in csr([s[5]] * qcopies + s[:queries])]
+    n = len(sorting[0].query(idx, *q, k))
+    print(f"[partition] {nref} references, {queries} queries, {n} pairs", flush=True)
+    general = sorting[2 if n >= 1 << 20 else 1]
+    not_slower(sorting[0], general, lambda ctx: ctx.query(idx, *q, k), equal)
+    idx.free()
