@@ -278,6 +278,15 @@ int sd_pair_distance(sd_ctx* ctx, const sd_seqs* a, const sd_seqs* b, const uint
  * build (several contexts on the same device may query it concurrently).
  * Release with sd_index_free (no context needed). k must be 0, 1, 2 or 3.
  * Errors: as sd_self_search.
+ * Memory: sd_index_free keeps an index's device blocks for the next index of
+ * the context that built it, up to a 32nd of the device's memory in all
+ * (memory given back is cleared before it can be handed out again, which a
+ * program that rebuilds large indexes would wait for); blocks may be larger than
+ * their arrays, those of over 64 MiB by up to a fifth. They go back to the
+ * device when an allocation of any context of the process fails there, when the
+ * context's allocator is set, and when the context and its indexes are gone;
+ * other users of the device cannot get at them before. A context with a budget
+ * or an allocator hook keeps none.
  */
 typedef struct sd_index sd_index;
 int sd_index_build(sd_ctx* ctx, const sd_seqs* ref, int k, sd_index** out, void* stream);

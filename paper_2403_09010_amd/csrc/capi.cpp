@@ -101,7 +101,7 @@ void* dalloc(sd_ctx* c, size_t bytes) {
   if (e != hipSuccess) {
     (void)hipGetLastError();
     release_cache(c);
-    if (c->index_pool) c->index_pool->release();
+    release_index_pools(c->device);
     e = hipMalloc(&p, sz);
   }
   if (e != hipSuccess || !p) {
@@ -127,47 +127,6 @@ void dfree(sd_ctx* c, void* p) {
   c->live.erase(it);
 }
 
-void* IndexPool::take(size_t bytes, size_t* size) {
-  std::lock_guard<std::mutex> g(m);
-  auto it = blocks.lower_bound(bytes);
-  if (it == blocks.end() || it->first > bytes + bytes / 8) return nullptr;
-  void* p = it->second;
-  *size = it->first;
-  held -= it->first;
-  blocks.erase(it);
-  return p;
-}
-
-bool IndexPool::put(void* const* p, const size_t* size, int n) {
-  std::lock_guard<std::mutex> g(m);
-  size_t sum = 0;
-  for (int x = 0; x < n; ++x) sum += size[x];
-  if (sum > limit) return false;
-  if (held + sum > limit) {  // the newest blocks stay
-    for (auto& b : blocks) (void)hipFree(b.second);
-    blocks.clear();
-    held = 0;
-  }
-  for (int x = 0; x < n; ++x) {
-    try {
-      blocks.insert({size[x], p[x]});
-      held += size[x];
-    } catch (...) {
-      (void)hipFree(p[x]);
-    }
-  }
-  return true;
-}
-
-void IndexPool::release() {
-  std::lock_guard<std::mutex> g(m);
-  if (blocks.empty()) return;
-  (void)hipSetDevice(device);
-  for (auto& b : blocks) (void)hipFree(b.second);
-  blocks.clear();
-  held = 0;
-}
-
 void* index_alloc(sd_ctx* c, sd_index* idx, size_t bytes) {
   if (!bytes) bytes = 16;
   void* p = nullptr;
@@ -180,13 +139,7 @@ void* index_alloc(sd_ctx* c, sd_index* idx, size_t bytes) {
   }
   size_t sz = bytes;
   if (!c->budget) {
-    if (!c->index_pool) {
-      c->index_pool = std::make_shared<IndexPool>();
-      c->index_pool->device = c->device;
-      size_t total = 0;
-      if (hipDeviceTotalMem(&total, c->device) != hipSuccess) (void)hipGetLastError();
-      c->index_pool->limit = total / 32;
-    }
+    if (!c->index_pool) c->index_pool = make_index_pool(c->device);
     idx->pool = c->index_pool;
     // a little more than asked for, so that the next index of about as many
     // sequences takes the same blocks
@@ -199,7 +152,7 @@ void* index_alloc(sd_ctx* c, sd_index* idx, size_t bytes) {
   }
   if (!p && hipMalloc(&p, sz) != hipSuccess) {
     (void)hipGetLastError();
-    if (c->index_pool) c->index_pool->release();
+    release_index_pools(c->device);
     sz = bytes;
     if (hipMalloc(&p, sz) != hipSuccess) p = nullptr;
   }

@@ -506,8 +506,9 @@ namespace sd {
 // handed out again, at about 35 GB/s, so a program that rebuilds an index over
 // and over waits for that once the card's clean memory is used up (2M
 // sequences, 1.6 GB: 45 ms a build, whatever the build takes). It keeps at most
-// `limit` bytes (a 32nd of the device's memory); an index that outlives its
-// context holds its pool's last reference.
+// `limit` bytes (a 32nd of the device's memory), which an allocation of any
+// context that fails gets back; an index that outlives its context holds its
+// pool's last reference.
 struct IndexPool {
   std::mutex m;
   int device = 0;
@@ -518,6 +519,9 @@ struct IndexPool {
   void release();
   ~IndexPool() { release(); }
 };
+std::shared_ptr<IndexPool> make_index_pool(int device);
+// every context's pool on the device, when an allocation there fails
+void release_index_pools(int device);
 }  // namespace sd
 
 struct sd_ctx {

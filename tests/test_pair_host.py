@@ -34,3 +34,15 @@ def test_device_set_offsets(tmp_path):
     build_and_run(tmp_path, "set_checks",
                   [os.path.join(ROOT, "tests", "sanitize", "set_checks.cpp")],
                   ["-I" + os.path.join(ROOT, "paper_2403_09010_amd", "csrc")])
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="needs g++ and the ROCm headers")
+def test_index_pool(tmp_path):
+    """Blocks of freed indexes: what is kept, and who gets it back."""
+    csrc = os.path.join(ROOT, "paper_2403_09010_amd", "csrc")
+    build_and_run(tmp_path, "pool_checks",
+                  [os.path.join(csrc, "index_pool.cpp"),
+                   os.path.join(ROOT, "tests", "sanitize", "pool_checks.cpp")],
+                  ["-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                   "-I" + os.path.join(ROOT, "include"), "-I" + csrc])
