@@ -74,9 +74,6 @@ ZeroRange cursors(const PairBins& b) {
   return {b.cursor, (uint64_t)b.nbins << b.nxl << b.pad};
 }
 
-// most candidates: beyond them the bins would take more memory than a sort
-constexpr uint64_t PAIR_MOST = 750000000;
-
 Shape shape(uint64_t guess, int k, int spread, bool uneven, bool lists) {
   Shape sh;
   sh.split = lists || guess >= (1ull << 20);
@@ -98,6 +95,22 @@ Shape shape(uint64_t guess, int k, int spread, bool uneven, bool lists) {
 
 }  // namespace
 
+uint64_t pairs_expected(const sd_ctx* c, const char* hint, uint64_t nkeys, int k) {
+  constexpr double first[4] = {1.0 / 64, 1.0 / 48, 1.0 / 22, 1.0 / 9};
+  double expect = (double)nkeys * first[k & 3];
+  auto raw = c->out_hint.find(hint), keys = c->out_hint.find(std::string(hint) + "/variants");
+  if (raw != c->out_hint.end() && keys != c->out_hint.end()) {
+    const double scale = (double)nkeys / std::max((double)keys->second, 1.0);
+    expect = std::max(expect, 1.1 * (double)raw->second * std::min(1.0, scale));
+  }
+  return (uint64_t)expect;
+}
+
+void pairs_found(sd_ctx* c, const char* hint, uint64_t nkeys, uint64_t raw) {
+  c->out_hint[hint] = raw;
+  c->out_hint[std::string(hint) + "/variants"] = nkeys;
+}
+
 bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
                   const PairSeqs& q,
                   const std::function<void(const PairBins&)>& produce,
@@ -106,19 +119,8 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
                   const char* stage, TileOut* out) {
   sd_ctx* c = cl0.c;
   hipStream_t s = cl0.s;
-  // candidates expected: a share of the variants by radius, or what the last
-  // search of this kind on the context made, scaled down to this one's
-  // variants (never up: one input of many copies must not size the next)
-  constexpr double first[4] = {1.0 / 64, 1.0 / 48, 1.0 / 22, 1.0 / 9};
-  const std::string hint_raw(hint), hint_keys = hint_raw + "/variants",
-                    hint_lists = hint_raw + "/lists";
-  double expect = (double)nkeys * first[q.k & 3];
-  if (c->out_hint.count(hint_raw)) {
-    const double last = (double)c->out_hint[hint_raw], keys = (double)c->out_hint[hint_keys];
-    expect = std::max(expect, 1.1 * last * std::min(1.0, (double)nkeys / std::max(keys, 1.0)));
-  }
-  expect = std::max(expect, (double)least);
-  uint64_t guess = (uint64_t)expect + 1024;
+  const std::string hint_lists = std::string(hint) + "/lists";
+  uint64_t guess = std::max(pairs_expected(c, hint, nkeys, q.k), least) + 1024;
   uint64_t cap = guess;
   int spread = 0;
   bool uneven = false;  // the level between overflowed
@@ -213,7 +215,10 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
       throw Error{SD_E_HIP, "internal error: a candidate id out of range"};
     // more candidates than a search answers, or than it would without the repeats
     // of a bin that was grouped twice: the path that counts them once decides
-    if (raw >= 0xFFFFFFFFull) return false;
+    if (raw > PAIR_MOST) {
+      pairs_found(c, hint, nkeys, raw);
+      return false;
+    }
     const PairNext next = check(st.counters, &more);
     if (next == PairNext::give_up || raw + more >= 0xFFFFFFFFull) return false;
     if (overflow || next == PairNext::again) {
@@ -237,8 +242,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
       cap = guess;
       continue;
     }
-    c->out_hint[hint_raw] = raw;
-    c->out_hint[hint_keys] = nkeys;
+    pairs_found(c, hint, nkeys, raw);
     c->out_hint[hint_lists] = to_lists;
     out->ncand = raw;
     if (st.flags & PF_LONG) {

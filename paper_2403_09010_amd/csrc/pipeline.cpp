@@ -518,6 +518,15 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   const int lb = plan.lb, lb1 = plan.lb1, nxl = plan.nxl;
   const uint64_t over_cap = nk / 16 + 65536;
   if (!plan_fits(plan, nk, over_cap)) return false;
+  // Candidates that come of the input's density: with 32 hash bits (over 2^24
+  // sequences) equal hashes of different variants, and in a first search the pairs
+  // of ever nearer neighbours, by repertoires of 1M to 28M sequences (2.8 billion
+  // variants: 1.46 billion candidates at k = 2 and 32 hash bits, 1.1 billion at k = 3).
+  constexpr double dense[4] = {0, 0, 0.9e-10, 1.4e-10};
+  const double nk2 = (double)nk * (double)nk;
+  const uint64_t least = (uint64_t)((idbits == 32 ? nk2 / 8.6e9 : 0.0) +
+                                    (c->out_hint.count(hint) ? 0.0 : nk2 * dense[q.k & 3]));
+  if (std::max(least, pairs_expected(c, hint, nk, q.k)) > PAIR_MOST) return false;
   uint32_t* over = cl.counters + CNT_OVER;
   // (regions of an estimate hold 1.2 times the most)
   const PartOut p1 = part_out(cl, std::max(nk, most / 5 * 3), lb1, nxl, over_cap,
@@ -542,7 +551,7 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   if (!memory_bounded(c)) partition();
   TileOut out;
   const bool done = binned_pairs(
-      cl, hint, nk, 0, q,
+      cl, hint, nk, least, q,
       [&](const PairBins& bins) {
         if (again) launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
         if (!generated) partition();
@@ -846,6 +855,7 @@ void paired_self_search(sd_ctx* c, const sd_seqs* a, const sd_seqs* b, int k, sd
     Cands cand = group_segments(cl, flip ? e2 : e1, nk, cap, bits, idbits);
     sc.blocks.push_back(cand.p);
     c->stats.n_cand_raw = (int64_t)cand.n;
+    pairs_found(c, "pairs/paired", nkeys, cand.n);
     v = sort_and_verify(cl, cand.p, cand.n, n, k, sa, pa, sb, pb);
   }
   try {
@@ -952,6 +962,7 @@ void self_search(sd_ctx* c, const sd_seqs* seqs, int k, sd_pairs* out, hipStream
       sc.blocks.push_back(cand.p);
       c->stats.n_sort_passes = passes;
       c->stats.n_cand_raw = (int64_t)cand.n;
+      pairs_found(c, "pairs/self", nkeys, cand.n);
       // 6-7: pair sort, verification
       v = sort_and_verify(cl, cand.p, cand.n, n, k, seq, planes);
     }

@@ -347,10 +347,17 @@ enum class PairNext {
   give_up   // the search takes another path
 };
 struct TileOut;
-// Returns false if check gave up, if there were 2^32 - 1 candidates or more, or
+// Returns false if check gave up, if there are more than PAIR_MOST candidates, or
 // if no shape of the bins held them. out: pairs sorted by (i, j), in pool blocks. sort_pairs orders a
 // dense array of distinct verified pairs instead, where one first id has
 // thousands of them.
+// Candidates expected: a share of the variants by radius, or what the last search
+// of this kind on the context made (pairs_found), scaled down to this one's variants
+// (never up: one input of many copies must not size the next).
+uint64_t pairs_expected(const sd_ctx* c, const char* hint, uint64_t nkeys, int k);
+void pairs_found(sd_ctx* c, const char* hint, uint64_t nkeys, uint64_t raw);
+// Most candidates: beyond them the bins take more memory than a sort, and are not made.
+constexpr uint64_t PAIR_MOST = 1000000000;
 // least: the fewest candidates to expect, whatever came of the last search.
 bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, uint64_t least,
                   const PairSeqs& q,

@@ -177,8 +177,17 @@ int main() {
           "2^32 - 1 candidates: left to the path that counts each once");
     o = search(100000000, {answer(0, (9ull << 32) + 77, sd::PF_OVERFLOW)});
     check(!o.found && o.code == SD_OK && o.produced == 1, "far more than 2^32 candidates: the same");
-    o = search(100000000, {answer(0, limit - 1, sd::PF_OVERFLOW)});
-    check(!o.found && o.code == SD_OK && o.checked == 1, "one less: no shape of the bins holds them");
+    o = search(100000000, {answer(0, sd::PAIR_MOST, sd::PF_OVERFLOW)});
+    check(!o.found && o.code == SD_OK && o.checked == 1, "as many as the bins take, without room");
+    // and the next search of as many variants knows; a smaller one is not affected
+    sd_ctx ctx;
+    o = search(100000000, {answer(0, sd::PAIR_MOST + 1, sd::PF_OVERFLOW)}, {}, &ctx);
+    check(!o.found && o.produced == 1 && sd::pairs_expected(&ctx, "pairs/test", 100000000, 2) > sd::PAIR_MOST,
+          "more than the bins take: expected from now on");
+    check(sd::pairs_expected(&ctx, "pairs/test", 1000, 2) < 20000, "not of a smaller search");
+    sd::pairs_found(&ctx, "pairs/test", 100000000, 5000);
+    check(sd::pairs_expected(&ctx, "pairs/test", 100000000, 2) == 100000000 / 22,
+          "until the path that sorts found fewer");
   }
   for (const uint32_t bit : {SD_ERRBIT_LOOKBACK, SD_ERRBIT_PLACEMENT, SD_ERRBIT_INDEX}) {
     // an error of the sorts that `check` ran shows in the read-back after them
