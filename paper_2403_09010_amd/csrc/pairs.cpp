@@ -93,6 +93,10 @@ Shape shape(uint64_t guess, int k, int spread, bool uneven, bool lists) {
   return sh;
 }
 
+// Searches that expect more candidates than this read the lists' counts before the
+// levels: 25 us, of more than 8 ms.
+constexpr uint64_t EARLY_LOOK = 1ull << 26;
+
 }  // namespace
 
 uint64_t pairs_expected(const sd_ctx* c, const char* hint, uint64_t nkeys, int k) {
@@ -114,6 +118,7 @@ void pairs_found(sd_ctx* c, const char* hint, uint64_t nkeys, uint64_t raw) {
 bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
                   const PairSeqs& q,
                   const std::function<void(const PairBins&)>& produce,
+                  const std::function<void(const PairBins&)>& append,
                   const std::function<PairNext(const uint32_t*, uint64_t*)>& check,
                   const std::function<TileOut(uint64_t*, uint64_t)>& sort_pairs,
                   const char* stage, TileOut* out) {
@@ -131,7 +136,12 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
   Scratch lists_sc(c);
   PairBins lists{};
   uint64_t list_room = 0;  // 0: from the guess
-  bool held = false;
+  bool held = false, adding = false;  // (adding: before the levels, to the lists)
+  // what a list needs for what the fullest was sent and its part of `more`
+  auto needs = [](const unsigned long long* sent, uint64_t more) {
+    const uint64_t most = *std::max_element(sent, sent + 8);
+    return std::min<uint64_t>(most + more / 8 + 16384, 0xFFFFFFFFull);
+  };
   for (int attempt = 0; attempt < 8; ++attempt) {
     Scratch sc(c);
     Call cl{c, s, sc, cl0.tm, cl0.counters};
@@ -184,6 +194,42 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
       to.missed = b.missed;
       produce(to);
       cl.tm.mark(stage, (double)nkeys * 8 + (double)guess * 8, 1);
+    } else if (adding) {
+      append(lists);
+      cl.tm.mark("append", (double)guess * 8, 1);
+    }
+    adding = false;
+    if (run && sh.split && guess >= EARLY_LOOK) {
+      // the levels take milliseconds: first look whether the lists are complete
+      unsigned long long sent[8];
+      const auto* l = static_cast<const unsigned long long*>(
+          readback(c, lists.lists, 8 * PAIR_LIST_STRIDE * 8, s));
+      for (int x = 0; x < 8; ++x) sent[x] = l[x * PAIR_LIST_STRIDE];
+      uint64_t raw = 0, more = 0;
+      for (unsigned long long n : sent) raw += n;
+      if (raw > PAIR_MOST) {
+        pairs_found(c, hint, nkeys, raw);
+        return false;
+      }
+      const PairNext next =
+          check(static_cast<const uint32_t*>(readback(c, cl.counters, CNT_TOTAL * 4, s)), &more);
+      if (next == PairNext::give_up) return false;
+      if (raw + more > PAIR_MOST) {
+        pairs_found(c, hint, nkeys, raw + more);
+        return false;
+      }
+      const bool full = *std::max_element(sent, sent + 8) > lists.region;
+      if (full || next == PairNext::again ||
+          (next == PairNext::add && needs(sent, more) > lists.region)) {
+        list_room = next == PairNext::done || more ? needs(sent, more) : 0;
+        guess = std::max(guess, raw + more + raw / 16 + 1024);
+        cap = guess;
+        continue;
+      }
+      if (next == PairNext::add) {
+        append(lists);
+        cl.tm.mark("append", (double)more * 16, 1);
+      }
     }
     if (sh.split) {
       launch_pair_split(lists, sh.l1, b.state, s);
@@ -221,12 +267,15 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
     }
     const PairNext next = check(st.counters, &more);
     if (next == PairNext::give_up || raw + more >= 0xFFFFFFFFull) return false;
-    if (overflow || next == PairNext::again) {
+    if (overflow || next != PairNext::done) {
       // more room: what was counted and what comes; where the room was there
       // but pairs have very many repeats, fewer of them per bin
       const uint64_t want = raw + more + raw / 16 + 1024;
       const bool full = st.flags & PF_LISTS;
-      held = sh.split && !full && next != PairNext::again;
+      held = sh.split && !full &&
+             (next == PairNext::done ||
+              (next == PairNext::add && needs(st.lists, more) <= lists.region));
+      adding = held && next == PairNext::add;
       const bool mid = st.flags & PF_MID;
       if (overflow && !full && !missed && want <= guess) {
         uneven = uneven || mid;
@@ -234,10 +283,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
       }
       // (what a producer sends each list does not change; `more` is shared out in
       // chunks)
-      list_room = 0;
-      if (sh.split && (more || next != PairNext::again))
-        for (uint64_t n : st.lists) list_room = std::max(list_room, n + more / 8 + 16384);
-      list_room = std::min<uint64_t>(list_room, 0xFFFFFFFFull);
+      list_room = sh.split && (more || next == PairNext::done) ? needs(st.lists, more) : 0;
       guess = std::max(guess, want);
       cap = guess;
       continue;

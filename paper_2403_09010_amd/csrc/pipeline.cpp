@@ -559,6 +559,7 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
         launch_filter_group(p, nk, idbits, bins, big, nbig, s);
         launch_pair_scatter(extra.p, extra.n, bins, s);
       },
+      [&](const PairBins& bins) { launch_pair_scatter(extra.p, extra.n, bins, s); },
       [&](const uint32_t* h, uint64_t* more) {
         check(h);
         if (h[CNT_OVER1] || h[CNT_OVER] > over_cap)
@@ -570,7 +571,7 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
         extra = oversized_group(cl, p.elem, big, nb, idbits);
         sc.blocks.push_back(extra.p);
         *more = extra.n;
-        return PairNext::again;
+        return PairNext::add;
       },
       [&](uint64_t* cand, uint64_t m) {
         const Verified w = sort_pairs(cl, cand, m);

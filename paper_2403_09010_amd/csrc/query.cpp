@@ -191,6 +191,17 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
                     w ? w->subst : nullptr,
                     w ? w->indel : 0,
                     w ? w->max_score : 0};
+  auto make_queue = [&] {
+    if (queue.cap >= runs) return;
+    queue.runs = sc.get<PairRun>(runs);
+    queue.cap = (uint32_t)runs;
+  };
+  auto put_copies = [&](const PairBins& bins) {
+    if (join)
+      launch_join_runs(p, idx->E, idx->seg_start, idx->seg_end, idx->bits, sub, idx->idbits,
+                       parts, queue, s);
+    launch_put_runs(idx->E, idx->idbits, queue, queue.cap, bins, s);
+  };
   const bool done = binned_pairs(
       // (queries that are in the index find each of their variants there: bins for that
       // cost nothing, and their counters have lines of their own: 3,000 queries of 5M
@@ -200,21 +211,18 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
         if (again) launch_fill_u32(cl.counters + CNT_PARTS, 0, 2, s);
         if (!generated) generate();
         again = true;
-        if (follow && queue.cap < runs) {
-          queue.runs = sc.get<PairRun>(runs);
-          queue.cap = (uint32_t)runs;
-        }
+        if (follow) make_queue();
         if (join)
           launch_join_bins(p, idx->E, idx->seg_start, idx->seg_end, idx->bits, sub, idx->idbits,
                            bins, parts, s);
         else
           launch_gen_probe(seq, q.n, k, idx->E, (uint32_t)idx->n_keys, idx->seg_start, idx->seg_end, idx->bits,
                            idx->idbits, bins, queue, s);
-        if (!follow) return;
-        if (join)
-          launch_join_runs(p, idx->E, idx->seg_start, idx->seg_end, idx->bits, sub, idx->idbits,
-                           parts, queue, s);
-        launch_put_runs(idx->E, idx->idbits, queue, queue.cap, bins, s);
+        if (follow) put_copies(bins);
+      },
+      [&](const PairBins& bins) {
+        make_queue();
+        put_copies(bins);
       },
       [&](const uint32_t* h, uint64_t*) {
         if (!known) raise_packed(q, h[CNT_ERR]);
@@ -227,8 +235,10 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
         // what is queued, or about what the parts will queue
         runs = std::max(queued, over + left * 4096) + 4096;
         if (runs > (1ull << 30)) return PairNext::give_up;
+        // (a join's parts and its overflow area are still there; lookups queue anew)
+        const PairNext next = join && !follow ? PairNext::add : PairNext::again;
         follow = true;
-        return PairNext::again;
+        return next;
       },
       [&](uint64_t* cand, uint64_t m) {
         return verify_candidates(cl, seq, planes, q.n, idx->ref_seq, idx->n_ref, cand, m, k, w);

@@ -339,11 +339,13 @@ void fill_host_slices(sd_ctx* c, const uint32_t* di, const uint32_t* dj, const u
 
 // Candidates of a search through the bins of pairs.hip (pairs.cpp).
 // `produce` enqueues the kernels that put every candidate, once all memory is taken;
-// it may run again, with more room, after `check` looked at the call's counters. nkeys: about how
+// it may run again, with more room, after `check` looked at the call's counters.
+// `append` puts only what check has asked for, to lists that hold the rest. nkeys: about how
 // many variants produce the candidates.
 enum class PairNext {
   done,     // every candidate was put
-  again,    // produce has more candidates to put now (`guess` more)
+  add,      // `append` has more candidates (about *more, if known), and `produce` too
+  again,    // only `produce` has, which puts all of them
   give_up   // the search takes another path
 };
 struct TileOut;
@@ -362,6 +364,7 @@ constexpr uint64_t PAIR_MOST = 1000000000;
 bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, uint64_t least,
                   const PairSeqs& q,
                   const std::function<void(const PairBins&)>& produce,
+                  const std::function<void(const PairBins&)>& append,
                   const std::function<PairNext(const uint32_t*, uint64_t*)>& check,
                   const std::function<TileOut(uint64_t*, uint64_t)>& sort_pairs,
                   const char* stage, TileOut* out);

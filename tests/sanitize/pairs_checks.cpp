@@ -19,6 +19,9 @@ int pending = 0;  // launches since the stream was waited for
 std::vector<sd::PairState> answers;
 size_t answered = 0;
 std::vector<std::string> log_;  // launches, in order
+std::vector<uint64_t> looks;    // candidates in the lists at each early look
+int looked = 0;
+unsigned long long sent[128];
 std::vector<uint32_t> rooms;    // of what each producer was given
 int allocations = 0;            // the last of them fails (0: none does)
 
@@ -45,6 +48,13 @@ void hip_check(hipError_t e, const char* what) {
 }
 void* readback(sd_ctx*, const void*, size_t bytes, hipStream_t) {
   pending = 0;
+  if (bytes == 1024) {  // an early look: the lists' counters, then the call's
+    static uint32_t zeros[256];
+    if (++looked % 2 == 0) return zeros;
+    std::memset(sent, 0, sizeof(sent));
+    for (int x = 0; x < 8; ++x) sent[16 * x] = looks.at((size_t)looked / 2) / 8;
+    return sent;
+  }
   if (answered >= answers.size()) throw Error{SD_E_STATE, "one read-back too many"};
   if (bytes != sizeof(PairState)) throw Error{SD_E_STATE, "a read-back of another size"};
   return &answers[answered++];
@@ -100,7 +110,7 @@ struct Outcome {
   bool found = false;
   int code = SD_OK;
   sd::TileOut out;
-  int produced = 0, checked = 0;
+  int produced = 0, checked = 0, appended = 0;
 };
 
 // one search of nkeys variants, k = 2, answered by `a` in turn; `next` is what
@@ -114,6 +124,7 @@ Outcome search(uint64_t nkeys, std::vector<sd::PairState> a,
   answered = 0;
   log_.clear();
   rooms.clear();
+  looked = 0;
   pending = 0;
   Outcome o;
   uint32_t counters[sd::CNT_TOTAL] = {};
@@ -129,8 +140,13 @@ Outcome search(uint64_t nkeys, std::vector<sd::PairState> a,
           rooms.push_back(b.region);
           launched("produce");
         },
-        [&](const uint32_t*, uint64_t*) {
+        [&](const sd::PairBins&) {
+          ++o.appended;
+          launched("append");
+        },
+        [&](const uint32_t*, uint64_t* more) {
           const size_t x = (size_t)o.checked++;
+          if (x < next.size() && next[x] == sd::PairNext::add) *more = 100000;
           return x < next.size() ? next[x] : sd::PairNext::done;
         },
         [&](uint64_t*, uint64_t m) {
@@ -253,6 +269,35 @@ int main() {
     check(o.found && launches("split") == 2, "lists once more");
     o = search(100000, {answer(500, 2000)}, {}, &ctx);
     check(o.found && launches("split") == 0, "bins again");
+  }
+  {
+    // more candidates for lists that hold the rest: only they are put
+    Outcome o = search(100000000, {answer(500, 4000000), answer(500, 4100000)}, {sd::PairNext::add});
+    check(o.found && o.produced == 1 && o.appended == 1 && launches("split") == 4,
+          "more candidates: appended, split again");
+    sd::PairState near = answer(500, 4000000);
+    near.lists[2] = 990000;  // of about a million
+    o = search(100000000, {near, answer(500, 4100000)}, {sd::PairNext::add});
+    check(o.found && o.produced == 2 && o.appended == 0 && rooms[1] == 990000 + 100000 / 8 + 16384,
+          "no room for them: produced again, with room");
+    o = search(100000, {answer(500, 3000), answer(500, 103000)}, {sd::PairNext::add});
+    check(o.found && o.produced == 2 && o.appended == 0, "no lists: produced again");
+    // a very large search looks at its lists first
+    const uint64_t nk = 22ull << 27;
+    looks = {90000000};
+    o = search(nk, {answer(500, 90000000)});
+    check(o.found && o.produced == 1 && o.checked == 2 && launches("split") == 2 && looked == 2,
+          "an early look: the levels once");
+    o = search(nk, {answer(500, 90100000)}, {sd::PairNext::add});
+    check(o.found && o.produced == 1 && o.appended == 1 && launches("split") == 2,
+          "an early look: more candidates before the levels");
+    looks = {400000000, 400000000};
+    o = search(nk, {answer(500, 400000000)});
+    check(o.found && o.produced == 2 && launches("split") == 2 && rooms[1] == 50000000 + 16384,
+          "an early look: full lists, produced again with room");
+    looks = {sd::PAIR_MOST + 8};
+    o = search(nk, {});
+    check(!o.found && o.code == SD_OK && launches("split") == 0, "an early look: too many");
   }
   std::printf(failures ? "%d checks failed\n" : "ok\n", failures);
   return failures ? 1 : 0;
