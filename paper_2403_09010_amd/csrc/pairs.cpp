@@ -97,6 +97,11 @@ Shape shape(uint64_t guess, int k, int spread, bool uneven, bool lists) {
 // levels: 25 us, of more than 8 ms.
 constexpr uint64_t EARLY_LOOK = 1ull << 26;
 
+// Room for a few more candidates than were found: the same for another attempt and for
+// the next search, whose blocks are then the same (560M candidates of equal sequences:
+// 38 GB more at the second search where they were not).
+uint64_t with_slack(uint64_t found) { return found + found / (found >= EARLY_LOOK ? 16 : 10); }
+
 }  // namespace
 
 uint64_t pairs_expected(const sd_ctx* c, const char* hint, uint64_t nkeys, int k) {
@@ -105,7 +110,7 @@ uint64_t pairs_expected(const sd_ctx* c, const char* hint, uint64_t nkeys, int k
   auto raw = c->out_hint.find(hint), keys = c->out_hint.find(std::string(hint) + "/variants");
   if (raw != c->out_hint.end() && keys != c->out_hint.end()) {
     const double scale = (double)nkeys / std::max((double)keys->second, 1.0);
-    expect = std::max(expect, 1.1 * (double)raw->second * std::min(1.0, scale));
+    expect = std::max(expect, (double)with_slack(raw->second) * std::min(1.0, scale));
   }
   return (uint64_t)expect;
 }
@@ -222,7 +227,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
       if (full || next == PairNext::again ||
           (next == PairNext::add && needs(sent, more) > lists.region)) {
         list_room = next == PairNext::done || more ? needs(sent, more) : 0;
-        guess = std::max(guess, raw + more + raw / 16 + 1024);
+        guess = std::max(guess, with_slack(raw + more) + 1024);
         cap = guess;
         continue;
       }
@@ -270,7 +275,7 @@ bool binned_pairs(Call& cl0, const char* hint, uint64_t nkeys, uint64_t least,
     if (overflow || next != PairNext::done) {
       // more room: what was counted and what comes; where the room was there
       // but pairs have very many repeats, fewer of them per bin
-      const uint64_t want = raw + more + raw / 16 + 1024;
+      const uint64_t want = with_slack(raw + more) + 1024;
       const bool full = st.flags & PF_LISTS;
       held = sh.split && !full &&
              (next == PairNext::done ||
