@@ -1,4 +1,5 @@
-// Partitioned grouping path for gfx950: the automatic path of self searches.
+// Partitioned grouping path for gfx950: the automatic path of self searches and
+// of queries against a hashed index, and the index build.
 //
 //   k_gen_part      generates every distinct <= k-deletion variant as a 64-bit
 //                   element [hash | id] into an LDS tile, orders the tile by
@@ -7,6 +8,12 @@
 //   k_filter_group  one workgroup per bin: an LDS bitmap finds the elements
 //                   whose hash may be shared, which are grouped by their full
 //                   stored hash in LDS and emit their id pairs
+//   k_part_split    a first level's bins, each split by further hash bits
+//   k_sort_bins     bins in order of the whole element (index build)
+//   k_join_bins     query bins joined with the index elements of the same bits
+//   k_gen_probe     query variants looked up in the index as they are generated
+//   k_join_runs,    queries and variants with more matches than a workgroup of
+//   k_put_runs      those two follows
 //
 // Equal variants have equal hashes and so share a bin; a collision of hashes
 // only adds a candidate that the verification rejects.
@@ -1598,7 +1605,8 @@ __global__ __launch_bounds__(256) void k_put_runs(const uint64_t* __restrict__ E
 
 namespace sd {
 
-// Dynamic LDS beyond the default limit, once per kernel and device.
+// Dynamic LDS beyond the default limit. It is asked for at each launch: the attribute
+// is the device's own, and a context may be of any.
 template <class F>
 static void allow_lds(F* f, size_t bytes) {
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(f),

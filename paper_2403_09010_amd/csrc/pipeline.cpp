@@ -316,10 +316,6 @@ PartOut part_out(Call& cl, uint64_t nk, int lb, int nxl, uint64_t over_cap, uint
   return o;
 }
 
-namespace {
-
-}  // namespace
-
 uint64_t bucket_sort_verify(Call& cl, const BucketPlan& p, uint64_t* cand, uint64_t nc,
                             uint64_t* cand2, uint64_t na, uint64_t nbseq, const u128* a,
                             const u128* sb, int k, int self_pairs,
@@ -603,8 +599,11 @@ constexpr uint64_t kStreamBytesPerSeq = 64;
 // Elements per column group of a streamed search, or 0 to search in memory:
 // SD_OPT_STREAM 1 never streams, 2 always does; automatically, a search
 // streams when its variants exceed what 32-bit element counts address or what
-// the in-memory path (two 8-byte element buffers, tile counts and candidates:
-// about 18 bytes per variant) would need beyond the context's budget.
+// the sorted path (two 8-byte element buffers, tile counts and candidates:
+// about 18 bytes per variant) would need beyond the context's budget. The bins of
+// partitioned_search take about 10 bytes on one level and 19 on two, beside the pairs';
+// where the budget has no room for those, the sorted path runs, and nothing was
+// generated.
 uint64_t stream_group_elems(const sd_ctx* c, uint64_t n, uint64_t nkeys) {
   if (c->stream == 1 || c->path == 1) {
     if (nkeys >= 0xFFFFFFFFull) throw Error{SD_E_TOO_MANY, "more than 2^32 - 2 deletion variants"};

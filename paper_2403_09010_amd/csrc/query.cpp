@@ -7,10 +7,13 @@
 //   the full hash, repeated elements removed, and a directory of 2^B hash
 //   segments. The index owns its device memory and is shared read-only.
 // Query (per tile of query sequences, one or many sets concatenated):
-//   pack, scan, query variants as [hash | query id], LSD passes over the same
-//   top B hash bits, query segment table, a segment-wise join against the
-//   index, pair sort, exact verification (or weighted rescoring), and for a
-//   batch of sets a split of the sorted result into per-set slices.
+//   query_tile_binned: query variants looked up as they are generated, or in bins
+//   joined with the index; id pairs through the pair bins (pairs.cpp).
+//   The general tile, where that does not apply: pack, scan, query variants as
+//   [hash | query id], LSD passes over the same top B hash bits, query segment
+//   table, a segment-wise join against the index, pair sort, exact verification
+//   (or weighted rescoring). For a batch of sets the sorted result is split into
+//   per-set slices.
 #include <hip/hip_runtime.h>
 
 #include <chrono>

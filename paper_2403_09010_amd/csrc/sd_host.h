@@ -369,7 +369,6 @@ bool binned_pairs(Call& cl, const char* hint, uint64_t nkeys, uint64_t least,
                   const std::function<TileOut(uint64_t*, uint64_t)>& sort_pairs,
                   const char* stage, TileOut* out);
 
-// Regions of one partition level, cursors zeroed (pipeline.cpp).
 // Sequences of the usual lengths have about this many distinct variants, and no
 // sequence has more than the second number.
 constexpr uint32_t TYPICAL_VARIANTS[4] = {1, 16, 110, 500}, MOST_VARIANTS[4] = {1, 25, 301, 2325};
@@ -377,6 +376,7 @@ constexpr uint32_t TYPICAL_VARIANTS[4] = {1, 16, 110, 500}, MOST_VARIANTS[4] = {
 // packing kernel: their searches size everything for the estimate, and read the
 // flags and the total with the result.
 constexpr uint64_t UNREAD_KEYS = 1ull << 20;
+// Regions of one partition level, cursors zeroed (pipeline.cpp).
 PartOut part_out(Call& cl, uint64_t nk, int lb, int nxl, uint64_t over_cap, uint32_t* over_count);
 
 // Under a budget or in a fixed area a search takes all its memory before its first
