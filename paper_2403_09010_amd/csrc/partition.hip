@@ -1099,7 +1099,10 @@ __device__ __forceinline__ void push_run(const sd::RunQueue& q, uint32_t p, uint
   uint32_t at = 0;
   if (mask_rank(act) == 0) at = atomicAdd(q.count, (uint32_t)__popcll(act));
   at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + mask_rank(act);
-  if (at < q.cap) q.runs[at] = sd::PairRun{p, n, id};
+  if (at < q.cap)
+    q.runs[at] = sd::PairRun{p, n, id};
+  else if (at - q.cap < sd::RUN_SAMPLE)
+    atomicAdd(q.missed, (unsigned long long)n);
 }
 
 template <bool K3>

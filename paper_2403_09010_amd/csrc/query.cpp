@@ -174,7 +174,8 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
   uint64_t runs = c->out_hint[hint_runs];
   bool follow = runs > 0, again = false;
   runs += runs / 4 + 4096;
-  RunQueue queue{nullptr, 0, cl.counters + CNT_RUNS};
+  RunQueue queue{nullptr, 0, cl.counters + CNT_RUNS,
+                 reinterpret_cast<unsigned long long*>(cl.counters + CNT_MISSED)};
   bool generated = !join;
   auto generate = [&] {
     generated = true;
@@ -211,7 +212,7 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
       // references 239 us, 233 with them)
       cl, hint, nk, join ? 0 : std::min<uint64_t>(nk + nk / 4, 640 << 10), ps,
       [&](const PairBins& bins) {
-        if (again) launch_fill_u32(cl.counters + CNT_PARTS, 0, 2, s);
+        if (again) launch_fill_u32(cl.counters + CNT_PARTS, 0, 4, s);
         if (!generated) generate();
         again = true;
         if (follow) make_queue();
@@ -227,7 +228,7 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
         make_queue();
         put_copies(bins);
       },
-      [&](const uint32_t* h, uint64_t*) {
+      [&](const uint32_t* h, uint64_t* more) {
         if (!known) raise_packed(q, h[CNT_ERR]);
         nk = pack_total(h);
         if (join && h[CNT_OVER] > over_cap) return PairNext::give_up;
@@ -238,6 +239,14 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
         // what is queued, or about what the parts will queue
         runs = std::max(queued, over + left * 4096) + 4096;
         if (runs > (1ull << 30)) return PairNext::give_up;
+        // (their candidates, from those that were summed; the next count is exact)
+        if (queued > queue.cap) {
+          unsigned long long sum = 0;
+          std::memcpy(&sum, h + CNT_MISSED, 8);
+          const double beyond = (double)(queued - queue.cap);
+          *more = (uint64_t)std::min((double)sum * beyond / std::min(beyond, (double)RUN_SAMPLE),
+                                     (double)(1u << 28));
+        }
         // (a join's parts and its overflow area are still there; lookups queue anew)
         const PairNext next = join && !follow ? PairNext::add : PairNext::again;
         follow = true;

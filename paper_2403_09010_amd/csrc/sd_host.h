@@ -68,6 +68,7 @@ enum : int {
   CNT_OVER1 = 111,    // the same of its first level
   CNT_PARTS = 112,    // segments or rounds that a join left
   CNT_RUNS = 113,     // queued runs of copies
+  CNT_MISSED = 114,   // u64 elements of some of those that the queue had no room for
   CNT_SUMS = 128,     // u64 partial sums of the variant counts
   CNT_TOTAL = CNT_SUMS + 2 * PACK_SUMS
 };

@@ -362,7 +362,8 @@ void launch_pair_scatter(const uint64_t* cand, uint64_t n, const PairBins& o, hi
 // are generated, or joined bin by bin from a partition of them (in.lb + sub <=
 // bits: 2^sub workgroups share a bin).
 // A query's variant and the index elements [p, p + n) of its hash; runs of copies
-// wait in a queue (its counter, zeroed before, also counts those past its room).
+// wait in a queue (its counter, zeroed before, also counts those past its room; the
+// elements of the first RUN_SAMPLE of these are summed in `missed`).
 struct PairRun {
   uint32_t p, n, id;
 };
@@ -370,7 +371,9 @@ struct RunQueue {
   PairRun* runs;
   uint32_t cap;
   uint32_t* count;
+  unsigned long long* missed;
 };
+constexpr uint32_t RUN_SAMPLE = 1024;
 // (runs of more than a few hundred elements go to `longs`)
 void launch_gen_probe(const u128* seq, uint64_t n, int k, const uint64_t* E, uint32_t nkeys,
                       const uint32_t* seg_start, const uint32_t* seg_end, int bits, uint32_t idbits,

@@ -461,3 +461,23 @@ def test_query_copies_take_no_longer(sorting, nref, copies, k, queries, qcopies)
     general = sorting[2 if n >= 1 << 20 else 1]
     not_slower(sorting[0], general, lambda ctx: ctx.query(idx, *q, k), equal)
     idx.free()
+
+
+# the first queries with copies: one search finds out how many there are, one puts them
+@pytest.mark.parametrize("copies,queries,qcopies", [(500, 50, 3), (2_000, 50, 3), (500, 3_000, 30)])
+def test_first_query_with_copies(sorting, copies, queries, qcopies):
+    from paper_2403_09010_amd import Context
+    from paper_2403_09010_amd.symdel import OPT_TIMING
+    s = strings_of(31, 100_000)
+    q = csr([s[5]] * qcopies + s[:queries])
+    with Context(0) as ctx:
+        ctx.set_option(OPT_TIMING, 1)
+        idx = ctx.build_index(*csr([s[5]] * copies + s), 2)
+        print(f"[partition] {copies} copies, {queries} queries", flush=True)
+        found = ctx.query(idx, *q, 2)
+        stages = [x["name"] for x in ctx.stats()["stages"]]
+        idx.free()
+    idx = sorting[1].build_index(*csr([s[5]] * copies + s), 2)
+    equal(found, sorting[1].query(idx, *q, 2))
+    idx.free()
+    assert stages.count("join") <= 2, stages
