@@ -165,8 +165,16 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
     const int nxl = nk >= (2u << 20) ? 3 : 0;
     over_cap = !memory_bounded(c) && nk <= (1ull << 28) ? nk : nk / 16 + 65536;
     p = part_out(cl, nk, lb, nxl, over_cap, cl.counters + CNT_OVER);
-    parts = JoinParts{sc.get<JoinPart>(join_parts(p, sub)), cl.counters + CNT_PARTS};
   }
+  bool generated = !join;
+  auto generate = [&] {
+    generated = true;
+    launch_gen_part(seq, vcnt, q.n, nk, k, idx->idbits, p, s);
+    cl.tm.mark("q_vargen_part", (double)nk * 8 + (double)q.n * 20, 1);
+  };
+  // (the device waits for it: everything else is taken afterwards)
+  if (join && !memory_bounded(c)) generate();
+  if (join) parts = JoinParts{sc.get<JoinPart>(join_parts(p, sub)), cl.counters + CNT_PARTS};
   const char* const hint = join ? "pairs/join" : "pairs/probe";
   const std::string hint_runs = std::string(hint) + "/runs";
   // copies, if there are any: what the join left and long runs are followed up by
@@ -176,13 +184,6 @@ bool query_tile_binned(Call& cl0, const sd_index* idx, const DevSeqs& q, int k,
   runs += runs / 4 + 4096;
   RunQueue queue{nullptr, 0, cl.counters + CNT_RUNS,
                  reinterpret_cast<unsigned long long*>(cl.counters + CNT_MISSED)};
-  bool generated = !join;
-  auto generate = [&] {
-    generated = true;
-    launch_gen_part(seq, vcnt, q.n, nk, k, idx->idbits, p, s);
-    cl.tm.mark("q_vargen_part", (double)nk * 8 + (double)q.n * 20, 1);
-  };
-  if (join && !memory_bounded(c)) generate();
   const bool hamming = c->metric == SD_METRIC_HAMMING;
   const PairSeqs ps{w ? planes : hamming ? seq : planes,
                     idx->ref_seq,
