@@ -527,6 +527,15 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   // (regions of an estimate hold 1.2 times the most)
   const PartOut p1 = part_out(cl, std::max(nk, most / 5 * 3), lb1, nxl, over_cap,
                               lb1 < lb ? over + 1 : over);
+  bool generated = false;
+  auto first_level = [&] {
+    generated = true;
+    generate(p1, idbits);
+    cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
+  };
+  // (the device waits for it: where memory is bounded all of it comes first, elsewhere
+  // the rest afterwards)
+  if (!memory_bounded(c)) first_level();
   const PartOut p = lb1 < lb ? part_out(cl, nk, lb, nxl, over_cap, over) : p1;
   const uint64_t nbig_cap = ((uint64_t)p.nbins << nxl) + 1;
   uint64_t* big = cl.sc.get<uint64_t>(2 * nbig_cap);
@@ -534,23 +543,21 @@ bool partitioned_search(Call& cl0, uint64_t n, uint64_t nk, uint64_t most, const
   Cands extra;  // candidates of the listed ranges
   uint64_t listed = 0;
   bool again = false;  // (a call's counters start as zeros)
-  bool generated = false;
-  auto partition = [&] {
-    generated = true;
-    generate(p1, idbits);
-    cl.tm.mark("vargen_part", (double)nk * 8 + (double)n * 20, 1);
-    if (lb1 < lb) {
-      launch_part_split(p1, p, s);
-      cl.tm.mark("part_split", (double)nk * 16, 1);
-    }
+  auto second_level = [&] {
+    if (lb1 == lb) return;
+    launch_part_split(p1, p, s);
+    cl.tm.mark("part_split", (double)nk * 16, 1);
   };
-  if (!memory_bounded(c)) partition();
+  if (generated) second_level();
   TileOut out;
   const bool done = binned_pairs(
       cl, hint, nk, least, q,
       [&](const PairBins& bins) {
         if (again) launch_fill_u64(reinterpret_cast<uint64_t*>(nbig), 0, 1, s);
-        if (!generated) partition();
+        if (!generated) {
+          first_level();
+          second_level();
+        }
         again = true;
         launch_filter_group(p, nk, idbits, bins, big, nbig, s);
         launch_pair_scatter(extra.p, extra.n, bins, s);
